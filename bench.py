@@ -539,7 +539,7 @@ def main():
     for st in warm["per_step"]:
         log(f"[bench] warmup {st['it']}: bound={st['bound_ppm']} rounds={st['rounds']}")
     from paper_2605_01989_amd import binding
-    # the timed region brackets only the launches of the dominant kernel, the staged gather, with events
+    # the timed region brackets only the launches of the dominant kernel, gather_stream, with events
     # (two event records per dense batch; the direct kernel's launches on sparse retransmission batches
     # are a group of their own); the per-group breakdown comes from a replay of its first steps with
     # every group bracketed
@@ -550,8 +550,8 @@ def main():
 
     fill = L.N / (L.n_pkts * L.P)
     value = accepted_total * 4 * L.P * fill / wall / 1e9
-    # dominant kernel: gather_accumulate_staged, which takes the first transmissions (a retransmission
-    # batch goes to the direct kernel unless it is dense; one that the staged kernel does take adds its
+    # dominant kernel: gather_stream, which takes the first transmissions (a retransmission
+    # batch goes to the direct kernel unless it is dense; one that gather_stream does take adds its
     # time here and not its bytes).  Algorithmic bytes = every packet accepted from a first transmission
     # read once (header + payload + padding = stride) + the accumulator written once per iteration.
     g_ms, g_n = prof["gather"]
@@ -560,7 +560,7 @@ def main():
     achieved = g_bytes / (g_ms * 1e-3) / 1e9 if g_ms > 0 else 0.0
     ratio_pmc = PMC_TRAFFIC_RATIO.get((_kernel_source_hash(), w.name))
     roofline = dict(bound="hbm", achieved=round(achieved, 1), peak=HBM_PEAK_GBPS, unit="GB/s",
-                    frac=round(achieved / HBM_PEAK_GBPS, 4), kernel="gather_accumulate_staged",
+                    frac=round(achieved / HBM_PEAK_GBPS, 4), kernel="gather_stream",
                     launches=g_n, avg_launch_ms=round(g_ms / max(g_n, 1), 4),
                     algorithmic_bytes_per_launch=round(g_bytes / max(g_n, 1)),
                     traffic=None if ratio_pmc is None else round(ratio_pmc * g_bytes / max(g_n, 1)))

@@ -6,7 +6,7 @@
 //                    (arrival rank << 32 | slot) into the arrival index `pending[w][seq]`, so the
 //                    earliest copy of a packet in the batch wins; per-block tallies (stale, invalid,
 //                    candidates, touched seq range) that every gather block adds up for itself
-//   gather_accumulate_staged / gather_accumulate
+//   gather_stream / gather_accumulate (dense / sparse batches)
 //                    organised by OUTPUT packet: a block takes a group of consecutive sequence
 //                    numbers, reads the index entries of all workers, drops copies of packets
 //                    that an earlier batch delivered, sets the bitmap bits, then streams the
@@ -468,8 +468,8 @@ __device__ __forceinline__ BatchInfo fold_index_tallies(const u32* __restrict__ 
 #define NONE32 0xFFFFFFFFu
 
 // A batch is sparse when it holds fewer than one packet per SPARSE_DIV (worker, seq) pairs of the
-// sequence range it touches (retransmission batches).  Sparse batches take the direct kernel
-// (independent waves, no staging pipeline to fill per group), dense ones the staged kernel; both
+// sequence range it touches (retransmission batches).  Sparse batches take the direct kernel (it skips
+// groups without arrivals many at a time), dense ones gather_stream; where the host cannot tell, both
 // are launched and the one whose regime it is not returns at once.
 #define SPARSE_DIV 8
 __device__ __forceinline__ bool batch_is_sparse(const BatchInfo& bi, u32 W) {
@@ -532,7 +532,7 @@ __device__ __forceinline__ float4 finish_unit(float4 a, float inv_w, bool rmw, c
 // One block per group of SUB consecutive sequence numbers, grid-stride over the groups the
 // batch touched.
 //   phase A  64 lanes = 4 workers x 16 packets per load of the arrival index: ballot -> new
-//            bitmap bits (one atomicOr per worker and group), slots staged in LDS, index
+//            bitmap bits (one atomicOr per worker and group), slots in LDS, index
 //            entries reset; the 16 packets' element spans are computed by 16 lanes in parallel
 //   phase B  the waves split the 16 packets: per packet, 16-byte payload loads from every
 //            worker that delivered it, summed in registers in worker order, one write of the span
@@ -704,279 +704,268 @@ __global__ __launch_bounds__(GA_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
     }
 }
 
-// Staged variant of the gather (used whenever two groups of packets fit in LDS).
-// Mixing the accumulator stores into the waves that stream the payloads costs far more than the
-// stores' bytes (a payload-only loop sustains 6.2 TB/s on this chip, the same loop with its
-// 3 % of stores 4.9 TB/s).  Here up to GS_READERS waves only load and add, and hand each summed
-// packet to LDS; one extra writer wave drains the previous group from LDS to the accumulator
-// while the readers work on the next one (double-buffered).  Because the writer reads LDS at
-// arbitrary float offsets, its global accesses are 16-byte aligned float4s whatever the
-// alignment of the packet's element span.
-#ifndef GS_READERS
-#define GS_READERS 8
-#endif
-#ifndef GS_READERS_SHORT
-#define GS_READERS_SHORT 4            // reader waves and blocks per CU for packets of up to 2 KB
-#endif
-#ifndef GS_MAX_PER_CU_SHORT
-#define GS_MAX_PER_CU_SHORT 3
-#endif
-#ifndef GS_LDS_BUDGET
-#define GS_LDS_BUDGET (48u * 1024u)   // bytes for the two packet buffers
-#endif
-#ifndef GS_WRITER_PREPARES_MAX_W
-#define GS_WRITER_PREPARES_MAX_W 16   // up to this many workers the writer wave also prepares the next group (see the kernel)
-#endif
-#ifndef GS_MAX_PER_CU
-#define GS_MAX_PER_CU 2               // blocks per CU for packets longer than 2 KB (more waves in flight
-#endif                                // only spread the DRAM accesses over more open rows); see apply_batch
+// Dense batches.  A block takes a group of `sub` = 16 (or 8) consecutive sequence numbers: every wave
+// reads the group's arrival index (64 / sub workers x sub packets per load), ballots which packets are
+// new, and keeps their slots in its own LDS rows; after a barrier the first wave resets the index
+// entries and sets the bitmap, whose bytes the group owns (16 or 8 bits: a plain store, where one
+// memory-side atomic per worker and group took up to a microsecond of a small group's time).  The
+// waves then share the group's packets, cut into pieces of NP KB when they are longer than 5 KB.
+//
+// What bounds it is the memory system, so the loop is there to keep it asked: a step loads G workers'
+// pieces of one packet (16 bytes per lane and KB), D steps are in flight in registers, and a packet's
+// stores are issued between the loads of later steps.  The loads are the same in every step, without
+// branches or masks, so the compiler can wait for exactly the oldest step (s_waitcnt vmcnt counts in
+// order): each worker's piece is a buffer descriptor of its own (base and length in scalar registers),
+// of length zero for a worker that delivered nothing, and lanes beyond the length read zeros without
+// asking memory.  Any packet length goes this way: the sums stay in registers and leave them as
+// 16-byte stores at the span's own (4-byte) alignment.
+//
+// Measured against the kernel it replaces (reader waves, LDS, a writer wave per block; packets above
+// 12 KB went to the direct kernel), us per launch, algorithmic TB/s in brackets:
+//   8 workers x 8992-byte packets, 4.5 GB       1430 -> 930  (3.1 -> 4.8)
+//   16 x 4112 B, 23.8 GB                         4740 -> 4630 (5.0 -> 5.1)
+//   8 x 1472 B, 0.92 GB                           194 -> 177  (4.7 -> 5.2)
+//   8 x 1472 B, 4.5 GB                            912 -> 892  (4.9 -> 5.0)
+//   1 x 1472 B, 0.2 GB (as much written as read)   94 -> 45   (2.2 -> 4.6)
+//   4 x 1040 B, 21 MB                              19 -> 12
+typedef f4v f4v_a4 __attribute__((aligned(4)));      // a 16-byte access at a 4-byte aligned address
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef f2v f2v_a4 __attribute__((aligned(4)));
 
-// Sum of one whole packet over the workers in `sub`: lane l holds 16-byte units l, l+64, ...
-// (NP of them).  All NP loads of one worker's packet are issued together, so a packet's
-// cache lines are requested back to back (a line shared by two 1 KB passes is fetched once),
-// and 8/NP workers (at least 2) are in flight at a time.  Same addition order as sum_unit.
-template <int NP>
-__device__ __forceinline__ void sum_packet(const uint8_t* __restrict__ packets, u32 stride, u32 lane, u32 units,
-                                           u64 sub, u32 slot32, float4 (&a)[NP]) {
-    constexpr int G = NP <= 2 ? 8 / NP : 2;
-    #pragma unroll
-    for (int q = 0; q < NP; ++q) a[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-    while (sub) {
-        float4 v[G][NP];
-        #pragma unroll
-        for (int j = 0; j < G; ++j) {
-            #pragma unroll
-            for (int q = 0; q < NP; ++q) v[j][q] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (sub) {
-                const u32 w = (u32)__builtin_ctzll(sub);
-                sub &= sub - 1;
-                const u32 slot = (u32)__builtin_amdgcn_readlane((int)slot32, (int)w);
-                const uint8_t* base = packets + (u64)slot * stride + 16ull * lane;
-                #pragma unroll
-                for (int q = 0; q < NP; ++q)
-                    if (q * WAVE + lane < units) v[j][q] = ld_stream4(base + 1024ull * q);
-            }
-        }
-        #pragma unroll
-        for (int j = 0; j < G; ++j) {
-            #pragma unroll
-            for (int q = 0; q < NP; ++q) { a[q].x += v[j][q].x; a[q].y += v[j][q].y; a[q].z += v[j][q].z; a[q].w += v[j][q].w; }
-        }
-    }
+#define GS_WAVES 4           // waves per block
+#define GS_TEAM_LDS(W, sub_log2) ((((W) + (WAVE >> (sub_log2)) - 1) >> (6 - (sub_log2)) << (6 - (sub_log2))) * ((1u << (sub_log2)) + 1u))
+
+__device__ __forceinline__ u32 uniform(u32 v) { return (u32)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ u64 uniform(u64 v) { return ((u64)uniform((u32)(v >> 32)) << 32) | uniform((u32)v); }
+
+// Orders the LDS accesses of one wave (a wave's LDS operations execute in order; this keeps the
+// compiler from moving them across).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// NP = 16-byte-unit passes per packet handled in one go (1..5), 0 = generic one pass at a time.
-template <int NP>
-__global__ __launch_bounds__((GS_READERS + 1) * WAVE) __attribute__((amdgpu_waves_per_eu(NP == 0 ? 7 : NP <= 3 ? 6 : NP == 4 ? 5 : 4))) void gather_accumulate_staged(
+template <int NP, int G, int D>
+__global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void gather_stream(
     Geo g, const uint8_t* __restrict__ packets, u64* __restrict__ pending, u64* __restrict__ bitmap,
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
     const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters, int whole_batch,
     u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
-    u32 sub, u32 sub_log2, u32 n_pass, u32 table_in_lds, u32 writer_prepares) {
-    extern __shared__ float4 sh_dyn[];              // buf[2][sub * stride / 16] float4, slots, bucket table
-    __shared__ double sh_sq[GS_READERS];
-    __shared__ u64 sh_elem[2][SUB];
-    __shared__ u32 sh_len[2][SUB];
-    __shared__ u32 sh_home[2][SUB];                 // accumulator copy each packet of the group goes to
-    __shared__ u32 sh_new[2][GS_READERS], sh_old[2][GS_READERS];   // per preparing wave: packets of the group that arrived in this batch / in an earlier one
-    __shared__ u32 sh_accepted[GS_READERS + 1];
-    __shared__ u32 sh_tally[(GS_READERS + 1) * 5];
-    // this launch is the first of the batch's gather launches: its block 0 books the index pass's tallies
-    const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0, sh_tally);
-    const u64 lo = bi.lo, hi = bi.hi;
-    if (hi == 0) return;                            // no candidate in this batch (uniform over the grid)
-    if (!whole_batch && batch_is_sparse(bi, g.W)) return;     // left to the direct kernel
+    u32 sub_log2, u32 n_piece, u32 table_in_lds) {
+    extern __shared__ u32 sh_slots[];               // per wave: slots [W rounded up][sub + 1]; then the bucket table
+    __shared__ u32 sh_tally[GS_WAVES * 5];
+    __shared__ u32 sh_accepted[GS_WAVES];
+    __shared__ double sh_sq[GS_WAVES];
     const u32 lane = lane_id();
-    const u32 wave = threadIdx.x / WAVE;
-    const u32 n_readers = blockDim.x / WAVE - 1;      // the last wave of the block is the writer
-    const u32 W = g.W;
-    const u32 upp = g.stride >> 4;                  // float4 units per packet
-    float4* buf0 = sh_dyn;
-    float4* buf1 = sh_dyn + sub * upp;
-    const u32 wpl = WAVE >> sub_log2;               // workers per 64-lane load of the index
-    const u32 slot_words = (W + wpl - 1) / wpl * wpl * sub;
-    u32* sh_slot0 = (u32*)(sh_dyn + 2 * sub * upp); // slot tables [W rounded up to a multiple of 64/sub][sub]:
-    u32* sh_slot1 = writer_prepares ? sh_slot0 + slot_words : sh_slot0;   // two when the next group is prepared during this one's gather
-    // bucket boundaries in LDS when the host made room for them (the span lookup of phase A is ten
-    // dependent loads)
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    const u32 W = g.W, sub = 1u << sub_log2, wpl = WAVE >> sub_log2, pitch = sub + 1;
+    const u32 team_words = GS_TEAM_LDS(W, sub_log2);
+    u32* const slots = sh_slots + wave * team_words;
     const u32* fs = g.first_seq;
     if (table_in_lds) {
-        u32* tab = sh_slot1 + slot_words;
+        u32* tab = sh_slots + GS_WAVES * team_words;
         for (u32 i = threadIdx.x; i <= g.B; i += blockDim.x) tab[i] = g.first_seq[i];
         fs = tab;
-        __syncthreads();
     }
+    // this launch is the first of the batch's gather launches: its block 0 books the index pass's tallies
+    const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0, sh_tally);   // has barriers: covers the table too
+    const u64 lo = bi.lo, hi = bi.hi;
+    if (hi == 0) return;                            // no candidate in this batch (uniform over the grid)
+    if (!whole_batch && batch_is_sparse(bi, W)) return;       // left to the direct kernel
     const u32 s_lane = lane & (sub - 1), w_sub = lane >> sub_log2;
-    const u32 submask = (1u << sub) - 1;
-    const u32 grp0 = (u32)(lo >> sub_log2) + blockIdx.x;
-    const u32 grp_end = (u32)((hi + sub - 1) >> sub_log2);
-    const u32 n_it = grp0 < grp_end ? (grp_end - grp0 + gridDim.x - 1) / gridDim.x : 0;
+    const u32 submask = sub == 32 ? 0xFFFFFFFFu : (1u << sub) - 1;
+        const bool leader = wave == 0;
+    const u32 grp_lo = (u32)__builtin_amdgcn_readfirstlane((int)(u32)(lo >> sub_log2));
+    const u32 grp_end = (u32)__builtin_amdgcn_readfirstlane((int)(u32)((hi + sub - 1) >> sub_log2));
     u32 accepted = 0;
     double sq = 0.0;      // change of the sum of squares of the stored values caused by this lane's packets
 
-    // ---- phase A of group `ia`: arrival index -> bitmap bits, slots, spans.  The calling wave takes
-    // the index loads w_first, w_first + w_step, ... (wpl workers each) and leaves the group's
-    // flags as seen by it in entry `part`; one of the callers also computes the spans.
-    const u32 n_parts = writer_prepares ? 1u : n_readers;
-    auto phase_a = [&](u32 ia, u32 w_first, u32 w_step, bool spans, u32 part) {
-        const u32 nb_buf = ia & 1;
-        u32* slot_tab = nb_buf ? sh_slot1 : sh_slot0;
-        const u32 seq0 = (grp0 + ia * gridDim.x) << sub_log2;
-        const u32 seq_l = seq0 + s_lane;
+    for (u64 grp = (u64)grp_lo + blockIdx.x; grp < grp_end; grp += gridDim.x) {
+        // ---- arrival index -> slots of the group's new packets, bitmap bits, spans
+        const u32 seq0 = (u32)grp << sub_log2, seq_l = seq0 + s_lane;
         const u32 word = seq0 >> 6, shift = seq0 & 63;
-        u32 new_or = 0, old_or = 0;
-        for (u32 w0 = w_first; w0 < W; w0 += w_step) {
-            const u32 w = w0 + w_sub;
-            const bool valid = w < W && seq_l < g.n_pkts;
-            u64 p = NONE64, bits = 0;
-            if (valid) {
-                p = pending[(u64)w * g.n_pkts + seq_l];
-                bits = bitmap[(u64)w * g.words_pw + word];
-            }
-            const bool has = p != NONE64;
-            const bool had = valid && ((bits >> (shift + s_lane)) & 1ull);   // delivered by an earlier batch
-            const bool fresh = has && !had;                     // a copy of a delivered packet is dropped
-            const u64 nb = __ballot(fresh);
-            slot_tab[w * sub + s_lane] = fresh ? (u32)p : NONE32;
-            if (has) pending[(u64)w * g.n_pkts + seq_l] = NONE64;   // leave the index empty
-            const u32 mine = (u32)(nb >> (w_sub * sub)) & submask;
-            if (s_lane == 0 && mine) atomicOr(&bitmap[(u64)w * g.words_pw + word], (u64)mine << shift);
-            const u64 ob = __ballot(had);
-            for (u32 j = 0; j < wpl; ++j) {
-                new_or |= (u32)(nb >> (j * sub)) & submask;
-                old_or |= (u32)(ob >> (j * sub)) & submask;
-            }
-            accepted += (u32)__popcll(nb);
-        }
-        if (spans && lane < sub && seq_l < g.n_pkts) {
+        u64 elem_l = 0;
+        u32 len_l = 0, home_l = pick, new_any = 0, old_any = 0;
+        if (lane < sub && seq_l < g.n_pkts) {
             const u32 b = find_bucket(fs, g.B, seq_l);
             const u64 start = (u64)(seq_l - fs[b]) * g.P;
             const u64 left = g.b_cnt[b] - start;
-            sh_elem[nb_buf][lane] = g.b_off[b] + start;
-            sh_len[nb_buf][lane] = left < g.P ? (u32)left : g.P;
+            elem_l = g.b_off[b] + start;
+            len_l = left < g.P ? (u32)left : g.P;
+            home_l = home[seq_l];                       // only meaningful (and only used) for spans written before
         }
-        if (lane == 0) { sh_new[nb_buf][part] = new_or; sh_old[nb_buf][part] = old_or; }
-    };
+        for (u32 w0 = 0; w0 < W; w0 += 4 * wpl) {
+            u64 p[4], bits[4], nb[4];
+            #pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const u32 w = w0 + j * wpl + w_sub;
+                p[j] = NONE64; bits[j] = 0;
+                if (w < W && seq_l < g.n_pkts) {
+                    p[j] = pending[(u64)w * g.n_pkts + seq_l];
+                    bits[j] = bitmap[(u64)w * g.words_pw + word];
+                }
+            }
+            #pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                nb[j] = 0;
+                if (w0 + j * wpl >= W) continue;
+                const u32 w = w0 + j * wpl + w_sub;
+                const bool had = (bits[j] >> (shift + s_lane)) & 1ull;      // delivered by an earlier batch
+                const bool fresh = p[j] != NONE64 && !had;                  // a copy of a delivered packet is dropped
+                nb[j] = __ballot(fresh);
+                slots[w * pitch + s_lane] = fresh ? (u32)p[j] : NONE32;
+                u64 n = nb[j], o = __ballot(had);
+                for (u32 k = 0; k < wpl; ++k) { new_any |= (u32)n & submask; old_any |= (u32)o & submask; n >>= sub; o >>= sub; }
+            }
+            __syncthreads();         // every wave of the block has read the index before the first one resets it
+            if (leader) {
+                #pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const u32 w = w0 + j * wpl + w_sub;
+                    if (p[j] != NONE64) pending[(u64)w * g.n_pkts + seq_l] = NONE64;   // leave the index empty
+                    const u32 mine = (u32)(nb[j] >> (w_sub * sub)) & submask;
+                    // a group of 8 or 16 sequence numbers owns its bytes of the bitmap: no atomics
+                    if (s_lane == 0 && mine) {
+                        uint8_t* bp = (uint8_t*)(bitmap + (u64)w * g.words_pw) + (seq0 >> 3);
+                        const u32 both = mine | ((u32)(bits[j] >> shift) & submask);
+                        if (sub_log2 == 4) *(uint16_t*)bp = (uint16_t)both; else *bp = (uint8_t)both;
+                    }
+                    accepted += (u32)__popcll(nb[j]);
+                }
+            }
+        }
+        new_any = uniform(new_any); old_any = uniform(old_any);
+        if (lane < sub && !((old_any >> lane) & 1u)) {
+            home_l = pick;
+            if (leader && ((new_any >> lane) & 1u)) home[seq_l] = (uint8_t)pick;
+        }
+        wave_lds_fence();
 
-    // Turn `it`, two schedules (the host picks by the number of workers; every LDS table exists
-    // twice, by turn parity):
-    //   writer_prepares   the reader waves gather group it (phase B) while the writer wave drains
-    //                     group it - 1 to the accumulator and then prepares group it + 1 (phase A):
-    //                     the readers never wait for the arrival index; one barrier per turn
-    //   otherwise         the reader waves share phase A of group it while the writer drains group
-    //                     it - 1; barrier; phase B; barrier
-    if (writer_prepares) {
-        if (wave == n_readers && n_it > 0) phase_a(0, 0, wpl, true, 0);
-        __syncthreads();
-    }
-    for (u32 it = 0; it <= n_it; ++it) {            // one extra turn so the writer drains the last group
-        const u32 cur = it & 1;
-        const u32 seq0 = (grp0 + it * gridDim.x) << sub_log2;
-        if (wave < n_readers) {
-            if (!writer_prepares && it < n_it) phase_a(it, wave * wpl, n_readers * wpl, wave == n_readers - 1, wave);
-        } else {
-            if (it > 0) {
-            // ---- writer: drain group it-1 from LDS to the accumulator (plain aligned stores; a span
-            // that earlier batches had written already has its old value folded in by the readers)
-            const u32 prev = cur ^ 1;
-            const float* src = (const float*)(prev ? buf1 : buf0);
-            u32 nf = 0;
-            for (u32 i = 0; i < n_parts; ++i) nf |= sh_new[prev][i];
-            for (u32 t = 0; t < sub; ++t) {
-                if (!((nf >> t) & 1u)) continue;
-                const u64 elem = sh_elem[prev][t];
-                const u32 len = sh_len[prev][t];
-                const float* pk = src + t * (g.stride >> 2) + 2;   // payload float j at pk[j]
-                float* acc = sh_home[prev][t] ? acc1 : acc0;
-                const u64 c0 = elem >> 2, c1 = (elem + len - 1) >> 2;
-                for (u64 c = c0 + lane; c <= c1; c += WAVE) {
-                    const u64 e0 = c << 2;
-                    float* d = acc + e0;
-                    if (e0 >= elem && e0 + 4 <= elem + len) {
-                        const u32 j = (u32)(e0 - elem);
-                        *(float4*)d = make_float4(pk[j], pk[j + 1], pk[j + 2], pk[j + 3]);
-                    } else {
-                        #pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const u64 e = e0 + k;
-                            if (e >= elem && e < elem + len) d[k] = pk[(u32)(e - elem)];
-                        }
+        // ---- payloads: items = pieces of NP KB of the group's packets; G workers' pieces make one
+        // step, D steps are in flight
+        u32 t_gen = 0, piece_gen = 0, t_next = 0, piece_next = wave;   // item the generator is at: piece of packet t_gen; (t_next, piece_next) comes after it
+        u64 left_gen = 0;               // its workers still to be loaded
+        u32 slot32 = NONE32;            // lane w: slot of worker w's copy of packet t_gen
+        f4v v[D][G][NP];
+        u32 tag[D];                     // t | piece << 8 | last << 30 | valid << 31
+        f4v a[NP];
+        #pragma unroll
+        for (int q = 0; q < NP; ++q) a[q] = f4v{0.f, 0.f, 0.f, 0.f};
+
+        auto issue = [&](int d) {
+            if (left_gen == 0) {
+                for (;;) {
+                    while (piece_next >= n_piece) { piece_next -= n_piece; ++t_next; }
+                    if (t_next >= sub) break;
+                    t_gen = t_next; piece_gen = piece_next;
+                    piece_next += GS_WAVES;
+                    if ((new_any >> t_gen) & 1u) {
+                        slot32 = lane < W ? slots[lane * pitch + t_gen] : NONE32;
+                        left_gen = uniform((u64)__ballot(slot32 != NONE32));
+                        break;
                     }
                 }
             }
+            const u32 len = (u32)__builtin_amdgcn_readlane((int)len_l, (int)t_gen);
+            const u32 bytes = ((len + 2 + 3) >> 2) * 16, skip = piece_gen * (NP * 1024u);
+            const u32 have = bytes > skip ? bytes - skip : 0;
+            u32 tg = left_gen ? 0x80000000u : 0u;
+            #pragma unroll
+            for (int j = 0; j < G; ++j) {
+                const bool any = left_gen != 0;
+                const u32 w = any ? (u32)__builtin_ctzll(left_gen) : 0u;
+                left_gen &= left_gen - 1;
+                const u32 slot = any ? (u32)__builtin_amdgcn_readlane((int)slot32, (int)w) : 0u;
+                // a buffer of `have` bytes at the piece (none for a worker without one): lanes beyond it
+                // read zeros and ask memory for nothing, so every step issues the same loads
+                __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+                    (void*)(packets + uniform((u64)slot * g.stride + skip)), 0, (int)uniform(any ? have : 0u), 0x00020000);
+                #pragma unroll
+                for (int q = 0; q < NP; ++q)
+                    v[d][j][q] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + q * 1024, 0, 2));
             }
-            // writes the tables of parity (it + 1) & 1, which the drain above has just read
-            if (writer_prepares && it + 1 < n_it) phase_a(it + 1, 0, wpl, true, 0);
-        }
-        if (!writer_prepares) __syncthreads();
-        if (wave < n_readers && it < n_it) {
-            // ---- phase B: payload gather, worker order, results to LDS
-            u32 new_any = 0, old_any = 0;
-            for (u32 i = 0; i < n_parts; ++i) { new_any |= sh_new[cur][i]; old_any |= sh_old[cur][i]; }
-            const u32* sh_slot = cur ? sh_slot1 : sh_slot0;
-            float4* dstbuf = cur ? buf1 : buf0;
-            if (NP > 0) {
-                for (u32 t = wave; t < sub; t += n_readers) {
-                    if (!((new_any >> t) & 1u)) continue;
-                    const u32 len = sh_len[cur][t];
-                    const u32 units = (len + 2 + 3) >> 2;        // 16-byte units holding header + payload
-                    const u32 slot32 = lane < W ? sh_slot[lane * sub + t] : NONE32;
-                    const u64 subm = __ballot(slot32 != NONE32);
-                    float4 a[NP > 0 ? NP : 1];
-                    sum_packet<(NP > 0 ? NP : 1)>(packets, g.stride, lane, units, subm, slot32, a);
-                    const bool rmw = (old_any >> t) & 1u;         // earlier batches already wrote this span
-                    u32 h = pick;
-                    if (rmw) h = home[seq0 + t];
-                    else if (lane == 0) home[seq0 + t] = (uint8_t)pick;
-                    if (lane == 0) sh_home[cur][t] = h;
-                    const float* acc = h ? acc1 : acc0;
-                    #pragma unroll
-                    for (int q = 0; q < (NP > 0 ? NP : 1); ++q) {
-                        const u32 u = q * WAVE + lane;
-                        if (u >= units) continue;
-                        const float* o = acc + sh_elem[cur][t] - 2 + 4 * u;       // packet float position 4u+c -> o[c]
-                        dstbuf[t * upp + u] = finish_unit(a[q], inv_w, rmw, o, u, len, sq);
-                    }
-                }
-            } else {
-            const u32 items = n_pass << sub_log2;
-            for (u32 i = wave; i < items; i += n_readers) {
-                const u32 t = i & (sub - 1), pass = i >> sub_log2;
-                if (!((new_any >> t) & 1u)) continue;
-                const u32 len = sh_len[cur][t];
-                const u32 units = (len + 2 + 3) >> 2;        // 16-byte units holding header + payload
-                const u32 u = pass * WAVE + lane;
-                if (pass * WAVE >= units) continue;
-                const bool active = u < units;
-                const u32 slot32 = lane < W ? sh_slot[lane * sub + t] : NONE32;
-                const u64 subm = __ballot(slot32 != NONE32);
-                float4 a = sum_unit(packets, g.stride, u, active, subm, slot32);
+            if (left_gen == 0) tg |= 0x40000000u;
+            tag[d] = tg | t_gen | (piece_gen << 8);
+        };
+        auto consume = [&](int d) {
+            #pragma unroll
+            for (int j = 0; j < G; ++j)
+                #pragma unroll
+                for (int q = 0; q < NP; ++q) a[q] += v[d][j][q];
+            if ((tag[d] & 0xC0000000u) == 0xC0000000u) {
+                const u32 t = tag[d] & 0xFFu, piece = (tag[d] >> 8) & 0x3FFFFFu;
+                const u32 len = (u32)__builtin_amdgcn_readlane((int)len_l, (int)t);
+                const u64 elem = ((u64)(u32)__builtin_amdgcn_readlane((int)(u32)(elem_l >> 32), (int)t) << 32) |
+                                 (u32)__builtin_amdgcn_readlane((int)(u32)elem_l, (int)t);
+                const u32 h = (u32)__builtin_amdgcn_readlane((int)home_l, (int)t);
                 const bool rmw = (old_any >> t) & 1u;
-                u32 h = pick;                       // every pass of packet t derives and records the same value
-                if (rmw) h = home[seq0 + t];
-                else if (lane == 0) home[seq0 + t] = (uint8_t)pick;
-                if (lane == 0) sh_home[cur][t] = h;
-                if (active) {
-                    const float* o = (h ? acc1 : acc0) + sh_elem[cur][t] - 2 + 4 * u;   // packet float position 4u+c -> o[c]
-                    dstbuf[t * upp + u] = finish_unit(a, inv_w, rmw, o, u, len, sq);
+                float* dst = (h ? acc1 : acc0) + elem - 2;            // float position i of the packet -> dst[i]
+                const bool tail = (len + 2) & 3u;                     // the last unit holds floats beyond the payload
+                #pragma unroll
+                for (int q = 0; q < NP; ++q) {
+                    const u32 u = (piece * NP + q) * WAVE + lane;
+                    f4v r = a[q] * inv_w;
+                    if (q == 0 && u == 0) r.x = r.y = 0.f;            // the header
+                    if (tail && 4 * u + 2 > len) {                    // float position i is payload while i < len + 2
+                        if (4 * u >= len + 2) r.x = 0.f;
+                        if (4 * u + 1 >= len + 2) r.y = 0.f;
+                        if (4 * u >= len) r.z = 0.f;
+                        r.w = 0.f;
+                    }
+                    float* o = dst + 4 * u;
+                    const bool full = u > 0 && 4 * u + 2 <= len;
+                    const bool v0 = u > 0 && 4 * u < len + 2, v1 = u > 0 && 4 * u + 1 < len + 2, v2 = 4 * u < len, v3 = 4 * u + 1 < len;
+                    if (rmw) {                                        // result = old value + this batch's sum
+                        f4v ov = {0.f, 0.f, 0.f, 0.f};
+                        if (full) ov = *(const f4v_a4*)o;
+                        else {
+                            if (v0) ov.x = o[0];
+                            if (v1) ov.y = o[1];
+                            if (v2) ov.z = o[2];
+                            if (v3) ov.w = o[3];
+                        }
+                        sq -= (double)ov.x * (double)ov.x; sq -= (double)ov.y * (double)ov.y;
+                        sq -= (double)ov.z * (double)ov.z; sq -= (double)ov.w * (double)ov.w;
+                        r = ov + r;
+                    }
+                    sq += (double)r.x * (double)r.x; sq += (double)r.y * (double)r.y;
+                    sq += (double)r.z * (double)r.z; sq += (double)r.w * (double)r.w;
+                    if (full) *(f4v_a4*)o = r;
+                    else if (u == 0) {
+                        if (v2) o[2] = r.z;
+                        if (v3) o[3] = r.w;
+                    } else if (tail) {
+                        if (v0) o[0] = r.x;
+                        if (v1) o[1] = r.y;
+                        if (v2) o[2] = r.z;
+                    }
+                    a[q] = f4v{0.f, 0.f, 0.f, 0.f};
                 }
             }
+        };
+        #pragma unroll
+        for (int d = 0; d < D; ++d) issue(d);
+        for (;;) {
+            bool more = false;
+            #pragma unroll
+            for (int d = 0; d < D; ++d) {
+                consume(d);
+                issue(d);
+                more = more || (tag[d] >> 31);
             }
+            if (!more) break;
         }
-        __syncthreads();
     }
     // accepted packets and sum-of-squares change of this block: plain adds to the block's own rows
     sq = wave_sum_f64(sq);
-    if (lane == 0) {
-        sh_accepted[wave] = accepted;               // counted by whichever waves ran phase A
-        if (wave < n_readers) sh_sq[wave] = sq;
-    }
+    if (lane == 0) { sh_accepted[wave] = accepted; sh_sq[wave] = sq; }
     __syncthreads();
     if (threadIdx.x == 0) {
         u32 total = 0;
         double t = 0.0;
-        for (u32 i = 0; i <= n_readers; ++i) total += sh_accepted[i];
-        for (u32 i = 0; i < n_readers; ++i) t += sh_sq[i];
+        #pragma unroll
+        for (int i = 0; i < GS_WAVES; ++i) { total += sh_accepted[i]; t += sh_sq[i]; }
         if (total) { accept_rows[blockIdx.x] += total; sumsq_rows[blockIdx.x] += t; }
     }
 }
@@ -1106,7 +1095,7 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
                                                      float* out, int scale_mode, float wf, int move_home,
                                                      double* __restrict__ partials, u32 n_work_blocks,
                                                      const double* __restrict__ sumsq_rows, const u64* __restrict__ accept_rows,
-                                                     u32 rows_staged, u32 rows_direct, u32 row_pitch,
+                                                     u32 rows_stream, u32 rows_direct, u32 row_pitch,
                                                      u64* __restrict__ counters, u64* __restrict__ mailbox) {
     __shared__ double wsum[4];
     __shared__ u64 asum[4];
@@ -1118,14 +1107,14 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
         // packets), and the round's counters mirrored into the host mailbox:
         // mailbox[1] = sum of squares (when the gather kept it), mailbox[8..11] = accepted,
         // candidates, stale, invalid
-        // Only the rows that a launch of this round can have written are read: rows_staged of the
-        // staged kernel's, rows_direct of the direct kernel's (row_pitch apart); the rest are zero.
+        // Only the rows that a launch of this round can have written are read: rows_stream of
+        // gather_stream's, rows_direct of the direct kernel's (row_pitch apart); the rest are zero.
         double s = 0.0;
         u64 a = 0;
         for (u32 k = 0; k < 2; ++k) {
             const double* sr = sumsq_rows + (size_t)k * row_pitch;
             const u64* ar = accept_rows + (size_t)k * row_pitch;
-            const u32 n = k ? rows_direct : rows_staged;
+            const u32 n = k ? rows_direct : rows_stream;
             for (u32 i0 = 0; i0 < n; i0 += 4 * 256) {      // four independent loads of each kind in flight
                 double sv[4]; u64 av[4];
                 #pragma unroll
@@ -1357,8 +1346,8 @@ struct dblp_ctx {
     hipEvent_t cls_ev[2];
     u32* d_need; u32* d_missing; u64* d_offs; double* d_partials;
     u32* d_block_tallies;   // [IDX_BLOCKS_PER_CU * n_cus][5], written by index_arrivals
-    u64* d_accept_rows;     // [2][ACCEPT_ROWS] accepted packets per gather block (staged grid, direct grid)
-    u32 rows_used[2];       // largest staged / direct gather grid launched in the open round
+    u64* d_accept_rows;     // [2][ACCEPT_ROWS] accepted packets per gather block (gather_stream's grid, the direct kernel's)
+    u32 rows_used[2];       // largest gather_stream / direct gather grid launched in the open round
     int result_in_place;    // the form of the last dblp_finalize (in place until one says otherwise): prices the second copy
     double* d_sumsq_rows;   // [2][ACCEPT_ROWS] sum of squares of what each gather block stored (same allocation)
     u64* h_mailbox;         // pinned host memory, 16 x u64, also mapped into the device
@@ -1879,57 +1868,49 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
     }
     const float inv_w = c->fold ? 1.0f / (float)g.W : 1.0f;   // exact for the powers of two it is used with
     {
-        u32 sub = SUB, sub_log2 = 4;
-        while (sub >= 2 && 2u * sub * g.stride > GS_LDS_BUDGET) { sub >>= 1; --sub_log2; }
-        // Which gather kernel: the staged one for dense batches, the direct one for sparse ones
-        // (and for packets too long to stage).  Where the number of arrivals settles it, only that
-        // one is launched: at least one arrival per SPARSE_DIV (worker, seq) pairs of the whole
-        // round is dense whatever range it touches; fewer than one per 8 * SPARSE_DIV pairs is
-        // taken as sparse.  In between both are launched and each decides on the device, from the
-        // sequence range the index pass found, whether the batch is its own.
+        // Which gather kernel: the streaming one for dense batches, the direct one for sparse ones.
+        // Where the number of arrivals settles it, only that one is launched: at least one arrival per
+        // SPARSE_DIV (worker, seq) pairs of the whole round is dense whatever range it touches; fewer
+        // than one per 8 * SPARSE_DIV pairs is taken as sparse.  In between both are launched and each
+        // decides on the device, from the sequence range the index pass found, whether the batch is its own.
         const u64 pairs = (u64)g.W * g.n_pkts;
-        const bool can_stage = sub >= 2;
-        const bool surely_dense = can_stage && n_arrivals * SPARSE_DIV >= pairs;
-        const bool surely_sparse = n_arrivals * SPARSE_DIV * 8 < pairs;
-        const bool launch_staged = can_stage && !surely_sparse;
+        const bool surely_dense = n_arrivals * SPARSE_DIV >= pairs;
+        const bool launch_stream = surely_dense || n_arrivals * SPARSE_DIV * 8 >= pairs;
         const bool launch_direct = !surely_dense;
-        if (launch_staged) {   // two groups of packets fit in LDS: readers + writer wave
-            const u32 wpl = WAVE / sub;
-            // Up to GS_WRITER_PREPARES_MAX_W workers the writer wave prepares the next group while the
-            // readers gather this one (measured: 4-6 % off the launch with 8 workers, 2 % with 16, but
-            // 3.5 % slower with 32, where the readers share the index loads of a group instead).
-            const u32 writer_prepares = g.W <= GS_WRITER_PREPARES_MAX_W ? 1u : 0u;
-            // two packet buffers, one or two slot tables, and the bucket table when it fits a block's LDS limit
-            size_t lds = 2ull * sub * g.stride + (writer_prepares ? 2 : 1) * (size_t)((g.W + wpl - 1) / wpl * wpl) * sub * sizeof(u32);
-            const size_t table = ((size_t)g.B + 1) * sizeof(u32);
-            const u32 table_in_lds = table <= IDX_TABLE_LDS_MAX && lds + table <= 64u * 1024u ? 1u : 0u;
-            if (table_in_lds) lds += table;
-            const u64 groups = ((u64)g.n_pkts + sub - 1) / sub;
+        if (launch_stream) {
+            // Packets of up to 5 KB are one piece, longer ones are cut evenly into pieces of 3 or 4 KB.
             const u32 n_pass = (g.units + WAVE - 1) / WAVE;
-            // Block shape: packets of up to 2 KB (one or two 1 KB passes) go fastest with 4 reader waves
-            // and three blocks per CU (measured: 5 % off the launch with 8 workers, 0.6 % with 32);
-            // longer packets with up to 8 reader waves and two blocks per CU (three: 9 % slower at 4 KB).
-            const u32 readers_max = n_pass <= 2 ? (u32)GS_READERS_SHORT : (u32)GS_READERS;
-            const u32 per_cu_max = n_pass <= 2 ? (u32)GS_MAX_PER_CU_SHORT : (u32)GS_MAX_PER_CU;
-            const u32 readers = sub < readers_max ? sub : readers_max;   // a reader wave takes whole packets
-            u32 per_cu = (u32)((160u * 1024u) / (lds + 1024));
-            if (per_cu > 32 / (readers + 1)) per_cu = 32 / (readers + 1);
-            if (per_cu > per_cu_max) per_cu = per_cu_max;
-            if (per_cu < 1) per_cu = 1;
-            void (*kern)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, int, u64*, double*, float, u32, u32, u32, u32, u32) =
-                n_pass == 1 ? gather_accumulate_staged<1> : n_pass == 2 ? gather_accumulate_staged<2>
-                : n_pass == 3 ? gather_accumulate_staged<3> : n_pass == 4 ? gather_accumulate_staged<4>
-                : n_pass == 5 ? gather_accumulate_staged<5> : gather_accumulate_staged<0>;
+            const u32 n_piece = n_pass <= 5 ? 1 : (n_pass + 3) / 4, np = (n_pass + n_piece - 1) / n_piece;
+            // Groups of 16 packets; of 8 when the round is too short to give every CU two of them (4 x 1040
+            // bytes, 4096 packets: 11.7 against 12.6 us).  Longer rounds pay for the shorter rows of the
+            // index (8 x 1472 B, 340 k packets: 920 against 893 us), and packets in pieces fill the block's
+            // waves from 16 as well (64 KB datagrams: 224 us with 16, 232 with 8).
+            const u32 sub_log2 = n_piece == 1 && g.n_pkts < 2u * 16u * (u32)c->n_cus ? 3 : 4;
+            size_t lds = (size_t)GS_WAVES * GS_TEAM_LDS(g.W, sub_log2) * sizeof(u32);
+            const size_t table = ((size_t)g.B + 1) * sizeof(u32);
+            const u32 table_in_lds = table <= IDX_TABLE_LDS_MAX ? 1u : 0u;
+            if (table_in_lds) lds += table;
+            const u64 groups = ((u64)g.n_pkts + (1u << sub_log2) - 1) >> sub_log2;
+            // One to three workers: a step is one worker's piece, four of them in flight, and six blocks per
+            // CU (1 worker: 45 us, against 54 with three blocks, 68 with steps of four workers).  More: 4 to
+            // 8 KB per step, two steps in flight, three blocks per CU for short packets, two for long ones
+            // (8992 B: 930 against 940 us; more blocks only spread the DRAM accesses over more open rows).
+            const bool few = g.W < 4;
+            const u32 per_cu = few ? 6 : np <= 2 ? 3 : 2;
+            void (*kern)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, int, u64*, double*, float, u32, u32, u32) =
+                np == 1 ? (few ? gather_stream<1, 1, 4> : gather_stream<1, 4, 2>)
+                : np == 2 ? (few ? gather_stream<2, 1, 4> : gather_stream<2, 4, 2>)
+                : np == 3 ? (few ? gather_stream<3, 1, 3> : gather_stream<3, 2, 2>)
+                : np == 4 ? (few ? gather_stream<4, 1, 3> : gather_stream<4, 2, 2>) : gather_stream<5, 1, 3>;
             const u32 grid = grid_for(c, groups, per_cu);
             if (grid > c->rows_used[0]) c->rows_used[0] = grid;
             ProfScope ps(c, DBLP_K_GATHER);
-            hipLaunchKernelGGL(kern, dim3(grid), dim3((readers + 1) * WAVE),
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(GS_WAVES * WAVE),
                                lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap, c->d_acc[0],
                                c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
-                               surely_dense ? 1 : 0, c->d_accept_rows, c->d_sumsq_rows, inv_w, sub, sub_log2, n_pass, table_in_lds,
-                               writer_prepares);
+                               surely_dense ? 1 : 0, c->d_accept_rows, c->d_sumsq_rows, inv_w, sub_log2, n_piece, table_in_lds);
         }
-        if (launch_direct) {   // sparse batches, and packets too long to stage: direct stores from the gathering waves
+        if (launch_direct) {   // sparse batches
             const u64 groups = ((u64)g.n_pkts + SUB - 1) / SUB;
             size_t lds = (size_t)((g.W + 3) / 4 * 4) * SUB * sizeof(u32);
             const size_t table = ((size_t)g.B + 1) * sizeof(u32);
@@ -1941,8 +1922,8 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
             hipLaunchKernelGGL(gather_accumulate, dim3(grid), dim3(GA_WAVES * WAVE),
                                lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap, c->d_acc[0],
                                c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
-                               launch_staged ? 0 : 1, c->d_accept_rows + ACCEPT_ROWS, c->d_sumsq_rows + ACCEPT_ROWS, inv_w,
-                               launch_staged ? 1 : 0, table_in_lds);
+                               launch_stream ? 0 : 1, c->d_accept_rows + ACCEPT_ROWS, c->d_sumsq_rows + ACCEPT_ROWS, inv_w,
+                               launch_stream ? 1 : 0, table_in_lds);
         }
     }
     LAUNCH_CHECK(c, "apply_arrivals");

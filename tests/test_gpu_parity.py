@@ -71,9 +71,9 @@ CASES = [
     (3, [4_000_000], 1000, 0.01, 8_000),                                     # one bucket = whole-round accounting
     (2, [65535 * 3 + 1], 65535, 0.0, 0),                                     # maximum packet length
     (4, [600 * 40 + 7, 100], 600, 0.05, 30_000),                             # three 1 KB passes per packet
-    (3, [1400 * 33 + 5], 1400, 0.05, 30_000),                                # six passes: generic staged path
-    (2, [3000 * 9 + 1], 3000, 0.1, 50_000),                                  # 12 KB packets: two-packet groups
-    (2, [4000 * 5 + 3], 4000, 0.1, 50_000),                                  # too long to stage: direct stores
+    (3, [1400 * 33 + 5], 1400, 0.05, 30_000),                                # six passes: two pieces of three
+    (2, [3000 * 9 + 1], 3000, 0.1, 50_000),                                  # 12 KB packets: three pieces
+    (2, [4000 * 5 + 3], 4000, 0.1, 50_000),                                  # 16 KB packets: four pieces
 ]
 
 
@@ -103,6 +103,26 @@ def test_parity_small_and_ragged_in_place(W, sizes, P, loss, ppm, result):
     one = run_iteration(g1, sc, ppm)
     assert np.array_equal(one["out"].view(np.uint32), got["out"].view(np.uint32))
     assert one["norm"] == got["norm"] and one["counters"] == got["counters"]
+
+
+# 16-byte units per packet at the edges of the 1 KB passes (64, 65, 128, 129, 320 units) and of the cut
+# into pieces (321 units: two pieces; 6, 9 and 16 passes), each with a last float that fills its unit or
+# not; few and many workers; groups of 8 and of 16 packets (8192 packets of a 256-CU chip on).  The
+# tolerance is the parity tests' own: a 32-bit sum in worker order against the addends' magnitude.
+STREAM_CASES = [(W, P, n) for W, P, n in (
+    (1, 254, 700), (3, 255, 40), (4, 254, 41), (5, 257, 40), (1, 510, 60), (3, 513, 33), (17, 510, 19), (33, 514, 17),
+    (2, 1278, 20), (4, 1278, 18), (4, 1279, 18), (64, 1279, 9), (3, 1537, 17), (8, 1535, 17), (6, 2243, 16), (3, 4094, 5),
+    (1, 6, 8191), (4, 6, 8192), (19, 5, 8193), (2, 1, 9000))]
+
+
+@pytest.mark.parametrize("W,P,n", STREAM_CASES)
+def test_dense_gather_at_the_edges_of_passes_pieces_and_groups(W, P, n):
+    """Dense batches through every instance of the streaming gather: two buckets, the second with a
+    short last packet and a start that is not a multiple of 4 elements; a tenth of the packets lost."""
+    sc = build_scenario(mk(W, [P * (n // 3) + 1, P * (n - n // 3) - (P // 2)], P, 0.1))
+    for kw in (dict(), dict(queue=True, result="caller") if W & (W - 1) == 0 else dict(queue=True)):
+        stats, got, ref = run_both(sc, 1_000_000, **kw)
+        assert stats["rel_to_addends"] <= FLOAT_TOL
 
 
 # ------------------------------------------------------------------------------ two accumulator copies
