@@ -306,7 +306,7 @@ int dblp_get_prev_norm(const dblp_ctx* ctx, double* h_norm, int* h_have);
 #define DBLP_K_GATHER 1   /* payload gather + accumulate, streaming kernel (dense batches) */
 #define DBLP_K_PROBE 2    /* loss count + prefix + retransmit list (three launches, one bracket) */
 #define DBLP_K_FINALIZE 3 /* zero-fill mean + partial sums of squares */
-#define DBLP_K_GATHER_DIRECT 4 /* the same, direct kernel (sparse batches) */
+#define DBLP_K_GATHER_DIRECT 4 /* the same, its instance for sparse batches */
 #define DBLP_K_COUNT 5
 int dblp_profile_enable(dblp_ctx* ctx, int on);
 int dblp_profile_read(dblp_ctx* ctx, int kernel, double* h_total_ms, uint64_t* h_launches);

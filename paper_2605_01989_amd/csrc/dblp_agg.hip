@@ -6,7 +6,7 @@
 //                    (arrival rank << 32 | slot) into the arrival index `pending[w][seq]`, so the
 //                    earliest copy of a packet in the batch wins; per-block tallies (stale, invalid,
 //                    candidates, touched seq range) that every gather block adds up for itself
-//   gather_stream / gather_accumulate (dense / sparse batches)
+//   gather_stream (one instance for sparse batches, the others for dense ones)
 //                    organised by OUTPUT packet: a block takes a group of consecutive sequence
 //                    numbers, reads the index entries of all workers, drops copies of packets
 //                    that an earlier batch delivered, sets the bitmap bits, then streams the
@@ -113,15 +113,7 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
     return __longlong_as_double((long long)(((u64)hi << 32) | lo));
 }
 
-// 16-byte load with the non-temporal hint: the payload is read exactly once, so it should not
-// displace the accumulator and index lines that are being written in L2 / the memory-side cache
-// (measured: 8 % off the payload pass).  Headers are NOT loaded this way in the index pass:
-// their lines are read again by the payload pass and are worth keeping.
 typedef float f4v __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float4 ld_stream4(const void* p) {
-    const f4v t = __builtin_nontemporal_load((const f4v*)p);
-    return make_float4(t.x, t.y, t.z, t.w);
-}
 
 // 16-byte store with the non-temporal hint (the sender's packets are not read again by the sender).
 typedef u32 u4v __attribute__((ext_vector_type(4)));
@@ -455,259 +447,21 @@ __device__ __forceinline__ BatchInfo fold_index_tallies(const u32* __restrict__ 
 // ------------------------------------------------------------------------------------------
 // receiver step 2: gather payloads per output packet and accumulate
 // ------------------------------------------------------------------------------------------
-#ifndef GROUP
-#define GROUP 8             // payload loads kept in flight per lane
-#endif
-#ifndef GA_WAVES
-#define GA_WAVES 8          // waves per block
-#endif
-#ifndef GA_BLOCKS_PER_CU
-#define GA_BLOCKS_PER_CU 4
-#endif
-#define SUB 16              // consecutive sequence numbers a block handles at a time (divides 64)
 #define NONE32 0xFFFFFFFFu
 
 // A batch is sparse when it holds fewer than one packet per SPARSE_DIV (worker, seq) pairs of the
-// sequence range it touches (retransmission batches).  Sparse batches take the direct kernel (it skips
-// groups without arrivals many at a time), dense ones gather_stream; where the host cannot tell, both
-// are launched and the one whose regime it is not returns at once.
+// sequence range it touches (retransmission batches).  Sparse batches take an instance of gather_stream
+// of their own (below); where the host cannot tell, both are launched and the one whose regime it is not
+// returns at once.
 #define SPARSE_DIV 8
 __device__ __forceinline__ bool batch_is_sparse(const BatchInfo& bi, u32 W) {
     return bi.cand * SPARSE_DIV < (bi.hi - bi.lo) * W;
 }
 
-// Sum the payload unit `u` (16 bytes at offset 16u of each packet) over the workers in `sub`
-// (bit w set = worker w delivered this packet in this batch), ascending worker order.
-// slot32 holds worker w's slot in lane w.
-__device__ __forceinline__ float4 sum_unit(const uint8_t* __restrict__ packets, u32 stride, u32 u, bool active,
-                                           u64 sub, u32 slot32) {
-    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-    while (sub) {
-        float4 v[GROUP];
-        #pragma unroll
-        for (int j = 0; j < GROUP; ++j) {
-            v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (sub) {
-                const u32 w = (u32)__builtin_ctzll(sub);
-                sub &= sub - 1;
-                const u32 slot = (u32)__builtin_amdgcn_readlane((int)slot32, (int)w);
-                if (active) v[j] = *(const float4*)(packets + (u64)slot * stride + 16ull * u);
-            }
-        }
-        #pragma unroll
-        for (int j = 0; j < GROUP; ++j) { a.x += v[j].x; a.y += v[j].y; a.z += v[j].z; a.w += v[j].w; }
-    }
-    return a;
-}
-
-// Epilogue of one 16-byte unit of a summed packet: scale, fold in the old accumulator value when the
-// span was written before (rmw is uniform over the wave), and keep the running sum of squares of
-// what is stored.  Written without per-element branches: positions outside the payload (the two
-// header words of unit 0, the tail beyond len) are carried along and masked out of the sum of
-// squares only; the writer never reads them.  o points at the accumulator element that packet
-// float position 4u corresponds to (only dereferenced where the position is payload).
-__device__ __forceinline__ float4 finish_unit(float4 a, float inv_w, bool rmw, const float* o, u32 u, u32 len, double& sq) {
-    float qv[4] = {a.x * inv_w, a.y * inv_w, a.z * inv_w, a.w * inv_w};
-    bool ok[4];
-    #pragma unroll
-    for (int c = 0; c < 4; ++c) { const u32 i4 = 4 * u + c; ok[c] = i4 >= 2 && i4 - 2 < len; }
-    if (rmw) {                                    // result = old value + this batch's sum
-        float ov[4];
-        #pragma unroll
-        for (int c = 0; c < 4; ++c) ov[c] = ok[c] ? o[c] : 0.f;      // four loads in flight, one wait
-        #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            sq -= (double)ov[c] * (double)ov[c];
-            qv[c] = ov[c] + qv[c];
-        }
-    }
-    #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const double d = (double)(ok[c] ? qv[c] : 0.f);
-        sq += d * d;
-    }
-    return make_float4(qv[0], qv[1], qv[2], qv[3]);
-}
-
-// One block per group of SUB consecutive sequence numbers, grid-stride over the groups the
-// batch touched.
-//   phase A  64 lanes = 4 workers x 16 packets per load of the arrival index: ballot -> new
-//            bitmap bits (one atomicOr per worker and group), slots in LDS, index
-//            entries reset; the 16 packets' element spans are computed by 16 lanes in parallel
-//   phase B  the waves split the 16 packets: per packet, 16-byte payload loads from every
-//            worker that delivered it, summed in registers in worker order, one write of the span
-//
-// The accumulator may exist in two copies (acc0, acc1; acc1 == acc0 when there is one): a span
-// written for the first time in this round goes to copy `pick` and home[seq] records it; a span
-// that earlier batches wrote is read and rewritten where home[seq] says it lives.
-__global__ __launch_bounds__(GA_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu(8))) void gather_accumulate(Geo g, const uint8_t* __restrict__ packets,
-                                                                    u64* __restrict__ pending, u64* __restrict__ bitmap,
-                                                                    float* acc0, float* acc1,
-                                                                    uint8_t* __restrict__ home, u32 pick,
-                                                                    const u32* __restrict__ block_tallies, u32 n_tally_rows,
-                                                                    u64* __restrict__ counters, int tally_owner,
-                                                                    u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows,
-                                                                    float inv_w, int only_if_sparse, u32 table_in_lds) {
-    extern __shared__ u32 sh_slot[];           // [W rounded up to 4][SUB], then the bucket boundaries when table_in_lds
-    __shared__ u64 sh_elem[SUB];
-    __shared__ u32 sh_len[SUB], sh_home[SUB];
-    __shared__ u32 sh_new[GA_WAVES], sh_old[GA_WAVES];
-    __shared__ double sh_sq[GA_WAVES];
-    __shared__ u32 sh_tally[GA_WAVES * 5];
-    __shared__ u32 sh_mask[2][2];
-    const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, tally_owner && blockIdx.x == 0, sh_tally);
-    const u64 lo = bi.lo, hi = bi.hi;
-    if (hi == 0) return;                                    // no candidate in this batch
-    if (only_if_sparse && !batch_is_sparse(bi, g.W)) return;
-    const u32 lane = lane_id();
-    const u32 wave = threadIdx.x / WAVE;
-    const u32 W = g.W;
-    const u32 s_lane = lane & (SUB - 1), w_sub = lane / SUB;   // packet and worker-within-load of this lane
-    const u32 grp_lo = (u32)(lo / SUB), grp_end = (u32)((hi + SUB - 1) / SUB);
-    u32 accepted = 0;
-    double sq = 0.0;      // change of the sum of squares of the stored values caused by this lane's writes
-    // bucket boundaries in LDS when the host made room for them: the span lookup is a chain of
-    // dependent loads that every packet of a small batch would wait for
-    const u32* fs = g.first_seq;
-    if (table_in_lds) {
-        u32* tab = sh_slot + (W + 3) / 4 * 4 * SUB;
-        for (u32 i = threadIdx.x; i <= g.B; i += blockDim.x) tab[i] = g.first_seq[i];
-        fs = tab;
-        __syncthreads();
-    }
-
-    // Every block walks the groups of the touched range grid-stride.  When most groups hold no
-    // arrival at all (a small retransmission batch spread over the round: fewer than one candidate
-    // per four groups), the block first looks through the arrival index of up to 64 of its groups at
-    // a time, one wave per group and all loads in flight together, and then walks only the groups
-    // that hold an entry.
-    const bool skim = bi.cand * (4 * SUB) < hi - lo;
-    u32 grp_next = grp_lo + blockIdx.x;
-    u32 tile_base = 0, tile_no = 0;
-    u64 tile_mask = 0;
-    for (;;) {
-        u32 grp;
-        if (skim) {      // block-uniform control flow throughout: the barriers below are reached by all
-            while (tile_mask == 0 && grp_next < grp_end) {
-                u32* mask = sh_mask[tile_no & 1];      // two buffers: the next look clears one while this one is read
-                ++tile_no;
-                tile_base = grp_next;                  // group k of the tile is tile_base + k * gridDim.x
-                const u32 left = (grp_end - grp_next + gridDim.x - 1) / gridDim.x;
-                const u32 n_g = left < 64 ? left : 64;
-                grp_next = left <= 64 ? grp_end : grp_next + 64 * gridDim.x;
-                if (threadIdx.x < 2) mask[threadIdx.x] = 0;
-                __syncthreads();
-                u32 m0 = 0, m1 = 0;
-                for (u32 k = wave; k < n_g; k += GA_WAVES) {
-                    const u32 seq_k = (tile_base + k * gridDim.x) * SUB + s_lane;
-                    bool any = false;
-                    #pragma unroll 4
-                    for (u32 w0 = 0; w0 < W; w0 += 4) {
-                        const u32 w = w0 + w_sub;
-                        if (w < W && seq_k < g.n_pkts) any |= pending[(u64)w * g.n_pkts + seq_k] != NONE64;
-                    }
-                    if (__ballot(any)) { if (k < 32) m0 |= 1u << k; else m1 |= 1u << (k - 32); }
-                }
-                if (lane == 0 && (m0 | m1)) { atomicOr(&mask[0], m0); atomicOr(&mask[1], m1); }
-                __syncthreads();
-                tile_mask = (u64)mask[0] | ((u64)mask[1] << 32);
-            }
-            if (tile_mask == 0) break;
-            grp = tile_base + (u32)__builtin_ctzll(tile_mask) * gridDim.x;
-            tile_mask &= tile_mask - 1;
-        } else {
-            grp = grp_next;
-            if (grp >= grp_end) break;
-            grp_next += gridDim.x;
-        }
-        const u32 seq0 = grp * SUB;
-        const u32 seq_l = seq0 + s_lane;
-        const u32 word = seq0 >> 6, shift = seq0 & 63;
-        u32 new_or = 0, old_or = 0;
-        for (u32 w0 = wave * 4; w0 < W; w0 += GA_WAVES * 4) {
-            const u32 w = w0 + w_sub;
-            const bool valid = w < W && seq_l < g.n_pkts;
-            u64 p = NONE64, bits = 0;
-            if (valid) {
-                p = pending[(u64)w * g.n_pkts + seq_l];
-                bits = bitmap[(u64)w * g.words_pw + word];
-            }
-            const bool has = p != NONE64;
-            const bool had = valid && ((bits >> (shift + s_lane)) & 1ull);   // delivered by an earlier batch
-            const bool fresh = has && !had;                                  // a copy of a delivered packet is dropped
-            const u64 nb = __ballot(fresh);
-            sh_slot[w * SUB + s_lane] = fresh ? (u32)p : NONE32;
-            if (has) pending[(u64)w * g.n_pkts + seq_l] = NONE64;   // leave the index empty for the next batch
-            const u32 mine = (u32)(nb >> (w_sub * SUB)) & 0xFFFFu;  // this lane's worker: new bits of the group
-            if (s_lane == 0 && mine) atomicOr(&bitmap[(u64)w * g.words_pw + word], (u64)mine << shift);
-            const u64 ob = __ballot(had);
-            #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                new_or |= (u32)(nb >> (j * SUB)) & 0xFFFFu;
-                old_or |= (u32)(ob >> (j * SUB)) & 0xFFFFu;
-            }
-            accepted += (u32)__popcll(nb);
-        }
-        if (wave == GA_WAVES - 1 && lane < SUB && seq_l < g.n_pkts) {
-            const u32 hm = home[seq_l];                      // only meaningful (and only used) for spans written before
-            const u32 b = find_bucket(fs, g.B, seq_l);
-            const u64 start = (u64)(seq_l - fs[b]) * g.P;    // packet_span with the boundary from the table at hand
-            const u64 left = g.b_cnt[b] - start;
-            sh_elem[lane] = g.b_off[b] + start; sh_len[lane] = left < g.P ? (u32)left : g.P; sh_home[lane] = hm;
-        }
-        if (lane == 0) { sh_new[wave] = new_or; sh_old[wave] = old_or; }
-        __syncthreads();
-        u32 new_any = 0, old_any = 0;
-        #pragma unroll
-        for (int i = 0; i < GA_WAVES; ++i) { new_any |= sh_new[i]; old_any |= sh_old[i]; }
-
-        for (u32 t = wave; t < SUB; t += GA_WAVES) {
-            if (!((new_any >> t) & 1u)) continue;
-            const bool rmw = (old_any >> t) & 1u;            // span already holds earlier arrivals
-            const u64 elem = sh_elem[t];
-            const u32 len = sh_len[t];
-            const u32 slot32 = lane < W ? sh_slot[lane * SUB + t] : NONE32;
-            const u64 sub = __ballot(slot32 != NONE32);
-            const u32 units = (len + 2 + 3) >> 2;            // 16-byte units holding header + payload
-            u32 h = pick;
-            if (rmw) h = sh_home[t];
-            else if (lane == 0) home[seq0 + t] = (uint8_t)pick;
-            float* dst0 = (h ? acc1 : acc0) + elem - 2;      // float position i of the packet -> dst0[i]
-            for (u32 u0 = 0; u0 < units; u0 += WAVE) {
-                const u32 u = u0 + lane;
-                const bool active = u < units;
-                const float4 a = sum_unit(packets, g.stride, u, active, sub, slot32);
-                if (active) {
-                    float* d = dst0 + 4 * u;                 // packet float position 4u+c -> d[c]
-                    const float4 r = finish_unit(a, inv_w, rmw, d, u, len, sq);
-                    const float q[4] = {r.x, r.y, r.z, r.w};
-                    #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const u32 i4 = 4 * u + c;
-                        if (i4 >= 2 && i4 - 2 < len) d[c] = q[c];
-                    }
-                }
-            }
-        }
-        __syncthreads();                                     // LDS is reused by the next group
-    }
-    // accepted packets and sum-of-squares change of this block: plain adds to the block's own rows
-    // (no shared atomics; kernels on the stream run one after the other)
-    sq = wave_sum_f64(sq);
-    if (lane == 0) { sh_new[wave] = accepted; sh_sq[wave] = sq; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        u32 total = 0;
-        double t = 0.0;
-        for (int i = 0; i < GA_WAVES; ++i) { total += sh_new[i]; t += sh_sq[i]; }
-        if (total) { accept_rows[blockIdx.x] += total; sumsq_rows[blockIdx.x] += t; }
-    }
-}
-
-// Dense batches.  A block takes a group of `sub` = 16 (or 8) consecutive sequence numbers: every wave
+// A block takes a group of `sub` = 16 (8 in short rounds, 32 in sparse batches) consecutive sequence numbers: every wave
 // reads the group's arrival index (64 / sub workers x sub packets per load), ballots which packets are
 // new, and keeps their slots in its own LDS rows; after a barrier the first wave resets the index
-// entries and sets the bitmap, whose bytes the group owns (16 or 8 bits: a plain store, where one
+// entries and sets the bitmap, whose bytes the group owns (8, 16 or 32 bits: a plain store, where one
 // memory-side atomic per worker and group took up to a microsecond of a small group's time).  The
 // waves then share the group's packets, cut into pieces of NP KB when they are longer than 5 KB.
 //
@@ -728,11 +482,25 @@ __global__ __launch_bounds__(GA_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
 //   8 x 1472 B, 4.5 GB                            912 -> 892  (4.9 -> 5.0)
 //   1 x 1472 B, 0.2 GB (as much written as read)   94 -> 45   (2.2 -> 4.6)
 //   4 x 1040 B, 21 MB                              19 -> 12
+//
+// SPARSE (retransmissions): a step is one worker's 2 KB, four in flight, and the last step of a packet
+// loads the span's old contents with it (they were a second trip to memory after the payload's), again
+// through a descriptor, of length zero where the span is new.  It replaces a kernel whose waves took
+// whole packets one after the other, us per launch:
+//   553 k packets of a round of 541 k x 32, 1472 B      620 -> 463
+//   about 12 k of 340 k x 8, 1472 B                      72 -> 54
+//   about 10 of 3740 x 4, 64 KB                          72 -> 22
+//   about 90 k in three runs of 347 k x 16, 4112 B      187 -> 162
 typedef f4v f4v_a4 __attribute__((aligned(4)));      // a 16-byte access at a 4-byte aligned address
 typedef float f2v __attribute__((ext_vector_type(2)));
 typedef f2v f2v_a4 __attribute__((aligned(4)));
 
 #define GS_WAVES 4           // waves per block
+// Cache policy of the payload's buffer loads: non-temporal.  The payload is read exactly once and should
+// not displace the accumulator and index lines that are being written (measured: 8 % off the payload
+// pass).  Headers are NOT loaded this way in the index pass: their lines are read again by the gather.
+#define BUF_NT 2
+#define BUF_RAW 0x00020000   // word 3 of a raw buffer descriptor: 32-bit data format, no swizzle
 #define GS_TEAM_LDS(W, sub_log2) ((((W) + (WAVE >> (sub_log2)) - 1) >> (6 - (sub_log2)) << (6 - (sub_log2))) * ((1u << (sub_log2)) + 1u))
 
 __device__ __forceinline__ u32 uniform(u32 v) { return (u32)__builtin_amdgcn_readfirstlane((int)v); }
@@ -746,13 +514,13 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int NP, int G, int D>
+template <int NP, int G, int D, bool SPARSE = false>
 __global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void gather_stream(
     Geo g, const uint8_t* __restrict__ packets, u64* __restrict__ pending, u64* __restrict__ bitmap,
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
     const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters, int whole_batch,
     u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
-    u32 sub_log2, u32 n_piece, u32 table_in_lds) {
+    u32 sub_log2, u32 n_piece, u32 table_in_lds, int tally_owner) {
     extern __shared__ u32 sh_slots[];               // per wave: slots [W rounded up][sub + 1]; then the bucket table
     __shared__ u32 sh_tally[GS_WAVES * 5];
     __shared__ u32 sh_accepted[GS_WAVES];
@@ -768,16 +536,17 @@ __global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
         for (u32 i = threadIdx.x; i <= g.B; i += blockDim.x) tab[i] = g.first_seq[i];
         fs = tab;
     }
-    // this launch is the first of the batch's gather launches: its block 0 books the index pass's tallies
-    const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0, sh_tally);   // has barriers: covers the table too
+    // block 0 of the batch's first gather launch books the index pass's tallies
+    const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, tally_owner && blockIdx.x == 0, sh_tally);   // has barriers: covers the table too
     const u64 lo = bi.lo, hi = bi.hi;
     if (hi == 0) return;                            // no candidate in this batch (uniform over the grid)
-    if (!whole_batch && batch_is_sparse(bi, W)) return;       // left to the direct kernel
+    if (!whole_batch && batch_is_sparse(bi, W) != SPARSE) return;       // left to the other kernel
     const u32 s_lane = lane & (sub - 1), w_sub = lane >> sub_log2;
-    const u32 submask = sub == 32 ? 0xFFFFFFFFu : (1u << sub) - 1;
-        const bool leader = wave == 0;
+    const u64 submask = NONE64 >> (WAVE - sub);
+    const bool leader = wave == 0;
     const u32 grp_lo = (u32)__builtin_amdgcn_readfirstlane((int)(u32)(lo >> sub_log2));
     const u32 grp_end = (u32)__builtin_amdgcn_readfirstlane((int)(u32)((hi + sub - 1) >> sub_log2));
+    constexpr int J = SPARSE ? 8 : 4;               // index loads in flight
     u32 accepted = 0;
     double sq = 0.0;      // change of the sum of squares of the stored values caused by this lane's packets
 
@@ -785,20 +554,12 @@ __global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
         // ---- arrival index -> slots of the group's new packets, bitmap bits, spans
         const u32 seq0 = (u32)grp << sub_log2, seq_l = seq0 + s_lane;
         const u32 word = seq0 >> 6, shift = seq0 & 63;
-        u64 elem_l = 0;
-        u32 len_l = 0, home_l = pick, new_any = 0, old_any = 0;
-        if (lane < sub && seq_l < g.n_pkts) {
-            const u32 b = find_bucket(fs, g.B, seq_l);
-            const u64 start = (u64)(seq_l - fs[b]) * g.P;
-            const u64 left = g.b_cnt[b] - start;
-            elem_l = g.b_off[b] + start;
-            len_l = left < g.P ? (u32)left : g.P;
-            home_l = home[seq_l];                       // only meaningful (and only used) for spans written before
-        }
-        for (u32 w0 = 0; w0 < W; w0 += 4 * wpl) {
-            u64 p[4], bits[4], nb[4];
+        u64 elem_l = 0, new_any = 0, old_any = 0;
+        u32 len_l = 0, home_l = pick;
+        for (u32 w0 = 0; w0 < W; w0 += J * wpl) {
+            u64 p[J], bits[J], nb[J];
             #pragma unroll
-            for (int j = 0; j < 4; ++j) {
+            for (int j = 0; j < J; ++j) {
                 const u32 w = w0 + j * wpl + w_sub;
                 p[j] = NONE64; bits[j] = 0;
                 if (w < W && seq_l < g.n_pkts) {
@@ -806,8 +567,16 @@ __global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
                     bits[j] = bitmap[(u64)w * g.words_pw + word];
                 }
             }
+            if (w0 == 0 && lane < sub && seq_l < g.n_pkts) {
+                const u32 b = find_bucket(fs, g.B, seq_l);
+                const u64 start = (u64)(seq_l - fs[b]) * g.P;
+                const u64 left = g.b_cnt[b] - start;
+                elem_l = g.b_off[b] + start;
+                len_l = left < g.P ? (u32)left : g.P;
+                home_l = home[seq_l];                       // only meaningful (and only used) for spans written before
+            }
             #pragma unroll
-            for (int j = 0; j < 4; ++j) {
+            for (int j = 0; j < J; ++j) {
                 nb[j] = 0;
                 if (w0 + j * wpl >= W) continue;
                 const u32 w = w0 + j * wpl + w_sub;
@@ -816,26 +585,31 @@ __global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
                 nb[j] = __ballot(fresh);
                 slots[w * pitch + s_lane] = fresh ? (u32)p[j] : NONE32;
                 u64 n = nb[j], o = __ballot(had);
-                for (u32 k = 0; k < wpl; ++k) { new_any |= (u32)n & submask; old_any |= (u32)o & submask; n >>= sub; o >>= sub; }
+                new_any |= n; old_any |= o;
+                for (u32 k = 1; k < wpl; ++k) { n >>= sub; o >>= sub; new_any |= n; old_any |= o; }
             }
             __syncthreads();         // every wave of the block has read the index before the first one resets it
             if (leader) {
                 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
+                for (int j = 0; j < J; ++j) {
                     const u32 w = w0 + j * wpl + w_sub;
                     if (p[j] != NONE64) pending[(u64)w * g.n_pkts + seq_l] = NONE64;   // leave the index empty
-                    const u32 mine = (u32)(nb[j] >> (w_sub * sub)) & submask;
-                    // a group of 8 or 16 sequence numbers owns its bytes of the bitmap: no atomics
+                    const u64 mine = (nb[j] >> (w_sub << sub_log2)) & submask;
+                    // a group owns its 1, 2, 4 or 8 bytes of the bitmap: no atomics
                     if (s_lane == 0 && mine) {
                         uint8_t* bp = (uint8_t*)(bitmap + (u64)w * g.words_pw) + (seq0 >> 3);
-                        const u32 both = mine | ((u32)(bits[j] >> shift) & submask);
-                        if (sub_log2 == 4) *(uint16_t*)bp = (uint16_t)both; else *bp = (uint8_t)both;
+                        const u64 both = mine | ((bits[j] >> shift) & submask);
+                        if (sub_log2 == 4) *(uint16_t*)bp = (uint16_t)both;
+                        else if (sub_log2 == 3) *bp = (uint8_t)both;
+                        else if (sub_log2 == 5) *(u32*)bp = (u32)both;
+                        else *(u64*)bp = both;
                     }
                     accepted += (u32)__popcll(nb[j]);
                 }
             }
         }
-        new_any = uniform(new_any); old_any = uniform(old_any);
+        new_any = uniform(new_any & submask); old_any = uniform(old_any & submask);
+        if (new_any == 0) continue;
         if (lane < sub && !((old_any >> lane) & 1u)) {
             home_l = pick;
             if (leader && ((new_any >> lane) & 1u)) home[seq_l] = (uint8_t)pick;
@@ -847,7 +621,7 @@ __global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
         u32 t_gen = 0, piece_gen = 0, t_next = 0, piece_next = wave;   // item the generator is at: piece of packet t_gen; (t_next, piece_next) comes after it
         u64 left_gen = 0;               // its workers still to be loaded
         u32 slot32 = NONE32;            // lane w: slot of worker w's copy of packet t_gen
-        f4v v[D][G][NP];
+        f4v v[D][G][NP], old[D][NP];    // old: what earlier batches left in the span (SPARSE: loaded with the last step's payloads)
         u32 tag[D];                     // t | piece << 8 | last << 30 | valid << 31
         f4v a[NP];
         #pragma unroll
@@ -880,12 +654,27 @@ __global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
                 // a buffer of `have` bytes at the piece (none for a worker without one): lanes beyond it
                 // read zeros and ask memory for nothing, so every step issues the same loads
                 __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-                    (void*)(packets + uniform((u64)slot * g.stride + skip)), 0, (int)uniform(any ? have : 0u), 0x00020000);
+                    (void*)(packets + uniform((u64)slot * g.stride + skip)), 0, (int)uniform(any ? have : 0u), BUF_RAW);
                 #pragma unroll
                 for (int q = 0; q < NP; ++q)
-                    v[d][j][q] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + q * 1024, 0, 2));
+                    v[d][j][q] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + q * 1024, 0, BUF_NT));
             }
             if (left_gen == 0) tg |= 0x40000000u;
+            if (SPARSE) {
+                // the 16-byte units that lie in the span whole (and the first four floats for unit 0)
+                const bool upd = tg >> 30 == 3u && ((old_any >> t_gen) & 1u);
+                const u64 elem = ((u64)(u32)__builtin_amdgcn_readlane((int)(u32)(elem_l >> 32), (int)t_gen) << 32) |
+                                 (u32)__builtin_amdgcn_readlane((int)(u32)elem_l, (int)t_gen);
+                const u32 h = (u32)__builtin_amdgcn_readlane((int)home_l, (int)t_gen);
+                __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+                    (void*)uniform((u64)((h ? acc1 : acc0) + elem)), 0, (int)uniform(upd ? 4 * len : 0u), BUF_RAW);
+                #pragma unroll
+                for (int q = 0; q < NP; ++q) {
+                    const u32 u = (piece_gen * NP + q) * WAVE + lane;
+                    const bool whole = u == 0 ? len >= 4 : 4 * u + 2 <= len;
+                    old[d][q] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r, !whole ? 0x40000000 : u == 0 ? 0 : (int)(16 * u - 8), 0, 0));
+                }
+            }
             tag[d] = tg | t_gen | (piece_gen << 8);
         };
         auto consume = [&](int d) {
@@ -918,8 +707,12 @@ __global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
                     const bool v0 = u > 0 && 4 * u < len + 2, v1 = u > 0 && 4 * u + 1 < len + 2, v2 = 4 * u < len, v3 = 4 * u + 1 < len;
                     if (rmw) {                                        // result = old value + this batch's sum
                         f4v ov = {0.f, 0.f, 0.f, 0.f};
-                        if (full) ov = *(const f4v_a4*)o;
-                        else {
+                        if (SPARSE) {
+                            ov = old[d][q];
+                            if (q == 0 && u == 0) ov = f4v{0.f, 0.f, ov.x, ov.y};
+                        } else if (full) ov = *(const f4v_a4*)o;
+                        if (SPARSE ? (tail || len < 4) && !full : !full) {
+                            ov = f4v{0.f, 0.f, 0.f, 0.f};
                             if (v0) ov.x = o[0];
                             if (v1) ov.y = o[1];
                             if (v2) ov.z = o[2];
@@ -1108,7 +901,7 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
         // mailbox[1] = sum of squares (when the gather kept it), mailbox[8..11] = accepted,
         // candidates, stale, invalid
         // Only the rows that a launch of this round can have written are read: rows_stream of
-        // gather_stream's, rows_direct of the direct kernel's (row_pitch apart); the rest are zero.
+        // the dense instances', rows_direct of the sparse instance's (row_pitch apart); the rest are zero.
         double s = 0.0;
         u64 a = 0;
         for (u32 k = 0; k < 2; ++k) {
@@ -1346,8 +1139,8 @@ struct dblp_ctx {
     hipEvent_t cls_ev[2];
     u32* d_need; u32* d_missing; u64* d_offs; double* d_partials;
     u32* d_block_tallies;   // [IDX_BLOCKS_PER_CU * n_cus][5], written by index_arrivals
-    u64* d_accept_rows;     // [2][ACCEPT_ROWS] accepted packets per gather block (gather_stream's grid, the direct kernel's)
-    u32 rows_used[2];       // largest gather_stream / direct gather grid launched in the open round
+    u64* d_accept_rows;     // [2][ACCEPT_ROWS] accepted packets per gather block (dense instances' grid, sparse instance's)
+    u32 rows_used[2];       // largest dense / sparse gather grid launched in the open round
     int result_in_place;    // the form of the last dblp_finalize (in place until one says otherwise): prices the second copy
     double* d_sumsq_rows;   // [2][ACCEPT_ROWS] sum of squares of what each gather block stored (same allocation)
     u64* h_mailbox;         // pinned host memory, 16 x u64, also mapped into the device
@@ -1868,8 +1661,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
     }
     const float inv_w = c->fold ? 1.0f / (float)g.W : 1.0f;   // exact for the powers of two it is used with
     {
-        // Which gather kernel: the streaming one for dense batches, the direct one for sparse ones.
-        // Where the number of arrivals settles it, only that one is launched: at least one arrival per
+        // Which instances of the gather: dense or sparse.  Where the number of arrivals settles it, only that one is launched: at least one arrival per
         // SPARSE_DIV (worker, seq) pairs of the whole round is dense whatever range it touches; fewer
         // than one per 8 * SPARSE_DIV pairs is taken as sparse.  In between both are launched and each
         // decides on the device, from the sequence range the index pass found, whether the batch is its own.
@@ -1896,8 +1688,8 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
             // 8 KB per step, two steps in flight, three blocks per CU for short packets, two for long ones
             // (8992 B: 930 against 940 us; more blocks only spread the DRAM accesses over more open rows).
             const bool few = g.W < 4;
-            const u32 per_cu = few ? 6 : np <= 2 ? 3 : 2;
-            void (*kern)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, int, u64*, double*, float, u32, u32, u32) =
+            const u32 per_cu = few ? (np <= 2 ? 6 : 4) : np <= 2 ? 3 : 2;
+            void (*kern)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, int, u64*, double*, float, u32, u32, u32, int) =
                 np == 1 ? (few ? gather_stream<1, 1, 4> : gather_stream<1, 4, 2>)
                 : np == 2 ? (few ? gather_stream<2, 1, 4> : gather_stream<2, 4, 2>)
                 : np == 3 ? (few ? gather_stream<3, 1, 3> : gather_stream<3, 2, 2>)
@@ -1908,22 +1700,28 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
             hipLaunchKernelGGL(kern, dim3(grid), dim3(GS_WAVES * WAVE),
                                lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap, c->d_acc[0],
                                c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
-                               surely_dense ? 1 : 0, c->d_accept_rows, c->d_sumsq_rows, inv_w, sub_log2, n_piece, table_in_lds);
+                               surely_dense ? 1 : 0, c->d_accept_rows, c->d_sumsq_rows, inv_w, sub_log2, n_piece, table_in_lds, 1);
         }
         if (launch_direct) {   // sparse batches
-            const u64 groups = ((u64)g.n_pkts + SUB - 1) / SUB;
-            size_t lds = (size_t)((g.W + 3) / 4 * 4) * SUB * sizeof(u32);
+            // The same loop with one worker's 2 KB per step, and groups of 32 packets of up to 2 KB (longer rows
+            // of the index, fewer empty groups to pass: 54 us against 69 with 16 and 51 with 64 for 12 k packets
+            // over a round of 340 k x 8), of 16 longer ones (64 KB datagrams: 22 us against 36; larger groups
+            // leave too much to one block where the lost packets lie in a few runs: 16 x 4112 B, 162 us with 16,
+            // 270 with 64).
+            const u32 n_piece = (g.units + 2 * WAVE - 1) / (2 * WAVE);
+            const u32 sub_log2 = n_piece == 1 ? 5 : 4;
+            size_t lds = (size_t)GS_WAVES * GS_TEAM_LDS(g.W, sub_log2) * sizeof(u32);
             const size_t table = ((size_t)g.B + 1) * sizeof(u32);
             const u32 table_in_lds = table <= IDX_TABLE_LDS_MAX ? 1u : 0u;
             if (table_in_lds) lds += table;
-            const u32 grid = grid_for(c, groups, GA_BLOCKS_PER_CU);
+            const u64 groups = ((u64)g.n_pkts + (1u << sub_log2) - 1) >> sub_log2;
+            const u32 grid = grid_for(c, groups, 4);
             if (grid > c->rows_used[1]) c->rows_used[1] = grid;
             ProfScope ps(c, DBLP_K_GATHER_DIRECT);
-            hipLaunchKernelGGL(gather_accumulate, dim3(grid), dim3(GA_WAVES * WAVE),
+            hipLaunchKernelGGL((gather_stream<2, 1, 4, true>), dim3(grid), dim3(GS_WAVES * WAVE),
                                lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap, c->d_acc[0],
                                c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
-                               launch_stream ? 0 : 1, c->d_accept_rows + ACCEPT_ROWS, c->d_sumsq_rows + ACCEPT_ROWS, inv_w,
-                               launch_stream ? 1 : 0, table_in_lds);
+                               launch_stream ? 0 : 1, c->d_accept_rows + ACCEPT_ROWS, c->d_sumsq_rows + ACCEPT_ROWS, inv_w, sub_log2, n_piece, table_in_lds, launch_stream ? 0 : 1);
         }
     }
     LAUNCH_CHECK(c, "apply_arrivals");

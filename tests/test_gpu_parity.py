@@ -125,6 +125,18 @@ def test_dense_gather_at_the_edges_of_passes_pieces_and_groups(W, P, n):
         assert stats["rel_to_addends"] <= FLOAT_TOL
 
 
+@pytest.mark.parametrize("loss", [0.05, 0.012])       # both instances launched; the sparse one alone
+@pytest.mark.parametrize("W,P,n", [(2, 1, 3000), (3, 2, 900), (4, 3, 900), (5, 5, 700), (8, 6, 700), (1, 510, 400), (4, 511, 130),
+                                   (9, 512, 65), (3, 514, 97), (17, 1023, 33), (64, 366, 40), (2, 4097, 129)])
+def test_sparse_gather_updates_spans_of_earlier_batches(W, P, n, loss):
+    """Retransmissions into spans that the first transmission wrote, and into spans nobody delivered:
+    spans of 1 to 3 floats, last units of every length, whole pieces of 512 floats and one float more
+    or less, groups of 32 and of 16 packets with a remainder.  Everything is delivered in the end."""
+    sc = build_scenario(mk(W, [P * (n // 3) + 1, P * (n - n // 3) - (P // 2)], P, loss))
+    stats, got, ref = run_both(sc, 0, queue=True)
+    assert stats["rel_to_addends"] <= FLOAT_TOL
+
+
 # ------------------------------------------------------------------------------ two accumulator copies
 TWO_COPY_CASES = [CASES[i] for i in (3, 5, 6, 7, 10, 13, 14, 15)]
 
