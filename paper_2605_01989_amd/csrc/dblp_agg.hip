@@ -514,17 +514,18 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int NP, int G, int D, bool SPARSE = false>
-__global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void gather_stream(
+template <int NP, int G, int D, int NW, bool SPARSE = false>
+__global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void gather_stream(
     Geo g, const uint8_t* __restrict__ packets, u64* __restrict__ pending, u64* __restrict__ bitmap,
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
     const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters, int whole_batch,
     u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
     u32 sub_log2, u32 n_piece, u32 table_in_lds, int tally_owner) {
     extern __shared__ u32 sh_slots[];               // per wave: slots [W rounded up][sub + 1]; then the bucket table
-    __shared__ u32 sh_tally[GS_WAVES * 5];
-    __shared__ u32 sh_accepted[GS_WAVES];
-    __shared__ double sh_sq[GS_WAVES];
+    __shared__ u32 sh_tally[NW * 5];
+    __shared__ u32 sh_accepted[NW];
+    __shared__ double sh_sq[NW];
+    __shared__ u32 sh_tile[2];
     const u32 lane = lane_id();
     const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     const u32 W = g.W, sub = 1u << sub_log2, wpl = WAVE >> sub_log2, pitch = sub + 1;
@@ -532,7 +533,7 @@ __global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
     u32* const slots = sh_slots + wave * team_words;
     const u32* fs = g.first_seq;
     if (table_in_lds) {
-        u32* tab = sh_slots + GS_WAVES * team_words;
+        u32* tab = sh_slots + NW * team_words;
         for (u32 i = threadIdx.x; i <= g.B; i += blockDim.x) tab[i] = g.first_seq[i];
         fs = tab;
     }
@@ -550,7 +551,44 @@ __global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
     u32 accepted = 0;
     double sq = 0.0;      // change of the sum of squares of the stored values caused by this lane's packets
 
-    for (u64 grp = (u64)grp_lo + blockIdx.x; grp < grp_end; grp += gridDim.x) {
+    // The block's groups (grid-stride), up to 64 at a time.  Where most of them hold no arrival (a small
+    // retransmission batch over a long round: fewer than one candidate per 64 sequence numbers), the block
+    // first looks through their index entries, eight loads in flight per wave, and then takes the groups
+    // that hold one (26 against 46 us for a few packets in a round of 589 k x 8; with less than 8 groups to
+    // look through it costs what it saves).
+    const bool skim = SPARSE && bi.cand * 64 < hi - lo;
+    constexpr u32 TILE = SPARSE ? 64 : 1;
+    for (u64 tile = (u64)grp_lo + blockIdx.x; tile < grp_end; tile += (u64)TILE * gridDim.x) {
+    const u32 tile_left = SPARSE ? (grp_end - (u32)tile + gridDim.x - 1) / gridDim.x : 1, n_tile = tile_left < TILE ? tile_left : TILE;
+    u64 todo = NONE64 >> (64 - n_tile);
+    if (skim && n_tile >= 8) {
+        const u32 rows = (W + wpl - 1) >> (6 - sub_log2);
+        u32 k = 0, r = wave;                        // group k of the tile, index row r of the group
+        u64 found = 0;
+        __syncthreads();
+        if (threadIdx.x < 2) sh_tile[threadIdx.x] = 0;
+        __syncthreads();
+        while (k < n_tile) {
+            u64 e[8];
+            u32 kk[8];
+            #pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                while (r >= rows && k < n_tile) { r -= rows; ++k; }
+                const u32 w = (r << (6 - sub_log2)) + w_sub, seq = ((u32)(tile + (u64)k * gridDim.x) << sub_log2) + s_lane;
+                kk[j] = k;
+                e[j] = k < n_tile && w < W && seq < g.n_pkts ? pending[(u64)w * g.n_pkts + seq] : NONE64;
+                r += NW;
+            }
+            #pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (__ballot(e[j] != NONE64)) found |= 1ull << kk[j];
+        }
+        if (lane == 0 && found) { atomicOr(&sh_tile[0], (u32)found); atomicOr(&sh_tile[1], (u32)(found >> 32)); }
+        __syncthreads();
+        todo = uniform(((u64)sh_tile[1] << 32) | sh_tile[0]);
+    }
+    for (; todo; todo &= todo - 1) {
+        const u64 grp = tile + (u64)__builtin_ctzll(todo) * gridDim.x;
         // ---- arrival index -> slots of the group's new packets, bitmap bits, spans
         const u32 seq0 = (u32)grp << sub_log2, seq_l = seq0 + s_lane;
         const u32 word = seq0 >> 6, shift = seq0 & 63;
@@ -602,7 +640,7 @@ __global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
                         if (sub_log2 == 4) *(uint16_t*)bp = (uint16_t)both;
                         else if (sub_log2 == 3) *bp = (uint8_t)both;
                         else if (sub_log2 == 5) *(u32*)bp = (u32)both;
-                        else *(u64*)bp = both;
+                        else atomicOr(&bitmap[(u64)w * g.words_pw + word], mine << shift);   // shorter groups share a byte
                     }
                     accepted += (u32)__popcll(nb[j]);
                 }
@@ -633,8 +671,8 @@ __global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
                     while (piece_next >= n_piece) { piece_next -= n_piece; ++t_next; }
                     if (t_next >= sub) break;
                     t_gen = t_next; piece_gen = piece_next;
-                    piece_next += GS_WAVES;
-                    if ((new_any >> t_gen) & 1u) {
+                    piece_next += NW;
+                    if (((new_any >> t_gen) & 1u) && piece_gen * (NP * 256u) < (u32)__builtin_amdgcn_readlane((int)len_l, (int)t_gen) + 2) {
                         slot32 = lane < W ? slots[lane * pitch + t_gen] : NONE32;
                         left_gen = uniform((u64)__ballot(slot32 != NONE32));
                         break;
@@ -750,6 +788,7 @@ __global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
             if (!more) break;
         }
     }
+    }
     // accepted packets and sum-of-squares change of this block: plain adds to the block's own rows
     sq = wave_sum_f64(sq);
     if (lane == 0) { sh_accepted[wave] = accepted; sh_sq[wave] = sq; }
@@ -758,7 +797,7 @@ __global__ __launch_bounds__(GS_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
         u32 total = 0;
         double t = 0.0;
         #pragma unroll
-        for (int i = 0; i < GS_WAVES; ++i) { total += sh_accepted[i]; t += sh_sq[i]; }
+        for (int i = 0; i < NW; ++i) { total += sh_accepted[i]; t += sh_sq[i]; }
         if (total) { accept_rows[blockIdx.x] += total; sumsq_rows[blockIdx.x] += t; }
     }
 }
@@ -1636,6 +1675,29 @@ extern "C" int dblp_packetize_list(dblp_ctx* c, uint16_t round, const float* con
     return DBLP_OK;
 }
 
+typedef void (*gather_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, int, u64*, double*, float,
+                          u32, u32, u32, int);
+
+// Waves of a gather block: 16 in rounds of few and heavy packets (fewer than 8 sequence numbers per CU, 128 KB
+// or more from all workers for one of them), where a CU has one block at a time; 4 elsewhere.
+static u32 block_waves(const dblp_ctx* c) {
+    return c->g.n_pkts < 8u * (u32)c->n_cus && (u64)c->g.W * c->g.stride >= 131072u ? 16 : GS_WAVES;
+}
+
+// Sequence numbers (log2) that a block of the gather takes at a time: 16; 8 when the round is too short to
+// give every CU two groups of 16 (4 x 1040 bytes, 4096 packets: 11.7 against 12.6 us; longer rounds pay for
+// the shorter rows of the index: 8 x 1472 B, 340 k packets, 920 against 893 us), for packets in pieces only
+// when it is shorter still (64 KB datagrams, 3740 packets: 224 us with 16, 232 with 8).  Blocks of 16 waves
+// take 4, 2 or 1, whatever gives every CU a group (32 workers, 340 datagrams: 161 us against 650 with 16;
+// 32 x 8992 B, 900 packets: 58 against 104); light packets are not worth the atomics on the shared bytes
+// of the bitmap (3 x 4112 B, 420 packets: 24 us with 1, 12 with 8).
+static u32 group_log2(const dblp_ctx* c, bool pieces, u32 nw) {
+    const u32 n = c->g.n_pkts, cus = (u32)c->n_cus;
+    if (n >= (pieces ? 12u : 32u) * cus) return 4;
+    if (nw != 16) return 3;
+    return n >= 4u * cus ? 2 : n >= 2u * cus ? 1 : 0;
+}
+
 // Index pass + gather pass over one batch.  Exactly one of (d_src_worker [+ d_mask, d_order]) and
 // d_queue describes the arrivals.
 static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src_worker, uint64_t n_slots,
@@ -1670,15 +1732,18 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         const bool launch_stream = surely_dense || n_arrivals * SPARSE_DIV * 8 >= pairs;
         const bool launch_direct = !surely_dense;
         if (launch_stream) {
-            // Packets of up to 5 KB are one piece, longer ones are cut evenly into pieces of 3 or 4 KB.
+            // Packets of up to 5 KB are one piece, longer ones are cut evenly into pieces of 3 or 4 KB; in
+            // a short round finer, so that a group gives each of the block's waves a piece.
             const u32 n_pass = (g.units + WAVE - 1) / WAVE;
-            const u32 n_piece = n_pass <= 5 ? 1 : (n_pass + 3) / 4, np = (n_pass + n_piece - 1) / n_piece;
-            // Groups of 16 packets; of 8 when the round is too short to give every CU two of them (4 x 1040
-            // bytes, 4096 packets: 11.7 against 12.6 us).  Longer rounds pay for the shorter rows of the
-            // index (8 x 1472 B, 340 k packets: 920 against 893 us), and packets in pieces fill the block's
-            // waves from 16 as well (64 KB datagrams: 224 us with 16, 232 with 8).
-            const u32 sub_log2 = n_piece == 1 && g.n_pkts < 2u * 16u * (u32)c->n_cus ? 3 : 4;
-            size_t lds = (size_t)GS_WAVES * GS_TEAM_LDS(g.W, sub_log2) * sizeof(u32);
+            u32 n_piece = n_pass <= 5 ? 1 : (n_pass + 3) / 4;
+            const u32 nw = block_waves(c), sub_log2 = group_log2(c, n_piece > 1, nw);
+            if (nw == 16) {
+                const u32 want = nw >> sub_log2 < n_pass ? nw >> sub_log2 : n_pass;
+                if (n_piece < want) n_piece = want;
+            }
+            const u32 np = (n_pass + n_piece - 1) / n_piece;
+            n_piece = (n_pass + np - 1) / np;
+            size_t lds = (size_t)nw * GS_TEAM_LDS(g.W, sub_log2) * sizeof(u32);
             const size_t table = ((size_t)g.B + 1) * sizeof(u32);
             const u32 table_in_lds = table <= IDX_TABLE_LDS_MAX ? 1u : 0u;
             if (table_in_lds) lds += table;
@@ -1688,37 +1753,37 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
             // 8 KB per step, two steps in flight, three blocks per CU for short packets, two for long ones
             // (8992 B: 930 against 940 us; more blocks only spread the DRAM accesses over more open rows).
             const bool few = g.W < 4;
-            const u32 per_cu = few ? (np <= 2 ? 6 : 4) : np <= 2 ? 3 : 2;
-            void (*kern)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, int, u64*, double*, float, u32, u32, u32, int) =
-                np == 1 ? (few ? gather_stream<1, 1, 4> : gather_stream<1, 4, 2>)
-                : np == 2 ? (few ? gather_stream<2, 1, 4> : gather_stream<2, 4, 2>)
-                : np == 3 ? (few ? gather_stream<3, 1, 3> : gather_stream<3, 2, 2>)
-                : np == 4 ? (few ? gather_stream<4, 1, 3> : gather_stream<4, 2, 2>) : gather_stream<5, 1, 3>;
+            const u32 per_cu = nw == 16 ? 1 : few ? (np <= 2 ? 6 : 4) : np <= 2 ? 3 : 2;
+            gather_fn kern;
+            if (nw == 16) kern = np == 1 ? gather_stream<1, 4, 2, 16> : np == 2 ? gather_stream<2, 2, 2, 16> : gather_stream<4, 2, 2, 16>;
+            else if (few) kern = np == 1 ? gather_stream<1, 1, 4, 4> : np == 2 ? gather_stream<2, 1, 4, 4> : np == 3 ? gather_stream<3, 1, 3, 4> : np == 4 ? gather_stream<4, 1, 3, 4> : gather_stream<5, 1, 3, 4>;
+            else kern = np == 1 ? gather_stream<1, 4, 2, 4> : np == 2 ? gather_stream<2, 4, 2, 4> : np == 3 ? gather_stream<3, 2, 2, 4> : np == 4 ? gather_stream<4, 2, 2, 4> : gather_stream<5, 1, 3, 4>;
             const u32 grid = grid_for(c, groups, per_cu);
             if (grid > c->rows_used[0]) c->rows_used[0] = grid;
             ProfScope ps(c, DBLP_K_GATHER);
-            hipLaunchKernelGGL(kern, dim3(grid), dim3(GS_WAVES * WAVE),
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(nw * WAVE),
                                lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap, c->d_acc[0],
                                c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
                                surely_dense ? 1 : 0, c->d_accept_rows, c->d_sumsq_rows, inv_w, sub_log2, n_piece, table_in_lds, 1);
         }
         if (launch_direct) {   // sparse batches
-            // The same loop with one worker's 2 KB per step, and groups of 32 packets of up to 2 KB (longer rows
-            // of the index, fewer empty groups to pass: 54 us against 69 with 16 and 51 with 64 for 12 k packets
-            // over a round of 340 k x 8), of 16 longer ones (64 KB datagrams: 22 us against 36; larger groups
-            // leave too much to one block where the lost packets lie in a few runs: 16 x 4112 B, 162 us with 16,
-            // 270 with 64).
+            // One worker's 2 KB per step.  Groups of 32 packets of up to 2 KB in long rounds (longer rows of the
+            // index, fewer empty groups to pass: 54 us against 69 with 16 and 51 with 64 for 12 k packets over a
+            // round of 340 k x 8); otherwise as for dense batches (64 KB datagrams: 22 us with 16 against 36;
+            // larger groups leave too much to one block where the lost packets lie in a few runs: 16 x 4112 B,
+            // 162 us with 16, 270 with 64).
             const u32 n_piece = (g.units + 2 * WAVE - 1) / (2 * WAVE);
-            const u32 sub_log2 = n_piece == 1 ? 5 : 4;
-            size_t lds = (size_t)GS_WAVES * GS_TEAM_LDS(g.W, sub_log2) * sizeof(u32);
+            const u32 nw = g.stride >= 8192 ? block_waves(c) : GS_WAVES;     // 16 waves for a handful of 4 KB packets: 29 against 22 us
+            const u32 sub_log2 = n_piece == 1 && g.n_pkts >= 32u * (u32)c->n_cus ? 5 : group_log2(c, n_piece > 1, nw);
+            size_t lds = (size_t)nw * GS_TEAM_LDS(g.W, sub_log2) * sizeof(u32);
             const size_t table = ((size_t)g.B + 1) * sizeof(u32);
             const u32 table_in_lds = table <= IDX_TABLE_LDS_MAX ? 1u : 0u;
             if (table_in_lds) lds += table;
             const u64 groups = ((u64)g.n_pkts + (1u << sub_log2) - 1) >> sub_log2;
-            const u32 grid = grid_for(c, groups, 4);
+            const u32 grid = grid_for(c, groups, nw == 16 ? 1 : 4);
             if (grid > c->rows_used[1]) c->rows_used[1] = grid;
             ProfScope ps(c, DBLP_K_GATHER_DIRECT);
-            hipLaunchKernelGGL((gather_stream<2, 1, 4, true>), dim3(grid), dim3(GS_WAVES * WAVE),
+            hipLaunchKernelGGL((nw == 16 ? gather_stream<2, 1, 4, 16, true> : gather_stream<2, 1, 4, 4, true>), dim3(grid), dim3(nw * WAVE),
                                lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap, c->d_acc[0],
                                c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
                                launch_stream ? 0 : 1, c->d_accept_rows + ACCEPT_ROWS, c->d_sumsq_rows + ACCEPT_ROWS, inv_w, sub_log2, n_piece, table_in_lds, launch_stream ? 0 : 1);

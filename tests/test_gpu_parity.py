@@ -112,7 +112,9 @@ def test_parity_small_and_ragged_in_place(W, sizes, P, loss, ppm, result):
 STREAM_CASES = [(W, P, n) for W, P, n in (
     (1, 254, 700), (3, 255, 40), (4, 254, 41), (5, 257, 40), (1, 510, 60), (3, 513, 33), (17, 510, 19), (33, 514, 17),
     (2, 1278, 20), (4, 1278, 18), (4, 1279, 18), (64, 1279, 9), (3, 1537, 17), (8, 1535, 17), (6, 2243, 16), (3, 4094, 5),
-    (1, 6, 8191), (4, 6, 8192), (19, 5, 8193), (2, 1, 9000))]
+    (1, 6, 8191), (4, 6, 8192), (19, 5, 8193), (2, 1, 9000),
+    # few and heavy packets: blocks of 16 waves with groups of 1, 2 and 4 packets
+    (64, 600, 200), (33, 1021, 513), (40, 822, 1030), (9, 3700, 300))]
 
 
 @pytest.mark.parametrize("W,P,n", STREAM_CASES)
@@ -127,7 +129,9 @@ def test_dense_gather_at_the_edges_of_passes_pieces_and_groups(W, P, n):
 
 @pytest.mark.parametrize("loss", [0.05, 0.012])       # both instances launched; the sparse one alone
 @pytest.mark.parametrize("W,P,n", [(2, 1, 3000), (3, 2, 900), (4, 3, 900), (5, 5, 700), (8, 6, 700), (1, 510, 400), (4, 511, 130),
-                                   (9, 512, 65), (3, 514, 97), (17, 1023, 33), (64, 366, 40), (2, 4097, 129)])
+                                   (9, 512, 65), (3, 514, 97), (17, 1023, 33), (64, 366, 40), (2, 4097, 129),
+                                   (16, 2100, 300), (33, 2048, 523),            # blocks of 16 waves
+                                   (2, 3, 400_000)])                            # empty groups passed over, 32 at a time
 def test_sparse_gather_updates_spans_of_earlier_batches(W, P, n, loss):
     """Retransmissions into spans that the first transmission wrote, and into spans nobody delivered:
     spans of 1 to 3 floats, last units of every length, whole pieces of 512 floats and one float more
