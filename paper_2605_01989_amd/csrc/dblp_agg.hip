@@ -122,6 +122,9 @@ __device__ __forceinline__ void st_stream4(uint4* p, uint4 v) {
     __builtin_nontemporal_store(t, (u4v*)p);
 }
 
+__device__ __forceinline__ u32 uniform(u32 v) { return (u32)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ u64 uniform(u64 v) { return ((u64)uniform((u32)(v >> 32)) << 32) | uniform((u32)v); }
+
 __device__ __forceinline__ u32 lane_id() { return threadIdx.x & (WAVE - 1); }
 
 // ------------------------------------------------------------------------------------------
@@ -502,9 +505,6 @@ typedef f2v f2v_a4 __attribute__((aligned(4)));
 #define BUF_NT 2
 #define BUF_RAW 0x00020000   // word 3 of a raw buffer descriptor: 32-bit data format, no swizzle
 #define GS_TEAM_LDS(W, sub_log2) ((((W) + (WAVE >> (sub_log2)) - 1) >> (6 - (sub_log2)) << (6 - (sub_log2))) * ((1u << (sub_log2)) + 1u))
-
-__device__ __forceinline__ u32 uniform(u32 v) { return (u32)__builtin_amdgcn_readfirstlane((int)v); }
-__device__ __forceinline__ u64 uniform(u64 v) { return ((u64)uniform((u32)(v >> 32)) << 32) | uniform((u32)v); }
 
 // Orders the LDS accesses of one wave (a wave's LDS operations execute in order; this keeps the
 // compiler from moving them across).
@@ -895,16 +895,6 @@ __global__ __launch_bounds__(256) void emit_retx(Geo g, const u64* __restrict__ 
 // ------------------------------------------------------------------------------------------
 // finalize (zero-fill + mean over all W) with fused partial sums of squares; norm reduction
 // ------------------------------------------------------------------------------------------
-#define FIN_TILE 8   // consecutive packets per wave step; divides 64 so a tile sits in one bitmap word
-
-// x / P for x < FIN_TILE * P (fits a float exactly enough to be fixed up by one step).
-__device__ __forceinline__ u32 div_small(u32 x, u32 P, float inv_p) {
-    u32 t = (u32)((float)x * inv_p);
-    if (t * P > x) --t;
-    if ((t + 1) * P <= x) ++t;
-    return t;
-}
-
 // Compensation pass (Alg. "DBLP_RECV" last statements, Alg. "Server" mean).  Per packet span:
 //   some worker delivered it   out = src            (scale_mode 0: the gather already divided by W)
 //                              out = src / W        (scale_mode 1: W is not a power of two)
@@ -912,20 +902,26 @@ __device__ __forceinline__ u32 div_small(u32 x, u32 P, float inv_p) {
 //                              nothing at all when src and out are the same memory and there is
 //                              no scaling (in-place form: only moved and missing spans are touched)
 //   nobody delivered it        out = 0 exactly
-// A tile of 8 packets inside one bucket is one contiguous element range: it is walked in
-// 16-byte aligned chunks (float4 load, store); chunks that straddle a packet or the range's
-// ends, and tiles that cross a bucket boundary, go element by element.
-// home[seq] (padded to a multiple of 8 entries) names the copy that holds the packet's span; with
-// move_home set (in-place form) the entries of moved spans are reset to copy 0.
+// A wave takes a group of 2^grp_log2 consecutive packets (at most 64: one bitmap word), or one of the
+// n_piece pieces of at most FIN_PIECE elements of its range.  Consecutive packets are consecutive elements,
+// across bucket boundaries too, so a group that arrived whole and lives in one copy is a plain copy of its
+// range in aligned 16-byte units, four in flight per lane; other groups go run by run.  Memory bounds
+// it; a wave's share is bounded in elements because with 8 packets per wave, whatever their length, a round
+// of long packets had a few hundred waves, and groups that cross a bucket went element by element:
+//   3 workers x 15.5 M in 64 KB packets    568 -> 27 us
+//   3 x 5.3 M, 1472 B (2 x 21 MB moved)     23 -> 13 us
+//   8 x 215 M, 1472 B (2 x 862 MB moved)   443 -> 387 us
+// move_home (in-place form, n_piece = 1): the homes of spans that were moved are reset to copy 0.
 // With scale_mode 1 the per-block sums of out^2 go to partials[blockIdx.x].  Otherwise the sum of
 // squares is already known: the gather kernels kept it per block in sumsq_rows, and the one extra
 // block of this launch (blockIdx.x == n_work_blocks) adds those rows up in a fixed order (fixed
 // for given launch sizes of the round's gather kernels) and writes the total to the host mailbox.
+#define FIN_PIECE 4096
 template <bool TABLE_IN_LDS>
 __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restrict__ bitmap, const float* acc0,
                                                      const float* acc1, uint8_t* __restrict__ home,
                                                      float* out, int scale_mode, float wf, int move_home,
-                                                     double* __restrict__ partials, u32 n_work_blocks,
+                                                     u32 grp_log2, u32 n_piece, double* __restrict__ partials, u32 n_work_blocks,
                                                      const double* __restrict__ sumsq_rows, const u64* __restrict__ accept_rows,
                                                      u32 rows_stream, u32 rows_direct, u32 row_pitch,
                                                      u64* __restrict__ counters, u64* __restrict__ mailbox) {
@@ -980,84 +976,92 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
     }
     const u32 wave = blockIdx.x * (blockDim.x / WAVE) + wave_in_block;
     const u32 n_waves = n_work_blocks * (blockDim.x / WAVE);
-    const u32 n_tiles = (g.n_pkts + FIN_TILE - 1) / FIN_TILE;
-    const float inv_p = 1.0f / (float)g.P;
+    const u32 grp = 1u << grp_log2;
+    const u64 n_items = (((u64)g.n_pkts + grp - 1) >> grp_log2) * n_piece;
     const bool skip_same = scale_mode == 0;     // a span that already sits in `out` needs no copy
     double dsum = 0.0;
-    for (u32 tile = wave; tile < n_tiles; tile += n_waves) {
-        const u32 seq0 = tile * FIN_TILE;
-        const u32 n_t = g.n_pkts - seq0 < FIN_TILE ? g.n_pkts - seq0 : FIN_TILE;
+
+    // Elements [e0, e1) of the result by the whole wave: src / W, src, or zeros where src is null.
+    auto write_range = [&](const float* src, u64 e0, u64 e1) {
+        auto scaled = [&](f4v v) {
+            if (scale_mode) {
+                v.x = v.x / wf; v.y = v.y / wf; v.z = v.z / wf; v.w = v.w / wf;
+                dsum += (double)((v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w));
+            }
+            return v;
+        };
+        const u64 up = (e0 + 3) & ~3ull, a0 = up < e1 ? up : e1, a1 = (e1 & ~3ull) > a0 ? e1 & ~3ull : a0;
+        if (lane < (u32)(a0 - e0) || (lane >= 32 && lane - 32 < (u32)(e1 - a1))) {      // what lies outside whole 16-byte units
+            const u64 e = lane < 32 ? e0 + lane : a1 + (lane - 32);
+            f4v v = {src ? src[e] : 0.f, 0.f, 0.f, 0.f};
+            if (src) v = scaled(v);
+            out[e] = v.x;
+        }
+        u64 c = (a0 >> 2) + lane;
+        const u64 c1 = a1 >> 2;
+        f4v* o = (f4v*)out;
+        const f4v zero = {0.f, 0.f, 0.f, 0.f};
+        if (!src) {
+            for (; c < c1; c += WAVE) o[c] = zero;
+            return;
+        }
+        const f4v* s = (const f4v*)src;
+        for (; c + 3 * WAVE < c1; c += 4 * WAVE) {
+            f4v v[4];
+            #pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = s[c + k * WAVE];
+            #pragma unroll
+            for (int k = 0; k < 4; ++k) o[c + k * WAVE] = scaled(v[k]);
+        }
+        for (; c < c1; c += WAVE) o[c] = scaled(s[c]);
+    };
+
+    for (u64 item = wave; item < n_items; item += n_waves) {
+        const u32 gi = n_piece == 1 ? (u32)item : (u32)(item / n_piece), piece = (u32)(item - (u64)gi * n_piece);
+        const u32 seq0 = gi << grp_log2, n_t = g.n_pkts - seq0 < grp ? g.n_pkts - seq0 : grp;
         // OR of the workers' bitmap words: lane w loads worker w's word (one load instruction
         // for the wave, W <= 64), the OR runs across the lanes
         const u64 mine = lane < g.W ? bitmap[(u64)lane * g.words_pw + (seq0 >> 6)] : 0ull;
-        u64 any = ((u64)wave_reduce<OpOr>((u32)(mine >> 32)) << 32) | wave_reduce<OpOr>((u32)mine);
-        any >>= (seq0 & 63);
-        const u64 hm = *(const u64*)(home + seq0);          // byte t = copy of packet seq0 + t (valid where `any` has bit t)
-        // which of the tile's packets need work at all (wave-uniform)
-        u32 todo = 0;
-        for (u32 t = 0; t < n_t; ++t) {
-            const bool got = (any >> t) & 1ull;
-            const float* src = ((hm >> (8 * t)) & 1ull) ? acc1 : acc0;
-            if (!got || !(skip_same && src == out)) todo |= 1u << t;
-        }
+        const u32 hm = lane < n_t ? home[seq0 + lane] : 0;       // copy of packet seq0 + lane (meaningful where it arrived)
+        const u64 full = NONE64 >> (64 - n_t);
+        const u64 any = uniform(((((u64)wave_reduce<OpOr>((u32)(mine >> 32)) << 32) | wave_reduce<OpOr>((u32)mine)) >> (seq0 & 63)) & full);
+        const u64 second = (u64)__ballot(hm & 1u);
+        // the packets that need work at all
+        const u64 same = skip_same ? (acc0 == out ? ~second : 0ull) | (acc1 == out ? second : 0ull) : 0ull;
+        const u64 todo = uniform(full & ~(any & same));
         if (!todo) continue;
-        u32 b = find_bucket(fs, g.B, seq0);
-        if (seq0 + n_t <= fs[b + 1]) {
-            const u64 elem0 = g.b_off[b] + (u64)(seq0 - fs[b]) * g.P;
-            const u64 bucket_end = g.b_off[b] + g.b_cnt[b];
-            const u64 end = elem0 + (u64)n_t * g.P < bucket_end ? elem0 + (u64)n_t * g.P : bucket_end;
-            const u64 c1 = (end - 1) >> 2;
-            for (u64 c = (elem0 >> 2) + lane; c <= c1; c += WAVE) {
-                const u64 e0 = c << 2;
-                const u64 lo_e = e0 > elem0 ? e0 : elem0, hi_e = e0 + 3 < end - 1 ? e0 + 3 : end - 1;
-                const u32 t_lo = div_small((u32)(lo_e - elem0), g.P, inv_p), t_hi = div_small((u32)(hi_e - elem0), g.P, inv_p);
-                if (e0 >= elem0 && e0 + 4 <= end && t_lo == t_hi) {
-                    if (!((todo >> t_lo) & 1u)) continue;
-                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);      // never received: exactly zero
-                    if ((any >> t_lo) & 1ull) {
-                        v = *(const float4*)((((hm >> (8 * t_lo)) & 1ull) ? acc1 : acc0) + e0);
-                        if (scale_mode) {
-                            v.x = v.x / wf; v.y = v.y / wf; v.z = v.z / wf; v.w = v.w / wf;
-                            dsum += (double)((v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w));
-                        }
-                    }
-                    *(float4*)(out + e0) = v;
-                } else {
-                    for (u64 e = lo_e; e <= hi_e; ++e) {
-                        const u32 t_e = div_small((u32)(e - elem0), g.P, inv_p);
-                        if (!((todo >> t_e) & 1u)) continue;
-                        float v = 0.f;
-                        if ((any >> t_e) & 1ull) {
-                            v = (((hm >> (8 * t_e)) & 1ull) ? acc1 : acc0)[e];
-                            if (scale_mode) { v = v / wf; dsum += (double)(v * v); }
-                        }
-                        out[e] = v;
-                    }
-                }
-            }
-        } else {
-            for (u32 t = 0; t < n_t; ++t) {
-                const u32 seq = seq0 + t;
-                while (seq >= fs[b + 1]) ++b;
-                if (!((todo >> t) & 1u)) continue;
-                u64 elem; u32 len;
-                packet_span(g, seq, b, &elem, &len);
-                float s = 0.f;
-                if ((any >> t) & 1ull) {
-                    const float* acc = ((hm >> (8 * t)) & 1ull) ? acc1 : acc0;
-                    for (u32 j = lane; j < len; j += WAVE) {
-                        float v = acc[elem + j];
-                        if (scale_mode) { v = v / wf; s += v * v; }
-                        out[elem + j] = v;
-                    }
-                } else {
-                    for (u32 j = lane; j < len; j += WAVE) out[elem + j] = 0.f;
-                }
-                dsum += (double)s;
-            }
+        u64 elem_l = 0;
+        u32 len_l = 0;
+        if (lane < n_t) {
+            const u32 b = find_bucket(fs, g.B, seq0 + lane);
+            const u64 start = (u64)(seq0 + lane - fs[b]) * g.P, left = g.b_cnt[b] - start;
+            elem_l = g.b_off[b] + start;
+            len_l = left < g.P ? (u32)left : g.P;
+        }
+        auto elem_of = [&](u32 t) {
+            return ((u64)(u32)__builtin_amdgcn_readlane((int)(u32)(elem_l >> 32), (int)t) << 32) | (u32)__builtin_amdgcn_readlane((int)(u32)elem_l, (int)t);
+        };
+        const u64 g0 = elem_of(0), g1 = elem_of(n_t - 1) + (u32)__builtin_amdgcn_readlane((int)len_l, (int)(n_t - 1));
+        const u64 p0 = g0 + (u64)piece * FIN_PIECE, p1 = n_piece == 1 || p0 + FIN_PIECE > g1 ? g1 : p0 + FIN_PIECE;
+        if (p0 >= p1) continue;
+        if (todo == full && any == full && ((second & full) == 0 || (second & full) == full)) {
+            write_range((second & 1ull) ? acc1 : acc0, p0, p1);
+            if (move_home && (second & 1ull) && lane < n_t) home[seq0 + lane] = 0;
+            continue;
+        }
+        for (u64 m = todo; m;) {                                // runs of packets of one kind
+            const u32 t = (u32)__builtin_ctzll(m);
+            const u64 kind = uniform(m & (!((any >> t) & 1ull) ? ~any : ((second >> t) & 1ull) ? any & second : any & ~second));
+            const u64 after = ~(kind >> t);                     // bit k: packet t + k is of another kind
+            const u32 n = after ? (u32)__builtin_ctzll(after) : 64 - t, z = t + n - 1;
+            m &= z == 63 ? 0ull : NONE64 << (z + 1);
+            const u64 e0 = elem_of(t), e1 = elem_of(z) + (u32)__builtin_amdgcn_readlane((int)len_l, (int)z);
+            const u64 lo = e0 > p0 ? e0 : p0, hi = e1 < p1 ? e1 : p1;
+            if (lo >= hi) continue;
+            write_range(!((any >> t) & 1ull) ? nullptr : ((second >> t) & 1ull) ? acc1 : acc0, lo, hi);
         }
         // in-place form: the spans that were moved now live in copy 0
-        if (move_home && lane < n_t && ((any >> lane) & 1ull) && ((hm >> (8 * lane)) & 1ull)) home[seq0 + lane] = 0;
+        if (move_home && lane < n_t && ((any >> lane) & 1ull) && (hm & 1u)) home[seq0 + lane] = 0;
     }
     if (scale_mode) {
         dsum = wave_sum_f64(dsum);
@@ -1774,7 +1778,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
             // 162 us with 16, 270 with 64).
             const u32 n_piece = (g.units + 2 * WAVE - 1) / (2 * WAVE);
             const u32 nw = g.stride >= 8192 ? block_waves(c) : GS_WAVES;     // 16 waves for a handful of 4 KB packets: 29 against 22 us
-            const u32 sub_log2 = n_piece == 1 && g.n_pkts >= 32u * (u32)c->n_cus ? 5 : group_log2(c, n_piece > 1, nw);
+            const u32 sub_log2 = n_piece == 1 && g.n_pkts >= (g.W <= 4 ? 32u : 64u) * (u32)c->n_cus ? 5 : group_log2(c, n_piece > 1, nw);
             size_t lds = (size_t)nw * GS_TEAM_LDS(g.W, sub_log2) * sizeof(u32);
             const size_t table = ((size_t)g.B + 1) * sizeof(u32);
             const u32 table_in_lds = table <= IDX_TABLE_LDS_MAX ? 1u : 0u;
@@ -1857,18 +1861,25 @@ extern "C" int dblp_finalize(dblp_ctx* c, int compensation, float* d_out) {
     if (((uintptr_t)d_out & 15) != 0) return fail(c, DBLP_EINVAL, "finalize: d_out must be 16-byte aligned");
     HIP_TRY(c, hipSetDevice(c->device));
     const Geo& g = c->g;
-    const u64 tiles = ((u64)g.n_pkts + FIN_TILE - 1) / FIN_TILE;
-    const u32 work = grid_for(c, (tiles + 3) / 4, FIN_BLOCKS_PER_CU);
+    // Packets per wave: where the result is left in place most waves have nothing to write, so they look
+    // at a whole bitmap word (fewer packets when they are long: what is written is written by one wave);
+    // into another buffer as many as make about 4096 elements, longer ones in pieces.
+    u32 grp_log2 = 6;
+    const u64 most = in_place ? 32768 : 2 * FIN_PIECE;
+    while (grp_log2 > 0 && ((u64)g.P << grp_log2) > most) --grp_log2;
+    const u32 n_piece = in_place ? 1 : (u32)((((u64)g.P << grp_log2) + FIN_PIECE - 1) / FIN_PIECE);
+    const u64 items = (((u64)g.n_pkts + (1u << grp_log2) - 1) >> grp_log2) * n_piece;
+    const u32 work = grid_for(c, (items + 3) / 4, FIN_BLOCKS_PER_CU);
     const u32 grid = work + 1;      // one more block sums the gather's rows: accepted packets, and the sum of squares for Eq. 1
     float* out = in_place ? c->d_acc[0] : d_out;
     {
         ProfScope ps(c, DBLP_K_FINALIZE);
         const size_t table = ((size_t)g.B + 1) * sizeof(u32);
-        void (*kern)(Geo, const u64*, const float*, const float*, uint8_t*, float*, int, float, int, double*, u32,
+        void (*kern)(Geo, const u64*, const float*, const float*, uint8_t*, float*, int, float, int, u32, u32, double*, u32,
                      const double*, const u64*, u32, u32, u32, u64*, u64*) = table <= IDX_TABLE_LDS_MAX ? finalize_pass<true> : finalize_pass<false>;
         hipLaunchKernelGGL(kern, dim3(grid), dim3(256), table <= IDX_TABLE_LDS_MAX ? table : 0, c->stream, g, c->d_bitmap,
                            (const float*)c->d_acc[0], (const float*)c->d_acc[1], c->d_home, out, c->fold ? 0 : 1, (float)g.W,
-                           in_place ? 1 : 0, c->d_partials, work, (const double*)c->d_sumsq_rows, (const u64*)c->d_accept_rows,
+                           in_place ? 1 : 0, grp_log2, n_piece, c->d_partials, work, (const double*)c->d_sumsq_rows, (const u64*)c->d_accept_rows,
                            c->rows_used[0], c->rows_used[1], (u32)ACCEPT_ROWS, c->d_counters, c->d_mailbox);
     }
     LAUNCH_CHECK(c, "finalize");

@@ -898,3 +898,23 @@ def test_early_stop_sub_batches_match_oracle():
         nz = scale > 0
         assert (np.abs(got["out"] - ref["out"])[nz] / scale[nz]).max() <= FLOAT_TOL
     assert ref["probes"] < 200 and ref["accepted"] < sc.survive0.sum()      # it did stop early
+
+
+# ------------------------------------------------------------------------------ compensation pass, by pieces and runs
+@pytest.mark.parametrize("result", ["copy", "in_place"])
+@pytest.mark.parametrize("W,sizes,P,loss,copies", [
+    (1, [74 * 300 + 5, 74 * 64, 1, 2, 3], 74, 0.3, 1),           # 64 packets a wave, runs of missing ones, two pieces
+    (2, [1, 2, 3, 4, 5, 6, 7, 8, 9] * 20, 8, 0.5, 2),            # buckets of one short packet
+    (1, [4096 * 2, 4097, 4095, 12289], 4096, 0.3, 1),            # one packet a wave, whole pieces and one float more or less
+    (3, [16374 * 5 + 1, 700, 16374 * 2], 16374, 0.5, 1),         # pieces of long packets, another W
+    (2, [65535 * 3 + 1, 1], 65535, 0.4, 2),
+    (6, [256 * 129 + 255, 255], 256, 0.4, 1),
+    (4, [1024 * 70 + 1], 1024, 0.6, 2)])
+def test_compensation_copies_zeroes_and_moves_runs(W, sizes, P, loss, copies, result):
+    """Spans nobody delivered, spans of either accumulator copy and what lies between, in groups that are
+    cut into pieces and in groups of 64; no retransmission, so that spans stay missing."""
+    if result == "in_place" and W & (W - 1):
+        result = "copy"
+    sc = build_scenario(mk(W, sizes, P, loss))
+    stats, got, ref = run_both(sc, 1_000_000, queue=True, result=result, acc_copies=copies, acc_policy=2 if copies == 2 else 0)
+    assert stats["rel_to_addends"] <= FLOAT_TOL
