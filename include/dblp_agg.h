@@ -304,7 +304,7 @@ int dblp_get_prev_norm(const dblp_ctx* ctx, double* h_norm, int* h_have);
  * reads; further ones are dropped.  dblp_profile_enable may return ENOMEM. */
 #define DBLP_K_INDEX 0    /* header parse / validation / arrival index */
 #define DBLP_K_GATHER 1   /* payload gather + accumulate, streaming kernel (dense batches) */
-#define DBLP_K_PROBE 2    /* loss count + prefix + retransmit list (three launches, one bracket) */
+#define DBLP_K_PROBE 2    /* loss count + retransmit list (two or three launches, one bracket) */
 #define DBLP_K_FINALIZE 3 /* zero-fill mean + partial sums of squares */
 #define DBLP_K_GATHER_DIRECT 4 /* the same, its instance for sparse batches */
 #define DBLP_K_COUNT 5

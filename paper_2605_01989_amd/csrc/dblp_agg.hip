@@ -19,8 +19,8 @@
 // per-packet byte map records where each span lives.
 //
 // The probe (Sec. "Dynamically Changing Loss Tolerance"): loss_count (popcount of bitmap words +
-// DPP wave reduction), scan_need (exclusive prefix of the per-(worker,bucket) list lengths) and
-// emit_retx (ordered compaction).  The mean of Alg. "Server" is formed as the payloads are summed when
+// DPP wave reduction, list length per block of (worker, bucket) pairs) and emit_retx (ordered compaction
+// from the sum of the lengths before it on).  The mean of Alg. "Server" is formed as the payloads are summed when
 // W is a power of two (the division is exact), and the gather kernels keep the sum of squares of
 // what they store, so finalize_pass only writes zeros where nothing arrived (and moves or copies
 // spans where the result is wanted elsewhere); for other W it divides and squares itself.
@@ -814,80 +814,178 @@ __device__ __forceinline__ u64 range_mask(u32 wd, u32 s0, u32 s1) {
     return m;
 }
 
-__global__ __launch_bounds__(256) void loss_count(Geo g, const u64* __restrict__ bitmap, u32 bound_ppm,
-                                                  u32* __restrict__ missing_out, u32* __restrict__ need) {
-    const u32 lane = lane_id();
-    const u32 wave = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
-    const u32 n_waves = gridDim.x * blockDim.x / WAVE;
-    const u32 pairs = g.W * g.B;
-    for (u32 pr = wave; pr < pairs; pr += n_waves) {
-        const u32 w = pr / g.B, b = pr - w * g.B;
-        const u32 s0 = g.first_seq[b], s1 = g.first_seq[b + 1];
-        const u32 wd0 = s0 >> 6, wd1 = (s1 - 1) >> 6;
-        u32 cnt = 0;
-        for (u32 wd = wd0 + lane; wd <= wd1; wd += WAVE)
-            cnt += (u32)__popcll(bitmap[(u64)w * g.words_pw + wd] & range_mask(wd, s0, s1));
-        const u32 got = wave_reduce<OpAdd>(cnt);
-        if (lane == 0) {
-            const u32 n_b = s1 - s0;
-            const u32 miss = n_b - got;
-            const u64 allowed = ((u64)bound_ppm * n_b) / 1000000ull;
-            if (missing_out) missing_out[pr] = miss;
-            need[pr] = (u64)miss > allowed ? miss : 0u;
-        }
+// BLOCK_PAIR (few pairs, buckets of more words than a wave keeps in flight): a block takes a pair, each of
+// its waves a quarter of the words (148 x 8, the longest of 105 k packets: 13 + 5 + 5 us with three launches, 6.5 + 6.4 now).  Otherwise
+// a wave takes `ppw` consecutive (worker, bucket) pairs, one per lane (ppw = 1 while there are fewer pairs
+// than waves, up to 64).  A pair of at most PROBE_SMALL bitmap words is its lane's own work, a larger one
+// the whole wave's, PROBE_UNROLL words per lane in flight.  Latency bounds both passes: with one wave per
+// pair, and one block that added the list lengths up between them, a probe over 120 k buckets x 16 workers
+// took 250 us and now takes 11, one of 161 x 8 took 14 and now takes 9.
+#define PROBE_SMALL 4
+#define PROBE_UNROLL 8
+struct ProbePair {
+    u32 w, s0, s1;
+    bool small;
+    __device__ __forceinline__ ProbePair(const Geo& g, u64 pr, bool valid) : w(0), s0(0), s1(0), small(true) {
+        if (!valid) return;
+        w = (u32)(pr / g.B);
+        const u32 b = (u32)(pr - (u64)w * g.B);
+        s0 = g.first_seq[b]; s1 = g.first_seq[b + 1];
+        small = ((s1 - 1) >> 6) - (s0 >> 6) < PROBE_SMALL;
     }
+    // lane t's pair, in every lane
+    __device__ __forceinline__ ProbePair(const ProbePair& o, u32 t)
+        : w((u32)__builtin_amdgcn_readlane((int)o.w, (int)t)), s0((u32)__builtin_amdgcn_readlane((int)o.s0, (int)t)),
+          s1((u32)__builtin_amdgcn_readlane((int)o.s1, (int)t)), small(o.small) {}
+    // wave k's quarter of the words [*wd0, *wd1] (none: *wd0 > *wd1)
+    __device__ __forceinline__ void share(u32 k, u32* wd0, u32* wd1) const {
+        const u32 per = (*wd1 - *wd0 + 4) / 4, a = *wd0 + k * per, z = a + per - 1;
+        *wd0 = a;
+        if (z < *wd1) *wd1 = z;
+    }
+};
+
+// Missing packets per pair, list length it asks for (need), and the block's total of those.
+template <bool BLOCK_PAIR>
+__global__ __launch_bounds__(256) void loss_count(Geo g, const u64* __restrict__ bitmap, u32 bound_ppm, u32 ppw, u64 pairs,
+                                                  u32* __restrict__ missing_out, u32* __restrict__ need, u64* __restrict__ totals) {
+    __shared__ u64 sh[4];
+    const u32 lane = lane_id(), wave = uniform(threadIdx.x / WAVE);
+    const u64 pr = BLOCK_PAIR ? blockIdx.x : ((u64)blockIdx.x * 4 + wave) * ppw + lane;
+    const bool valid = lane < ppw && pr < pairs;
+    const ProbePair p(g, pr, valid);
+    const bool alone = ppw > 1 && p.small;
+    u32 got = 0;
+    if (valid && alone)
+        for (u32 wd = p.s0 >> 6; wd <= (p.s1 - 1) >> 6; ++wd) got += (u32)__popcll(bitmap[(u64)p.w * g.words_pw + wd] & range_mask(wd, p.s0, p.s1));
+    for (u64 m = uniform((u64)__ballot(valid && !alone)); m; m &= m - 1) {
+        const u32 t = (u32)__builtin_ctzll(m);
+        const ProbePair q(p, t);
+        u32 wd0 = q.s0 >> 6, wd1 = (q.s1 - 1) >> 6;
+        if (BLOCK_PAIR) q.share(wave, &wd0, &wd1);
+        u32 cnt = 0;
+        for (u32 w0 = wd0; w0 <= wd1; w0 += PROBE_UNROLL * WAVE) {
+            u64 v[PROBE_UNROLL];
+            #pragma unroll
+            for (int k = 0; k < PROBE_UNROLL; ++k) {
+                const u32 wd = w0 + k * WAVE + lane;
+                v[k] = wd <= wd1 ? bitmap[(u64)q.w * g.words_pw + wd] & range_mask(wd, q.s0, q.s1) : 0ull;
+            }
+            #pragma unroll
+            for (int k = 0; k < PROBE_UNROLL; ++k) cnt += (u32)__popcll(v[k]);
+        }
+        cnt = wave_reduce<OpAdd>(cnt);
+        if (lane == t) got = cnt;
+    }
+    if (BLOCK_PAIR) {
+        if (lane == 0) sh[wave] = got;
+        __syncthreads();
+        got = (u32)((sh[0] + sh[1]) + (sh[2] + sh[3]));
+        __syncthreads();
+    }
+    u32 want = 0;
+    if (valid && (!BLOCK_PAIR || wave == 0)) {
+        const u32 n_b = p.s1 - p.s0, miss = n_b - got;
+        const u64 allowed = ((u64)bound_ppm * n_b) / 1000000ull;
+        if (missing_out) missing_out[pr] = miss;
+        want = (u64)miss > allowed ? miss : 0u;
+        need[pr] = want;
+    }
+    const u64 sum = ((u64)wave_reduce<OpAdd>(want >> 16) << 16) + wave_reduce<OpAdd>(want & 0xFFFFu);
+    if (lane == 0) sh[wave] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) totals[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
-// Exclusive prefix of need[0..n) into offs[0..n); total list length to *total (device) and to
-// the host mailbox.  Single block of 1024 threads.
-__global__ __launch_bounds__(1024) void scan_need(const u32* __restrict__ need, u32 n, u64* __restrict__ offs,
-                                                  u64* __restrict__ mailbox) {
+// Where blocks are many: exclusive prefix of totals[0..n) in place, by one block of 1024 threads.
+#define PROBE_SCAN_BLOCKS 4096u
+__global__ __launch_bounds__(1024) void scan_totals(u64* __restrict__ totals, u32 n) {
     __shared__ u64 part[1024];
     const u32 t = threadIdx.x;
-    const u32 per = (n + 1023) / 1024;
-    const u32 i0 = t * per, i1 = min(n, i0 + per);
-    u64 s = 0;
-    for (u32 i = i0; i < i1; ++i) s += need[i];
-    part[t] = s;
-    __syncthreads();
-    for (u32 d = 1; d < 1024; d <<= 1) {
-        u64 v = t >= d ? part[t - d] : 0;
+    u64 base = 0;
+    for (u32 i0 = 0; i0 < n; i0 += 1024) {
+        const u64 v = i0 + t < n ? totals[i0 + t] : 0;
+        part[t] = v;
         __syncthreads();
-        part[t] += v;
+        for (u32 d = 1; d < 1024; d <<= 1) {
+            const u64 u = t >= d ? part[t - d] : 0;
+            __syncthreads();
+            part[t] += u;
+            __syncthreads();
+        }
+        if (i0 + t < n) totals[i0 + t] = base + part[t] - v;
+        base += part[1023];
         __syncthreads();
     }
-    u64 run = part[t] - s;     // exclusive prefix of this thread's chunk
-    for (u32 i = i0; i < i1; ++i) { offs[i] = run; run += need[i]; }
-    if (t == 1023) mailbox[0] = part[1023];
 }
 
-__global__ __launch_bounds__(256) void emit_retx(Geo g, const u64* __restrict__ bitmap, const u32* __restrict__ need,
-                                                 const u64* __restrict__ offs, u64* __restrict__ list, u64 capacity) {
-    const u32 lane = lane_id();
-    const u32 wave = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
-    const u32 n_waves = gridDim.x * blockDim.x / WAVE;
-    const u32 pairs = g.W * g.B;
-    for (u32 pr = wave; pr < pairs; pr += n_waves) {
-        if (need[pr] == 0) continue;
-        const u32 w = pr / g.B, b = pr - w * g.B;
-        const u32 s0 = g.first_seq[b], s1 = g.first_seq[b + 1];
-        const u32 wd0 = s0 >> 6, wd1 = (s1 - 1) >> 6;
-        u64 base = offs[pr];
-        for (u32 c0 = wd0; c0 <= wd1; c0 += WAVE) {
-            const u32 wd = c0 + lane;
-            u64 m = 0;
-            if (wd <= wd1) m = ~bitmap[(u64)w * g.words_pw + wd] & range_mask(wd, s0, s1);
-            const u32 c = (u32)__popcll(m);
-            const u32 incl = wave_scan_incl<OpAdd>(c);
-            const u32 total = (u32)__builtin_amdgcn_readlane((int)incl, 63);
-            u64 pos = base + (incl - c);
-            while (m) {
-                const u32 bit = (u32)__builtin_ctzll(m);
-                m &= m - 1;
-                if (pos < capacity) list[pos] = ((u64)w << 32) | ((u64)wd * 64 + bit);
-                ++pos;
+// The list: block j writes the entries of the pairs that block j of loss_count counted, from the sum of the
+// totals before its own on (scanned: totals holds those sums).  The last block tells the host the length.
+template <bool BLOCK_PAIR>
+__global__ __launch_bounds__(256) void emit_retx(Geo g, const u64* __restrict__ bitmap, u32 ppw, u64 pairs, const u32* __restrict__ need,
+                                                 const u64* __restrict__ totals, int scanned, u64* __restrict__ list, u64 capacity,
+                                                 u64* __restrict__ mailbox) {
+    __shared__ u64 sh[4], sh_sum[4];
+    const u32 lane = lane_id(), wave = uniform(threadIdx.x / WAVE);
+    const u64 pr = BLOCK_PAIR ? blockIdx.x : ((u64)blockIdx.x * 4 + wave) * ppw + lane;
+    const bool valid = lane < ppw && pr < pairs;
+    const u32 want = valid ? need[pr] : 0;
+    u64 before = 0;
+    if (scanned) before = threadIdx.x == 0 ? totals[blockIdx.x] : 0;
+    else
+        for (u32 i = threadIdx.x; i < blockIdx.x; i += 256) before += totals[i];
+    u32 lo = (u32)before & 0xFFFFFu, mid = (u32)(before >> 20) & 0xFFFFFu, hi = (u32)(before >> 40);     // 64 x 2^20 fits 32 bits
+    before = ((u64)wave_reduce<OpAdd>(hi) << 40) + ((u64)wave_reduce<OpAdd>(mid) << 20) + wave_reduce<OpAdd>(lo);
+    const u32 inc_hi = wave_scan_incl<OpAdd>(want >> 16), inc_lo = wave_scan_incl<OpAdd>(want & 0xFFFFu);
+    const u64 incl = ((u64)inc_hi << 16) + inc_lo;
+    const u64 sum = ((u64)(u32)__builtin_amdgcn_readlane((int)inc_hi, 63) << 16) + (u32)__builtin_amdgcn_readlane((int)inc_lo, 63);
+    if (lane == 0) { sh[wave] = before; sh_sum[wave] = sum; }
+    __syncthreads();
+    u64 base = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) mailbox[0] = base + (BLOCK_PAIR ? sh_sum[0] : (sh_sum[0] + sh_sum[1]) + (sh_sum[2] + sh_sum[3]));
+    if (!BLOCK_PAIR)
+        for (u32 i = 0; i < wave; ++i) base += sh_sum[i];
+    if (capacity == 0 || sum == 0) return;
+    const ProbePair p(g, pr, valid);
+    const bool alone = ppw > 1 && p.small;
+    const u64 pos0 = base + incl - want;
+    if (want && alone) {
+        u64 pos = pos0;
+        for (u32 wd = p.s0 >> 6; wd <= (p.s1 - 1) >> 6; ++wd)
+            for (u64 m = ~bitmap[(u64)p.w * g.words_pw + wd] & range_mask(wd, p.s0, p.s1); m; m &= m - 1, ++pos)
+                if (pos < capacity) list[pos] = ((u64)p.w << 32) | ((u64)wd * 64 + (u32)__builtin_ctzll(m));
+    }
+    for (u64 todo = uniform((u64)__ballot(want && !alone)); todo; todo &= todo - 1) {
+        const u32 t = (u32)__builtin_ctzll(todo);
+        const ProbePair q(p, t);
+        u64 at = ((u64)(u32)__builtin_amdgcn_readlane((int)(u32)(pos0 >> 32), (int)t) << 32) | (u32)__builtin_amdgcn_readlane((int)(u32)pos0, (int)t);
+        u32 wd0 = q.s0 >> 6, wd1 = (q.s1 - 1) >> 6;
+        if (BLOCK_PAIR) {           // (want is the same in all waves: all come here) what the quarters before this one hold
+            q.share(wave, &wd0, &wd1);
+            u32 c = 0;
+            #pragma unroll PROBE_UNROLL
+            for (u32 wd = wd0 + lane; wd <= wd1; wd += WAVE) c += (u32)__popcll(~bitmap[(u64)q.w * g.words_pw + wd] & range_mask(wd, q.s0, q.s1));
+            c = wave_reduce<OpAdd>(c);
+            if (lane == 0) sh_sum[wave] = c;
+            __syncthreads();
+            for (u32 i = 0; i < wave; ++i) at += sh_sum[i];
+        }
+        for (u32 w0 = wd0; w0 <= wd1; w0 += PROBE_UNROLL * WAVE) {
+            u64 v[PROBE_UNROLL];
+            #pragma unroll
+            for (int k = 0; k < PROBE_UNROLL; ++k) {
+                const u32 wd = w0 + k * WAVE + lane;
+                v[k] = wd <= wd1 ? ~bitmap[(u64)q.w * g.words_pw + wd] & range_mask(wd, q.s0, q.s1) : 0ull;
             }
-            base += total;
+            #pragma unroll
+            for (int k = 0; k < PROBE_UNROLL; ++k) {
+                if (w0 + k * WAVE > wd1) break;
+                const u32 c = (u32)__popcll(v[k]), inc = wave_scan_incl<OpAdd>(c);
+                u64 pos = at + (inc - c);
+                for (u64 m = v[k]; m; m &= m - 1, ++pos)
+                    if (pos < capacity) list[pos] = ((u64)q.w << 32) | ((u64)(w0 + k * WAVE + lane) * 64 + (u32)__builtin_ctzll(m));
+                at += (u32)__builtin_amdgcn_readlane((int)inc, 63);
+            }
         }
     }
 }
@@ -1180,7 +1278,8 @@ struct dblp_ctx {
     struct Picked { const void* p; u64 bytes; int pick; } picked[32];   // measured buffers
     u32 n_picked;
     hipEvent_t cls_ev[2];
-    u32* d_need; u32* d_missing; u64* d_offs; double* d_partials;
+    int probe_block_pair;   // probe: a block per (worker, bucket) pair
+    u32* d_need; u64* d_totals; double* d_partials;   // probe: list length per pair, and per block of pairs
     u32* d_block_tallies;   // [IDX_BLOCKS_PER_CU * n_cus][5], written by index_arrivals
     u64* d_accept_rows;     // [2][ACCEPT_ROWS] accepted packets per gather block (dense instances' grid, sparse instance's)
     u32 rows_used[2];       // largest dense / sparse gather grid launched in the open round
@@ -1260,7 +1359,7 @@ extern "C" int dblp_destroy(dblp_ctx* c) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     void* dev[] = {c->d_first_seq, c->d_b_off, c->d_b_cnt, c->d_bitmap, c->d_pending,
-                   c->acc_caller ? nullptr : c->acc_alloc[0], c->acc_caller ? nullptr : c->acc_alloc[1], c->d_home, c->d_counters, c->d_need, c->d_missing, c->d_offs, c->d_partials, c->d_block_tallies,
+                   c->acc_caller ? nullptr : c->acc_alloc[0], c->acc_caller ? nullptr : c->acc_alloc[1], c->d_home, c->d_counters, c->d_need, c->d_totals, c->d_partials, c->d_block_tallies,
                    c->d_accept_rows};
     for (void* p : dev) if (p) (void)hipFree(p);
     for (hipEvent_t e : c->cls_ev) if (e) (void)hipEventDestroy(e);
@@ -1421,6 +1520,17 @@ static int pick_copy(dblp_ctx* c, const void* d_packets, u64 bytes, u64 n_slots,
 // (finalize) this keeps all of them resident in the CU's 160 KB.  Larger tables are searched in global memory.
 #define IDX_TABLE_LDS_MAX 16384u
 
+// Probe: pairs per wave, blocks.
+static u32 probe_ppw(const dblp_ctx* c, u64 pairs) {
+    const u64 waves = (u64)c->n_cus * 32, ppw = (pairs + waves - 1) / waves;
+    return ppw > WAVE ? WAVE : ppw ? (u32)ppw : 1;
+}
+static u64 probe_blocks(const dblp_ctx* c, u64 pairs) {
+    if (c->probe_block_pair) return pairs;
+    const u64 per = 4ull * probe_ppw(c, pairs);
+    return (pairs + per - 1) / per;
+}
+
 extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     if (!out || !cfg || !cfg->buckets) return DBLP_EINVAL;
     if (cfg->n_workers == 0 || cfg->n_workers > DBLP_MAX_WORKERS) return DBLP_EINVAL;
@@ -1485,6 +1595,9 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
 
     const u64 pairs = (u64)g.W * B;
     const u32 max_partials = (u32)c->n_cus * FIN_BLOCKS_PER_CU;
+    u32 longest = 0;        // packets of the longest bucket
+    for (u32 b = 0; b < B; ++b) longest = c->h_first_seq[b + 1] - c->h_first_seq[b] > longest ? c->h_first_seq[b + 1] - c->h_first_seq[b] : longest;
+    c->probe_block_pair = pairs <= 8u * (u32)c->n_cus && longest > WAVE * WAVE * PROBE_UNROLL;
     bool ok = true;
     ok = ok && hipMalloc(&c->d_first_seq, (B + 1) * sizeof(u32)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_b_off, B * sizeof(u64)) == hipSuccess;
@@ -1494,8 +1607,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     ok = ok && hipMalloc(&c->d_home, (n_pkts + 7) / 8 * 8 + 8) == hipSuccess;
     ok = ok && hipMalloc(&c->d_counters, C_COUNT * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_need, pairs * sizeof(u32)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_missing, pairs * sizeof(u32)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_offs, pairs * sizeof(u64)) == hipSuccess;
+    ok = ok && hipMalloc(&c->d_totals, probe_blocks(c, pairs) * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_partials, max_partials * sizeof(double)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_accept_rows, 4 * ACCEPT_ROWS * sizeof(u64)) == hipSuccess;   // + the sum-of-squares rows
     ok = ok && hipMalloc(&c->d_block_tallies, (size_t)c->n_cus * IDX_BLOCKS_PER_CU * 5 * sizeof(u32)) == hipSuccess;
@@ -1831,15 +1943,19 @@ extern "C" int dblp_loss_account(dblp_ctx* c, uint32_t bound_ppm, uint32_t* d_mi
     if (bound_ppm > 1000000u) return fail(c, DBLP_EINVAL, "loss_account: bound above 100%");
     HIP_TRY(c, hipSetDevice(c->device));
     const Geo& g = c->g;
-    const u32 pairs = g.W * g.B;
+    const u64 pairs = (u64)g.W * g.B, blocks = probe_blocks(c, pairs);
+    const u32 ppw = probe_ppw(c, pairs);
+    if (blocks > 0x7FFFFFFFull) return fail(c, DBLP_EINVAL, "loss_account: too many (worker, bucket) pairs");
     {
+        // Each block of emit_retx adds up the totals of the blocks before it (2048 of them: about a
+        // microsecond) unless they are so many that a pass in between is shorter.
+        const int scanned = blocks > PROBE_SCAN_BLOCKS ? 1 : 0;
         ProfScope ps(c, DBLP_K_PROBE);
-        hipLaunchKernelGGL(loss_count, dim3(grid_for(c, (pairs + 3) / 4, 8)), dim3(256), 0, c->stream, g, c->d_bitmap,
-                           bound_ppm, d_missing ? d_missing : c->d_missing, c->d_need);
-        hipLaunchKernelGGL(scan_need, dim3(1), dim3(1024), 0, c->stream, c->d_need, pairs, c->d_offs, c->d_mailbox);
-        if (retx_capacity)
-            hipLaunchKernelGGL(emit_retx, dim3(grid_for(c, (pairs + 3) / 4, 8)), dim3(256), 0, c->stream, g, c->d_bitmap,
-                               c->d_need, c->d_offs, (u64*)d_retx_list, (u64)retx_capacity);
+        hipLaunchKernelGGL(c->probe_block_pair ? loss_count<true> : loss_count<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g,
+                           c->d_bitmap, bound_ppm, ppw, pairs, d_missing, c->d_need, c->d_totals);
+        if (scanned) hipLaunchKernelGGL(scan_totals, dim3(1), dim3(1024), 0, c->stream, c->d_totals, (u32)blocks);
+        hipLaunchKernelGGL(c->probe_block_pair ? emit_retx<true> : emit_retx<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g, c->d_bitmap, ppw, pairs, (const u32*)c->d_need,
+                           (const u64*)c->d_totals, scanned, (u64*)d_retx_list, (u64)retx_capacity, c->d_mailbox);
     }
     LAUNCH_CHECK(c, "loss_account");
     HIP_TRY(c, hipStreamSynchronize(c->stream));

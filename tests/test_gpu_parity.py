@@ -918,3 +918,27 @@ def test_compensation_copies_zeroes_and_moves_runs(W, sizes, P, loss, copies, re
     sc = build_scenario(mk(W, sizes, P, loss))
     stats, got, ref = run_both(sc, 1_000_000, queue=True, result=result, acc_copies=copies, acc_policy=2 if copies == 2 else 0)
     assert stats["rel_to_addends"] <= FLOAT_TOL
+
+
+# ------------------------------------------------------------------------------ probe: lanes, waves, blocks, blocks scanned
+@pytest.mark.parametrize("W,B,big", [(3, 1, 40_000), (2, 1, 1_000_003), (5, 40, 5000), (4, 3, 32_769), (8, 1025, 700), (16, 700, 33_000), (64, 9000, 300)])
+@pytest.mark.parametrize("ppm", [0, 300_000])
+def test_probe_counts_and_lists_of_few_and_many_buckets(W, B, big, ppm):
+    """One pair per block (few, one of them long), per wave (up to 32 waves per CU), several, 64 with more blocks than are added up in
+    the list kernel; buckets of 1 to 4 packets beside one of `big` (more words than a wave keeps in
+    flight); the list in full, cut short, and not asked for."""
+    rng = np.random.default_rng(B)
+    sizes = rng.integers(1, 5, size=B)
+    sizes[B // 2] = big
+    sc = build_scenario(mk(W, sizes.tolist(), 1, 0.2))
+    o, g = both(sc, queue=True)
+    for rx in (o, g):
+        rx.begin_round(sc.rnd_id)
+        for b in sc.batches:
+            rx.apply(b.slot_base, b.n_slots, b.mask, b.order)
+    missing, lst, count, met = o.loss_account(ppm)
+    got = g.loss_account(ppm)
+    assert count == got[2] and met == got[3] and np.array_equal(missing, got[0]) and np.array_equal(lst, got[1])
+    part = g.loss_account(ppm, capacity=count // 2)
+    assert part[2] == count and np.array_equal(part[1], lst[:count // 2])
+    assert g.agg.loss_account(ppm, None, None) == (count, count == 0, count > 0)
