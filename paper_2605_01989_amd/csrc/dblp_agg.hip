@@ -44,7 +44,7 @@ typedef uint32_t u32;
 #define WAVE 64
 
 // device counters (u64 each)
-enum { C_ACCEPTED = 0, C_STALE, C_INVALID, C_CANDIDATES, C_PKT_BAD, C_COUNT };
+enum { C_ACCEPTED = 0, C_STALE, C_INVALID, C_CANDIDATES, C_COUNT };
 
 struct Geo {
     const u32* first_seq;   // [B+1]
@@ -236,13 +236,16 @@ __device__ __forceinline__ void write_packet(const float* __restrict__ src, u32 
     }
 }
 
+// *bad (host memory, mapped) becomes 1 when an entry has to be skipped: the host reads it after the wait it
+// needs anyway, where a counter in device memory cost a copy back (10 us of a 77 us retransmission).
+//
 // Sender, a range of sequence numbers of one worker: packet first_seq + i -> slot slot_map[i] (or
 // slot_base + i).  The bucket boundaries are searched in LDS when the table fits (TABLE_IN_LDS).
 template <bool TABLE_IN_LDS>
 __global__ __launch_bounds__(256) void packetize_kernel(Geo g, u32 w, u32 round, const float* __restrict__ grad,
                                                         u64 elem_base, u32 first_seq, u32 n, const u32* __restrict__ slot_map,
                                                         u64 slot_base, u64 n_slots, uint8_t* __restrict__ packets,
-                                                        uint16_t* __restrict__ src_worker, u64* __restrict__ counters) {
+                                                        uint16_t* __restrict__ src_worker, u64* __restrict__ bad) {
     extern __shared__ u32 fs_lds[];
     const u32* fs = g.first_seq;
     if (TABLE_IN_LDS) {
@@ -257,7 +260,7 @@ __global__ __launch_bounds__(256) void packetize_kernel(Geo g, u32 w, u32 round,
         u32 seq = first_seq + i;
         u64 slot = slot_map ? (u64)slot_map[i] : slot_base + i;
         if (slot >= n_slots) {
-            if (lane == 0) atomicAdd(&counters[C_PKT_BAD], 1ull);
+            if (lane == 0) *bad = 1;
             continue;
         }
         u32 b = find_bucket(fs, g.B, seq);
@@ -276,7 +279,7 @@ struct GradPtrs { const float* p[DBLP_MAX_WORKERS]; };
 template <bool TABLE_IN_LDS>
 __global__ __launch_bounds__(256) void packetize_list_kernel(Geo g, GradPtrs grads, u32 round, const u64* __restrict__ list,
                                                              u64 n, u64 slot_base, uint8_t* __restrict__ packets,
-                                                             uint16_t* __restrict__ src_worker, u64* __restrict__ counters) {
+                                                             uint16_t* __restrict__ src_worker, u64* __restrict__ bad) {
     extern __shared__ u32 fs_lds[];
     const u32* fs = g.first_seq;
     if (TABLE_IN_LDS) {
@@ -291,7 +294,7 @@ __global__ __launch_bounds__(256) void packetize_list_kernel(Geo g, GradPtrs gra
         const u64 e = list[i];
         const u32 w = (u32)(e >> 32), seq = (u32)e;
         if (w >= g.W || seq >= g.n_pkts) {
-            if (lane == 0) atomicAdd(&counters[C_PKT_BAD], 1ull);
+            if (lane == 0) *bad = 1;
             continue;
         }
         const u32 b = find_bucket(fs, g.B, seq);
@@ -1734,25 +1737,20 @@ extern "C" int dblp_packetize(dblp_ctx* c, uint32_t w, uint16_t round, const flo
     seq_window(c, first_seq, n_pkts, &lo, &hi);
     if (lo < elem_base || hi > elem_base + n_grad) return fail(c, DBLP_EINVAL, "packetize: packets outside the gradient window");
     HIP_TRY(c, hipSetDevice(c->device));
+    *(volatile u64*)(c->h_mailbox + 4) = 0;
     const size_t table = ((size_t)c->g.B + 1) * sizeof(u32);
     if (table <= IDX_TABLE_LDS_MAX)
         hipLaunchKernelGGL(packetize_kernel<true>, dim3(grid_for(c, (n_pkts + 3) / 4, 8)), dim3(256), table, c->stream, c->g, w,
                            (u32)round, d_grad, (u64)elem_base, (u32)first_seq, (u32)n_pkts, d_slot_map, (u64)slot_base,
-                           (u64)n_slots, (uint8_t*)d_packets, d_src_worker, c->d_counters);
+                           (u64)n_slots, (uint8_t*)d_packets, d_src_worker, c->d_mailbox + 4);
     else
         hipLaunchKernelGGL(packetize_kernel<false>, dim3(grid_for(c, (n_pkts + 3) / 4, 8)), dim3(256), 0, c->stream, c->g, w,
                            (u32)round, d_grad, (u64)elem_base, (u32)first_seq, (u32)n_pkts, d_slot_map, (u64)slot_base,
-                           (u64)n_slots, (uint8_t*)d_packets, d_src_worker, c->d_counters);
+                           (u64)n_slots, (uint8_t*)d_packets, d_src_worker, c->d_mailbox + 4);
     LAUNCH_CHECK(c, "packetize");
     if (d_slot_map) {   // slots come from device memory: the kernel checks them, report here
-        u64 bad = 0;
-        HIP_TRY(c, hipMemcpyAsync(c->h_mailbox + 4, c->d_counters + C_PKT_BAD, sizeof(u64), hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
-        bad = c->h_mailbox[4];
-        if (bad) {
-            HIP_TRY(c, hipMemsetAsync(c->d_counters + C_PKT_BAD, 0, sizeof(u64), c->stream));
-            return fail(c, DBLP_EINVAL, "packetize: slot map entry outside the packet buffer");
-        }
+        if (*(volatile u64*)(c->h_mailbox + 4)) return fail(c, DBLP_EINVAL, "packetize: slot map entry outside the packet buffer");
     }
     return DBLP_OK;
 }
@@ -1772,22 +1770,19 @@ extern "C" int dblp_packetize_list(dblp_ctx* c, uint16_t round, const float* con
         gp.p[w] = h_grads[w];
     }
     HIP_TRY(c, hipSetDevice(c->device));
+    *(volatile u64*)(c->h_mailbox + 4) = 0;
     const size_t table = ((size_t)c->g.B + 1) * sizeof(u32);
     if (table <= IDX_TABLE_LDS_MAX)
         hipLaunchKernelGGL(packetize_list_kernel<true>, dim3(grid_for(c, (n + 3) / 4, 8)), dim3(256), table, c->stream, c->g, gp,
                            (u32)round, (const u64*)d_list, (u64)n, (u64)slot_base, (uint8_t*)d_packets, d_src_worker,
-                           c->d_counters);
+                           c->d_mailbox + 4);
     else
         hipLaunchKernelGGL(packetize_list_kernel<false>, dim3(grid_for(c, (n + 3) / 4, 8)), dim3(256), 0, c->stream, c->g, gp,
                            (u32)round, (const u64*)d_list, (u64)n, (u64)slot_base, (uint8_t*)d_packets, d_src_worker,
-                           c->d_counters);
+                           c->d_mailbox + 4);
     LAUNCH_CHECK(c, "packetize_list");
-    HIP_TRY(c, hipMemcpyAsync(c->h_mailbox + 4, c->d_counters + C_PKT_BAD, sizeof(u64), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (c->h_mailbox[4]) {
-        HIP_TRY(c, hipMemsetAsync(c->d_counters + C_PKT_BAD, 0, sizeof(u64), c->stream));
-        return fail(c, DBLP_EINVAL, "packetize_list: list entry with worker or seq out of range");
-    }
+    if (*(volatile u64*)(c->h_mailbox + 4)) return fail(c, DBLP_EINVAL, "packetize_list: list entry with worker or seq out of range");
     return DBLP_OK;
 }
 
