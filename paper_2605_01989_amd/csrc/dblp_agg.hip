@@ -517,7 +517,7 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int NP, int G, int D, int NW, bool SPARSE = false>
+template <int NP, int G, int D, int NW, bool SPARSE = false, u32 LEAD = 2>
 __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void gather_stream(
     Geo g, const uint8_t* __restrict__ packets, u64* __restrict__ pending, u64* __restrict__ bitmap,
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
@@ -675,7 +675,7 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
                     if (t_next >= sub) break;
                     t_gen = t_next; piece_gen = piece_next;
                     piece_next += NW;
-                    if (((new_any >> t_gen) & 1u) && piece_gen * (NP * 256u) < (u32)__builtin_amdgcn_readlane((int)len_l, (int)t_gen) + 2) {
+                    if (((new_any >> t_gen) & 1u) && piece_gen * (NP * 256u) < (u32)__builtin_amdgcn_readlane((int)len_l, (int)t_gen) + LEAD) {
                         slot32 = lane < W ? slots[lane * pitch + t_gen] : NONE32;
                         left_gen = uniform((u64)__ballot(slot32 != NONE32));
                         break;
@@ -683,8 +683,18 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
                 }
             }
             const u32 len = (u32)__builtin_amdgcn_readlane((int)len_l, (int)t_gen);
-            const u32 bytes = ((len + 2 + 3) >> 2) * 16, skip = piece_gen * (NP * 1024u);
-            const u32 have = bytes > skip ? bytes - skip : 0;
+            const u32 skip = piece_gen * (NP * 1024u);
+            // the end of what is read: the last unit (LEAD 2: it may hold padding), the payload's end (LEAD 0:
+            // a last unit of fewer than four floats is read as the 16 bytes that end there, turned into
+            // place when it is stored, so that every access lies inside the packet)
+            const u32 end = LEAD ? ((len + 2 + 3) >> 2) * 16 : len > 2 ? 8 + 4 * len : 16;
+            const u32 have = end > skip ? end - skip : 0;
+            int off[NP];
+            #pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                off[q] = (int)(lane * 16 + q * 1024 + (LEAD ? 0 : 8));
+                if (!LEAD && (len & 3u) && (piece_gen * NP + q) * WAVE + lane == len >> 2) off[q] = (int)(end - 16 - skip);
+            }
             u32 tg = left_gen ? 0x80000000u : 0u;
             #pragma unroll
             for (int j = 0; j < G; ++j) {
@@ -698,7 +708,7 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
                     (void*)(packets + uniform((u64)slot * g.stride + skip)), 0, (int)uniform(any ? have : 0u), BUF_RAW);
                 #pragma unroll
                 for (int q = 0; q < NP; ++q)
-                    v[d][j][q] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + q * 1024, 0, BUF_NT));
+                    v[d][j][q] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r, off[q], 0, BUF_NT));
             }
             if (left_gen == 0) tg |= 0x40000000u;
             if (SPARSE) {
@@ -712,8 +722,8 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
                 #pragma unroll
                 for (int q = 0; q < NP; ++q) {
                     const u32 u = (piece_gen * NP + q) * WAVE + lane;
-                    const bool whole = u == 0 ? len >= 4 : 4 * u + 2 <= len;
-                    old[d][q] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r, !whole ? 0x40000000 : u == 0 ? 0 : (int)(16 * u - 8), 0, 0));
+                    const bool whole = !LEAD ? u < len >> 2 : u == 0 ? len >= 4 : 4 * u + 2 <= len;
+                    old[d][q] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r, !whole ? 0x40000000 : u == 0 ? 0 : (int)(16 * u - 4 * LEAD), 0, 0));
                 }
             }
             tag[d] = tg | t_gen | (piece_gen << 8);
@@ -730,29 +740,34 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
                                  (u32)__builtin_amdgcn_readlane((int)(u32)elem_l, (int)t);
                 const u32 h = (u32)__builtin_amdgcn_readlane((int)home_l, (int)t);
                 const bool rmw = (old_any >> t) & 1u;
-                float* dst = (h ? acc1 : acc0) + elem - 2;            // float position i of the packet -> dst[i]
-                const bool tail = (len + 2) & 3u;                     // the last unit holds floats beyond the payload
+                // float position i of the unit grid -> dst[i]; the payload is positions LEAD .. LEAD + len - 1
+                float* dst = (h ? acc1 : acc0) + elem - LEAD;
+                const u32 past = len + LEAD, n_tail = past & 3u;      // n_tail: floats of a last unit that is not full
                 #pragma unroll
                 for (int q = 0; q < NP; ++q) {
                     const u32 u = (piece * NP + q) * WAVE + lane;
-                    f4v r = a[q] * inv_w;
-                    if (q == 0 && u == 0) r.x = r.y = 0.f;            // the header
-                    if (tail && 4 * u + 2 > len) {                    // float position i is payload while i < len + 2
-                        if (4 * u >= len + 2) r.x = 0.f;
-                        if (4 * u + 1 >= len + 2) r.y = 0.f;
-                        if (4 * u >= len) r.z = 0.f;
-                        r.w = 0.f;
-                    }
+                    const bool head = LEAD && u == 0;                 // two header words, then the first two floats
+                    const bool full = !head && 4 * u + 4 <= past, part = !head && n_tail && u == past >> 2;
+                    const bool v0 = part, v1 = part && n_tail > 1, v2 = head ? len > 0 : part && n_tail > 2, v3 = head && len > 1;
                     float* o = dst + 4 * u;
-                    const bool full = u > 0 && 4 * u + 2 <= len;
-                    const bool v0 = u > 0 && 4 * u < len + 2, v1 = u > 0 && 4 * u + 1 < len + 2, v2 = 4 * u < len, v3 = 4 * u + 1 < len;
+                    f4v r = a[q] * inv_w, ov = {0.f, 0.f, 0.f, 0.f};
+                    if (head) {
+                        r.x = r.y = 0.f;
+                        if (!v3) r.w = 0.f;
+                    }
+                    if (n_tail && !head && 4 * u + 4 > past) {        // the last unit's floats in place, zeros beyond the payload
+                        if (LEAD) r = f4v{v0 ? r.x : 0.f, v1 ? r.y : 0.f, v2 ? r.z : 0.f, 0.f};
+                        else {
+                            const u32 first = len > 1 ? 4 - n_tail : 2;
+                            r = f4v{v0 ? (first == 1 ? r.y : first == 2 ? r.z : r.w) : 0.f, v1 ? (first == 1 ? r.z : r.w) : 0.f, v2 ? r.w : 0.f, 0.f};
+                        }
+                    }
                     if (rmw) {                                        // result = old value + this batch's sum
-                        f4v ov = {0.f, 0.f, 0.f, 0.f};
                         if (SPARSE) {
                             ov = old[d][q];
-                            if (q == 0 && u == 0) ov = f4v{0.f, 0.f, ov.x, ov.y};
+                            if (head) ov = f4v{0.f, 0.f, ov.x, ov.y};
                         } else if (full) ov = *(const f4v_a4*)o;
-                        if (SPARSE ? (tail || len < 4) && !full : !full) {
+                        if (part || (head && (!SPARSE || len < 4))) {
                             ov = f4v{0.f, 0.f, 0.f, 0.f};
                             if (v0) ov.x = o[0];
                             if (v1) ov.y = o[1];
@@ -766,13 +781,11 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
                     sq += (double)r.x * (double)r.x; sq += (double)r.y * (double)r.y;
                     sq += (double)r.z * (double)r.z; sq += (double)r.w * (double)r.w;
                     if (full) *(f4v_a4*)o = r;
-                    else if (u == 0) {
-                        if (v2) o[2] = r.z;
-                        if (v3) o[3] = r.w;
-                    } else if (tail) {
+                    else {
                         if (v0) o[0] = r.x;
                         if (v1) o[1] = r.y;
                         if (v2) o[2] = r.z;
+                        if (v3) o[3] = r.w;
                     }
                     a[q] = f4v{0.f, 0.f, 0.f, 0.f};
                 }
@@ -1834,6 +1847,12 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
     }
     const float inv_w = c->fold ? 1.0f / (float)g.W : 1.0f;   // exact for the powers of two it is used with
     {
+        // Units of 16 bytes from the packet's start (LEAD 2), or from the payload's (LEAD 0) where that takes one
+        // pass of 64 less: payloads of 256, 512, 768 and 1024 floats (or one float fewer) would need one more
+        // for the two floats that the 8-byte header pushes out (16 x 256 floats, 60 M: 860 -> 818 us; 1 x 256,
+        // 25.6 M: 55 -> 48; 1024-float retransmissions: 162 -> 144).  Other lengths are better off from the
+        // start, where fewer passes begin inside a 128-byte line (32 x 1472 B: 1.64 against 1.65 ms).
+        const bool lead = !(g.P <= 1024 && (g.P + 255) / 256 < (g.P + 2 + 255) / 256) || block_waves(c) == 16;
         // Which instances of the gather: dense or sparse.  Where the number of arrivals settles it, only that one is launched: at least one arrival per
         // SPARSE_DIV (worker, seq) pairs of the whole round is dense whatever range it touches; fewer
         // than one per 8 * SPARSE_DIV pairs is taken as sparse.  In between both are launched and each
@@ -1845,9 +1864,9 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         if (launch_stream) {
             // Packets of up to 5 KB are one piece, longer ones are cut evenly into pieces of 3 or 4 KB; in
             // a short round finer, so that a group gives each of the block's waves a piece.
-            const u32 n_pass = (g.units + WAVE - 1) / WAVE;
+            const u32 n_pass = lead ? (g.units + WAVE - 1) / WAVE : (g.P + 4 * WAVE - 1) / (4 * WAVE);
             u32 n_piece = n_pass <= 5 ? 1 : (n_pass + 3) / 4;
-            const u32 nw = block_waves(c), sub_log2 = group_log2(c, n_piece > 1, nw);
+            const u32 nw = lead ? block_waves(c) : GS_WAVES, sub_log2 = group_log2(c, n_piece > 1, nw);
             if (nw == 16) {
                 const u32 want = nw >> sub_log2 < n_pass ? nw >> sub_log2 : n_pass;
                 if (n_piece < want) n_piece = want;
@@ -1867,6 +1886,8 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
             const u32 per_cu = nw == 16 ? 1 : few ? (np <= 2 ? 6 : 4) : np <= 2 ? 3 : 2;
             gather_fn kern;
             if (nw == 16) kern = np == 1 ? gather_stream<1, 4, 2, 16> : np == 2 ? gather_stream<2, 2, 2, 16> : gather_stream<4, 2, 2, 16>;
+            else if (!lead && few) kern = np == 1 ? gather_stream<1, 1, 4, 4, false, 0> : np == 2 ? gather_stream<2, 1, 4, 4, false, 0> : np == 3 ? gather_stream<3, 1, 3, 4, false, 0> : gather_stream<4, 1, 3, 4, false, 0>;
+            else if (!lead) kern = np == 1 ? gather_stream<1, 4, 2, 4, false, 0> : np == 2 ? gather_stream<2, 4, 2, 4, false, 0> : np == 3 ? gather_stream<3, 2, 2, 4, false, 0> : gather_stream<4, 2, 2, 4, false, 0>;
             else if (few) kern = np == 1 ? gather_stream<1, 1, 4, 4> : np == 2 ? gather_stream<2, 1, 4, 4> : np == 3 ? gather_stream<3, 1, 3, 4> : np == 4 ? gather_stream<4, 1, 3, 4> : gather_stream<5, 1, 3, 4>;
             else kern = np == 1 ? gather_stream<1, 4, 2, 4> : np == 2 ? gather_stream<2, 4, 2, 4> : np == 3 ? gather_stream<3, 2, 2, 4> : np == 4 ? gather_stream<4, 2, 2, 4> : gather_stream<5, 1, 3, 4>;
             const u32 grid = grid_for(c, groups, per_cu);
@@ -1883,8 +1904,8 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
             // round of 340 k x 8); otherwise as for dense batches (64 KB datagrams: 22 us with 16 against 36;
             // larger groups leave too much to one block where the lost packets lie in a few runs: 16 x 4112 B,
             // 162 us with 16, 270 with 64).
-            const u32 n_piece = (g.units + 2 * WAVE - 1) / (2 * WAVE);
-            const u32 nw = g.stride >= 8192 ? block_waves(c) : GS_WAVES;     // 16 waves for a handful of 4 KB packets: 29 against 22 us
+            const u32 n_piece = lead ? (g.units + 2 * WAVE - 1) / (2 * WAVE) : (g.P + 8 * WAVE - 1) / (8 * WAVE);
+            const u32 nw = lead && g.stride >= 8192 ? block_waves(c) : GS_WAVES;     // 16 waves for a handful of 4 KB packets: 29 against 22 us
             const u32 sub_log2 = n_piece == 1 && g.n_pkts >= (g.W <= 4 ? 32u : 64u) * (u32)c->n_cus ? 5 : group_log2(c, n_piece > 1, nw);
             size_t lds = (size_t)nw * GS_TEAM_LDS(g.W, sub_log2) * sizeof(u32);
             const size_t table = ((size_t)g.B + 1) * sizeof(u32);
@@ -1894,7 +1915,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
             const u32 grid = grid_for(c, groups, nw == 16 ? 1 : 4);
             if (grid > c->rows_used[1]) c->rows_used[1] = grid;
             ProfScope ps(c, DBLP_K_GATHER_DIRECT);
-            hipLaunchKernelGGL((nw == 16 ? gather_stream<2, 1, 4, 16, true> : gather_stream<2, 1, 4, 4, true>), dim3(grid), dim3(nw * WAVE),
+            hipLaunchKernelGGL((nw == 16 ? gather_stream<2, 1, 4, 16, true> : lead ? gather_stream<2, 1, 4, 4, true> : gather_stream<2, 1, 4, 4, true, 0>), dim3(grid), dim3(nw * WAVE),
                                lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap, c->d_acc[0],
                                c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
                                launch_stream ? 0 : 1, c->d_accept_rows + ACCEPT_ROWS, c->d_sumsq_rows + ACCEPT_ROWS, inv_w, sub_log2, n_piece, table_in_lds, launch_stream ? 0 : 1);

@@ -113,6 +113,8 @@ STREAM_CASES = [(W, P, n) for W, P, n in (
     (1, 254, 700), (3, 255, 40), (4, 254, 41), (5, 257, 40), (1, 510, 60), (3, 513, 33), (17, 510, 19), (33, 514, 17),
     (2, 1278, 20), (4, 1278, 18), (4, 1279, 18), (64, 1279, 9), (3, 1537, 17), (8, 1535, 17), (6, 2243, 16), (3, 4094, 5),
     (1, 6, 8191), (4, 6, 8192), (19, 5, 8193), (2, 1, 9000),
+    # units counted from the payload: 256 k floats or one fewer, short last packets of every remainder
+    (1, 256, 1000), (4, 255, 41), (3, 256, 9000), (8, 512, 33), (2, 511, 40), (5, 768, 19), (1, 767, 60), (4, 1024, 18), (3, 1023, 20),
     # few and heavy packets: blocks of 16 waves with groups of 1, 2 and 4 packets
     (64, 600, 200), (33, 1021, 513), (40, 822, 1030), (9, 3700, 300))]
 
@@ -130,6 +132,7 @@ def test_dense_gather_at_the_edges_of_passes_pieces_and_groups(W, P, n):
 @pytest.mark.parametrize("loss", [0.05, 0.012])       # both instances launched; the sparse one alone
 @pytest.mark.parametrize("W,P,n", [(2, 1, 3000), (3, 2, 900), (4, 3, 900), (5, 5, 700), (8, 6, 700), (1, 510, 400), (4, 511, 130),
                                    (9, 512, 65), (3, 514, 97), (17, 1023, 33), (64, 366, 40), (2, 4097, 129),
+                                   (4, 256, 700), (3, 255, 301), (8, 512, 130), (2, 1024, 302), (5, 767, 64),
                                    (16, 2100, 300), (33, 2048, 523),            # blocks of 16 waves
                                    (2, 3, 400_000)])                            # empty groups passed over, 32 at a time
 def test_sparse_gather_updates_spans_of_earlier_batches(W, P, n, loss):
