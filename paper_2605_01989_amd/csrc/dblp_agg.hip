@@ -457,8 +457,7 @@ __device__ __forceinline__ BatchInfo fold_index_tallies(const u32* __restrict__ 
 
 // A batch is sparse when it holds fewer than one packet per SPARSE_DIV (worker, seq) pairs of the
 // sequence range it touches (retransmission batches).  Sparse batches take an instance of gather_stream
-// of their own (below); where the host cannot tell, both are launched and the one whose regime it is not
-// returns at once.
+// of their own (below); where the host cannot tell, the launch holds both and its blocks decide.
 #define SPARSE_DIV 8
 __device__ __forceinline__ bool batch_is_sparse(const BatchInfo& bi, u32 W) {
     return bi.cand * SPARSE_DIV < (bi.hi - bi.lo) * W;
@@ -517,34 +516,25 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int NP, int G, int D, int NW, bool SPARSE = false, u32 LEAD = 2>
-__global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void gather_stream(
-    Geo g, const uint8_t* __restrict__ packets, u64* __restrict__ pending, u64* __restrict__ bitmap,
-    float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
-    const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters, int whole_batch,
-    u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
-    u32 sub_log2, u32 n_piece, u32 table_in_lds, int tally_owner) {
-    extern __shared__ u32 sh_slots[];               // per wave: slots [W rounded up][sub + 1]; then the bucket table
-    __shared__ u32 sh_tally[NW * 5];
+// What a gather launch is given for one regime: sequence numbers per group (log2), pieces per packet, blocks.
+struct GatherShape { u32 sub_log2, n_piece, blocks; };
+
+// The gather of one batch by blocks 0 .. s.blocks - 1 of the launch.  fs: the bucket boundaries.
+template <int NP, int G, int D, int NW, bool SPARSE, u32 LEAD>
+__device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi, const GatherShape& s, const u32* fs, u32* sh_slots,
+                                              const uint8_t* __restrict__ packets, u64* __restrict__ pending, u64* __restrict__ bitmap,
+                                              float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
+                                              u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w) {
     __shared__ u32 sh_accepted[NW];
     __shared__ double sh_sq[NW];
     __shared__ u32 sh_tile[2];
+    if (blockIdx.x >= s.blocks) return;
     const u32 lane = lane_id();
-    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    const u32 wave = uniform(threadIdx.x / WAVE);
+    const u32 sub_log2 = s.sub_log2, n_piece = s.n_piece, n_blocks = s.blocks;
     const u32 W = g.W, sub = 1u << sub_log2, wpl = WAVE >> sub_log2, pitch = sub + 1;
-    const u32 team_words = GS_TEAM_LDS(W, sub_log2);
-    u32* const slots = sh_slots + wave * team_words;
-    const u32* fs = g.first_seq;
-    if (table_in_lds) {
-        u32* tab = sh_slots + NW * team_words;
-        for (u32 i = threadIdx.x; i <= g.B; i += blockDim.x) tab[i] = g.first_seq[i];
-        fs = tab;
-    }
-    // block 0 of the batch's first gather launch books the index pass's tallies
-    const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, tally_owner && blockIdx.x == 0, sh_tally);   // has barriers: covers the table too
+    u32* const slots = sh_slots + wave * GS_TEAM_LDS(W, sub_log2);
     const u64 lo = bi.lo, hi = bi.hi;
-    if (hi == 0) return;                            // no candidate in this batch (uniform over the grid)
-    if (!whole_batch && batch_is_sparse(bi, W) != SPARSE) return;       // left to the other kernel
     const u32 s_lane = lane & (sub - 1), w_sub = lane >> sub_log2;
     const u64 submask = NONE64 >> (WAVE - sub);
     const bool leader = wave == 0;
@@ -561,8 +551,8 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     // look through it costs what it saves).
     const bool skim = SPARSE && bi.cand * 64 < hi - lo;
     constexpr u32 TILE = SPARSE ? 64 : 1;
-    for (u64 tile = (u64)grp_lo + blockIdx.x; tile < grp_end; tile += (u64)TILE * gridDim.x) {
-    const u32 tile_left = SPARSE ? (grp_end - (u32)tile + gridDim.x - 1) / gridDim.x : 1, n_tile = tile_left < TILE ? tile_left : TILE;
+    for (u64 tile = (u64)grp_lo + blockIdx.x; tile < grp_end; tile += (u64)TILE * n_blocks) {
+    const u32 tile_left = SPARSE ? (grp_end - (u32)tile + n_blocks - 1) / n_blocks : 1, n_tile = tile_left < TILE ? tile_left : TILE;
     u64 todo = NONE64 >> (64 - n_tile);
     if (skim && n_tile >= 8) {
         const u32 rows = (W + wpl - 1) >> (6 - sub_log2);
@@ -577,7 +567,7 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
             #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 while (r >= rows && k < n_tile) { r -= rows; ++k; }
-                const u32 w = (r << (6 - sub_log2)) + w_sub, seq = ((u32)(tile + (u64)k * gridDim.x) << sub_log2) + s_lane;
+                const u32 w = (r << (6 - sub_log2)) + w_sub, seq = ((u32)(tile + (u64)k * n_blocks) << sub_log2) + s_lane;
                 kk[j] = k;
                 e[j] = k < n_tile && w < W && seq < g.n_pkts ? pending[(u64)w * g.n_pkts + seq] : NONE64;
                 r += NW;
@@ -591,7 +581,7 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
         todo = uniform(((u64)sh_tile[1] << 32) | sh_tile[0]);
     }
     for (; todo; todo &= todo - 1) {
-        const u64 grp = tile + (u64)__builtin_ctzll(todo) * gridDim.x;
+        const u64 grp = tile + (u64)__builtin_ctzll(todo) * n_blocks;
         // ---- arrival index -> slots of the group's new packets, bitmap bits, spans
         const u32 seq0 = (u32)grp << sub_log2, seq_l = seq0 + s_lane;
         const u32 word = seq0 >> 6, shift = seq0 & 63;
@@ -816,6 +806,31 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
         for (int i = 0; i < NW; ++i) { total += sh_accepted[i]; t += sh_sq[i]; }
         if (total) { accept_rows[blockIdx.x] += total; sumsq_rows[blockIdx.x] += t; }
     }
+}
+
+// MODE 0: the batch is dense, 1: sparse, 2: the index pass's tallies decide.
+template <int NP, int G, int D, int NW, u32 LEAD, int MODE>
+__global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void gather_stream(
+    Geo g, const uint8_t* __restrict__ packets, u64* __restrict__ pending, u64* __restrict__ bitmap,
+    float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
+    const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters,
+    u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
+    GatherShape dense, GatherShape sparse, u32 table_at) {
+    extern __shared__ u32 sh_dyn[];                 // per wave: slots [W rounded up][sub + 1]; then the bucket table (table_at words in, 0: not there)
+    __shared__ u32 sh_tally[NW * 5];
+    const u32* fs = g.first_seq;
+    if (table_at) {
+        u32* tab = sh_dyn + table_at;
+        for (u32 i = threadIdx.x; i <= g.B; i += blockDim.x) tab[i] = g.first_seq[i];
+        fs = tab;
+    }
+    // block 0 books the index pass's tallies; the barriers in there cover the table too
+    const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0, sh_tally);
+    if (bi.hi == 0) return;                         // no candidate in this batch (uniform over the grid)
+    if (MODE == 1 || (MODE == 2 && batch_is_sparse(bi, g.W)))
+        gather_groups<2, 1, 4, NW, true, LEAD>(g, bi, sparse, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
+    else
+        gather_groups<NP, G, D, NW, false, LEAD>(g, bi, dense, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1799,8 +1814,29 @@ extern "C" int dblp_packetize_list(dblp_ctx* c, uint16_t round, const float* con
     return DBLP_OK;
 }
 
-typedef void (*gather_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, int, u64*, double*, float,
-                          u32, u32, u32, int);
+typedef void (*gather_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, u64*, double*, float,
+                          GatherShape, GatherShape, u32);
+
+// The instance for `np` KB of a packet per step; few: one to three workers.
+template <int MODE, u32 LEAD>
+static gather_fn dense_kernel(bool few, u32 np) {
+    if (few) return np == 1 ? gather_stream<1, 1, 4, 4, LEAD, MODE> : np == 2 ? gather_stream<2, 1, 4, 4, LEAD, MODE>
+                  : np == 3 ? gather_stream<3, 1, 3, 4, LEAD, MODE> : np == 4 || !LEAD ? gather_stream<4, 1, 3, 4, LEAD, MODE>
+                                                                                       : gather_stream<5, 1, 3, 4, 2, MODE>;
+    return np == 1 ? gather_stream<1, 4, 2, 4, LEAD, MODE> : np == 2 ? gather_stream<2, 4, 2, 4, LEAD, MODE>
+         : np == 3 ? gather_stream<3, 2, 2, 4, LEAD, MODE> : np == 4 || !LEAD ? gather_stream<4, 2, 2, 4, LEAD, MODE>
+                                                                              : gather_stream<5, 1, 3, 4, 2, MODE>;
+}
+template <int MODE>
+static gather_fn wide_kernel(u32 np) {
+    return np == 1 ? gather_stream<1, 4, 2, 16, 2, MODE> : np == 2 ? gather_stream<2, 2, 2, 16, 2, MODE> : gather_stream<4, 2, 2, 16, 2, MODE>;
+}
+static gather_fn gather_kernel(int mode, u32 nw, bool lead, bool few, u32 np) {
+    if (mode == 1) return nw == 16 ? gather_stream<1, 1, 1, 16, 2, 1> : lead ? gather_stream<1, 1, 1, 4, 2, 1> : gather_stream<1, 1, 1, 4, 0, 1>;
+    if (nw == 16) return mode == 0 ? wide_kernel<0>(np) : wide_kernel<2>(np);
+    if (mode == 0) return lead ? dense_kernel<0, 2>(few, np) : dense_kernel<0, 0>(few, np);
+    return lead ? dense_kernel<2, 2>(few, np) : dense_kernel<2, 0>(few, np);
+}
 
 // Waves of a gather block: 16 in rounds of few and heavy packets (fewer than 8 sequence numbers per CU, 128 KB
 // or more from all workers for one of them), where a CU has one block at a time; 4 elsewhere.
@@ -1853,73 +1889,61 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         // 25.6 M: 55 -> 48; 1024-float retransmissions: 162 -> 144).  Other lengths are better off from the
         // start, where fewer passes begin inside a 128-byte line (32 x 1472 B: 1.64 against 1.65 ms).
         const bool lead = !(g.P <= 1024 && (g.P + 255) / 256 < (g.P + 2 + 255) / 256) || block_waves(c) == 16;
-        // Which instances of the gather: dense or sparse.  Where the number of arrivals settles it, only that one is launched: at least one arrival per
-        // SPARSE_DIV (worker, seq) pairs of the whole round is dense whatever range it touches; fewer
-        // than one per 8 * SPARSE_DIV pairs is taken as sparse.  In between both are launched and each
-        // decides on the device, from the sequence range the index pass found, whether the batch is its own.
+        // Dense or sparse.  Where the number of arrivals settles it, the launch is told: at least one arrival
+        // per SPARSE_DIV (worker, seq) pairs of the whole round is dense whatever range it touches; fewer than
+        // one per 8 * SPARSE_DIV pairs is taken as sparse.  In between (a chunk step, a large retransmission
+        // batch) the blocks decide, from the sequence range the index pass found (two launches of which one
+        // returned at once: 6 to 9 us more per batch).
         const u64 pairs = (u64)g.W * g.n_pkts;
-        const bool surely_dense = n_arrivals * SPARSE_DIV >= pairs;
-        const bool launch_stream = surely_dense || n_arrivals * SPARSE_DIV * 8 >= pairs;
-        const bool launch_direct = !surely_dense;
-        if (launch_stream) {
-            // Packets of up to 5 KB are one piece, longer ones are cut evenly into pieces of 3 or 4 KB; in
-            // a short round finer, so that a group gives each of the block's waves a piece.
-            const u32 n_pass = lead ? (g.units + WAVE - 1) / WAVE : (g.P + 4 * WAVE - 1) / (4 * WAVE);
-            u32 n_piece = n_pass <= 5 ? 1 : (n_pass + 3) / 4;
-            const u32 nw = lead ? block_waves(c) : GS_WAVES, sub_log2 = group_log2(c, n_piece > 1, nw);
-            if (nw == 16) {
-                const u32 want = nw >> sub_log2 < n_pass ? nw >> sub_log2 : n_pass;
-                if (n_piece < want) n_piece = want;
-            }
-            const u32 np = (n_pass + n_piece - 1) / n_piece;
-            n_piece = (n_pass + np - 1) / np;
-            size_t lds = (size_t)nw * GS_TEAM_LDS(g.W, sub_log2) * sizeof(u32);
-            const size_t table = ((size_t)g.B + 1) * sizeof(u32);
-            const u32 table_in_lds = table <= IDX_TABLE_LDS_MAX ? 1u : 0u;
-            if (table_in_lds) lds += table;
-            const u64 groups = ((u64)g.n_pkts + (1u << sub_log2) - 1) >> sub_log2;
-            // One to three workers: a step is one worker's piece, four of them in flight, and six blocks per
-            // CU (1 worker: 45 us, against 54 with three blocks, 68 with steps of four workers).  More: 4 to
-            // 8 KB per step, two steps in flight, three blocks per CU for short packets, two for long ones
-            // (8992 B: 930 against 940 us; more blocks only spread the DRAM accesses over more open rows).
-            const bool few = g.W < 4;
-            const u32 per_cu = nw == 16 ? 1 : few ? (np <= 2 ? 6 : 4) : np <= 2 ? 3 : 2;
-            gather_fn kern;
-            if (nw == 16) kern = np == 1 ? gather_stream<1, 4, 2, 16> : np == 2 ? gather_stream<2, 2, 2, 16> : gather_stream<4, 2, 2, 16>;
-            else if (!lead && few) kern = np == 1 ? gather_stream<1, 1, 4, 4, false, 0> : np == 2 ? gather_stream<2, 1, 4, 4, false, 0> : np == 3 ? gather_stream<3, 1, 3, 4, false, 0> : gather_stream<4, 1, 3, 4, false, 0>;
-            else if (!lead) kern = np == 1 ? gather_stream<1, 4, 2, 4, false, 0> : np == 2 ? gather_stream<2, 4, 2, 4, false, 0> : np == 3 ? gather_stream<3, 2, 2, 4, false, 0> : gather_stream<4, 2, 2, 4, false, 0>;
-            else if (few) kern = np == 1 ? gather_stream<1, 1, 4, 4> : np == 2 ? gather_stream<2, 1, 4, 4> : np == 3 ? gather_stream<3, 1, 3, 4> : np == 4 ? gather_stream<4, 1, 3, 4> : gather_stream<5, 1, 3, 4>;
-            else kern = np == 1 ? gather_stream<1, 4, 2, 4> : np == 2 ? gather_stream<2, 4, 2, 4> : np == 3 ? gather_stream<3, 2, 2, 4> : np == 4 ? gather_stream<4, 2, 2, 4> : gather_stream<5, 1, 3, 4>;
-            const u32 grid = grid_for(c, groups, per_cu);
-            if (grid > c->rows_used[0]) c->rows_used[0] = grid;
-            ProfScope ps(c, DBLP_K_GATHER);
-            hipLaunchKernelGGL(kern, dim3(grid), dim3(nw * WAVE),
-                               lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap, c->d_acc[0],
-                               c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
-                               surely_dense ? 1 : 0, c->d_accept_rows, c->d_sumsq_rows, inv_w, sub_log2, n_piece, table_in_lds, 1);
+        const int mode = n_arrivals * SPARSE_DIV >= pairs ? 0 : n_arrivals * SPARSE_DIV * 8 < pairs ? 1 : 2;
+        const u32 nw = mode == 1 && g.stride < 8192 ? GS_WAVES      // 16 waves for a handful of 4 KB packets: 29 against 22 us
+                                                    : block_waves(c);
+        // Dense.  Packets of up to 5 KB are one piece, longer ones are cut evenly into pieces of 3 or 4 KB; in
+        // a short round finer, so that a group gives each of the block's waves a piece.
+        GatherShape dense, sparse;
+        const u32 n_pass = lead ? (g.units + WAVE - 1) / WAVE : (g.P + 4 * WAVE - 1) / (4 * WAVE);
+        dense.n_piece = n_pass <= 5 ? 1 : (n_pass + 3) / 4;
+        dense.sub_log2 = group_log2(c, dense.n_piece > 1, nw);
+        if (nw == 16) {
+            const u32 want = nw >> dense.sub_log2 < n_pass ? nw >> dense.sub_log2 : n_pass;
+            if (dense.n_piece < want) dense.n_piece = want;
         }
-        if (launch_direct) {   // sparse batches
-            // One worker's 2 KB per step.  Groups of 32 packets of up to 2 KB in long rounds (longer rows of the
-            // index, fewer empty groups to pass: 54 us against 69 with 16 and 51 with 64 for 12 k packets over a
-            // round of 340 k x 8); otherwise as for dense batches (64 KB datagrams: 22 us with 16 against 36;
-            // larger groups leave too much to one block where the lost packets lie in a few runs: 16 x 4112 B,
-            // 162 us with 16, 270 with 64).
-            const u32 n_piece = lead ? (g.units + 2 * WAVE - 1) / (2 * WAVE) : (g.P + 8 * WAVE - 1) / (8 * WAVE);
-            const u32 nw = lead && g.stride >= 8192 ? block_waves(c) : GS_WAVES;     // 16 waves for a handful of 4 KB packets: 29 against 22 us
-            const u32 sub_log2 = n_piece == 1 && g.n_pkts >= (g.W <= 4 ? 32u : 64u) * (u32)c->n_cus ? 5 : group_log2(c, n_piece > 1, nw);
-            size_t lds = (size_t)nw * GS_TEAM_LDS(g.W, sub_log2) * sizeof(u32);
-            const size_t table = ((size_t)g.B + 1) * sizeof(u32);
-            const u32 table_in_lds = table <= IDX_TABLE_LDS_MAX ? 1u : 0u;
-            if (table_in_lds) lds += table;
-            const u64 groups = ((u64)g.n_pkts + (1u << sub_log2) - 1) >> sub_log2;
-            const u32 grid = grid_for(c, groups, nw == 16 ? 1 : 4);
-            if (grid > c->rows_used[1]) c->rows_used[1] = grid;
-            ProfScope ps(c, DBLP_K_GATHER_DIRECT);
-            hipLaunchKernelGGL((nw == 16 ? gather_stream<2, 1, 4, 16, true> : lead ? gather_stream<2, 1, 4, 4, true> : gather_stream<2, 1, 4, 4, true, 0>), dim3(grid), dim3(nw * WAVE),
-                               lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap, c->d_acc[0],
-                               c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
-                               launch_stream ? 0 : 1, c->d_accept_rows + ACCEPT_ROWS, c->d_sumsq_rows + ACCEPT_ROWS, inv_w, sub_log2, n_piece, table_in_lds, launch_stream ? 0 : 1);
+        const u32 np = (n_pass + dense.n_piece - 1) / dense.n_piece;
+        dense.n_piece = (n_pass + np - 1) / np;
+        // One to three workers: a step is one worker's piece, four of them in flight, and six blocks per
+        // CU (1 worker: 45 us, against 54 with three blocks, 68 with steps of four workers).  More: 4 to
+        // 8 KB per step, two steps in flight, three blocks per CU for short packets, two for long ones
+        // (8992 B: 930 against 940 us; more blocks only spread the DRAM accesses over more open rows).
+        const bool few = g.W < 4;
+        const u32 per_cu = nw == 16 ? 1 : few ? (np <= 2 && mode == 0 ? 6 : 4) : np <= 2 ? 3 : 2;
+        dense.blocks = grid_for(c, ((u64)g.n_pkts + (1u << dense.sub_log2) - 1) >> dense.sub_log2, per_cu);
+        // Sparse.  One worker's 2 KB per step.  Groups of 32 packets of up to 2 KB in long rounds (longer rows of
+        // the index, fewer empty groups to pass: 54 us against 69 with 16 and 51 with 64 for 12 k packets over a
+        // round of 340 k x 8); otherwise as for dense batches (64 KB datagrams: 22 us with 16 against 36;
+        // larger groups leave too much to one block where the lost packets lie in a few runs: 16 x 4112 B,
+        // 162 us with 16, 270 with 64).
+        sparse.n_piece = lead ? (g.units + 2 * WAVE - 1) / (2 * WAVE) : (g.P + 8 * WAVE - 1) / (8 * WAVE);
+        sparse.sub_log2 = sparse.n_piece == 1 && g.n_pkts >= (g.W <= 4 ? 32u : 64u) * (u32)c->n_cus ? 5 : group_log2(c, sparse.n_piece > 1, nw);
+        sparse.blocks = grid_for(c, ((u64)g.n_pkts + (1u << sparse.sub_log2) - 1) >> sparse.sub_log2, nw == 16 ? 1 : 4);
+
+        u32 slots = 0, grid = 0;
+        if (mode != 1) { slots = GS_TEAM_LDS(g.W, dense.sub_log2); grid = dense.blocks; }
+        if (mode != 0) {
+            if (GS_TEAM_LDS(g.W, sparse.sub_log2) > slots) slots = GS_TEAM_LDS(g.W, sparse.sub_log2);
+            if (sparse.blocks > grid) grid = sparse.blocks;
         }
+        size_t lds = (size_t)nw * slots * sizeof(u32);
+        const size_t table = ((size_t)g.B + 1) * sizeof(u32);
+        const u32 table_at = table <= IDX_TABLE_LDS_MAX ? nw * slots : 0u;
+        if (table_at) lds += table;
+        const gather_fn kern = gather_kernel(mode, nw, lead, few, np);
+        const u32 set = mode == 1 ? 1 : 0;          // which rows the launch adds to
+        if (grid > c->rows_used[set]) c->rows_used[set] = grid;
+        // trace group: a batch that the blocks classify counts as dense unless its buffer is the whole round's
+        ProfScope ps(c, mode == 1 || (mode == 2 && n_slots >= pairs) ? DBLP_K_GATHER_DIRECT : DBLP_K_GATHER);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(nw * WAVE), lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap,
+                           c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
+                           c->d_accept_rows + set * ACCEPT_ROWS, c->d_sumsq_rows + set * ACCEPT_ROWS, inv_w, dense, sparse, table_at);
     }
     LAUNCH_CHECK(c, "apply_arrivals");
     c->finalized = 0; c->norm_in_mailbox = 0; c->counters_in_mailbox = 0;
