@@ -1937,11 +1937,15 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         dense.blocks = grid_for(c, ((u64)g.n_pkts + (1u << dense.sub_log2) - 1) >> dense.sub_log2, per_cu);
         // Sparse.  One worker's 2 KB per step.  Groups of 32 packets of up to 2 KB in long rounds (longer rows of
         // the index, fewer empty groups to pass: 54 us against 69 with 16 and 51 with 64 for 12 k packets over a
-        // round of 340 k x 8); otherwise as for dense batches (64 KB datagrams: 22 us with 16 against 36;
-        // larger groups leave too much to one block where the lost packets lie in a few runs: 16 x 4112 B,
-        // 162 us with 16, 270 with 64).
+        // round of 340 k x 8); otherwise as for dense batches (larger groups
+        // leave too much to one block where the lost packets lie in a few runs: 16 x 4112 B, 162 us with 16,
+        // 270 with 64).
         sparse.n_piece = lead ? (g.units + 2 * WAVE - 1) / (2 * WAVE) : (g.P + 8 * WAVE - 1) / (8 * WAVE);
         sparse.sub_log2 = sparse.n_piece == 1 && g.n_pkts >= (g.W <= 4 ? 32u : 64u) * (u32)c->n_cus ? 5 : group_log2(c, sparse.n_piece > 1, nw);
+        // Packets of 16 KB and more fill a block's waves four at a time: fewer to one block where lost packets
+        // follow each other (1 worker x 66 M in 64 KB packets: 35 against 64 us, 7 x 249 M 45 against 107, 4 x 61 M
+        // 20 against 26), until the groups get many.
+        if (sparse.n_piece >= 8 && sparse.sub_log2 > 2 && g.n_pkts <= 64u * (u32)c->n_cus) sparse.sub_log2 = 2;
         sparse.blocks = grid_for(c, ((u64)g.n_pkts + (1u << sparse.sub_log2) - 1) >> sparse.sub_log2, nw == 16 ? 1 : 4);
 
         u32 slots = 0, grid = 0;

@@ -133,6 +133,7 @@ def test_dense_gather_at_the_edges_of_passes_pieces_and_groups(W, P, n):
 @pytest.mark.parametrize("W,P,n", [(2, 1, 3000), (3, 2, 900), (4, 3, 900), (5, 5, 700), (8, 6, 700), (1, 510, 400), (4, 511, 130),
                                    (9, 512, 65), (3, 514, 97), (17, 1023, 33), (64, 366, 40), (2, 4097, 129),
                                    (4, 256, 700), (3, 255, 301), (8, 512, 130), (2, 1024, 302), (5, 767, 64),
+                                   (2, 4097, 2100),                             # groups of four long packets
                                    (16, 2100, 300), (33, 2048, 523),            # blocks of 16 waves
                                    (2, 3, 400_000)])                            # empty groups passed over, 32 at a time
 def test_sparse_gather_updates_spans_of_earlier_batches(W, P, n, loss):
