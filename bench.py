@@ -34,8 +34,8 @@ BENCH_DRAWN_ROUNDS = 3   # retransmission rounds with a drawn loss pattern; late
 # on and by workload; anything else reports null.
 # value = measured bytes / algorithmic bytes of a first-transmission launch.
 PMC_TRAFFIC_RATIO: dict[tuple[str, str], float] = {
-    ("3d4a1fc4cec74112deff2e5e7730b9e8e47595d4a41a9e5ff7a7fd105506a6c6", "cfg5"): 1.066,   # profiles/receiver_path_cfg5.md
-    ("3d4a1fc4cec74112deff2e5e7730b9e8e47595d4a41a9e5ff7a7fd105506a6c6", "cfg4"): 1.030,   # profiles/receiver_path_cfg4.md
+    ("55b4d38a4a71e7c67fb52366190232a5d14ad3697f9a0dc4eb3e287e8a1589ae", "cfg5"): 1.062,   # profiles/receiver_path_cfg5.md
+    ("55b4d38a4a71e7c67fb52366190232a5d14ad3697f9a0dc4eb3e287e8a1589ae", "cfg4"): 1.033,   # profiles/receiver_path_cfg4.md
 }
 
 
