@@ -36,6 +36,7 @@
 #include <vector>
 
 #include "../../include/dblp_agg.h"
+#include "packet_units.h"
 
 typedef unsigned long long u64;
 typedef uint32_t u32;
@@ -678,17 +679,10 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
             }
             const u32 len = (u32)__builtin_amdgcn_readlane((int)len_l, (int)t_gen);
             const u32 skip = piece_gen * (NP * 1024u);
-            // the end of what is read: the last unit (LEAD 2: it may hold padding), the payload's end (LEAD 0:
-            // a last unit of fewer than four floats is read as the 16 bytes that end there, turned into
-            // place when it is stored, so that every access lies inside the packet)
-            const u32 end = LEAD ? ((len + 2 + 3) >> 2) * 16 : len > 2 ? 8 + 4 * len : 16;
-            const u32 have = end > skip ? end - skip : 0;
+            const u32 have = unit_have<LEAD>(len, skip);
             int off[NP];
             #pragma unroll
-            for (int q = 0; q < NP; ++q) {
-                off[q] = (int)(lane * 16 + q * 1024 + (LEAD ? 0 : 8));
-                if (!LEAD && (len & 3u) && (piece_gen * NP + q) * WAVE + lane == len >> 2) off[q] = (int)(end - 16 - skip);
-            }
+            for (int q = 0; q < NP; ++q) off[q] = unit_offset<LEAD>(len, skip, q * WAVE + lane);
             u32 tg = left_gen ? 0x80000000u : 0u;
             #pragma unroll
             for (int j = 0; j < G; ++j) {
@@ -696,10 +690,10 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
                 const u32 w = any ? (u32)__builtin_ctzll(left_gen) : 0u;
                 left_gen &= left_gen - 1;
                 const u32 slot = any ? (u32)__builtin_amdgcn_readlane((int)slot32, (int)w) : 0u;
-                // a buffer of `have` bytes at the piece (none for a worker without one): lanes beyond it
-                // read zeros and ask memory for nothing, so every step issues the same loads
+                // a buffer of `have` bytes (none for a worker without one): lanes beyond it read zeros and ask
+                // memory for nothing, so every step issues the same loads; packet_units.h says where it lies
                 __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-                    (void*)(packets + uniform((u64)slot * g.stride + skip)), 0, (int)uniform(any ? have : 0u), BUF_RAW);
+                    (void*)(packets + uniform((u64)slot * g.stride + unit_base<LEAD>(skip))), 0, (int)uniform(any ? have : 0u), BUF_RAW);
                 #pragma unroll
                 for (int q = 0; q < NP; ++q)
                     v[d][j][q] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r, off[q], 0, BUF_NT));

@@ -113,7 +113,7 @@ STREAM_CASES = [(W, P, n) for W, P, n in (
     (1, 254, 700), (3, 255, 40), (4, 254, 41), (5, 257, 40), (1, 510, 60), (3, 513, 33), (17, 510, 19), (33, 514, 17),
     (2, 1278, 20), (4, 1278, 18), (4, 1279, 18), (64, 1279, 9), (3, 1537, 17), (8, 1535, 17), (6, 2243, 16), (3, 4094, 5),
     (1, 6, 8191), (4, 6, 8192), (19, 5, 8193), (2, 1, 9000),
-    # units counted from the payload: 256 k floats or one fewer, short last packets of every remainder
+    # units counted from the payload: 256 k floats or one fewer (short last packets of every remainder: the test after the next)
     (1, 256, 1000), (4, 255, 41), (3, 256, 9000), (8, 512, 33), (2, 511, 40), (5, 768, 19), (1, 767, 60), (4, 1024, 18), (3, 1023, 20),
     # few and heavy packets: blocks of 16 waves with groups of 1, 2 and 4 packets
     (64, 600, 200), (33, 1021, 513), (40, 822, 1030), (9, 3700, 300))]
@@ -138,11 +138,43 @@ def test_dense_gather_at_the_edges_of_passes_pieces_and_groups(W, P, n):
                                    (2, 3, 400_000)])                            # empty groups passed over, 32 at a time
 def test_sparse_gather_updates_spans_of_earlier_batches(W, P, n, loss):
     """Retransmissions into spans that the first transmission wrote, and into spans nobody delivered:
-    spans of 1 to 3 floats, last units of every length, whole pieces of 512 floats and one float more
-    or less, groups of 32 and of 16 packets with a remainder.  Everything is delivered in the end."""
+    spans of 1 to 3 floats, packets of whole pieces of 512 floats and of one float more or less (last packets
+    of 1 and P - P / 2 floats; other lengths: the next test), groups of 32 and of 16 packets with a remainder.
+    Everything is delivered in the end."""
     sc = build_scenario(mk(W, [P * (n // 3) + 1, P * (n - n // 3) - (P // 2)], P, loss))
     stats, got, ref = run_both(sc, 0, queue=True)
     assert stats["rel_to_addends"] <= FLOAT_TOL
+
+
+@pytest.mark.parametrize("filler", [200, 2800])       # the sparse batch: more, fewer than one packet per 64 pairs of the round
+@pytest.mark.parametrize("W", [3, 8])
+@pytest.mark.parametrize("P", [254, 255, 256, 511, 512, 767, 768, 1023, 1024, 1025, 1279])
+def test_last_packets_of_every_remainder_and_beside_piece_edges(P, W, filler):
+    """Last packets of 1, 2, 3 floats, of one float to three beside the edge of a 1 KB pass or a 2 KB piece, and
+    of P - 1: in a dense batch into new spans, in a second one into written spans, and in a sparse one into
+    both (two buckets per length; of the second all workers' last packets come with the sparse batch)."""
+    tails = sorted({t for e in (0, 256, 512, 768, 1024) for t in range(e - 3, e + 4) if 0 < t < P} | {P - 1})
+    sizes = [2 * P + t for t in tails for _ in range(2)] + [filler * P]
+    sc = build_scenario(mk(W, sizes, P))
+    L = sc.L
+    n = L.W * L.n_pkts
+    last = L.first_seq[1:1 + 2 * len(tails)].astype(np.int64) - 1
+    held = np.zeros((L.W, L.n_pkts), dtype=bool)
+    held[W // 2, last[0::2]] = True                  # a span that the others have written
+    held[:, last[1::2]] = True                       # a span that nobody has
+    half = np.random.default_rng(P).random((L.W, L.n_pkts)) < 0.5
+    assert n > held.sum() * 8 and (held.sum() * 64 < n) == (filler == 2800)
+    o, g = both(sc, queue=True)
+    for rx in (o, g):
+        rx.begin_round(sc.rnd_id)
+        for part in (half & ~held, ~half & ~held, held):
+            rx.apply(0, n, None, np.sort(sc.slot_of[part]))
+    assert g.bitmap().all() and g.counters() == o.counters() and o.counters()["accepted"] == n
+    from harness import abs_scale
+    ref, got = o.finalize(), g.finalize().astype(np.float64)
+    scale = abs_scale(sc, np.ones((L.W, L.n_pkts)))
+    assert (np.abs(got - ref) <= FLOAT_TOL * scale).all()
+    assert g.phase_signal()[0] == pytest.approx(o.phase_signal()[0], rel=1e-6)
 
 
 # ------------------------------------------------------------------------------ two accumulator copies
