@@ -304,11 +304,11 @@ int dblp_get_prev_norm(const dblp_ctx* ctx, double* h_norm, int* h_have);
  * since the last read of that group, and forgets them.  At most 16384 brackets are kept between
  * reads; further ones are dropped.  dblp_profile_enable may return ENOMEM. */
 #define DBLP_K_INDEX 0    /* header parse / validation / arrival index */
-#define DBLP_K_GATHER 1   /* payload gather + accumulate, dense batches (one that the device classifies counts as
-                             dense unless its packet buffer holds the whole round's slots) */
+#define DBLP_K_GATHER 1   /* payload gather + accumulate, dense batches */
 #define DBLP_K_PROBE 2    /* loss count + retransmit list (two or three launches, one bracket) */
 #define DBLP_K_FINALIZE 3 /* zero-fill mean + partial sums of squares */
-#define DBLP_K_GATHER_DIRECT 4 /* the same, sparse batches (retransmissions) */
+#define DBLP_K_GATHER_DIRECT 4 /* the same, sparse batches (retransmissions), and all of fewer than one arrival per
+                                  64 (worker, sequence number) pairs of the round */
 #define DBLP_K_COUNT 5
 int dblp_profile_enable(dblp_ctx* ctx, int on);
 int dblp_profile_read(dblp_ctx* ctx, int kernel, double* h_total_ms, uint64_t* h_launches);

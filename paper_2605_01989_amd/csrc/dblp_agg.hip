@@ -813,7 +813,7 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
     const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters,
     u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
-    GatherShape dense, GatherShape sparse, u32 table_at) {
+    GatherShape dense, GatherShape sparse, u32 table_at, u32* __restrict__ told) {
     extern __shared__ u32 sh_dyn[];                 // per wave: slots [W rounded up][sub + 1]; then the bucket table (table_at words in, 0: not there)
     __shared__ u32 sh_tally[NW * 5];
     const u32* fs = g.first_seq;
@@ -824,8 +824,10 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     }
     // block 0 books the index pass's tallies; the barriers in there cover the table too
     const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0, sh_tally);
+    const bool is_sparse = MODE == 1 || (MODE == 2 && batch_is_sparse(bi, g.W));
+    if (MODE == 2 && told && blockIdx.x == 0 && threadIdx.x == 0) *told = is_sparse;    // for the trace group of the launch
     if (bi.hi == 0) return;                         // no candidate in this batch (uniform over the grid)
-    if (MODE == 1 || (MODE == 2 && batch_is_sparse(bi, g.W)))
+    if (is_sparse)
         gather_groups<2, 1, 4, NW, true, LEAD>(g, bi, sparse, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
     else
         gather_groups<NP, G, D, NW, false, LEAD>(g, bi, dense, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
@@ -1324,8 +1326,10 @@ struct dblp_ctx {
     double prev_norm; int have_prev;
     // optional per-kernel timing (HIP events on the context's stream)
     int profiling;          // bit k set: launches of kernel group k are bracketed by events
-    struct Timed { hipEvent_t a, b; int kernel; };
+    struct Timed { hipEvent_t a, b; int kernel; u32 told; };     // kernel < 0: minus the wanted groups; h_told[told] says which
     std::vector<Timed>* timed;        // recorded, not yet read
+    u32* h_told; u32* d_told;         // mapped host memory: a gather launch that decides on the device tells here what it was (0 dense, 1 sparse)
+    u32 n_told;                       // entries in use, by records not yet read
     std::vector<hipEvent_t>* ev_pool; // free events
     char err[256];
 };
@@ -1337,19 +1341,27 @@ static hipEvent_t prof_event(dblp_ctx* c) {
     return e;
 }
 
-// Brackets one kernel launch with events when profiling is on.
+#define PROF_MAX_RECORDS 16384   // brackets kept between two dblp_profile_read calls; more are dropped
+
+// Brackets one kernel launch with events when profiling is on.  `told`: the launch decides on the device whether it
+// is a dense or a sparse gather, so the bracket's group is known when it is read.
 struct ProfScope {
-    dblp_ctx* c; hipEvent_t a; int kernel;
-    ProfScope(dblp_ctx* c_, int kernel_) : c(c_), a(nullptr), kernel(kernel_) {
-        if (((c->profiling >> kernel) & 1) && (a = prof_event(c))) (void)hipEventRecord(a, c->stream);
+    dblp_ctx* c; hipEvent_t a; int kernel; u32 at;
+    ProfScope(dblp_ctx* c_, int kernel_, bool told = false) : c(c_), a(nullptr), kernel(kernel_), at(0) {
+        const int want = c->profiling & (told ? 1 << DBLP_K_GATHER | 1 << DBLP_K_GATHER_DIRECT : 1 << kernel);
+        if (!want || (told && c->n_told >= PROF_MAX_RECORDS)) return;
+        if (!(a = prof_event(c))) return;
+        if (told) { kernel = -want; at = c->n_told++; }
+        (void)hipEventRecord(a, c->stream);
     }
+    u32* d_told() const { return a && kernel < 0 ? c->d_told + at : nullptr; }
     ~ProfScope() {
         if (!a) return;
         hipEvent_t b = prof_event(c);
         if (!b) { c->ev_pool->push_back(a); return; }
         (void)hipEventRecord(b, c->stream);
-        if (c->timed->size() < c->timed->capacity()) c->timed->push_back({a, b, kernel});   // never reallocates
-        else { c->ev_pool->push_back(a); c->ev_pool->push_back(b); }                        // buffer full: drop the sample
+        if (c->timed->size() < c->timed->capacity()) c->timed->push_back({a, b, kernel, at});   // never reallocates
+        else { c->ev_pool->push_back(a); c->ev_pool->push_back(b); }                            // buffer full: drop the sample
     }
 };
 
@@ -1393,6 +1405,7 @@ extern "C" int dblp_destroy(dblp_ctx* c) {
     for (void* p : dev) if (p) (void)hipFree(p);
     for (hipEvent_t e : c->cls_ev) if (e) (void)hipEventDestroy(e);
     if (c->h_mailbox) (void)hipHostFree(c->h_mailbox);
+    if (c->h_told) (void)hipHostFree(c->h_told);
     if (c->timed) { for (auto& t : *c->timed) { (void)hipEventDestroy(t.a); (void)hipEventDestroy(t.b); } delete c->timed; }
     if (c->ev_pool) { for (auto e : *c->ev_pool) (void)hipEventDestroy(e); delete c->ev_pool; }
     free(c->h_first_seq); free(c->h_b_off); free(c->h_b_cnt);
@@ -1827,7 +1840,7 @@ extern "C" int dblp_packetize_list(dblp_ctx* c, uint16_t round, const float* con
 }
 
 typedef void (*gather_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, u64*, double*, float,
-                          GatherShape, GatherShape, u32);
+                          GatherShape, GatherShape, u32, u32*);
 
 // The instance for `np` KB of a packet per step; few: one to three workers.
 template <int MODE, u32 LEAD>
@@ -1955,11 +1968,10 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         const gather_fn kern = gather_kernel(mode, nw, lead, few, np);
         const u32 set = mode == 1 ? 1 : 0;          // which rows the launch adds to
         if (grid > c->rows_used[set]) c->rows_used[set] = grid;
-        // trace group: a batch that the blocks classify counts as dense unless its buffer is the whole round's
-        ProfScope ps(c, mode == 1 || (mode == 2 && n_slots >= pairs) ? DBLP_K_GATHER_DIRECT : DBLP_K_GATHER);
+        ProfScope ps(c, mode == 1 ? DBLP_K_GATHER_DIRECT : DBLP_K_GATHER, mode == 2);
         hipLaunchKernelGGL(kern, dim3(grid), dim3(nw * WAVE), lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap,
                            c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
-                           c->d_accept_rows + set * ACCEPT_ROWS, c->d_sumsq_rows + set * ACCEPT_ROWS, inv_w, dense, sparse, table_at);
+                           c->d_accept_rows + set * ACCEPT_ROWS, c->d_sumsq_rows + set * ACCEPT_ROWS, inv_w, dense, sparse, table_at, ps.d_told());
     }
     LAUNCH_CHECK(c, "apply_arrivals");
     c->finalized = 0; c->norm_in_mailbox = 0; c->counters_in_mailbox = 0;
@@ -2177,8 +2189,6 @@ extern "C" int dblp_get_counters(dblp_ctx* c, uint64_t h[4]) {
     return DBLP_OK;
 }
 
-#define PROF_MAX_RECORDS 16384   // brackets kept between two dblp_profile_read calls; more are dropped
-
 extern "C" int dblp_profile_enable(dblp_ctx* c, int on) {
     if (!c) return DBLP_EINVAL;
     if (on) {
@@ -2188,6 +2198,13 @@ extern "C" int dblp_profile_enable(dblp_ctx* c, int on) {
         } catch (...) {
             return fail(c, DBLP_ENOMEM, "profile_enable: out of host memory");
         }
+        HIP_TRY(c, hipSetDevice(c->device));
+        if (!c->h_told && hipHostMalloc((void**)&c->h_told, PROF_MAX_RECORDS * sizeof(u32), hipHostMallocMapped) != hipSuccess) {
+            (void)hipGetLastError();
+            c->h_told = nullptr;
+            return fail(c, DBLP_ENOMEM, "profile_enable: out of pinned host memory");
+        }
+        HIP_TRY(c, hipHostGetDevicePointer((void**)&c->d_told, c->h_told, 0));
     }
     c->profiling = on & ((1 << DBLP_K_COUNT) - 1);
     return DBLP_OK;
@@ -2200,13 +2217,19 @@ extern "C" int dblp_profile_read(dblp_ctx* c, int kernel, double* h_total_ms, ui
     double total = 0.0; u64 n = 0;
     size_t kept = 0;                      // compact in place: no allocation on this path
     for (size_t i = 0; i < c->timed->size(); ++i) {
-        const dblp_ctx::Timed t = (*c->timed)[i];
+        dblp_ctx::Timed t = (*c->timed)[i];
+        if (t.kernel < 0) {               // the launch has ended and told its group
+            const int wanted = -t.kernel;
+            t.kernel = *(volatile u32*)(c->h_told + t.told) ? DBLP_K_GATHER_DIRECT : DBLP_K_GATHER;
+            if (!((wanted >> t.kernel) & 1)) { c->ev_pool->push_back(t.a); c->ev_pool->push_back(t.b); continue; }
+        }
         if (t.kernel != kernel) { (*c->timed)[kept++] = t; continue; }
         float ms = 0.f;
         if (hipEventElapsedTime(&ms, t.a, t.b) == hipSuccess) { total += ms; ++n; } else (void)hipGetLastError();
         c->ev_pool->push_back(t.a); c->ev_pool->push_back(t.b);   // within the reserved capacity
     }
     c->timed->resize(kept);
+    c->n_told = 0;                        // no record waits for an entry any more
     *h_total_ms = total; *h_launches = n;
     return DBLP_OK;
 }

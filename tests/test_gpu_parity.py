@@ -978,3 +978,37 @@ def test_probe_counts_and_lists_of_few_and_many_buckets(W, B, big, ppm):
     part = g.loss_account(ppm, capacity=count // 2)
     assert part[2] == count and np.array_equal(part[1], lst[:count // 2])
     assert g.agg.loss_account(ppm, None, None) == (count, count == 0, count > 0)
+
+
+# ------------------------------------------------------------------------------ trace groups of the gather
+@pytest.mark.parametrize("mask", ["both", "dense", "sparse"])
+@pytest.mark.parametrize("own_buffer", [False, True])
+def test_gather_launches_count_in_the_group_that_they_belong_to(own_buffer, mask):
+    """A contiguous step and a scattered retransmission, each of one arrival per 20 pairs of the round, handed over in
+    the whole round's buffer or in one of their own: the step counts as dense, the retransmission as sparse,
+    whichever buffer they come in and whichever of the two groups is traced."""
+    from paper_2605_01989_amd import binding
+    sc = build_scenario(mk(4, [366 * 2000], 366, place="worker_major"))
+    L = sc.L
+    g = GpuRx(sc, queue=True); g.packetize_all()
+    step = np.zeros((L.W, L.n_pkts), dtype=bool)
+    step[:, :L.n_pkts // 20] = True
+    scattered = np.zeros((L.W, L.n_pkts), dtype=bool)
+    scattered[:, 150::20] = True
+    g.agg.profile_enable(dict(both=True, dense=1 << binding.K_GATHER, sparse=1 << binding.K_GATHER_DIRECT)[mask])
+    st = g.agg.stride
+    for which, group in ((step, binding.K_GATHER), (scattered, binding.K_GATHER_DIRECT)):
+        slots = np.sort(sc.slot_of[which]).astype(np.int64)
+        packets = g.packets
+        if own_buffer:
+            packets = packets.view(-1, st)[g.torch.from_numpy(slots).cuda()].reshape(-1).contiguous()
+        src = g.src.cpu().numpy().view(np.uint16)[slots].astype(np.uint64)
+        where = np.arange(slots.size, dtype=np.uint64) if own_buffer else slots.astype(np.uint64)
+        queue = g.torch.from_numpy((where | (src << np.uint64(32))).view(np.int64)).cuda()
+        g.begin_round(sc.rnd_id)
+        for n in (1, 2):                                 # two launches, read after each
+            g.agg.apply_arrivals_queue(packets, slots.size if own_buffer else L.W * L.n_pkts, queue)
+            for k in (binding.K_GATHER, binding.K_GATHER_DIRECT):
+                traced = mask == "both" or (mask == "dense") == (k == binding.K_GATHER)
+                assert g.agg.profile_read(k)[1] == (1 if k == group and traced else 0), (k, group, n)
+        assert g.counters()["accepted"] == slots.size
