@@ -493,14 +493,16 @@ __device__ __forceinline__ bool batch_is_sparse(const BatchInfo& bi, u32 W) {
 //   1 x 1472 B, 0.2 GB (as much written as read)   94 -> 45   (2.2 -> 4.6)
 //   4 x 1040 B, 21 MB                              19 -> 12
 //
-// SPARSE (retransmissions): a step is one worker's 2 KB, four in flight, and the last step of a packet
+// SPARSE (retransmissions): a step is one worker's 2 KB, two in flight, and the last step of a packet
 // loads the span's old contents with it (they were a second trip to memory after the payload's), again
-// through a descriptor, of length zero where the span is new.  It replaces a kernel whose waves took
-// whole packets one after the other, us per launch:
-//   553 k packets of a round of 541 k x 32, 1472 B      620 -> 463
-//   about 12 k of 340 k x 8, 1472 B                      72 -> 54
-//   about 10 of 3740 x 4, 64 KB                          72 -> 22
-//   about 90 k in three runs of 347 k x 16, 4112 B      187 -> 162
+// through a descriptor, of length zero where the span is new.  Most waves have one to three steps, so none
+// is empty and little code is run through once (four steps in flight, empty ones among them, and eight
+// index rows: 1.5 to 2 us more for a few packets of a round of 4096).  Against a kernel whose waves of a
+// block took whole packets one after the other, us per launch:
+//   524 k packets of a round of 546 k x 32, 1472 B      722 -> 460
+//   14 k of 340 k x 8, 1472 B                            114 -> 46
+//   10 of 3740 x 4, 64 KB                                 72 -> 22
+//   57 k in three runs of 355 k x 16, 4016 B             345 -> 186
 typedef f4v f4v_a4 __attribute__((aligned(4)));      // a 16-byte access at a 4-byte aligned address
 typedef float f2v __attribute__((ext_vector_type(2)));
 typedef f2v f2v_a4 __attribute__((aligned(4)));
@@ -532,7 +534,7 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
                                               u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w) {
     __shared__ u32 sh_accepted[NW];
     __shared__ double sh_sq[NW];
-    __shared__ u32 sh_tile[2];
+    __shared__ u32 sh_tile[4];      // sparse: groups of the tile that hold an arrival; groups left to the whole block
     if (blockIdx.x >= s.blocks) return;
     const u32 lane = lane_id();
     const u32 wave = uniform(threadIdx.x / WAVE);
@@ -542,30 +544,42 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
     const u64 lo = bi.lo, hi = bi.hi;
     const u32 s_lane = lane & (sub - 1), w_sub = lane >> sub_log2;
     const u64 submask = NONE64 >> (WAVE - sub);
-    const bool leader = wave == 0;
     const u32 grp_lo = (u32)__builtin_amdgcn_readfirstlane((int)(u32)(lo >> sub_log2));
     const u32 grp_end = (u32)__builtin_amdgcn_readfirstlane((int)(u32)((hi + sub - 1) >> sub_log2));
-    constexpr int J = SPARSE ? 8 : 4;               // index loads in flight
+    constexpr int J = 4;                            // index loads in flight
     u32 accepted = 0;
     double sq = 0.0;      // change of the sum of squares of the stored values caused by this lane's packets
 
     // The block's groups (grid-stride), up to 64 at a time.  Where most of them hold no arrival (a small
     // retransmission batch over a long round: fewer than one candidate per 64 sequence numbers), the block
     // first looks through their index entries, eight loads in flight per wave, and then takes the groups
-    // that hold one (26 against 46 us for a few packets in a round of 589 k x 8; with less than 8 groups to
-    // look through it costs what it saves).
+    // that hold one (26 against 46 us for a few packets in a round of 589 k x 8; 15.0 against 16.7 for 56 of
+    // 187 k, six groups per block; with fewer than three groups to look through it costs what it saves).
     const bool skim = SPARSE && bi.cand * 64 < hi - lo;
     constexpr u32 TILE = SPARSE ? 64 : 1;
     for (u64 tile = (u64)grp_lo + blockIdx.x; tile < grp_end; tile += (u64)TILE * n_blocks) {
     const u32 tile_left = SPARSE ? (grp_end - (u32)tile + n_blocks - 1) / n_blocks : 1, n_tile = tile_left < TILE ? tile_left : TILE;
     u64 todo = NONE64 >> (64 - n_tile);
-    if (skim && n_tile >= 8) {
+    // A sparse batch's groups go to single waves (`solo`), every NW-th to one, unless the average group holds
+    // more than solo_max pieces; a wave leaves a group of more than twice that to the whole block, which takes those
+    // afterwards.  A group is a chain of about 6 us whatever it holds (index, payload, store), so what counts is
+    // how many are in hand.  Against blocks as teams, us: 4 x 1.9 M packets of 136 bytes, 22 k lost 267 -> 90; 8 x
+    // 340 k of 1472 B, 14 k lost 102 -> 46; 32 x 340 k, 3 k lost 110 -> 61 and 217 k lost 276 -> 210; 16 x 355 k
+    // of 4016 B, 57 k lost in three runs 265 -> 186.  Whole blocks win where groups are full (32 x 540 k, 527 k lost
+    // in bursts, 33 a group: 478 against 501), or fewer than the waves (two groups a block, 16 x 60 k of 416 B, 10 a
+    // group: 36 against 46), and with packets of three and more pieces (2 x 45 k of 8992 B, 1786 lost: 32 against 40).
+    const u32 solo_max = n_piece > 2 ? 0 : n_piece == 2 ? (n_tile > 2 ? 6 : 0) : n_tile > 2 ? 24 : 8;
+    const bool look = skim && n_tile >= 3;
+    bool solo = SPARSE && n_tile > 1 && (bi.cand << sub_log2) * n_piece <= (hi - lo) * solo_max;
+    if (solo || look) {
+        __syncthreads();                            // the tile before is done with sh_tile
+        if (threadIdx.x < 4) sh_tile[threadIdx.x] = 0;
+        __syncthreads();
+    }
+    if (look) {
         const u32 rows = (W + wpl - 1) >> (6 - sub_log2);
         u32 k = 0, r = wave;                        // group k of the tile, index row r of the group
         u64 found = 0;
-        __syncthreads();
-        if (threadIdx.x < 2) sh_tile[threadIdx.x] = 0;
-        __syncthreads();
         while (k < n_tile) {
             u64 e[8];
             u32 kk[8];
@@ -585,8 +599,20 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
         __syncthreads();
         todo = uniform(((u64)sh_tile[1] << 32) | sh_tile[0]);
     }
-    for (; todo; todo &= todo - 1) {
-        const u64 grp = tile + (u64)__builtin_ctzll(todo) * n_blocks;
+    if (solo) for (u32 i = 0; i < wave; ++i) todo &= todo - 1;
+    for (;;) {
+        if (todo == 0) {
+            if (!solo) break;
+            solo = false;
+            __syncthreads();
+            todo = uniform(((u64)sh_tile[3] << 32) | sh_tile[2]);
+            if (todo == 0) break;
+        }
+        const u32 at = (u32)__builtin_ctzll(todo);
+        const u64 grp = tile + (u64)at * n_blocks;
+        for (u32 i = 0; i < (solo ? NW : 1); ++i) todo &= todo - 1;
+        const bool leader = solo || wave == 0;
+        bool heavy = false;
         // ---- arrival index -> slots of the group's new packets, bitmap bits, spans
         const u32 seq0 = (u32)grp << sub_log2, seq_l = seq0 + s_lane;
         const u32 word = seq0 >> 6, shift = seq0 & 63;
@@ -624,7 +650,18 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
                 new_any |= n; old_any |= o;
                 for (u32 k = 1; k < wpl; ++k) { n >>= sub; o >>= sub; new_any |= n; old_any |= o; }
             }
-            __syncthreads();         // every wave of the block has read the index before the first one resets it
+            if (SPARSE && solo) {
+                if (w0 == 0) {       // judged by the first J * wpl workers, before an entry of the group is reset
+                    u32 n = 0;
+                    #pragma unroll
+                    for (int j = 0; j < J; ++j) n += (u32)__popcll(nb[j]);
+                    heavy = n * n_piece * ((W + J * wpl - 1) / (J * wpl)) > 2 * solo_max;
+                    if (heavy) {
+                        if (lane == 0) atomicOr(&sh_tile[2 + (at >> 5)], 1u << (at & 31));
+                        break;
+                    }
+                }
+            } else __syncthreads();  // every wave of the block has read the index before the first one resets it
             if (leader) {
                 #pragma unroll
                 for (int j = 0; j < J; ++j) {
@@ -645,7 +682,7 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
             }
         }
         new_any = uniform(new_any & submask); old_any = uniform(old_any & submask);
-        if (new_any == 0) continue;
+        if (heavy || new_any == 0) continue;
         if (lane < sub && !((old_any >> lane) & 1u)) {
             home_l = pick;
             if (leader && ((new_any >> lane) & 1u)) home[seq_l] = (uint8_t)pick;
@@ -654,7 +691,8 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
 
         // ---- payloads: items = pieces of NP KB of the group's packets; G workers' pieces make one
         // step, D steps are in flight
-        u32 t_gen = 0, piece_gen = 0, t_next = 0, piece_next = wave;   // item the generator is at: piece of packet t_gen; (t_next, piece_next) comes after it
+        const u32 n_team = solo ? 1 : NW;
+        u32 t_gen = 0, piece_gen = 0, t_next = 0, piece_next = solo ? 0 : wave;   // item the generator is at: piece of packet t_gen; (t_next, piece_next) comes after it
         u64 left_gen = 0;               // its workers still to be loaded
         u32 slot32 = NONE32;            // lane w: slot of worker w's copy of packet t_gen
         f4v v[D][G][NP], old[D][NP];    // old: what earlier batches left in the span (SPARSE: loaded with the last step's payloads)
@@ -663,13 +701,14 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
         #pragma unroll
         for (int q = 0; q < NP; ++q) a[q] = f4v{0.f, 0.f, 0.f, 0.f};
 
-        auto issue = [&](int d) {
+        // the next step's packet, piece and workers; false when the wave has no more
+        auto next = [&]() {
             if (left_gen == 0) {
                 for (;;) {
                     while (piece_next >= n_piece) { piece_next -= n_piece; ++t_next; }
                     if (t_next >= sub) break;
                     t_gen = t_next; piece_gen = piece_next;
-                    piece_next += NW;
+                    piece_next += n_team;
                     if (((new_any >> t_gen) & 1u) && piece_gen * (NP * 256u) < (u32)__builtin_amdgcn_readlane((int)len_l, (int)t_gen) + LEAD) {
                         slot32 = lane < W ? slots[lane * pitch + t_gen] : NONE32;
                         left_gen = uniform((u64)__ballot(slot32 != NONE32));
@@ -677,6 +716,9 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
                     }
                 }
             }
+            return left_gen != 0;
+        };
+        auto issue = [&](int d) {
             const u32 len = (u32)__builtin_amdgcn_readlane((int)len_l, (int)t_gen);
             const u32 skip = piece_gen * (NP * 1024u);
             const u32 have = unit_have<LEAD>(len, skip);
@@ -779,17 +821,31 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
                 }
             }
         };
-        #pragma unroll
-        for (int d = 0; d < D; ++d) issue(d);
-        for (;;) {
-            bool more = false;
-            #pragma unroll
-            for (int d = 0; d < D; ++d) {
-                consume(d);
-                issue(d);
-                more = more || (tag[d] >> 31);
+        if (SPARSE) {
+            // two steps in flight and none of them empty: most waves have one to three
+            static_assert(!SPARSE || (G == 1 && D == 2), "sparse: one worker per step, two steps");
+            if (next()) {
+                issue(0);
+                for (;;) {
+                    if (!next()) { consume(0); break; }
+                    issue(1); consume(0);
+                    if (!next()) { consume(1); break; }
+                    issue(0); consume(1);
+                }
             }
-            if (!more) break;
+        } else {
+            #pragma unroll
+            for (int d = 0; d < D; ++d) { next(); issue(d); }
+            for (;;) {
+                bool more = false;
+                #pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    consume(d);
+                    next(); issue(d);
+                    more = more || (tag[d] >> 31);
+                }
+                if (!more) break;
+            }
         }
     }
     }
@@ -828,7 +884,7 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     if (MODE == 2 && told && blockIdx.x == 0 && threadIdx.x == 0) *told = is_sparse;    // for the trace group of the launch
     if (bi.hi == 0) return;                         // no candidate in this batch (uniform over the grid)
     if (is_sparse)
-        gather_groups<2, 1, 4, NW, true, LEAD>(g, bi, sparse, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
+        gather_groups<2, 1, 2, NW, true, LEAD>(g, bi, sparse, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
     else
         gather_groups<NP, G, D, NW, false, LEAD>(g, bi, dense, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
 }

@@ -177,6 +177,30 @@ def test_last_packets_of_every_remainder_and_beside_piece_edges(P, W, filler):
     assert g.phase_signal()[0] == pytest.approx(o.phase_signal()[0], rel=1e-6)
 
 
+@pytest.mark.parametrize("per_seq", [0.004, 0.1])        # groups looked through first, and not
+@pytest.mark.parametrize("W,P,n", [(1, 3, 140_000), (5, 2, 140_003), (40, 2, 70_001), (3, 520, 40_000), (64, 600, 2000)])
+def test_sparse_gather_shares_groups_between_waves_and_blocks(W, P, n, per_seq):
+    """Scattered packets, which single waves take, beside runs of 300 sequence numbers lost by all workers, which are left to
+    the whole block: tiles of several groups per block, of one and (W 64) blocks of 16 waves, with packets of one and
+    of two pieces."""
+    sc = build_scenario(mk(W, [P * (n // 3) + 1, P * (n - n // 3) - (P // 2)], P))
+    L = sc.L
+    held = np.random.default_rng(n).random((L.W, L.n_pkts)) < per_seq / W
+    for at in (7, L.n_pkts // 2) if n > 2000 else (7,):
+        held[:, at:at + (300 if n > 2000 else 40)] = True
+    assert 8 * held.sum() < held.size
+    o, g = both(sc, queue=True)
+    for rx in (o, g):
+        rx.begin_round(sc.rnd_id)
+        for part in (~held, held):
+            rx.apply(0, held.size, None, np.sort(sc.slot_of[part]))
+    assert g.bitmap().all() and g.counters() == o.counters() and o.counters()["accepted"] == held.size
+    from harness import abs_scale
+    ref, got = o.finalize(), g.finalize().astype(np.float64)
+    assert (np.abs(got - ref) <= FLOAT_TOL * abs_scale(sc, np.ones((L.W, L.n_pkts)))).all()
+    assert g.phase_signal()[0] == pytest.approx(o.phase_signal()[0], rel=1e-6)
+
+
 # ------------------------------------------------------------------------------ two accumulator copies
 TWO_COPY_CASES = [CASES[i] for i in (3, 5, 6, 7, 10, 13, 14, 15)]
 
