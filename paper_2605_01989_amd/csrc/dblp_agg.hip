@@ -6,7 +6,7 @@
 //                    (arrival rank << 32 | slot) into the arrival index `pending[w][seq]`, so the
 //                    earliest copy of a packet in the batch wins; per-block tallies (stale, invalid,
 //                    candidates, touched seq range) that every gather block adds up for itself
-//   gather_stream (one instance for sparse batches, the others for dense ones)
+//   gather_stream (dense batches, or both kinds and the blocks decide)
 //                    organised by OUTPUT packet: a block takes a group of consecutive sequence
 //                    numbers, reads the index entries of all workers, drops copies of packets
 //                    that an earlier batch delivered, sets the bitmap bits, then streams the
@@ -461,8 +461,8 @@ __device__ __forceinline__ BatchInfo fold_index_tallies(const u32* __restrict__ 
 #define NONE32 0xFFFFFFFFu
 
 // A batch is sparse when it holds fewer than one packet per SPARSE_DIV (worker, seq) pairs of the
-// sequence range it touches (retransmission batches).  Sparse batches take an instance of gather_stream
-// of their own (below); where the host cannot tell, the launch holds both and its blocks decide.
+// sequence range it touches (retransmission batches).  Sparse batches go through gather_stream in a
+// way of their own (below); where the host cannot tell, the launch holds both and its blocks decide.
 #define SPARSE_DIV 8
 __device__ __forceinline__ bool batch_is_sparse(const BatchInfo& bi, u32 W) {
     return bi.cand * SPARSE_DIV < (bi.hi - bi.lo) * W;
@@ -862,8 +862,8 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
     }
 }
 
-// MODE 0: the batch is dense, 1: sparse, 2: the index pass's tallies decide.
-template <int NP, int G, int D, int NW, u32 LEAD, int MODE>
+// DENSE: the host knows that the batch is dense; otherwise the index pass's tallies decide.
+template <int NP, int G, int D, int NW, u32 LEAD, bool DENSE>
 __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void gather_stream(
     Geo g, const uint8_t* __restrict__ packets, u64* __restrict__ pending, u64* __restrict__ bitmap,
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
@@ -880,8 +880,8 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     }
     // block 0 books the index pass's tallies; the barriers in there cover the table too
     const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0, sh_tally);
-    const bool is_sparse = MODE == 1 || (MODE == 2 && batch_is_sparse(bi, g.W));
-    if (MODE == 2 && told && blockIdx.x == 0 && threadIdx.x == 0) *told = is_sparse;    // for the trace group of the launch
+    const bool is_sparse = !DENSE && batch_is_sparse(bi, g.W);
+    if (!DENSE && told && blockIdx.x == 0 && threadIdx.x == 0) *told = is_sparse;    // for the trace group of the launch
     if (bi.hi == 0) return;                         // no candidate in this batch (uniform over the grid)
     if (is_sparse)
         gather_groups<2, 1, 2, NW, true, LEAD>(g, bi, sparse, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
@@ -1108,7 +1108,7 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
                                                      float* out, int scale_mode, float wf, int move_home,
                                                      u32 grp_log2, u32 n_piece, double* __restrict__ partials, u32 n_work_blocks,
                                                      const double* __restrict__ sumsq_rows, const u64* __restrict__ accept_rows,
-                                                     u32 rows_stream, u32 rows_direct, u32 row_pitch,
+                                                     u32 n_rows,
                                                      u64* __restrict__ counters, u64* __restrict__ mailbox) {
     __shared__ double wsum[4];
     __shared__ u64 asum[4];
@@ -1120,25 +1120,19 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
         // packets), and the round's counters mirrored into the host mailbox:
         // mailbox[1] = sum of squares (when the gather kept it), mailbox[8..11] = accepted,
         // candidates, stale, invalid
-        // Only the rows that a launch of this round can have written are read: rows_stream of
-        // the dense instances', rows_direct of the sparse instance's (row_pitch apart); the rest are zero.
+        // Only the n_rows rows that a launch of this round can have written are read; the rest are zero.
         double s = 0.0;
         u64 a = 0;
-        for (u32 k = 0; k < 2; ++k) {
-            const double* sr = sumsq_rows + (size_t)k * row_pitch;
-            const u64* ar = accept_rows + (size_t)k * row_pitch;
-            const u32 n = k ? rows_direct : rows_stream;
-            for (u32 i0 = 0; i0 < n; i0 += 4 * 256) {      // four independent loads of each kind in flight
-                double sv[4]; u64 av[4];
-                #pragma unroll
-                for (u32 j = 0; j < 4; ++j) {
-                    const u32 i = i0 + j * 256 + threadIdx.x;
-                    sv[j] = i < n ? sr[i] : 0.0;
-                    av[j] = i < n ? ar[i] : 0ull;
-                }
-                #pragma unroll
-                for (u32 j = 0; j < 4; ++j) { s += sv[j]; a += av[j]; }
+        for (u32 i0 = 0; i0 < n_rows; i0 += 4 * 256) {      // four independent loads of each kind in flight
+            double sv[4]; u64 av[4];
+            #pragma unroll
+            for (u32 j = 0; j < 4; ++j) {
+                const u32 i = i0 + j * 256 + threadIdx.x;
+                sv[j] = i < n_rows ? sumsq_rows[i] : 0.0;
+                av[j] = i < n_rows ? accept_rows[i] : 0ull;
             }
+            #pragma unroll
+            for (u32 j = 0; j < 4; ++j) { s += sv[j]; a += av[j]; }
         }
         s = wave_sum_f64(s);
         const u32 a_lo = wave_reduce<OpAdd>((u32)(a & 0xFFFFFu)), a_hi = wave_reduce<OpAdd>((u32)(a >> 20));   // 64 x 2^20 fits 32 bits
@@ -1368,10 +1362,10 @@ struct dblp_ctx {
     int probe_block_pair;   // probe: a block per (worker, bucket) pair
     u32* d_need; u64* d_totals; double* d_partials;   // probe: list length per pair, and per block of pairs
     u32* d_block_tallies;   // [IDX_BLOCKS_PER_CU * n_cus][5], written by index_arrivals
-    u64* d_accept_rows;     // [2][ACCEPT_ROWS] accepted packets per gather block (dense instances' grid, sparse instance's)
-    u32 rows_used[2];       // largest dense / sparse gather grid launched in the open round
+    u64* d_accept_rows;     // [ACCEPT_ROWS] accepted packets per gather block
+    u32 rows_used;          // largest gather grid launched in the open round
     int result_in_place;    // the form of the last dblp_finalize (in place until one says otherwise): prices the second copy
-    double* d_sumsq_rows;   // [2][ACCEPT_ROWS] sum of squares of what each gather block stored (same allocation)
+    double* d_sumsq_rows;   // [ACCEPT_ROWS] sum of squares of what each gather block stored (same allocation)
     u64* h_mailbox;         // pinned host memory, 16 x u64, also mapped into the device
     u64* d_mailbox;         // device address of h_mailbox
     // host copies of the geometry
@@ -1707,7 +1701,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     ok = ok && hipMalloc(&c->d_need, pairs * sizeof(u32)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_totals, probe_blocks(c, pairs) * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_partials, max_partials * sizeof(double)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_accept_rows, 4 * ACCEPT_ROWS * sizeof(u64)) == hipSuccess;   // + the sum-of-squares rows
+    ok = ok && hipMalloc(&c->d_accept_rows, 2 * ACCEPT_ROWS * sizeof(u64)) == hipSuccess;   // + the sum-of-squares rows
     ok = ok && hipMalloc(&c->d_block_tallies, (size_t)c->n_cus * IDX_BLOCKS_PER_CU * 5 * sizeof(u32)) == hipSuccess;
     ok = ok && hipHostMalloc((void**)&c->h_mailbox, 16 * sizeof(u64), hipHostMallocMapped) == hipSuccess;
     if (!ok) { (void)hipGetLastError(); dblp_destroy(c); return DBLP_ENOMEM; }
@@ -1731,7 +1725,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
         if (ce != hipSuccess) { (void)hipGetLastError(); dblp_destroy(c); return DBLP_EHIP; }
         g.hint = c->d_hint;
     }
-    c->d_sumsq_rows = (double*)(c->d_accept_rows + 2 * ACCEPT_ROWS);
+    c->d_sumsq_rows = (double*)(c->d_accept_rows + ACCEPT_ROWS);
 
     const u64 n_pending = (u64)g.W * n_pkts;
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (n_pending + 255) / 256, 16)), dim3(256), 0, c->stream,
@@ -1739,7 +1733,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (g.W * g.words_pw + 255) / 256, 16)), dim3(256), 0, c->stream,
                        c->d_bitmap, g.W * g.words_pw, 0ull);
     hipLaunchKernelGGL(reset_counters, dim3(1), dim3(64), 0, c->stream, c->d_counters);
-    hipLaunchKernelGGL(fill_u64, dim3(32), dim3(256), 0, c->stream, c->d_accept_rows, (u64)(4 * ACCEPT_ROWS), 0ull);
+    hipLaunchKernelGGL(fill_u64, dim3(32), dim3(256), 0, c->stream, c->d_accept_rows, (u64)(2 * ACCEPT_ROWS), 0ull);
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (n_pkts + 16 + 2047) / 2048, 16)), dim3(256), 0, c->stream,
                        (u64*)c->d_home, (u64)((n_pkts + 7) / 8 + 1), 0ull);
     e = hipStreamSynchronize(c->stream);
@@ -1807,11 +1801,11 @@ extern "C" int dblp_begin_round(dblp_ctx* c, uint16_t round) {
     if (!c->acc_alloc[0]) return fail(c, DBLP_ESTATE, "begin_round: no accumulator (dblp_accumulator_copies ran out of memory)");
     HIP_TRY(c, hipSetDevice(c->device));
     const u64 n = c->g.W * c->g.words_pw;
-    hipLaunchKernelGGL(reset_round, dim3(grid_for(c, (n + 4 * ACCEPT_ROWS + 255) / 256, 16)), dim3(256), 0, c->stream,
-                       c->d_bitmap, n, c->d_accept_rows, (u64)(4 * ACCEPT_ROWS), c->d_counters);
+    hipLaunchKernelGGL(reset_round, dim3(grid_for(c, (n + 2 * ACCEPT_ROWS + 255) / 256, 16)), dim3(256), 0, c->stream,
+                       c->d_bitmap, n, c->d_accept_rows, (u64)(2 * ACCEPT_ROWS), c->d_counters);
     LAUNCH_CHECK(c, "begin_round");
     c->round = round; c->round_open = 1; c->finalized = 0; c->norm_in_mailbox = 0; c->counters_in_mailbox = 0;
-    c->rows_used[0] = c->rows_used[1] = 0;
+    c->rows_used = 0;
     return DBLP_OK;
 }
 
@@ -1899,24 +1893,19 @@ typedef void (*gather_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8
                           GatherShape, GatherShape, u32, u32*);
 
 // The instance for `np` KB of a packet per step; few: one to three workers.
-template <int MODE, u32 LEAD>
-static gather_fn dense_kernel(bool few, u32 np) {
-    if (few) return np == 1 ? gather_stream<1, 1, 4, 4, LEAD, MODE> : np == 2 ? gather_stream<2, 1, 4, 4, LEAD, MODE>
-                  : np == 3 ? gather_stream<3, 1, 3, 4, LEAD, MODE> : np == 4 || !LEAD ? gather_stream<4, 1, 3, 4, LEAD, MODE>
-                                                                                       : gather_stream<5, 1, 3, 4, 2, MODE>;
-    return np == 1 ? gather_stream<1, 4, 2, 4, LEAD, MODE> : np == 2 ? gather_stream<2, 4, 2, 4, LEAD, MODE>
-         : np == 3 ? gather_stream<3, 2, 2, 4, LEAD, MODE> : np == 4 || !LEAD ? gather_stream<4, 2, 2, 4, LEAD, MODE>
-                                                                              : gather_stream<5, 1, 3, 4, 2, MODE>;
+template <bool DENSE, u32 LEAD>
+static gather_fn short_kernel(bool few, u32 np) {
+    if (few) return np == 1 ? gather_stream<1, 1, 4, 4, LEAD, DENSE> : np == 2 ? gather_stream<2, 1, 4, 4, LEAD, DENSE>
+                  : np == 3 ? gather_stream<3, 1, 3, 4, LEAD, DENSE> : np == 4 || !LEAD ? gather_stream<4, 1, 3, 4, LEAD, DENSE>
+                                                                                       : gather_stream<5, 1, 3, 4, 2, DENSE>;
+    return np == 1 ? gather_stream<1, 4, 2, 4, LEAD, DENSE> : np == 2 ? gather_stream<2, 4, 2, 4, LEAD, DENSE>
+         : np == 3 ? gather_stream<3, 2, 2, 4, LEAD, DENSE> : np == 4 || !LEAD ? gather_stream<4, 2, 2, 4, LEAD, DENSE>
+                                                                              : gather_stream<5, 1, 3, 4, 2, DENSE>;
 }
-template <int MODE>
-static gather_fn wide_kernel(u32 np) {
-    return np == 1 ? gather_stream<1, 4, 2, 16, 2, MODE> : np == 2 ? gather_stream<2, 2, 2, 16, 2, MODE> : gather_stream<4, 2, 2, 16, 2, MODE>;
-}
-static gather_fn gather_kernel(int mode, u32 nw, bool lead, bool few, u32 np) {
-    if (mode == 1) return nw == 16 ? gather_stream<1, 1, 1, 16, 2, 1> : lead ? gather_stream<1, 1, 1, 4, 2, 1> : gather_stream<1, 1, 1, 4, 0, 1>;
-    if (nw == 16) return mode == 0 ? wide_kernel<0>(np) : wide_kernel<2>(np);
-    if (mode == 0) return lead ? dense_kernel<0, 2>(few, np) : dense_kernel<0, 0>(few, np);
-    return lead ? dense_kernel<2, 2>(few, np) : dense_kernel<2, 0>(few, np);
+template <bool DENSE>
+static gather_fn gather_kernel(u32 nw, bool lead, bool few, u32 np) {
+    if (nw == 16) return np == 1 ? gather_stream<1, 4, 2, 16, 2, DENSE> : np == 2 ? gather_stream<2, 2, 2, 16, 2, DENSE> : gather_stream<4, 2, 2, 16, 2, DENSE>;
+    return lead ? short_kernel<DENSE, 2>(few, np) : short_kernel<DENSE, 0>(few, np);
 }
 
 // Waves of a gather block: 16 in rounds of few and heavy packets (fewer than 8 sequence numbers per CU, 128 KB
@@ -1970,15 +1959,15 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         // 25.6 M: 55 -> 48; 1024-float retransmissions: 162 -> 144).  Other lengths are better off from the
         // start, where fewer passes begin inside a 128-byte line (32 x 1472 B: 1.64 against 1.65 ms).
         const bool lead = !(g.P <= 1024 && (g.P + 255) / 256 < (g.P + 2 + 255) / 256) || block_waves(c) == 16;
-        // Dense or sparse.  Where the number of arrivals settles it, the launch is told: at least one arrival
-        // per SPARSE_DIV (worker, seq) pairs of the whole round is dense whatever range it touches; fewer than
-        // one per 8 * SPARSE_DIV pairs is taken as sparse.  In between (a chunk step, a large retransmission
-        // batch) the blocks decide, from the sequence range the index pass found (two launches of which one
-        // returned at once: 6 to 9 us more per batch).
+        // Dense or sparse.  At least one arrival per SPARSE_DIV (worker, seq) pairs of the whole round is dense
+        // whatever range it touches, and the launch is told so.  Fewer are a retransmission or a step of a round
+        // that arrives in many steps; the number does not say which, so the blocks decide, from the sequence
+        // range that the index pass found (a launch that took fewer than one per 64 pairs for sparse saved it 0 to
+        // 0.4 us, and cost a round of 32 x 60 M elements in 129 steps 11.0 against 4.0 ms).
         const u64 pairs = (u64)g.W * g.n_pkts;
-        const int mode = n_arrivals * SPARSE_DIV >= pairs ? 0 : n_arrivals * SPARSE_DIV * 8 < pairs ? 1 : 2;
-        const u32 nw = mode == 1 && g.stride < 8192 ? GS_WAVES      // 16 waves for a handful of 4 KB packets: 29 against 22 us
-                                                    : block_waves(c);
+        const bool is_dense = n_arrivals * SPARSE_DIV >= pairs, small = n_arrivals * SPARSE_DIV * 8 < pairs;
+        const u32 nw = small && g.stride < 8192 ? GS_WAVES      // 16 waves for a handful of 4 KB packets: 29 against 22 us
+                                                : block_waves(c);
         // Dense.  Packets of up to 5 KB are one piece, longer ones are cut evenly into pieces of 3 or 4 KB; in
         // a short round finer, so that a group gives each of the block's waves a piece.
         GatherShape dense, sparse;
@@ -1996,7 +1985,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         // 8 KB per step, two steps in flight, three blocks per CU for short packets, two for long ones
         // (8992 B: 930 against 940 us; more blocks only spread the DRAM accesses over more open rows).
         const bool few = g.W < 4;
-        const u32 per_cu = nw == 16 ? 1 : few ? (np <= 2 && mode == 0 ? 6 : 4) : np <= 2 ? 3 : 2;
+        const u32 per_cu = nw == 16 ? 1 : few ? (np <= 2 && is_dense ? 6 : 4) : np <= 2 ? 3 : 2;
         dense.blocks = grid_for(c, ((u64)g.n_pkts + (1u << dense.sub_log2) - 1) >> dense.sub_log2, per_cu);
         // Sparse.  One worker's 2 KB per step.  Groups of 32 packets of up to 2 KB in long rounds (longer rows of
         // the index, fewer empty groups to pass: 54 us against 69 with 16 and 51 with 64 for 12 k packets over a
@@ -2011,9 +2000,8 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         if (sparse.n_piece >= 8 && sparse.sub_log2 > 2 && g.n_pkts <= 64u * (u32)c->n_cus) sparse.sub_log2 = 2;
         sparse.blocks = grid_for(c, ((u64)g.n_pkts + (1u << sparse.sub_log2) - 1) >> sparse.sub_log2, nw == 16 ? 1 : 4);
 
-        u32 slots = 0, grid = 0;
-        if (mode != 1) { slots = GS_TEAM_LDS(g.W, dense.sub_log2); grid = dense.blocks; }
-        if (mode != 0) {
+        u32 slots = GS_TEAM_LDS(g.W, dense.sub_log2), grid = dense.blocks;
+        if (!is_dense) {
             if (GS_TEAM_LDS(g.W, sparse.sub_log2) > slots) slots = GS_TEAM_LDS(g.W, sparse.sub_log2);
             if (sparse.blocks > grid) grid = sparse.blocks;
         }
@@ -2021,13 +2009,12 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         const size_t table = ((size_t)g.B + 1) * sizeof(u32);
         const u32 table_at = table <= IDX_TABLE_LDS_MAX ? nw * slots : 0u;
         if (table_at) lds += table;
-        const gather_fn kern = gather_kernel(mode, nw, lead, few, np);
-        const u32 set = mode == 1 ? 1 : 0;          // which rows the launch adds to
-        if (grid > c->rows_used[set]) c->rows_used[set] = grid;
-        ProfScope ps(c, mode == 1 ? DBLP_K_GATHER_DIRECT : DBLP_K_GATHER, mode == 2);
+        const gather_fn kern = is_dense ? gather_kernel<true>(nw, lead, few, np) : gather_kernel<false>(nw, lead, few, np);
+        if (grid > c->rows_used) c->rows_used = grid;
+        ProfScope ps(c, small ? DBLP_K_GATHER_DIRECT : DBLP_K_GATHER, !is_dense && !small);
         hipLaunchKernelGGL(kern, dim3(grid), dim3(nw * WAVE), lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap,
                            c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
-                           c->d_accept_rows + set * ACCEPT_ROWS, c->d_sumsq_rows + set * ACCEPT_ROWS, inv_w, dense, sparse, table_at, ps.d_told());
+                           c->d_accept_rows, c->d_sumsq_rows, inv_w, dense, sparse, table_at, ps.d_told());
     }
     LAUNCH_CHECK(c, "apply_arrivals");
     c->finalized = 0; c->norm_in_mailbox = 0; c->counters_in_mailbox = 0;
@@ -2116,11 +2103,11 @@ extern "C" int dblp_finalize(dblp_ctx* c, int compensation, float* d_out) {
         ProfScope ps(c, DBLP_K_FINALIZE);
         const size_t table = ((size_t)g.B + 1) * sizeof(u32);
         void (*kern)(Geo, const u64*, const float*, const float*, uint8_t*, float*, int, float, int, u32, u32, double*, u32,
-                     const double*, const u64*, u32, u32, u32, u64*, u64*) = table <= IDX_TABLE_LDS_MAX ? finalize_pass<true> : finalize_pass<false>;
+                     const double*, const u64*, u32, u64*, u64*) = table <= IDX_TABLE_LDS_MAX ? finalize_pass<true> : finalize_pass<false>;
         hipLaunchKernelGGL(kern, dim3(grid), dim3(256), table <= IDX_TABLE_LDS_MAX ? table : 0, c->stream, g, c->d_bitmap,
                            (const float*)c->d_acc[0], (const float*)c->d_acc[1], c->d_home, out, c->fold ? 0 : 1, (float)g.W,
                            in_place ? 1 : 0, grp_log2, n_piece, c->d_partials, work, (const double*)c->d_sumsq_rows, (const u64*)c->d_accept_rows,
-                           c->rows_used[0], c->rows_used[1], (u32)ACCEPT_ROWS, c->d_counters, c->d_mailbox);
+                           c->rows_used, c->d_counters, c->d_mailbox);
     }
     LAUNCH_CHECK(c, "finalize");
     c->result_in_place = in_place ? 1 : 0;
@@ -2233,7 +2220,7 @@ extern "C" int dblp_get_counters(dblp_ctx* c, uint64_t h[4]) {
     }
     HIP_TRY(c, hipSetDevice(c->device));
     u64 tmp[C_COUNT];
-    hipLaunchKernelGGL(fold_accept_rows, dim3(1), dim3(256), 0, c->stream, c->d_accept_rows, (u32)(2 * ACCEPT_ROWS),
+    hipLaunchKernelGGL(fold_accept_rows, dim3(1), dim3(256), 0, c->stream, c->d_accept_rows, (u32)ACCEPT_ROWS,
                        c->d_counters);
     LAUNCH_CHECK(c, "get_counters");
     HIP_TRY(c, hipMemcpyAsync(tmp, c->d_counters, sizeof tmp, hipMemcpyDeviceToHost, c->stream));

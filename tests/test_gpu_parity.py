@@ -201,6 +201,30 @@ def test_sparse_gather_shares_groups_between_waves_and_blocks(W, P, n, per_seq):
     assert g.phase_signal()[0] == pytest.approx(o.phase_signal()[0], rel=1e-6)
 
 
+@pytest.mark.parametrize("steps", [24, 100])             # launches whose blocks decide: fewer than one arrival per 8, per 64 pairs
+@pytest.mark.parametrize("W,P,n", [(2, 256, 3000), (3, 600, 2000), (5, 768, 1500), (8, 1024, 1500), (2, 1279, 1500), (9, 1279, 800), (4, 2243, 600),
+                                   (1, 5000, 300), (7, 40, 9000), (12, 254, 700), (3, 255, 9000), (40, 1500, 2200),   # (the last: heavy packets, a longer round)
+                                   (17, 2243, 400), (64, 600, 300), (33, 1021, 523)])        # blocks of 16 waves
+def test_rounds_that_arrive_in_many_contiguous_steps(W, P, n, steps):
+    """Each step covers a range of sequence numbers of its own, dense (one of 20 packets is lost), with the last packets of
+    one step's range and the first of the next in one group; what is lost comes in a sparse batch at the end."""
+    sc = build_scenario(mk(W, [P * (n // 3) + 1, P * (n - n // 3) - (P // 2)], P))
+    L = sc.L
+    alive = np.random.default_rng(P).random((L.W, L.n_pkts)) >= 0.05
+    o, g = both(sc, queue=True)
+    edges = np.linspace(0, L.n_pkts, steps + 1).astype(int)
+    order = [np.random.default_rng(i).permutation(sc.slot_of[:, a:b][alive[:, a:b]]) for i, (a, b) in enumerate(zip(edges, edges[1:]))]
+    for rx in (o, g):
+        rx.begin_round(sc.rnd_id)
+        for slots in order + [sc.slot_of[~alive]]:
+            rx.apply(0, alive.size, None, slots)
+    assert g.bitmap().all() and g.counters() == o.counters() and o.counters()["accepted"] == alive.size
+    from harness import abs_scale
+    ref, got = o.finalize(), g.finalize().astype(np.float64)
+    assert (np.abs(got - ref) <= FLOAT_TOL * abs_scale(sc, np.ones((L.W, L.n_pkts)))).all()
+    assert g.phase_signal()[0] == pytest.approx(o.phase_signal()[0], rel=1e-6)
+
+
 # ------------------------------------------------------------------------------ two accumulator copies
 TWO_COPY_CASES = [CASES[i] for i in (3, 5, 6, 7, 10, 13, 14, 15)]
 
