@@ -461,11 +461,11 @@ __device__ __forceinline__ BatchInfo fold_index_tallies(const u32* __restrict__ 
 #define NONE32 0xFFFFFFFFu
 
 // A batch is sparse when it holds fewer than one packet per SPARSE_DIV (worker, seq) pairs of the
-// sequence range it touches (retransmission batches).  Sparse batches go through gather_stream in a
+// sequence range it touches (retransmission batches), or one packet.  Sparse batches go through gather_stream in a
 // way of their own (below); where the host cannot tell, the launch holds both and its blocks decide.
 #define SPARSE_DIV 8
 __device__ __forceinline__ bool batch_is_sparse(const BatchInfo& bi, u32 W) {
-    return bi.cand * SPARSE_DIV < (bi.hi - bi.lo) * W;
+    return bi.cand == 1 || bi.cand * SPARSE_DIV < (bi.hi - bi.lo) * W;
 }
 
 // A block takes a group of `sub` = 16 (8 in short rounds, 32 in sparse batches) consecutive sequence numbers: every wave
@@ -523,6 +523,21 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Sequence numbers (log2) that a block of the gather takes at a time, where n of them hold packets: 16; 8 while such
+// groups fit the chip at once, three blocks per CU (4 x 1024 B, 4096 packets: 11.7 against 12.6 us; 5600: 12.2 against
+// 13.2; 6600: 14.7 against 13.2; far above that groups of 8 pay for the shorter rows of the index: 8 x 1472 B, 340 k
+// packets, 920 against 893 us), for packets in pieces only when they are fewer still (64 KB datagrams, 3740 packets:
+// 224 us with 16, 232 with 8).  4, 2 or 1 where one sequence number is heavy, whatever gives every CU a group: with 128
+// KB or more from all workers (2) below 8 per CU (32 workers, 340 datagrams: 161 us against 650 with 16; 32 x 8992 B,
+// 900 packets: 58 against 104), with 64 KB (1) below 4 (8 x 25.6 M elements of 8992 B in 60 steps: 1514 us with 8, 1042
+// with 1; 1600 packets at once: 29.6 with 8, 31.0 with 4); light packets are not worth the atomics on the shared bytes
+// of the bitmap (3 x 4112 B, 420 packets: 24 us with 1, 12 with 8).
+__host__ __device__ static inline u32 group_log2(u64 n, u32 cus, bool pieces, u32 heavy) {
+    if (n >= (pieces ? 12u : 24u) * cus) return 4;
+    if (heavy == 0 || n >= (heavy == 1 ? 4u : 8u) * cus) return 3;
+    return n >= 4u * cus ? 2 : n >= 2u * cus ? 1 : 0;
+}
+
 // What a gather launch is given for one regime: sequence numbers per group (log2), pieces per packet, blocks.
 struct GatherShape { u32 sub_log2, n_piece, blocks; };
 
@@ -568,7 +583,7 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
     // of 4016 B, 57 k lost in three runs 265 -> 186.  Whole blocks win where groups are full (32 x 540 k, 527 k lost
     // in bursts, 33 a group: 478 against 501), or fewer than the waves (two groups a block, 16 x 60 k of 416 B, 10 a
     // group: 36 against 46), and with packets of three and more pieces (2 x 45 k of 8992 B, 1786 lost: 32 against 40).
-    const u32 solo_max = n_piece > 2 ? 0 : n_piece == 2 ? (n_tile > 2 ? 6 : 0) : n_tile > 2 ? 24 : 8;
+    const u32 solo_max = n_piece > 2 ? 0 : n_piece == 2 ? (n_tile > 2 ? 10 : 0) : n_tile > 2 ? 24 : 8;
     const bool look = skim && n_tile >= 3;
     bool solo = SPARSE && n_tile > 1 && (bi.cand << sub_log2) * n_piece <= (hi - lo) * solo_max;
     if (solo || look) {
@@ -869,7 +884,7 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
     const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters,
     u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
-    GatherShape dense, GatherShape sparse, u32 table_at, u32* __restrict__ told) {
+    GatherShape dense, GatherShape sparse, u32 cus, u32 heavy, u32 table_at, u32* __restrict__ told) {
     extern __shared__ u32 sh_dyn[];                 // per wave: slots [W rounded up][sub + 1]; then the bucket table (table_at words in, 0: not there)
     __shared__ u32 sh_tally[NW * 5];
     const u32* fs = g.first_seq;
@@ -885,8 +900,14 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     if (bi.hi == 0) return;                         // no candidate in this batch (uniform over the grid)
     if (is_sparse)
         gather_groups<2, 1, 2, NW, true, LEAD>(g, bi, sparse, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
-    else
+    else {
+        // a dense batch's groups are sized for the range that it covers: a step of a round that arrives in many
+        // steps is a short round.  Blocks of four waves: at least a piece for each.
+        u32 l = group_log2(bi.hi - bi.lo, cus, dense.n_piece > 1, heavy);
+        if (NW == GS_WAVES) while (dense.n_piece << l < GS_WAVES) ++l;
+        dense.sub_log2 = uniform(l);
         gather_groups<NP, G, D, NW, false, LEAD>(g, bi, dense, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1890,7 +1911,7 @@ extern "C" int dblp_packetize_list(dblp_ctx* c, uint16_t round, const float* con
 }
 
 typedef void (*gather_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, u64*, double*, float,
-                          GatherShape, GatherShape, u32, u32*);
+                          GatherShape, GatherShape, u32, u32, u32, u32*);
 
 // The instance for `np` KB of a packet per step; few: one to three workers.
 template <bool DENSE, u32 LEAD>
@@ -1908,24 +1929,12 @@ static gather_fn gather_kernel(u32 nw, bool lead, bool few, u32 np) {
     return lead ? short_kernel<DENSE, 2>(few, np) : short_kernel<DENSE, 0>(few, np);
 }
 
-// Waves of a gather block: 16 in rounds of few and heavy packets (fewer than 8 sequence numbers per CU, 128 KB
-// or more from all workers for one of them), where a CU has one block at a time; 4 elsewhere.
+#define HEAVY_BYTES 131072u  // from all workers for one sequence number
+// Waves of a gather block: 4; 16 in rounds of heavy packets with fewer sequence numbers than CUs (64 workers x 4016 B,
+// 60 packets: 19 against 28 us; with 260 packets 35 against 31, with 1000 61 against 51: groups of one or two
+// packets spread four waves over the chip as well).
 static u32 block_waves(const dblp_ctx* c) {
-    return c->g.n_pkts < 8u * (u32)c->n_cus && (u64)c->g.W * c->g.stride >= 131072u ? 16 : GS_WAVES;
-}
-
-// Sequence numbers (log2) that a block of the gather takes at a time: 16; 8 when the round is too short to
-// give every CU two groups of 16 (4 x 1040 bytes, 4096 packets: 11.7 against 12.6 us; longer rounds pay for
-// the shorter rows of the index: 8 x 1472 B, 340 k packets, 920 against 893 us), for packets in pieces only
-// when it is shorter still (64 KB datagrams, 3740 packets: 224 us with 16, 232 with 8).  Blocks of 16 waves
-// take 4, 2 or 1, whatever gives every CU a group (32 workers, 340 datagrams: 161 us against 650 with 16;
-// 32 x 8992 B, 900 packets: 58 against 104); light packets are not worth the atomics on the shared bytes
-// of the bitmap (3 x 4112 B, 420 packets: 24 us with 1, 12 with 8).
-static u32 group_log2(const dblp_ctx* c, bool pieces, u32 nw) {
-    const u32 n = c->g.n_pkts, cus = (u32)c->n_cus;
-    if (n >= (pieces ? 12u : 32u) * cus) return 4;
-    if (nw != 16) return 3;
-    return n >= 4u * cus ? 2 : n >= 2u * cus ? 1 : 0;
+    return c->g.n_pkts < (u32)c->n_cus && (u64)c->g.W * c->g.stride >= HEAVY_BYTES ? 16 : GS_WAVES;
 }
 
 // Index pass + gather pass over one batch.  Exactly one of (d_src_worker [+ d_mask, d_order]) and
@@ -1973,7 +1982,8 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         GatherShape dense, sparse;
         const u32 n_pass = lead ? (g.units + WAVE - 1) / WAVE : (g.P + 4 * WAVE - 1) / (4 * WAVE);
         dense.n_piece = n_pass <= 5 ? 1 : (n_pass + 3) / 4;
-        dense.sub_log2 = group_log2(c, dense.n_piece > 1, nw);
+        const u32 heavy = (u64)g.W * g.stride >= HEAVY_BYTES ? 2 : (u64)g.W * g.stride >= HEAVY_BYTES / 2 ? 1 : 0;
+        dense.sub_log2 = group_log2(g.n_pkts, (u32)c->n_cus, dense.n_piece > 1, heavy);      // (the whole round's)
         if (nw == 16) {
             const u32 want = nw >> dense.sub_log2 < n_pass ? nw >> dense.sub_log2 : n_pass;
             if (dense.n_piece < want) dense.n_piece = want;
@@ -1993,14 +2003,16 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         // leave too much to one block where the lost packets lie in a few runs: 16 x 4112 B, 162 us with 16,
         // 270 with 64).
         sparse.n_piece = lead ? (g.units + 2 * WAVE - 1) / (2 * WAVE) : (g.P + 8 * WAVE - 1) / (8 * WAVE);
-        sparse.sub_log2 = sparse.n_piece == 1 && g.n_pkts >= (g.W <= 4 ? 32u : 64u) * (u32)c->n_cus ? 5 : group_log2(c, sparse.n_piece > 1, nw);
+        sparse.sub_log2 = sparse.n_piece == 1 && g.n_pkts >= (g.W <= 4 ? 32u : 64u) * (u32)c->n_cus ? 5 : group_log2(g.n_pkts, (u32)c->n_cus, sparse.n_piece > 1, heavy == 2 ? 2 : 0);
         // Packets of 16 KB and more fill a block's waves four at a time: fewer to one block where lost packets
         // follow each other (1 worker x 66 M in 64 KB packets: 35 against 64 us, 7 x 249 M 45 against 107, 4 x 61 M
         // 20 against 26), until the groups get many.
         if (sparse.n_piece >= 8 && sparse.sub_log2 > 2 && g.n_pkts <= 64u * (u32)c->n_cus) sparse.sub_log2 = 2;
         sparse.blocks = grid_for(c, ((u64)g.n_pkts + (1u << sparse.sub_log2) - 1) >> sparse.sub_log2, nw == 16 ? 1 : 4);
 
-        u32 slots = GS_TEAM_LDS(g.W, dense.sub_log2), grid = dense.blocks;
+        u32 slots = 0, grid = dense.blocks;
+        for (u32 l = 0; l <= (dense.sub_log2 > 2 ? dense.sub_log2 : 2); ++l)        // whatever the launch may choose
+            if (GS_TEAM_LDS(g.W, l) > slots) slots = GS_TEAM_LDS(g.W, l);
         if (!is_dense) {
             if (GS_TEAM_LDS(g.W, sparse.sub_log2) > slots) slots = GS_TEAM_LDS(g.W, sparse.sub_log2);
             if (sparse.blocks > grid) grid = sparse.blocks;
@@ -2014,7 +2026,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         ProfScope ps(c, small ? DBLP_K_GATHER_DIRECT : DBLP_K_GATHER, !is_dense && !small);
         hipLaunchKernelGGL(kern, dim3(grid), dim3(nw * WAVE), lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap,
                            c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
-                           c->d_accept_rows, c->d_sumsq_rows, inv_w, dense, sparse, table_at, ps.d_told());
+                           c->d_accept_rows, c->d_sumsq_rows, inv_w, dense, sparse, (u32)c->n_cus, heavy, table_at, ps.d_told());
     }
     LAUNCH_CHECK(c, "apply_arrivals");
     c->finalized = 0; c->norm_in_mailbox = 0; c->counters_in_mailbox = 0;

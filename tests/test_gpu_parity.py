@@ -115,8 +115,8 @@ STREAM_CASES = [(W, P, n) for W, P, n in (
     (1, 6, 8191), (4, 6, 8192), (19, 5, 8193), (2, 1, 9000),
     # units counted from the payload: 256 k floats or one fewer (short last packets of every remainder: the test after the next)
     (1, 256, 1000), (4, 255, 41), (3, 256, 9000), (8, 512, 33), (2, 511, 40), (5, 768, 19), (1, 767, 60), (4, 1024, 18), (3, 1023, 20),
-    # few and heavy packets: blocks of 16 waves with groups of 1, 2 and 4 packets
-    (64, 600, 200), (33, 1021, 513), (40, 822, 1030), (9, 3700, 300))]
+    # few and heavy packets: groups of 1, 2 and 4 packets; fewer than CUs: blocks of 16 waves, pieces of 1, 2, 3 and 4 KB
+    (64, 600, 200), (33, 1021, 513), (40, 822, 1030), (9, 3700, 300), (33, 1021, 200), (8, 5000, 60), (4, 8200, 60), (2, 16500, 31), (64, 1279, 2100))]
 
 
 @pytest.mark.parametrize("W,P,n", STREAM_CASES)
@@ -134,7 +134,8 @@ def test_dense_gather_at_the_edges_of_passes_pieces_and_groups(W, P, n):
                                    (9, 512, 65), (3, 514, 97), (17, 1023, 33), (64, 366, 40), (2, 4097, 129),
                                    (4, 256, 700), (3, 255, 301), (8, 512, 130), (2, 1024, 302), (5, 767, 64),
                                    (2, 4097, 2100),                             # groups of four long packets
-                                   (16, 2100, 300), (33, 2048, 523),            # blocks of 16 waves
+                                   (16, 2100, 300), (33, 2048, 523),            # heavy packets
+                                   (33, 1100, 200), (16, 2100, 130),            # blocks of 16 waves
                                    (2, 3, 400_000)])                            # empty groups passed over, 32 at a time
 def test_sparse_gather_updates_spans_of_earlier_batches(W, P, n, loss):
     """Retransmissions into spans that the first transmission wrote, and into spans nobody delivered:
@@ -181,8 +182,7 @@ def test_last_packets_of_every_remainder_and_beside_piece_edges(P, W, filler):
 @pytest.mark.parametrize("W,P,n", [(1, 3, 140_000), (5, 2, 140_003), (40, 2, 70_001), (3, 520, 40_000), (64, 600, 2000)])
 def test_sparse_gather_shares_groups_between_waves_and_blocks(W, P, n, per_seq):
     """Scattered packets, which single waves take, beside runs of 300 sequence numbers lost by all workers, which are left to
-    the whole block: tiles of several groups per block, of one and (W 64) blocks of 16 waves, with packets of one and
-    of two pieces."""
+    the whole block: tiles of several groups per block and of one, with packets of one and of two pieces."""
     sc = build_scenario(mk(W, [P * (n // 3) + 1, P * (n - n // 3) - (P // 2)], P))
     L = sc.L
     held = np.random.default_rng(n).random((L.W, L.n_pkts)) < per_seq / W
@@ -204,7 +204,8 @@ def test_sparse_gather_shares_groups_between_waves_and_blocks(W, P, n, per_seq):
 @pytest.mark.parametrize("steps", [24, 100])             # launches whose blocks decide: fewer than one arrival per 8, per 64 pairs
 @pytest.mark.parametrize("W,P,n", [(2, 256, 3000), (3, 600, 2000), (5, 768, 1500), (8, 1024, 1500), (2, 1279, 1500), (9, 1279, 800), (4, 2243, 600),
                                    (1, 5000, 300), (7, 40, 9000), (12, 254, 700), (3, 255, 9000), (40, 1500, 2200),   # (the last: heavy packets, a longer round)
-                                   (17, 2243, 400), (64, 600, 300), (33, 1021, 523)])        # blocks of 16 waves
+                                   (17, 2243, 400), (64, 600, 300), (33, 1021, 523),         # heavy ones in a short round
+                                   (17, 2243, 200), (64, 600, 200), (8, 5000, 60)])          # blocks of 16 waves
 def test_rounds_that_arrive_in_many_contiguous_steps(W, P, n, steps):
     """Each step covers a range of sequence numbers of its own, dense (one of 20 packets is lost), with the last packets of
     one step's range and the first of the next in one group; what is lost comes in a sparse batch at the end."""
