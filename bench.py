@@ -540,7 +540,7 @@ def main():
         log(f"[bench] warmup {st['it']}: bound={st['bound_ppm']} rounds={st['rounds']}")
     from paper_2605_01989_amd import binding
     # the timed region brackets only the launches of the dominant kernel, gather_stream, with events
-    # (two event records per dense batch; its sparse instance's launches on retransmission batches
+    # (two event records per dense batch; its launches on retransmission batches, which are sparse,
     # are a group of their own); the per-group breakdown comes from a replay of its first steps with
     # every group bracketed
     main_leg = run_leg(job, w, list(range(args.warmup, total)), profile=1 << binding.K_GATHER)
@@ -551,7 +551,7 @@ def main():
     fill = L.N / (L.n_pkts * L.P)
     value = accepted_total * 4 * L.P * fill / wall / 1e9
     # dominant kernel: gather_stream, which takes the first transmissions (a retransmission
-    # batch goes to its sparse instance unless it is dense; one that a dense instance does take adds its
+    # batch is sparse and of another trace group unless it is dense; one that is dense adds its
     # time here and not its bytes).  Algorithmic bytes = every packet accepted from a first transmission
     # read once (header + payload + padding = stride) + the accumulator written once per iteration.
     g_ms, g_n = prof["gather"]

@@ -205,8 +205,8 @@ __global__ __launch_bounds__(256) void fold_accept_rows(const u64* __restrict__ 
 // One wave writes one packet: lane l builds 16-byte units l, l + 64, ... (header in the first 8
 // bytes of unit 0, zero padding after the payload) and stores them aligned.  A unit inside the payload is
 // one 16-byte load at the gradient's own (4-byte) alignment (two 8-byte loads where it was even and four
-// single ones elsewhere: 46.0 -> 42.5 us for 25.6 M elements, 205 MB moved, and 74.6 -> 69.6 us for a list of
-// 81 k packets); the first and the last unit go float by float.  All loads of a packet are issued before the
+// single ones elsewhere: 25.6 M elements, 205 MB moved, ten sets of buffers in turn 48.3 -> 45.8 us, one set 37.8 ->
+// 37.7; a list of 56 k packets 63.3 -> 57.0 and 48.6 -> 45.8); the first and the last unit go float by float.  All loads of a packet are issued before the
 // first store; the stores carry the non-temporal hint (+11 %), the loads do not (with it: -8 %, neighbouring
 // units share lines).  PK_UNITS = units per lane kept in registers (packets of up to PK_UNITS KB go in
 // one pass, longer ones in several).
@@ -468,8 +468,8 @@ __device__ __forceinline__ bool batch_is_sparse(const BatchInfo& bi, u32 W) {
     return bi.cand == 1 || bi.cand * SPARSE_DIV < (bi.hi - bi.lo) * W;
 }
 
-// A block takes a group of `sub` = 16 (8 in short rounds, 32 in sparse batches) consecutive sequence numbers: every wave
-// reads the group's arrival index (64 / sub workers x sub packets per load), ballots which packets are
+// A block takes a group of `sub` = 16 (8 to 1 in short ranges, 32 in sparse batches, where a single wave may take one)
+// consecutive sequence numbers: every wave reads the group's arrival index (64 / sub workers x sub packets per load), ballots which packets are
 // new, and keeps their slots in its own LDS rows; after a barrier the first wave resets the index
 // entries and sets the bitmap, whose bytes the group owns (8, 16 or 32 bits: a plain store, where one
 // memory-side atomic per worker and group took up to a microsecond of a small group's time).  The
@@ -504,8 +504,6 @@ __device__ __forceinline__ bool batch_is_sparse(const BatchInfo& bi, u32 W) {
 //   10 of 3740 x 4, 64 KB                                 72 -> 22
 //   57 k in three runs of 355 k x 16, 4016 B             345 -> 186
 typedef f4v f4v_a4 __attribute__((aligned(4)));      // a 16-byte access at a 4-byte aligned address
-typedef float f2v __attribute__((ext_vector_type(2)));
-typedef f2v f2v_a4 __attribute__((aligned(4)));
 
 #define GS_WAVES 4           // waves per block
 // Cache policy of the payload's buffer loads: non-temporal.  The payload is read exactly once and should
@@ -1972,7 +1970,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         // whatever range it touches, and the launch is told so.  Fewer are a retransmission or a step of a round
         // that arrives in many steps; the number does not say which, so the blocks decide, from the sequence
         // range that the index pass found (a launch that took fewer than one per 64 pairs for sparse saved it 0 to
-        // 0.4 us, and cost a round of 32 x 60 M elements in 129 steps 11.0 against 4.0 ms).
+        // 0.4 us, and cost a round of 32 x 60 M elements in 129 steps 11.7 against 4.7 ms).
         const u64 pairs = (u64)g.W * g.n_pkts;
         const bool is_dense = n_arrivals * SPARSE_DIV >= pairs, small = n_arrivals * SPARSE_DIV * 8 < pairs;
         const u32 nw = small && g.stride < 8192 ? GS_WAVES      // 16 waves for a handful of 4 KB packets: 29 against 22 us
@@ -1991,22 +1989,22 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         const u32 np = (n_pass + dense.n_piece - 1) / dense.n_piece;
         dense.n_piece = (n_pass + np - 1) / np;
         // One to three workers: a step is one worker's piece, four of them in flight, and six blocks per
-        // CU (1 worker: 45 us, against 54 with three blocks, 68 with steps of four workers).  More: 4 to
-        // 8 KB per step, two steps in flight, three blocks per CU for short packets, two for long ones
-        // (8992 B: 930 against 940 us; more blocks only spread the DRAM accesses over more open rows).
+        // CU (1 worker: 45 us, against 54 with three blocks, 68 with steps of four workers; 25.6 M elements of 366
+        // floats, 2 workers 61 against 73 with steps of four, 3 workers 78 and 82, 4 workers 98 and 97, 8 workers 176
+        // and 174).  More: 4 to 8 KB per step, two steps in flight, three blocks per CU for short packets, two for
+        // long ones (8992 B: 930 against 940 us; more blocks only spread the DRAM accesses over more open rows).
         const bool few = g.W < 4;
         const u32 per_cu = nw == 16 ? 1 : few ? (np <= 2 && is_dense ? 6 : 4) : np <= 2 ? 3 : 2;
         dense.blocks = grid_for(c, ((u64)g.n_pkts + (1u << dense.sub_log2) - 1) >> dense.sub_log2, per_cu);
-        // Sparse.  One worker's 2 KB per step.  Groups of 32 packets of up to 2 KB in long rounds (longer rows of
-        // the index, fewer empty groups to pass: 54 us against 69 with 16 and 51 with 64 for 12 k packets over a
-        // round of 340 k x 8); otherwise as for dense batches (larger groups
-        // leave too much to one block where the lost packets lie in a few runs: 16 x 4112 B, 162 us with 16,
-        // 270 with 64).
+        // Sparse.  One worker's 2 KB per step.  Groups of 32 packets of up to 2 KB in long rounds, longer rows of the
+        // index and fewer empty groups to pass: 1 x 1.9 M packets of 136 bytes, 562 lost 26 us against 37 with 16; 8 x
+        // 340 k of 1472 B, 14 k lost 46 against 48 (with more of them, or in bursts, 16 would do better: 6.9 k lost
+        // there 50 against 43).  Otherwise as for dense batches.
         sparse.n_piece = lead ? (g.units + 2 * WAVE - 1) / (2 * WAVE) : (g.P + 8 * WAVE - 1) / (8 * WAVE);
         sparse.sub_log2 = sparse.n_piece == 1 && g.n_pkts >= (g.W <= 4 ? 32u : 64u) * (u32)c->n_cus ? 5 : group_log2(g.n_pkts, (u32)c->n_cus, sparse.n_piece > 1, heavy == 2 ? 2 : 0);
         // Packets of 16 KB and more fill a block's waves four at a time: fewer to one block where lost packets
-        // follow each other (1 worker x 66 M in 64 KB packets: 35 against 64 us, 7 x 249 M 45 against 107, 4 x 61 M
-        // 20 against 26), until the groups get many.
+        // follow each other (1 worker x 66 M in 64 KB packets, 12 lost 18 against 23 us, 247 lost 32 against 48; 4 x
+        // 61 M, 80 lost 29 against 42), until the groups get many.
         if (sparse.n_piece >= 8 && sparse.sub_log2 > 2 && g.n_pkts <= 64u * (u32)c->n_cus) sparse.sub_log2 = 2;
         sparse.blocks = grid_for(c, ((u64)g.n_pkts + (1u << sparse.sub_log2) - 1) >> sparse.sub_log2, nw == 16 ? 1 : 4);
 
