@@ -34,8 +34,8 @@ BENCH_DRAWN_ROUNDS = 3   # retransmission rounds with a drawn loss pattern; late
 # on and by workload; anything else reports null.
 # value = measured bytes / algorithmic bytes of a first-transmission launch.
 PMC_TRAFFIC_RATIO: dict[tuple[str, str], float] = {
-    ("55b4d38a4a71e7c67fb52366190232a5d14ad3697f9a0dc4eb3e287e8a1589ae", "cfg5"): 1.062,   # profiles/receiver_path_cfg5.md
-    ("55b4d38a4a71e7c67fb52366190232a5d14ad3697f9a0dc4eb3e287e8a1589ae", "cfg4"): 1.033,   # profiles/receiver_path_cfg4.md
+    ("594bae09504d7b2602fabbdb4a71c216bcb3912f096ff9ccd980af22d39aad34", "cfg5"): 1.062,   # profiles/receiver_path_cfg5.md
+    ("594bae09504d7b2602fabbdb4a71c216bcb3912f096ff9ccd980af22d39aad34", "cfg4"): 1.033,   # profiles/receiver_path_cfg4.md
 }
 
 
