@@ -12,6 +12,7 @@
 //                    that an earlier batch delivered, sets the bitmap bits, then streams the
 //                    payloads of each packet from every delivering worker (16-byte loads,
 //                    worker order) into registers and writes the accumulator span once.
+//   gather_burst     the same for large dense batches, with the spans of many packets stored together.
 // Every payload byte is read exactly once and the accumulator is written once per batch that
 // touches it; there are no floating-point atomics, so the sum is independent of the arrival
 // permutation.  The accumulator may exist in two copies placed in different thirds of the HBM
@@ -521,6 +522,57 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Unit u (16 bytes) of a packet of `len` floats in the grid that LEAD says: which of its floats are payload.
+__device__ __forceinline__ double squares(f4v v) {
+    return (((double)v.x * (double)v.x + (double)v.y * (double)v.y) + (double)v.z * (double)v.z) + (double)v.w * (double)v.w;
+}
+
+template <u32 LEAD>
+struct SpanUnit {
+    u32 u, n_tail;              // n_tail: floats of a last unit that is not full
+    bool head, full, part;      // head: two header words, then the first two floats
+    bool v0, v1, v2, v3;        // floats of a unit that is not full
+    bool past_end;
+    __device__ __forceinline__ SpanUnit(u32 u_, u32 len) : u(u_) {
+        const u32 past = len + LEAD;
+        n_tail = past & 3u;
+        head = LEAD && u == 0;
+        full = !head && 4 * u + 4 <= past;
+        part = !head && n_tail && u == past >> 2;
+        v0 = part; v1 = part && n_tail > 1; v2 = head ? len > 0 : part && n_tail > 2; v3 = head && len > 1;
+        past_end = n_tail && !head && 4 * u + 4 > past;
+    }
+    // The unit's floats in place, zeros where there is no payload.
+    __device__ __forceinline__ f4v take(f4v r, u32 len) const {
+        if (head) {
+            r.x = r.y = 0.f;
+            if (!v3) r.w = 0.f;
+        }
+        if (past_end) {
+            if (LEAD) r = f4v{v0 ? r.x : 0.f, v1 ? r.y : 0.f, v2 ? r.z : 0.f, 0.f};
+            else {
+                const u32 first = len > 1 ? 4 - n_tail : 2;
+                r = f4v{v0 ? (first == 1 ? r.y : first == 2 ? r.z : r.w) : 0.f, v1 ? (first == 1 ? r.z : r.w) : 0.f, v2 ? r.w : 0.f, 0.f};
+            }
+        }
+        return r;
+    }
+    // What is stored of a unit that is not full.
+    __device__ __forceinline__ f4v floats(const float* o) const {
+        return f4v{v0 ? o[0] : 0.f, v1 ? o[1] : 0.f, v2 ? o[2] : 0.f, v3 ? o[3] : 0.f};
+    }
+    template <class T>
+    __device__ __forceinline__ void store(T* o, f4v r) const {
+        if (full) *(f4v_a4*)o = r;
+        else {
+            if (v0) o[0] = r.x;
+            if (v1) o[1] = r.y;
+            if (v2) o[2] = r.z;
+            if (v3) o[3] = r.w;
+        }
+    }
+};
+
 // Sequence numbers (log2) that a block of the gather takes at a time, where n of them hold packets: 16; 8 while such
 // groups fit the chip at once, three blocks per CU (4 x 1024 B, 4096 packets: 11.7 against 12.6 us; 5600: 12.2 against
 // 13.2; 6600: 14.7 against 13.2; far above that groups of 8 pay for the shorter rows of the index: 8 x 1472 B, 340 k
@@ -785,51 +837,23 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
                 const bool rmw = (old_any >> t) & 1u;
                 // float position i of the unit grid -> dst[i]; the payload is positions LEAD .. LEAD + len - 1
                 float* dst = (h ? acc1 : acc0) + elem - LEAD;
-                const u32 past = len + LEAD, n_tail = past & 3u;      // n_tail: floats of a last unit that is not full
                 #pragma unroll
                 for (int q = 0; q < NP; ++q) {
-                    const u32 u = (piece * NP + q) * WAVE + lane;
-                    const bool head = LEAD && u == 0;                 // two header words, then the first two floats
-                    const bool full = !head && 4 * u + 4 <= past, part = !head && n_tail && u == past >> 2;
-                    const bool v0 = part, v1 = part && n_tail > 1, v2 = head ? len > 0 : part && n_tail > 2, v3 = head && len > 1;
-                    float* o = dst + 4 * u;
-                    f4v r = a[q] * inv_w, ov = {0.f, 0.f, 0.f, 0.f};
-                    if (head) {
-                        r.x = r.y = 0.f;
-                        if (!v3) r.w = 0.f;
-                    }
-                    if (n_tail && !head && 4 * u + 4 > past) {        // the last unit's floats in place, zeros beyond the payload
-                        if (LEAD) r = f4v{v0 ? r.x : 0.f, v1 ? r.y : 0.f, v2 ? r.z : 0.f, 0.f};
-                        else {
-                            const u32 first = len > 1 ? 4 - n_tail : 2;
-                            r = f4v{v0 ? (first == 1 ? r.y : first == 2 ? r.z : r.w) : 0.f, v1 ? (first == 1 ? r.z : r.w) : 0.f, v2 ? r.w : 0.f, 0.f};
-                        }
-                    }
+                    const SpanUnit<LEAD> su((piece * NP + q) * WAVE + lane, len);
+                    float* o = dst + 4 * su.u;
+                    f4v r = su.take(a[q] * inv_w, len);
                     if (rmw) {                                        // result = old value + this batch's sum
+                        f4v ov = {0.f, 0.f, 0.f, 0.f};
                         if (SPARSE) {
                             ov = old[d][q];
-                            if (head) ov = f4v{0.f, 0.f, ov.x, ov.y};
-                        } else if (full) ov = *(const f4v_a4*)o;
-                        if (part || (head && (!SPARSE || len < 4))) {
-                            ov = f4v{0.f, 0.f, 0.f, 0.f};
-                            if (v0) ov.x = o[0];
-                            if (v1) ov.y = o[1];
-                            if (v2) ov.z = o[2];
-                            if (v3) ov.w = o[3];
-                        }
-                        sq -= (double)ov.x * (double)ov.x; sq -= (double)ov.y * (double)ov.y;
-                        sq -= (double)ov.z * (double)ov.z; sq -= (double)ov.w * (double)ov.w;
+                            if (su.head) ov = f4v{0.f, 0.f, ov.x, ov.y};
+                        } else if (su.full) ov = *(const f4v_a4*)o;
+                        if (su.part || (su.head && (!SPARSE || len < 4))) ov = su.floats(o);
+                        sq -= squares(ov);
                         r = ov + r;
                     }
-                    sq += (double)r.x * (double)r.x; sq += (double)r.y * (double)r.y;
-                    sq += (double)r.z * (double)r.z; sq += (double)r.w * (double)r.w;
-                    if (full) *(f4v_a4*)o = r;
-                    else {
-                        if (v0) o[0] = r.x;
-                        if (v1) o[1] = r.y;
-                        if (v2) o[2] = r.z;
-                        if (v3) o[3] = r.w;
-                    }
+                    sq += squares(r);
+                    su.store(o, r);
                     a[q] = f4v{0.f, 0.f, 0.f, 0.f};
                 }
             }
@@ -882,7 +906,7 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
     const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters,
     u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
-    GatherShape dense, GatherShape sparse, u32 cus, u32 heavy, u32 table_at, u32* __restrict__ told) {
+    GatherShape dense, GatherShape sparse, u32 cus, u32 heavy, u32 table_at, u32 burst_seq, u32* __restrict__ told) {
     extern __shared__ u32 sh_dyn[];                 // per wave: slots [W rounded up][sub + 1]; then the bucket table (table_at words in, 0: not there)
     __shared__ u32 sh_tally[NW * 5];
     const u32* fs = g.first_seq;
@@ -892,10 +916,11 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
         fs = tab;
     }
     // block 0 books the index pass's tallies; the barriers in there cover the table too
-    const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0, sh_tally);
+    const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0 && !burst_seq, sh_tally);
     const bool is_sparse = !DENSE && batch_is_sparse(bi, g.W);
     if (!DENSE && told && blockIdx.x == 0 && threadIdx.x == 0) *told = is_sparse;    // for the trace group of the launch
     if (bi.hi == 0) return;                         // no candidate in this batch (uniform over the grid)
+    if (!DENSE && burst_seq && !is_sparse && bi.hi - bi.lo >= burst_seq) return;       // the gather_burst launch before took it and booked the tallies
     if (is_sparse)
         gather_groups<2, 1, 2, NW, true, LEAD>(g, bi, sparse, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
     else {
@@ -905,6 +930,317 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
         if (NW == GS_WAVES) while (dense.n_piece << l < GS_WAVES) ++l;
         dense.sub_log2 = uniform(l);
         gather_groups<NP, G, D, NW, false, LEAD>(g, bi, dense, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// gather in bursts: large dense batches
+// ------------------------------------------------------------------------------------------
+// What bounds a large gather is that it writes: read alone, its payloads stream at 6.5 TB/s, and with the 3 % of
+// result bytes of 32 workers stored as each packet's sum is ready, at 5.3 (a write that comes alone turns the memory
+// bus round for few bytes).  One block per CU therefore sums a whole group of consecutive packets, as many as fit its
+// LDS, into an image of their spans, and then stores the image at once: long, contiguous, whole 128-byte lines, while
+// the block reads nothing.  In turn, a loop with this access pattern, 32 workers x 1472 B, 8.5 GB: stored at once per
+// packet 1711 us, in bursts of 23 KB 1629, of 70 KB and more 1450 to 1500; read only 1290.  Three things that looked
+// natural made it slower: loads of the next group in flight while the image goes out (8 workers, 9.8 GB: 1709 us
+// without, 1788 with), two blocks per CU (1927), and more than one step of loads in flight per wave (equal, or up to
+// 2 % slower).  What stays between two groups is kept short instead: a group's arrival index is loaded a whole group
+// ahead and brought into LDS by each wave as it ends its share of the group before.
+//
+// Against gather_stream, us per launch (whole pass in brackets), buffers where the allocator put them:
+//   8 workers x 124 M elements, 1472 B packets      895 ->  795 (1157 -> 1035)
+//   8 x 124 M, 8992 B                               925 ->  790 (1033 ->  888)
+//   16 x 355 M, 4112 B                             4620 -> 4080 (4843 -> 4350)
+//   32 x 66 M (one of three steps), 1472 B         1632 -> 1450
+//   8 x 25.6 M, 1472 B                              179 ->  158 (285 -> 265)
+//   4 x 150 M, 1472 B                               596 ->  527 (777 -> 682)
+//
+// How the image is stored (`through`): written through to the memory-side cache (256 MB) where the written range
+// stays in it, else past it: 8 x 25.6 M, 158 and 163 us; 16 x 355 M, 4376 and 4178; the passes that follow are
+// faster too where the cache is left alone (index pass of 8 x 124 M 150 and 129 us).
+#define BURST_WAVES 16       // one block per CU: four waves on each SIMD
+#define BURST_MAX 256u       // sequence numbers of a group
+#define BURST_AHEAD 4        // (worker, 64 sequence numbers) of the next group's index that a wave holds in registers
+#define BURST_LDS 161792u    // dynamic: 160 KB less 2 KB for the rest
+#define BUF_SC1 16           // store policy: written through
+
+// Words of dynamic LDS: slots [W][r | 1], span starts and lengths (each for two groups), then the bucket table, then the
+// image of the group's spans (32 floats more, so that it can start where its first span lies in a 128-byte line).
+#define BURST_INFO_LDS(W, r) (2u * (W) * ((r) | 1u) + 6u * (r))
+
+template <int NP, int G, u32 LEAD>
+__global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
+    Geo g, const uint8_t* __restrict__ packets, u64* __restrict__ pending, u64* __restrict__ bitmap,
+    float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
+    const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters,
+    u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
+    u32 r_max, u32 r_step, u32 n_piece, u32 table_at, u32 image_at, u32 min_seq, u32 through_seq) {
+    extern __shared__ __attribute__((aligned(16))) u32 sh_dyn[];
+    __shared__ u32 sh_tally[BURST_WAVES * 5];
+    __shared__ u32 sh_new[3][BURST_MAX / 32], sh_old[3][BURST_MAX / 32];     // by packet of the group: new copies; delivered before
+    __shared__ u32 sh_accepted[BURST_WAVES];
+    __shared__ double sh_sq[BURST_WAVES];
+    const u32 tid = threadIdx.x, lane = lane_id();
+    const u32 wave = uniform(tid / WAVE);
+    const u32 W = g.W, pitch = r_max | 1u;
+    u32* const sh_elem = sh_dyn + 2 * W * pitch;                    // [2][r_max][2]
+    u32* const sh_len = sh_elem + 4 * r_max;                    // [2][r_max]: floats | home << 16
+    float* const image = (float*)(sh_dyn + image_at);
+    const u32* fs = g.first_seq;
+    if (table_at) {
+        u32* tab = sh_dyn + table_at;
+        for (u32 i = tid; i <= g.B; i += BURST_WAVES * WAVE) tab[i] = g.first_seq[i];
+        fs = tab;
+    }
+    if (tid < 3 * (BURST_MAX / 32)) sh_new[0][tid] = sh_old[0][tid] = 0;
+    const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0, sh_tally);
+    // A batch that is none of this kernel's is left to the gather_stream launch that follows.
+    if (bi.hi == 0 || (min_seq && (batch_is_sparse(bi, g.W) || bi.hi - bi.lo < min_seq))) return;
+    // Groups of equal size, as many turns of the grid as the longest group asks for.
+    const u32 lo = uniform((u32)bi.lo / r_step * r_step), n_seq = uniform((u32)bi.hi) - lo, n_blocks = gridDim.x;
+    const u32 turns = (u32)(((u64)n_seq + (u64)r_max * n_blocks - 1) / ((u64)r_max * n_blocks));
+    u32 R = (n_seq + turns * n_blocks - 1) / (turns * n_blocks);
+    R = uniform((R + r_step - 1) / r_step * r_step);
+    const u32 n_groups = (n_seq + R - 1) / R;
+    const bool through = n_seq <= through_seq;
+    const u32 n_chunk = (R + WAVE - 1) / WAVE, n_pair = W * n_chunk;        // a pair: a worker's index entries of 64 sequence numbers
+    const u32* const words = (const u32*)bitmap;
+    u32 accepted = 0;
+    double sq = 0.0;
+
+    struct Entry { u64 p; u32 bits; };
+    auto load_entry = [&](u32 pair, u32 s0) {
+        Entry e;
+        e.p = NONE64; e.bits = 0;
+        const u32 w = pair / n_chunk, t = (pair - w * n_chunk) * WAVE + lane, seq = s0 + t;
+        if (pair < n_pair && t < R && seq < g.n_pkts) {
+            e.p = pending[(u64)w * g.n_pkts + seq];
+            e.bits = words[2 * (u64)w * g.words_pw + (seq >> 5)];
+        }
+        return e;
+    };
+    Entry ahead[BURST_AHEAD];
+    u32 home_ahead = 0;
+    auto load_ahead = [&](u32 grp) {
+        const u32 s0 = lo + grp * R;
+        #pragma unroll
+        for (int j = 0; j < BURST_AHEAD; ++j) ahead[j] = load_entry(wave + j * BURST_WAVES, s0);
+        home_ahead = tid < R && s0 + tid < g.n_pkts ? home[s0 + tid] : 0;
+    };
+
+    // A group's arrival index -> slots, bitmap, spans, in its half of the tables (par) and its flags (f).
+    auto take_group = [&](u32 grp, u32 par, u32 f) {
+        const u32 seq0 = lo + grp * R;
+        u32* const slots = sh_dyn + par * W * pitch;
+        auto take_entry = [&](u32 pair, const Entry& e) {
+            if (pair >= n_pair) return;
+            const u32 w = pair / n_chunk, c = pair - w * n_chunk, t = c * WAVE + lane, seq = seq0 + t;
+            const bool in = t < R && seq < g.n_pkts;
+            const bool had = in && (e.bits >> (seq & 31)) & 1u;             // delivered by an earlier batch
+            const bool fresh = in && e.p != NONE64 && !had;
+            const u64 nb = __ballot(fresh), hb = __ballot(had);
+            if (t < R) slots[w * pitch + t] = fresh ? (u32)e.p : NONE32;
+            if (in && e.p != NONE64) pending[(u64)w * g.n_pkts + seq] = NONE64;         // leave the index empty
+            if (nb) {
+                if (r_step == 8) {      // a group owns its bytes of the bitmap
+                    const u32 mine = (u32)(nb >> (lane & ~7u)) & 0xFFu;
+                    if ((lane & 7) == 0 && mine)
+                        ((uint8_t*)(bitmap + (u64)w * g.words_pw))[seq >> 3] = (uint8_t)(mine | ((u32)(hb >> lane) & 0xFFu));
+                } else if (fresh) atomicOr((u32*)bitmap + 2 * (u64)w * g.words_pw + (seq >> 5), 1u << (seq & 31));
+            }
+            if (lane < 2) {
+                const u32 n = (u32)(nb >> (32 * lane)), o = (u32)(hb >> (32 * lane));
+                if (n) atomicOr(&sh_new[f][2 * c + lane], n);
+                if (o) atomicOr(&sh_old[f][2 * c + lane], o);
+            }
+            accepted += (u32)__popcll(nb);
+        };
+        #pragma unroll
+        for (int j = 0; j < BURST_AHEAD; ++j) take_entry(wave + j * BURST_WAVES, ahead[j]);
+        for (u32 pair = wave + BURST_AHEAD * BURST_WAVES; pair < n_pair; pair += BURST_WAVES) take_entry(pair, load_entry(pair, seq0));
+        if (tid < R && seq0 + tid < g.n_pkts) {
+            const u32 seq = seq0 + tid, b = find_bucket(g, fs, seq);
+            const u64 start = (u64)(seq - fs[b]) * g.P, left = g.b_cnt[b] - start, elem = g.b_off[b] + start;
+            u32* const elem_of = sh_elem + par * 2 * r_max;
+            elem_of[2 * tid] = (u32)elem; elem_of[2 * tid + 1] = (u32)(elem >> 32);
+            sh_len[par * r_max + tid] = (left < g.P ? (u32)left : g.P) | (home_ahead & 1u) << 16;
+        }
+    };
+
+    u32 par = 0, f = 0;
+    if (blockIdx.x < n_groups) { load_ahead(blockIdx.x); take_group(blockIdx.x, 0, 0); }
+    __syncthreads();
+    for (u32 grp = blockIdx.x; grp < n_groups; grp += n_blocks, par ^= 1, f = f == 2 ? 0 : f + 1) {
+        const u32 seq0 = lo + grp * R;
+        const u32 n_t = g.n_pkts - seq0 < R ? g.n_pkts - seq0 : R;
+        const u32* const slots = sh_dyn + par * W * pitch;
+        const u32* const elem_of = sh_elem + par * 2 * r_max;
+        const u32* const len_of = sh_len + par * r_max;
+        const u32* const is_new = sh_new[f];
+        const u32* const is_old = sh_old[f];
+        auto flag = [](const u32* m, u32 t) { return (m[t >> 5] >> (t & 31)) & 1u; };
+        const bool more_groups = grp + n_blocks < n_groups;
+        if (more_groups) load_ahead(grp + n_blocks);
+        const u64 e0 = uniform(((u64)elem_of[1] << 32) | elem_of[0]);
+        const u32 pad = (u32)e0 & 31u;                  // the image starts where its first span lies in a 128-byte line
+
+        // ---- payloads: lane i holds the wave's i-th item, a piece of NP KB of a packet; G workers' pieces make
+        // one step
+        const u32 item = wave + lane * BURST_WAVES;
+        const u32 t_l = n_piece == 1 ? item : item / n_piece, piece_l = item - t_l * n_piece;
+        u32 len_l = 0, at_l = 0, how_l = 0;             // at: first float of the span in the image; how: 1 it has contents, 3 and in the other copy
+        bool need = false;
+        if (t_l < n_t) {
+            const u32 lw = len_of[t_l];
+            len_l = lw & 0xFFFFu;
+            const bool old = flag(is_old, t_l);
+            need = flag(is_new, t_l) && piece_l * (NP * 256u) < len_l + LEAD;
+            at_l = pad + (u32)((((u64)elem_of[2 * t_l + 1] << 32) | elem_of[2 * t_l]) - e0);
+            how_l = old ? (lw >> 16 != pick ? 3u : 1u) : 0u;
+        }
+        u64 todo = uniform((u64)__ballot(need));
+        u64 left = 0;                   // workers of item i still to be loaded
+        u32 i = 0;
+        u32 slot32 = NONE32;            // lane w: slot of worker w's copy of the item's packet
+        f4v v[G][NP], a[NP];
+        #pragma unroll
+        for (int q = 0; q < NP; ++q) a[q] = f4v{0.f, 0.f, 0.f, 0.f};
+        auto load = [&]() {
+            if (left == 0) {
+                i = (u32)__builtin_ctzll(todo);
+                todo &= todo - 1;
+                slot32 = lane < W ? slots[lane * pitch + (u32)__builtin_amdgcn_readlane((int)t_l, (int)i)] : NONE32;
+                left = uniform((u64)__ballot(slot32 != NONE32));
+            }
+            const u32 len = (u32)__builtin_amdgcn_readlane((int)len_l, (int)i);
+            const u32 skip = (u32)__builtin_amdgcn_readlane((int)piece_l, (int)i) * (NP * 1024u);
+            const u32 have = unit_have<LEAD>(len, skip);
+            int off[NP];
+            #pragma unroll
+            for (int q = 0; q < NP; ++q) off[q] = unit_offset<LEAD>(len, skip, q * WAVE + lane);
+            #pragma unroll
+            for (int j = 0; j < G; ++j) {
+                const bool any = left != 0;
+                const u32 w = any ? (u32)__builtin_ctzll(left) : 0u;
+                left &= left - 1;
+                const u32 slot = any ? (u32)__builtin_amdgcn_readlane((int)slot32, (int)w) : 0u;
+                __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+                    (void*)(packets + uniform((u64)slot * g.stride + unit_base<LEAD>(skip))), 0, (int)uniform(any ? have : 0u), BUF_RAW);
+                #pragma unroll
+                for (int q = 0; q < NP; ++q)
+                    v[j][q] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r, off[q], 0, BUF_NT));
+            }
+        };
+        auto add = [&]() {
+            #pragma unroll
+            for (int j = 0; j < G; ++j)
+                #pragma unroll
+                for (int q = 0; q < NP; ++q) a[q] += v[j][q];
+            if (left) return;
+            const u32 len = (u32)__builtin_amdgcn_readlane((int)len_l, (int)i), at = (u32)__builtin_amdgcn_readlane((int)at_l, (int)i);
+            const u32 how = (u32)__builtin_amdgcn_readlane((int)how_l, (int)i), piece = (u32)__builtin_amdgcn_readlane((int)piece_l, (int)i);
+            if (how == 0 && (LEAD || (len & 3u) == 0)) {          // a span that this batch opens
+                #pragma unroll
+                for (int q = 0; q < NP; ++q) {
+                    const u32 row = (piece * NP + q) * (4 * WAVE);            // 256 floats of the unit grid
+                    const u32 p0 = row + 4 * lane - LEAD;                     // the unit's first float in the payload (wraps before it)
+                    f4v r = a[q] * inv_w;
+                    a[q] = f4v{0.f, 0.f, 0.f, 0.f};
+                    float* const o = image + (int)(at + p0);
+                    if (row >= LEAD && row + 4 * WAVE <= len + LEAD) {
+                        sq += squares(r);
+                        *(f4v_a4*)o = r;
+                    } else if (row < len + LEAD) {
+                        const bool m0 = p0 < len, m1 = p0 + 1 < len, m2 = p0 + 2 < len, m3 = p0 + 3 < len;
+                        r = f4v{m0 ? r.x : 0.f, m1 ? r.y : 0.f, m2 ? r.z : 0.f, m3 ? r.w : 0.f};
+                        sq += squares(r);
+                        if (m0 && m3) *(f4v_a4*)o = r;
+                        else {
+                            if (m0) o[0] = r.x;
+                            if (m1) o[1] = r.y;
+                            if (m2) o[2] = r.z;
+                            if (m3) o[3] = r.w;
+                        }
+                    }
+                }
+                return;
+            }
+            float* const img = image + (int)(at - LEAD);
+            float* const old = ((how == 3u) != (pick != 0) ? acc1 : acc0) + (e0 - pad + at) - LEAD;
+            #pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                const SpanUnit<LEAD> su((piece * NP + q) * WAVE + lane, len);
+                f4v r = su.take(a[q] * inv_w, len);
+                if (how) {                                        // result = old value + this batch's sum
+                    const f4v ov = su.full ? *(const f4v_a4*)(old + 4 * su.u) : su.floats(old + 4 * su.u);
+                    sq -= squares(ov);
+                    r = ov + r;
+                }
+                sq += squares(r);
+                if (how == 3u) su.store(old + 4 * su.u, r);       // stays in the other copy
+                else su.store(img + 4 * su.u, r);
+                a[q] = f4v{0.f, 0.f, 0.f, 0.f};
+            }
+        };
+        const bool any_item = todo != 0;
+        if (any_item) load();
+        __syncthreads();                // every wave has read the group before out of the image
+        {   // the flags of the group before are free: they are the ones of the group after the next
+            const u32 z = f == 0 ? 2 : f - 1;
+            if (tid < BURST_MAX / 32) sh_new[z][tid] = sh_old[z][tid] = 0;
+        }
+        if (tid < n_t && flag(is_new, tid) && !flag(is_old, tid)) home[seq0 + tid] = (uint8_t)pick;
+        if (any_item)
+            for (;;) {
+                add();
+                if (left == 0 && todo == 0) break;
+                load();
+            }
+        if (more_groups) take_group(grp + n_blocks, par ^ 1, f == 2 ? 0 : f + 1);
+        __syncthreads();
+        // ---- the image goes out, run by run of spans that belong to it
+        float* const out = (pick ? acc1 : acc0) + (e0 - pad);
+        auto in_image = [&](u32 t) { return flag(is_new, t) && !(flag(is_old, t) && len_of[t] >> 16 != pick); };
+        auto at_of = [&](u32 t) { return pad + (u32)((((u64)elem_of[2 * t + 1] << 32) | elem_of[2 * t]) - e0); };
+        auto store_run = [&](u32 t, u32 z) {            // spans of packets [t, z)
+            const u32 from = uniform(at_of(t)), to = uniform(at_of(z - 1) + (len_of[z - 1] & 0xFFFFu));     // floats [from, to) of the image
+            __amdgpu_buffer_rsrc_t o = __builtin_amdgcn_make_buffer_rsrc((void*)uniform((u64)out), 0, (int)(4 * to), BUF_RAW);
+            for (u32 u = (from >> 5 << 3) + tid; 4 * u < to; u += BURST_WAVES * WAVE) {
+                const f4v r = *(const f4v*)(image + 4 * u);
+                if (4 * u >= from && 4 * u + 4 <= to) {
+                    if (through) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4v, r), o, 16 * u, 0, BUF_SC1);
+                    else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4v, r), o, 16 * u, 0, BUF_NT);
+                } else {
+                    #pragma unroll
+                    for (u32 k = 0; k < 4; ++k)
+                        if (4 * u + k >= from && 4 * u + k < to) out[4 * u + k] = r[k];
+                }
+            }
+        };
+        u32 open = NONE32;                              // first packet of the run at hand
+        for (u32 c = 0; c < n_chunk; ++c) {
+            const u32 t = c * WAVE + lane;
+            const u64 m = uniform((u64)__ballot(t < n_t && in_image(t)));
+            for (u32 pos = 0; pos < WAVE;) {
+                const u64 rest = (open == NONE32 ? m : ~m) >> pos;
+                if (rest == 0) break;
+                pos += (u32)__builtin_ctzll(rest);
+                if (open == NONE32) open = c * WAVE + pos;
+                else { store_run(open, c * WAVE + pos); open = NONE32; }
+            }
+        }
+        if (open != NONE32) store_run(open, n_t);
+    }
+    // accepted packets and sum-of-squares change of this block: plain adds to the block's own rows
+    sq = wave_sum_f64(sq);
+    if (lane == 0) { sh_accepted[wave] = accepted; sh_sq[wave] = sq; }
+    __syncthreads();
+    if (tid == 0) {
+        u32 total = 0;
+        double t = 0.0;
+        #pragma unroll
+        for (int i = 0; i < BURST_WAVES; ++i) { total += sh_accepted[i]; t += sh_sq[i]; }
+        if (total) { accept_rows[blockIdx.x] += total; sumsq_rows[blockIdx.x] += t; }
     }
 }
 
@@ -1346,8 +1682,14 @@ __global__ __launch_bounds__(256) void classify_rw(const uint8_t* __restrict__ s
 // ------------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------------
+// What the context's gather_burst launches are given (burst_plan); fn null: none are made.
+typedef void (*burst_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, u64*, double*, float,
+                         u32, u32, u32, u32, u32, u32, u32);
+struct BurstPlan { burst_fn fn; u32 r_max, r_step, n_piece, table_at, image_at, min_seq, through_seq; size_t lds; };
+
 struct dblp_ctx {
     Geo g;
+    BurstPlan burst;
     u64 N;
     double eta;
     int device;
@@ -1642,6 +1984,69 @@ static u64 probe_blocks(const dblp_ctx* c, u64 pairs) {
     return (pairs + per - 1) / per;
 }
 
+template <u32 LEAD>
+static burst_fn burst_kernel(u32 np) {
+    return np == 1 ? gather_burst<1, 4, LEAD> : np == 2 ? gather_burst<2, 4, LEAD> : np == 3 ? gather_burst<3, 2, LEAD>
+         : np == 4 || !LEAD ? gather_burst<4, 2, LEAD> : gather_burst<5, 2, 2>;
+}
+
+// Units of 16 bytes from the packet's start (LEAD 2), or from the payload's (LEAD 0) where that takes one
+// pass of 64 less: payloads of 256, 512, 768 and 1024 floats (or one float fewer) would need one more
+// for the two floats that the 8-byte header pushes out (16 x 256 floats, 60 M: 860 -> 818 us; 1 x 256,
+// 25.6 M: 55 -> 48; 1024-float retransmissions: 162 -> 144).  Other lengths are better off from the
+// start, where fewer passes begin inside a 128-byte line (32 x 1472 B: 1.64 against 1.65 ms).
+static bool units_from_packet(const Geo& g) { return !(g.P <= 1024 && (g.P + 255) / 256 < (g.P + 2 + 255) / 256); }
+static u32 unit_passes(const Geo& g, bool lead) { return lead ? (g.units + WAVE - 1) / WAVE : (g.P + 4 * WAVE - 1) / (4 * WAVE); }
+
+// The line between gather_burst and gather_stream, by the bytes
+// that a batch reads (us of a whole pass with gather_stream, with bursts; P = 366 unless said):
+//   8 workers and more   150 MB (8 x 5 M elements, 160 MB: 116, 113; 16 x 2 M, 128 MB: 106, 106; 32 x 1 M: 114, 116)
+//   5 to 7               300 MB (6 x 10 M: 156, 155; 5 x 10 M: 149, 149; 6 x 25 M: 281, 269; 5 x 25 M: 261, 252)
+//   by the bytes that it writes, where these weigh more and a group's turn is short:
+//   3 and 4              144 MB (4 x 25 M: 184, 186; 3 x 25 M: 205, 206; 4 x 40 M: 265, 249; 3 x 40 M: 302, 291)
+//   2                    256 MB (2 x 38 M: 180, 180; 2 x 75 M: 290, 276; 2 x 150 M: 505, 467)
+//   1                    never (200 M: 473, 505)
+// Packets of up to 128 floats cost gather_stream, which finishes each in registers, more than they cost bursts: from
+// 48 MB read on (2 x 10 M of 128 floats: 130, 127; 4 x 10 M of 64: 220, 185; 4 x 40 M of 64: 608, 462).
+// The groups have to fill the chip: of 8 or a multiple of 8 packets (a group owns whole bytes of the bitmap) eleven
+// packets a CU, which leaves a CU in three idle at most (64 x 2 M of 1024 floats, 8 a CU: 183, 201; 32 x 3 M, 12 a
+// CU: 165, 156), of fewer and larger ones two (32 x 5 M of 16374, one a CU: 238, 251; 32 x 5 M of 8191: 238, 233).
+
+static BurstPlan burst_plan(const Geo& g, u32 cus) {
+    BurstPlan b = {};
+    if (g.W == 1) return b;
+    const bool lead = units_from_packet(g);
+    const u32 n_pass = unit_passes(g, lead);
+    const u64 span = 4ull * g.P, packets = (u64)g.W * g.stride;         // bytes written and read per sequence number
+    const u64 least = g.W > 1 && g.P <= 128 ? 48000000ull / packets : g.W >= 8 ? 150000000ull / packets : g.W >= 5 ? 300000000ull / packets
+                    : g.W >= 3 ? 144000000ull / span : 256000000ull / span;
+    const size_t table = ((size_t)g.B + 1) * sizeof(u32);
+    const u32 table_words = table <= IDX_TABLE_LDS_MAX ? g.B + 1 : 0u;
+    auto image_at = [&](u32 r) { return (BURST_INFO_LDS(g.W, r) + table_words + 31u) / 32u * 32u; };
+    auto lds = [&](u32 r) { return 4ull * (image_at(r) + (u64)r * g.P + 40u); };
+    u32 r = BURST_MAX, step = 8;
+    while (r > 8 && lds(r) > BURST_LDS) r -= 8;
+    if (lds(r) > BURST_LDS) { step = 1; while (r > 0 && lds(r) > BURST_LDS) --r; }
+    if (r == 0) return b;
+    const u32 turn = (u32)(((u64)g.n_pkts + cus - 1) / cus), most = (turn + step - 1) / step * step;
+    if (r > most) r = most;                             // short rounds: what gives every CU a group
+    const u64 fill = (u64)(step == 8 ? 11u : 2u) * cus;
+    b.min_seq = (u32)(least > fill ? (least < NONE32 ? least : NONE32) : fill);
+    if (b.min_seq > g.n_pkts) return b;
+    b.n_piece = n_pass <= 5 ? 1 : (n_pass + 3) / 4;
+    const u32 np = (n_pass + b.n_piece - 1) / b.n_piece;
+    b.n_piece = (n_pass + np - 1) / np;
+    b.r_max = r; b.r_step = step;
+    b.table_at = table_words ? BURST_INFO_LDS(g.W, r) : 0u;
+    b.image_at = image_at(r);
+    b.lds = lds(r);
+    // written through up to 16 MB per worker, 272 MB at most (us of a pass, through and past: 8 x 25 M 260, 263; 8 x 40 M
+    // 377, 373; 16 x 40 M 606, 622; 24 x 60 M 1392, 1417; 32 x 66 M 1896, 1903; 16 x 120 M 1806, 1782)
+    b.through_seq = (u32)((g.W < 17 ? 16000000ull * g.W : 272000000ull) / span);
+    b.fn = lead ? burst_kernel<2>(np) : burst_kernel<0>(np);
+    return b;
+}
+
 extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     if (!out || !cfg || !cfg->buckets) return DBLP_EINVAL;
     if (cfg->n_workers == 0 || cfg->n_workers > DBLP_MAX_WORKERS) return DBLP_EINVAL;
@@ -1745,6 +2150,11 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
         g.hint = c->d_hint;
     }
     c->d_sumsq_rows = (double*)(c->d_accept_rows + ACCEPT_ROWS);
+    c->burst = burst_plan(g, (u32)c->n_cus);
+    if (c->burst.fn && hipFuncSetAttribute((const void*)c->burst.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->burst.lds) != hipSuccess) {
+        (void)hipGetLastError();
+        c->burst.fn = nullptr;
+    }
 
     const u64 n_pending = (u64)g.W * n_pkts;
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (n_pending + 255) / 256, 16)), dim3(256), 0, c->stream,
@@ -1909,7 +2319,7 @@ extern "C" int dblp_packetize_list(dblp_ctx* c, uint16_t round, const float* con
 }
 
 typedef void (*gather_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, u64*, double*, float,
-                          GatherShape, GatherShape, u32, u32, u32, u32*);
+                          GatherShape, GatherShape, u32, u32, u32, u32, u32*);
 
 // The instance for `np` KB of a packet per step; few: one to three workers.
 template <bool DENSE, u32 LEAD>
@@ -1960,12 +2370,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
     }
     const float inv_w = c->fold ? 1.0f / (float)g.W : 1.0f;   // exact for the powers of two it is used with
     {
-        // Units of 16 bytes from the packet's start (LEAD 2), or from the payload's (LEAD 0) where that takes one
-        // pass of 64 less: payloads of 256, 512, 768 and 1024 floats (or one float fewer) would need one more
-        // for the two floats that the 8-byte header pushes out (16 x 256 floats, 60 M: 860 -> 818 us; 1 x 256,
-        // 25.6 M: 55 -> 48; 1024-float retransmissions: 162 -> 144).  Other lengths are better off from the
-        // start, where fewer passes begin inside a 128-byte line (32 x 1472 B: 1.64 against 1.65 ms).
-        const bool lead = !(g.P <= 1024 && (g.P + 255) / 256 < (g.P + 2 + 255) / 256) || block_waves(c) == 16;
+        const bool lead = units_from_packet(g) || block_waves(c) == 16;
         // Dense or sparse.  At least one arrival per SPARSE_DIV (worker, seq) pairs of the whole round is dense
         // whatever range it touches, and the launch is told so.  Fewer are a retransmission or a step of a round
         // that arrives in many steps; the number does not say which, so the blocks decide, from the sequence
@@ -1978,7 +2383,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         // Dense.  Packets of up to 5 KB are one piece, longer ones are cut evenly into pieces of 3 or 4 KB; in
         // a short round finer, so that a group gives each of the block's waves a piece.
         GatherShape dense, sparse;
-        const u32 n_pass = lead ? (g.units + WAVE - 1) / WAVE : (g.P + 4 * WAVE - 1) / (4 * WAVE);
+        const u32 n_pass = unit_passes(g, lead);
         dense.n_piece = n_pass <= 5 ? 1 : (n_pass + 3) / 4;
         const u32 heavy = (u64)g.W * g.stride >= HEAVY_BYTES ? 2 : (u64)g.W * g.stride >= HEAVY_BYTES / 2 ? 1 : 0;
         dense.sub_log2 = group_log2(g.n_pkts, (u32)c->n_cus, dense.n_piece > 1, heavy);      // (the whole round's)
@@ -2008,6 +2413,13 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         if (sparse.n_piece >= 8 && sparse.sub_log2 > 2 && g.n_pkts <= 64u * (u32)c->n_cus) sparse.sub_log2 = 2;
         sparse.blocks = grid_for(c, ((u64)g.n_pkts + (1u << sparse.sub_log2) - 1) >> sparse.sub_log2, nw == 16 ? 1 : 4);
 
+        // Bursts.  A batch of at least burst.min_seq packets per worker covers that many sequence numbers or more.  Known to be
+        // dense, it is one gather_burst launch; where the blocks have to find out, that launch leaves a sparse batch to a
+        // gather_stream launch after it, and the other way round.  The second launch costs about 3 us, so it is made
+        // for batches of 256 MB and more only, which take 60 us and more as a dense step and 130 as a retransmission.
+        const BurstPlan& burst = c->burst;
+        const bool in_bursts = burst.fn && n_arrivals >= (u64)burst.min_seq * g.W && (is_dense || n_arrivals * g.stride >= 256000000ull);
+
         u32 slots = 0, grid = dense.blocks;
         for (u32 l = 0; l <= (dense.sub_log2 > 2 ? dense.sub_log2 : 2); ++l)        // whatever the launch may choose
             if (GS_TEAM_LDS(g.W, l) > slots) slots = GS_TEAM_LDS(g.W, l);
@@ -2020,11 +2432,20 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         const u32 table_at = table <= IDX_TABLE_LDS_MAX ? nw * slots : 0u;
         if (table_at) lds += table;
         const gather_fn kern = is_dense ? gather_kernel<true>(nw, lead, few, np) : gather_kernel<false>(nw, lead, few, np);
-        if (grid > c->rows_used) c->rows_used = grid;
         ProfScope ps(c, small ? DBLP_K_GATHER_DIRECT : DBLP_K_GATHER, !is_dense && !small);
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(nw * WAVE), lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap,
-                           c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
-                           c->d_accept_rows, c->d_sumsq_rows, inv_w, dense, sparse, (u32)c->n_cus, heavy, table_at, ps.d_told());
+        if (in_bursts) {
+            if ((u32)c->n_cus > c->rows_used) c->rows_used = (u32)c->n_cus;
+            hipLaunchKernelGGL(burst.fn, dim3(c->n_cus), dim3(BURST_WAVES * WAVE), burst.lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap,
+                               c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
+                               c->d_accept_rows, c->d_sumsq_rows, inv_w, burst.r_max, burst.r_step, burst.n_piece, burst.table_at, burst.image_at,
+                               is_dense ? 0u : burst.min_seq, burst.through_seq);
+        }
+        if (!in_bursts || !is_dense) {
+            if (grid > c->rows_used) c->rows_used = grid;
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(nw * WAVE), lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap,
+                               c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
+                               c->d_accept_rows, c->d_sumsq_rows, inv_w, dense, sparse, (u32)c->n_cus, heavy, table_at, in_bursts ? burst.min_seq : 0u, ps.d_told());
+        }
     }
     LAUNCH_CHECK(c, "apply_arrivals");
     c->finalized = 0; c->norm_in_mailbox = 0; c->counters_in_mailbox = 0;
