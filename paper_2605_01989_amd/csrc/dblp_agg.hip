@@ -996,24 +996,29 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
     const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0, sh_tally);
     // A batch that is none of this kernel's is left to the gather_stream launch that follows.
     if (bi.hi == 0 || (min_seq && (batch_is_sparse(bi, g.W) || bi.hi - bi.lo < min_seq))) return;
-    // Groups of equal size, as many turns of the grid as the longest group asks for.
-    const u32 lo = uniform((u32)bi.lo / r_step * r_step), n_seq = uniform((u32)bi.hi) - lo, n_blocks = gridDim.x;
-    const u32 turns = (u32)(((u64)n_seq + (u64)r_max * n_blocks - 1) / ((u64)r_max * n_blocks));
-    u32 R = (n_seq + turns * n_blocks - 1) / (turns * n_blocks);
-    R = uniform((R + r_step - 1) / r_step * r_step);
-    const u32 n_groups = (n_seq + R - 1) / R;
+    // Groups of equal size but for one step: with all groups as long as the longest, the last turn of 4 x 61 M in 64
+    // KB packets left two CUs in three idle (7.3 turns of two packets and an eighth of that; now seven of two and one of
+    // one).
+    const u32 lo = uniform((u32)bi.lo / r_step * r_step), n_seq = uniform((u32)bi.hi) - lo;
+    const BurstTurns split(n_seq, gridDim.x, r_max, r_step);
+    const u32 r_long = uniform(split.r_long);
+    auto size_of = [&](u32 turn) { return uniform(split.size(turn)); };
+    auto first_of = [&](u32 turn) {
+        const u32 at = uniform(split.first(turn, blockIdx.x));
+        return at < n_seq ? lo + at : NONE32;
+    };
     const bool through = n_seq <= through_seq;
-    const u32 n_chunk = (R + WAVE - 1) / WAVE, n_pair = W * n_chunk;        // a pair: a worker's index entries of 64 sequence numbers
+    const u32 n_chunk = (r_long + WAVE - 1) / WAVE, n_pair = W * n_chunk;        // a pair: a worker's index entries of 64 sequence numbers
     const u32* const words = (const u32*)bitmap;
     u32 accepted = 0;
     double sq = 0.0;
 
     struct Entry { u64 p; u32 bits; };
-    auto load_entry = [&](u32 pair, u32 s0) {
+    auto load_entry = [&](u32 pair, u32 s0, u32 r) {
         Entry e;
         e.p = NONE64; e.bits = 0;
         const u32 w = pair / n_chunk, t = (pair - w * n_chunk) * WAVE + lane, seq = s0 + t;
-        if (pair < n_pair && t < R && seq < g.n_pkts) {
+        if (pair < n_pair && t < r && seq < g.n_pkts) {
             e.p = pending[(u64)w * g.n_pkts + seq];
             e.bits = words[2 * (u64)w * g.words_pw + (seq >> 5)];
         }
@@ -1021,25 +1026,23 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
     };
     Entry ahead[BURST_AHEAD];
     u32 home_ahead = 0;
-    auto load_ahead = [&](u32 grp) {
-        const u32 s0 = lo + grp * R;
+    auto load_ahead = [&](u32 s0, u32 r) {
         #pragma unroll
-        for (int j = 0; j < BURST_AHEAD; ++j) ahead[j] = load_entry(wave + j * BURST_WAVES, s0);
-        home_ahead = tid < R && s0 + tid < g.n_pkts ? home[s0 + tid] : 0;
+        for (int j = 0; j < BURST_AHEAD; ++j) ahead[j] = load_entry(wave + j * BURST_WAVES, s0, r);
+        home_ahead = tid < r && s0 + tid < g.n_pkts ? home[s0 + tid] : 0;
     };
 
     // A group's arrival index -> slots, bitmap, spans, in its half of the tables (par) and its flags (f).
-    auto take_group = [&](u32 grp, u32 par, u32 f) {
-        const u32 seq0 = lo + grp * R;
+    auto take_group = [&](u32 seq0, u32 r, u32 par, u32 f) {
         u32* const slots = sh_dyn + par * W * pitch;
         auto take_entry = [&](u32 pair, const Entry& e) {
             if (pair >= n_pair) return;
             const u32 w = pair / n_chunk, c = pair - w * n_chunk, t = c * WAVE + lane, seq = seq0 + t;
-            const bool in = t < R && seq < g.n_pkts;
+            const bool in = t < r && seq < g.n_pkts;
             const bool had = in && (e.bits >> (seq & 31)) & 1u;             // delivered by an earlier batch
             const bool fresh = in && e.p != NONE64 && !had;
             const u64 nb = __ballot(fresh), hb = __ballot(had);
-            if (t < R) slots[w * pitch + t] = fresh ? (u32)e.p : NONE32;
+            if (t < r) slots[w * pitch + t] = fresh ? (u32)e.p : NONE32;
             if (in && e.p != NONE64) pending[(u64)w * g.n_pkts + seq] = NONE64;         // leave the index empty
             if (nb) {
                 if (r_step == 8) {      // a group owns its bytes of the bitmap
@@ -1057,8 +1060,8 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
         };
         #pragma unroll
         for (int j = 0; j < BURST_AHEAD; ++j) take_entry(wave + j * BURST_WAVES, ahead[j]);
-        for (u32 pair = wave + BURST_AHEAD * BURST_WAVES; pair < n_pair; pair += BURST_WAVES) take_entry(pair, load_entry(pair, seq0));
-        if (tid < R && seq0 + tid < g.n_pkts) {
+        for (u32 pair = wave + BURST_AHEAD * BURST_WAVES; pair < n_pair; pair += BURST_WAVES) take_entry(pair, load_entry(pair, seq0, r));
+        if (tid < r && seq0 + tid < g.n_pkts) {
             const u32 seq = seq0 + tid, b = find_bucket(g, fs, seq);
             const u64 start = (u64)(seq - fs[b]) * g.P, left = g.b_cnt[b] - start, elem = g.b_off[b] + start;
             u32* const elem_of = sh_elem + par * 2 * r_max;
@@ -1068,19 +1071,19 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
     };
 
     u32 par = 0, f = 0;
-    if (blockIdx.x < n_groups) { load_ahead(blockIdx.x); take_group(blockIdx.x, 0, 0); }
+    u32 seq0 = first_of(0);
+    if (seq0 != NONE32) { load_ahead(seq0, size_of(0)); take_group(seq0, size_of(0), 0, 0); }
     __syncthreads();
-    for (u32 grp = blockIdx.x; grp < n_groups; grp += n_blocks, par ^= 1, f = f == 2 ? 0 : f + 1) {
-        const u32 seq0 = lo + grp * R;
-        const u32 n_t = g.n_pkts - seq0 < R ? g.n_pkts - seq0 : R;
+    for (u32 turn = 0; seq0 != NONE32; ++turn, par ^= 1, f = f == 2 ? 0 : f + 1) {
+        const u32 n_t = g.n_pkts - seq0 < size_of(turn) ? g.n_pkts - seq0 : size_of(turn);
+        const u32 seq_next = first_of(turn + 1);
         const u32* const slots = sh_dyn + par * W * pitch;
         const u32* const elem_of = sh_elem + par * 2 * r_max;
         const u32* const len_of = sh_len + par * r_max;
         const u32* const is_new = sh_new[f];
         const u32* const is_old = sh_old[f];
         auto flag = [](const u32* m, u32 t) { return (m[t >> 5] >> (t & 31)) & 1u; };
-        const bool more_groups = grp + n_blocks < n_groups;
-        if (more_groups) load_ahead(grp + n_blocks);
+        if (seq_next != NONE32) load_ahead(seq_next, size_of(turn + 1));
         const u64 e0 = uniform(((u64)elem_of[1] << 32) | elem_of[0]);
         const u32 pad = (u32)e0 & 31u;                  // the image starts where its first span lies in a 128-byte line
 
@@ -1196,7 +1199,7 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
                 if (left == 0 && todo == 0) break;
                 load();
             }
-        if (more_groups) take_group(grp + n_blocks, par ^ 1, f == 2 ? 0 : f + 1);
+        if (seq_next != NONE32) take_group(seq_next, size_of(turn + 1), par ^ 1, f == 2 ? 0 : f + 1);
         __syncthreads();
         // ---- the image goes out, run by run of spans that belong to it
         float* const out = (pick ? acc1 : acc0) + (e0 - pad);
@@ -1230,6 +1233,7 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
             }
         }
         if (open != NONE32) store_run(open, n_t);
+        seq0 = seq_next;
     }
     // accepted packets and sum-of-squares change of this block: plain adds to the block's own rows
     sq = wave_sum_f64(sq);

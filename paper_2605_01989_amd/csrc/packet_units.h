@@ -1,4 +1,5 @@
-// Where the gather reads a packet: plain integer rules, without device code.
+// Where the gather reads a packet, and which packets a block of the gather in bursts takes: plain integer rules,
+// without device code.
 #ifndef DBLP_PACKET_UNITS_H
 #define DBLP_PACKET_UNITS_H
 
@@ -29,5 +30,28 @@ template <uint32_t LEAD>
 constexpr int unit_offset(uint32_t len, uint32_t skip, uint32_t l) {
     return LEAD ? (int)(16 * l) : (len & 3u) && skip / 16 + l == len >> 2 ? (int)(unit_end<LEAD>(len) - 16) : (int)(skip + 16 * l + 8);
 }
+
+// A range of n_seq sequence numbers, shared out over n_blocks blocks in turns: in each turn every block takes one
+// group of consecutive numbers, of at most r_max (a multiple of r_step, the smallest group).  As few turns as r_max
+// allows, and every block is given the same number of steps, over its groups as evenly as whole steps go: the
+// first n_long turns have groups of r_long, the others one step less.
+struct BurstTurns {
+    uint32_t n_seq, n_blocks, r_step, turns, r_long, n_long;
+    constexpr BurstTurns(uint32_t n_seq_, uint32_t n_blocks_, uint32_t r_max, uint32_t r_step_)
+        : n_seq(n_seq_), n_blocks(n_blocks_), r_step(r_step_), turns(0), r_long(0), n_long(0) {
+        const uint32_t row = r_step * n_blocks, steps = (uint32_t)(((uint64_t)n_seq + row - 1) / row), most = r_max / r_step;
+        turns = (steps + most - 1) / most;
+        const uint32_t a = (steps + turns - 1) / turns;
+        r_long = a * r_step;
+        n_long = steps - turns * (a - 1);
+    }
+    constexpr uint32_t size(uint32_t turn) const { return turn < n_long ? r_long : r_long - r_step; }
+    // First number of the block's group in that turn; none (n_seq): the block has no more.
+    constexpr uint32_t first(uint32_t turn, uint32_t block) const {
+        const uint64_t before = (uint64_t)turn * r_long - (turn > n_long ? (uint64_t)(turn - n_long) * r_step : 0u);
+        const uint64_t at = before * n_blocks + (uint64_t)block * size(turn);
+        return turn < turns && at < n_seq ? (uint32_t)at : n_seq;
+    }
+};
 
 #endif
