@@ -1291,15 +1291,10 @@ struct ProbePair {
     }
 };
 
-// Missing packets per pair, list length it asks for (need), and the block's total of those.
+// Packets of this lane's pair that arrived (BLOCK_PAIR: in every lane of the block).  All threads call this.
 template <bool BLOCK_PAIR>
-__global__ __launch_bounds__(256) void loss_count(Geo g, const u64* __restrict__ bitmap, u32 bound_ppm, u32 ppw, u64 pairs,
-                                                  u32* __restrict__ missing_out, u32* __restrict__ need, u64* __restrict__ totals) {
-    __shared__ u64 sh[4];
+__device__ __forceinline__ u32 probe_got(const Geo& g, const u64* __restrict__ bitmap, const ProbePair& p, bool valid, u32 ppw, u64* sh) {
     const u32 lane = lane_id(), wave = uniform(threadIdx.x / WAVE);
-    const u64 pr = BLOCK_PAIR ? blockIdx.x : ((u64)blockIdx.x * 4 + wave) * ppw + lane;
-    const bool valid = lane < ppw && pr < pairs;
-    const ProbePair p(g, pr, valid);
     const bool alone = ppw > 1 && p.small;
     u32 got = 0;
     if (valid && alone)
@@ -1329,72 +1324,23 @@ __global__ __launch_bounds__(256) void loss_count(Geo g, const u64* __restrict__
         got = (u32)((sh[0] + sh[1]) + (sh[2] + sh[3]));
         __syncthreads();
     }
-    u32 want = 0;
-    if (valid && (!BLOCK_PAIR || wave == 0)) {
-        const u32 n_b = p.s1 - p.s0, miss = n_b - got;
-        const u64 allowed = ((u64)bound_ppm * n_b) / 1000000ull;
-        if (missing_out) missing_out[pr] = miss;
-        want = (u64)miss > allowed ? miss : 0u;
-        need[pr] = want;
-    }
-    const u64 sum = ((u64)wave_reduce<OpAdd>(want >> 16) << 16) + wave_reduce<OpAdd>(want & 0xFFFFu);
-    if (lane == 0) sh[wave] = sum;
-    __syncthreads();
-    if (threadIdx.x == 0) totals[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    return got;
 }
 
-// Where blocks are many: exclusive prefix of totals[0..n) in place, by one block of 1024 threads.
-#define PROBE_SCAN_BLOCKS 4096u
-__global__ __launch_bounds__(1024) void scan_totals(u64* __restrict__ totals, u32 n) {
-    __shared__ u64 part[1024];
-    const u32 t = threadIdx.x;
-    u64 base = 0;
-    for (u32 i0 = 0; i0 < n; i0 += 1024) {
-        const u64 v = i0 + t < n ? totals[i0 + t] : 0;
-        part[t] = v;
-        __syncthreads();
-        for (u32 d = 1; d < 1024; d <<= 1) {
-            const u64 u = t >= d ? part[t - d] : 0;
-            __syncthreads();
-            part[t] += u;
-            __syncthreads();
-        }
-        if (i0 + t < n) totals[i0 + t] = base + part[t] - v;
-        base += part[1023];
-        __syncthreads();
-    }
+// List length that a pair with `got` arrived packets asks for; *miss: packets that are missing.
+__device__ __forceinline__ u32 probe_want(const ProbePair& p, u32 got, u32 bound_ppm, u32* miss) {
+    const u32 n_b = p.s1 - p.s0;
+    *miss = n_b - got;
+    const u64 allowed = ((u64)bound_ppm * n_b) / 1000000ull;
+    return (u64)*miss > allowed ? *miss : 0u;
 }
 
-// The list: block j writes the entries of the pairs that block j of loss_count counted, from the sum of the
-// totals before its own on (scanned: totals holds those sums).  The last block tells the host the length.
+// The entries of the block's pairs (`want` of this lane's, at pos0 of the list on).  sh: a word per wave (BLOCK_PAIR).
 template <bool BLOCK_PAIR>
-__global__ __launch_bounds__(256) void emit_retx(Geo g, const u64* __restrict__ bitmap, u32 ppw, u64 pairs, const u32* __restrict__ need,
-                                                 const u64* __restrict__ totals, int scanned, u64* __restrict__ list, u64 capacity,
-                                                 u64* __restrict__ mailbox) {
-    __shared__ u64 sh[4], sh_sum[4];
+__device__ __forceinline__ void probe_emit(const Geo& g, const u64* __restrict__ bitmap, const ProbePair& p, u32 want, u64 pos0, u32 ppw,
+                                           u64* __restrict__ list, u64 capacity, u64* sh) {
     const u32 lane = lane_id(), wave = uniform(threadIdx.x / WAVE);
-    const u64 pr = BLOCK_PAIR ? blockIdx.x : ((u64)blockIdx.x * 4 + wave) * ppw + lane;
-    const bool valid = lane < ppw && pr < pairs;
-    const u32 want = valid ? need[pr] : 0;
-    u64 before = 0;
-    if (scanned) before = threadIdx.x == 0 ? totals[blockIdx.x] : 0;
-    else
-        for (u32 i = threadIdx.x; i < blockIdx.x; i += 256) before += totals[i];
-    u32 lo = (u32)before & 0xFFFFFu, mid = (u32)(before >> 20) & 0xFFFFFu, hi = (u32)(before >> 40);     // 64 x 2^20 fits 32 bits
-    before = ((u64)wave_reduce<OpAdd>(hi) << 40) + ((u64)wave_reduce<OpAdd>(mid) << 20) + wave_reduce<OpAdd>(lo);
-    const u32 inc_hi = wave_scan_incl<OpAdd>(want >> 16), inc_lo = wave_scan_incl<OpAdd>(want & 0xFFFFu);
-    const u64 incl = ((u64)inc_hi << 16) + inc_lo;
-    const u64 sum = ((u64)(u32)__builtin_amdgcn_readlane((int)inc_hi, 63) << 16) + (u32)__builtin_amdgcn_readlane((int)inc_lo, 63);
-    if (lane == 0) { sh[wave] = before; sh_sum[wave] = sum; }
-    __syncthreads();
-    u64 base = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) mailbox[0] = base + (BLOCK_PAIR ? sh_sum[0] : (sh_sum[0] + sh_sum[1]) + (sh_sum[2] + sh_sum[3]));
-    if (!BLOCK_PAIR)
-        for (u32 i = 0; i < wave; ++i) base += sh_sum[i];
-    if (capacity == 0 || sum == 0) return;
-    const ProbePair p(g, pr, valid);
     const bool alone = ppw > 1 && p.small;
-    const u64 pos0 = base + incl - want;
     if (want && alone) {
         u64 pos = pos0;
         for (u32 wd = p.s0 >> 6; wd <= (p.s1 - 1) >> 6; ++wd)
@@ -1412,9 +1358,9 @@ __global__ __launch_bounds__(256) void emit_retx(Geo g, const u64* __restrict__ 
             #pragma unroll PROBE_UNROLL
             for (u32 wd = wd0 + lane; wd <= wd1; wd += WAVE) c += (u32)__popcll(~bitmap[(u64)q.w * g.words_pw + wd] & range_mask(wd, q.s0, q.s1));
             c = wave_reduce<OpAdd>(c);
-            if (lane == 0) sh_sum[wave] = c;
+            if (lane == 0) sh[wave] = c;
             __syncthreads();
-            for (u32 i = 0; i < wave; ++i) at += sh_sum[i];
+            for (u32 i = 0; i < wave; ++i) at += sh[i];
         }
         for (u32 w0 = wd0; w0 <= wd1; w0 += PROBE_UNROLL * WAVE) {
             u64 v[PROBE_UNROLL];
@@ -1434,6 +1380,143 @@ __global__ __launch_bounds__(256) void emit_retx(Geo g, const u64* __restrict__ 
             }
         }
     }
+}
+
+// Sums over the 64 lanes: of u32 whose sum may not fit 32 bits, and of values below 2^46.
+__device__ __forceinline__ u64 wave_sum_wide(u32 v) { return ((u64)wave_reduce<OpAdd>(v >> 16) << 16) + wave_reduce<OpAdd>(v & 0xFFFFu); }
+__device__ __forceinline__ u64 wave_sum_u46(u64 v) {
+    const u32 lo = (u32)v & 0xFFFFFu, mid = (u32)(v >> 20) & 0xFFFFFu, hi = (u32)(v >> 40);     // 64 x 2^20 fits 32 bits
+    return ((u64)wave_reduce<OpAdd>(hi) << 40) + ((u64)wave_reduce<OpAdd>(mid) << 20) + wave_reduce<OpAdd>(lo);
+}
+
+// The probe in one launch, for up to eight blocks per CU: each block counts its pairs and tells the others the
+// length of its part of the list; a block whose part is not empty, and the last one, which tells the host the whole
+// length, then add up what the blocks before it told.  totals[j] = tag | length, in one 64-bit word that is stored
+// and loaded as a relaxed atomic at device scope, so no fence is needed (one would write back the L2 that the gather has
+// just dirtied); the tag differs from probe to probe, so nothing is cleared in between.
+//
+// The wait ends: a block tells its length before it waits for anything, and waits only for blocks of lower index.  Of
+// the blocks that have not told theirs the one of lowest index is never kept from starting by this launch, as
+// workgroups of a launch start in index order on each XCD and all before it end without it.
+//
+// Latency bounds the probe: a second launch for the list, which it was, costs its own start and a second walk to the same
+// words.  us of the two launches, and of this one, first probe of a round: 64 x 4 pairs of 64 packets 6.7, 4.2; 161 x 8
+// of 435 packets on average 8.9, 5.6; 148 x 8 of 2300 11.7, 9.8; 292 x 16 of 1190 15.7, 13.9.
+#define PROBE_TAG_SHIFT 40
+#define PROBE_POLL 8
+template <bool BLOCK_PAIR>
+__global__ __launch_bounds__(256) void probe_once(Geo g, const u64* __restrict__ bitmap, u32 bound_ppm, u32 ppw, u64 pairs, u32* __restrict__ missing_out,
+                                                  u64* totals, u64 tag, u64* __restrict__ list, u64 capacity, u64* __restrict__ mailbox) {
+    __shared__ u64 sh[4], sh_sum[4];
+    const u32 lane = lane_id(), wave = uniform(threadIdx.x / WAVE);
+    const u64 pr = BLOCK_PAIR ? blockIdx.x : ((u64)blockIdx.x * 4 + wave) * ppw + lane;
+    const bool valid = lane < ppw && pr < pairs;
+    const ProbePair p(g, pr, valid);
+    const u32 got = probe_got<BLOCK_PAIR>(g, bitmap, p, valid, ppw, sh);
+    u32 want = 0;
+    if (valid) {
+        u32 miss;
+        want = probe_want(p, got, bound_ppm, &miss);
+        if (missing_out && (!BLOCK_PAIR || wave == 0)) missing_out[pr] = miss;
+    }
+    const u32 inc_hi = wave_scan_incl<OpAdd>(want >> 16), inc_lo = wave_scan_incl<OpAdd>(want & 0xFFFFu);
+    const u64 incl = ((u64)inc_hi << 16) + inc_lo;
+    const u64 sum = ((u64)(u32)__builtin_amdgcn_readlane((int)inc_hi, 63) << 16) + (u32)__builtin_amdgcn_readlane((int)inc_lo, 63);
+    if (lane == 0) sh_sum[wave] = sum;
+    __syncthreads();
+    const u64 mine = BLOCK_PAIR ? sh_sum[0] : (sh_sum[0] + sh_sum[1]) + (sh_sum[2] + sh_sum[3]);
+    if (threadIdx.x == 0) __hip_atomic_store(&totals[blockIdx.x], tag | mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool last = blockIdx.x == gridDim.x - 1;
+    if (!last && (mine == 0 || capacity == 0)) return;          // the same in all threads of the block
+    u64 before = 0;
+    for (u32 i0 = threadIdx.x; i0 < blockIdx.x; i0 += PROBE_POLL * 256) {
+        u64 v[PROBE_POLL];
+        bool all;
+        do {
+            all = true;
+            #pragma unroll
+            for (u32 k = 0; k < PROBE_POLL; ++k) {
+                const u32 i = i0 + k * 256;
+                v[k] = i < blockIdx.x ? __hip_atomic_load(&totals[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : tag;
+            }
+            #pragma unroll
+            for (u32 k = 0; k < PROBE_POLL; ++k) all = all && v[k] >> PROBE_TAG_SHIFT == tag >> PROBE_TAG_SHIFT;
+        } while (!all);
+        #pragma unroll
+        for (u32 k = 0; k < PROBE_POLL; ++k) before += v[k] ^ tag;
+    }
+    before = wave_sum_u46(before);
+    if (lane == 0) sh[wave] = before;
+    __syncthreads();
+    u64 base = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    if (last && threadIdx.x == 0) mailbox[0] = base + mine;
+    if (!BLOCK_PAIR)
+        for (u32 i = 0; i < wave; ++i) base += sh_sum[i];
+    if (capacity == 0) return;
+    __syncthreads();                // sh and sh_sum have been read
+    probe_emit<BLOCK_PAIR>(g, bitmap, p, want, base + incl - want, ppw, list, capacity, sh);
+}
+
+// More blocks than that, in three launches.  Missing packets per pair, list length it asks for (need), and the block's
+// total of those.
+__global__ __launch_bounds__(256) void loss_count(Geo g, const u64* __restrict__ bitmap, u32 bound_ppm, u32 ppw, u64 pairs,
+                                                  u32* __restrict__ missing_out, u32* __restrict__ need, u64* __restrict__ totals) {
+    __shared__ u64 sh[4];
+    const u32 lane = lane_id(), wave = uniform(threadIdx.x / WAVE);
+    const u64 pr = ((u64)blockIdx.x * 4 + wave) * ppw + lane;
+    const bool valid = lane < ppw && pr < pairs;
+    const ProbePair p(g, pr, valid);
+    const u32 got = probe_got<false>(g, bitmap, p, valid, ppw, sh);
+    u32 want = 0;
+    if (valid) {
+        u32 miss;
+        want = probe_want(p, got, bound_ppm, &miss);
+        if (missing_out) missing_out[pr] = miss;
+        need[pr] = want;
+    }
+    const u64 sum = wave_sum_wide(want);
+    if (lane == 0) sh[wave] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) totals[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
+// Exclusive prefix of totals[0..n) in place, by one block of 1024 threads; the host is told the sum.
+__global__ __launch_bounds__(1024) void scan_totals(u64* __restrict__ totals, u32 n, u64* __restrict__ mailbox) {
+    __shared__ u64 part[1024];
+    const u32 t = threadIdx.x;
+    u64 base = 0;
+    for (u32 i0 = 0; i0 < n; i0 += 1024) {
+        const u64 v = i0 + t < n ? totals[i0 + t] : 0;
+        part[t] = v;
+        __syncthreads();
+        for (u32 d = 1; d < 1024; d <<= 1) {
+            const u64 u = t >= d ? part[t - d] : 0;
+            __syncthreads();
+            part[t] += u;
+            __syncthreads();
+        }
+        if (i0 + t < n) totals[i0 + t] = base + part[t] - v;
+        base += part[1023];
+        __syncthreads();
+    }
+    if (t == 0) mailbox[0] = base;
+}
+
+// The list: block j writes the entries of the pairs that block j of loss_count counted, from totals[j] on.
+__global__ __launch_bounds__(256) void emit_retx(Geo g, const u64* __restrict__ bitmap, u32 ppw, u64 pairs, const u32* __restrict__ need,
+                                                 const u64* __restrict__ totals, u64* __restrict__ list, u64 capacity) {
+    __shared__ u64 sh_sum[4];
+    const u32 lane = lane_id(), wave = uniform(threadIdx.x / WAVE);
+    const u64 pr = ((u64)blockIdx.x * 4 + wave) * ppw + lane;
+    const bool valid = lane < ppw && pr < pairs;
+    const u32 want = valid ? need[pr] : 0;
+    const u32 inc_hi = wave_scan_incl<OpAdd>(want >> 16), inc_lo = wave_scan_incl<OpAdd>(want & 0xFFFFu);
+    const u64 incl = ((u64)inc_hi << 16) + inc_lo;
+    if (lane == WAVE - 1) sh_sum[wave] = incl;
+    __syncthreads();
+    u64 base = totals[blockIdx.x];
+    for (u32 i = 0; i < wave; ++i) base += sh_sum[i];
+    probe_emit<false>(g, bitmap, ProbePair(g, pr, valid), want, base + incl - want, ppw, list, capacity, sh_sum);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1725,6 +1808,7 @@ struct dblp_ctx {
     u32 n_picked;
     hipEvent_t cls_ev[2];
     int probe_block_pair;   // probe: a block per (worker, bucket) pair
+    u32 probe_no;           // probes made: what their words in d_totals are told apart by
     u32* d_need; u64* d_totals; double* d_partials;   // probe: list length per pair, and per block of pairs
     u32* d_block_tallies;   // [IDX_BLOCKS_PER_CU * n_cus][5], written by index_arrivals
     u64* d_accept_rows;     // [ACCEPT_ROWS] accepted packets per gather block
@@ -2166,6 +2250,8 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (g.W * g.words_pw + 255) / 256, 16)), dim3(256), 0, c->stream,
                        c->d_bitmap, g.W * g.words_pw, 0ull);
     hipLaunchKernelGGL(reset_counters, dim3(1), dim3(64), 0, c->stream, c->d_counters);
+    hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (probe_blocks(c, pairs) + 255) / 256, 16)), dim3(256), 0, c->stream,
+                       c->d_totals, probe_blocks(c, pairs), 0ull);
     hipLaunchKernelGGL(fill_u64, dim3(32), dim3(256), 0, c->stream, c->d_accept_rows, (u64)(2 * ACCEPT_ROWS), 0ull);
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (n_pkts + 16 + 2047) / 2048, 16)), dim3(256), 0, c->stream,
                        (u64*)c->d_home, (u64)((n_pkts + 7) / 8 + 1), 0ull);
@@ -2493,15 +2579,18 @@ extern "C" int dblp_loss_account(dblp_ctx* c, uint32_t bound_ppm, uint32_t* d_mi
     const u32 ppw = probe_ppw(c, pairs);
     if (blocks > 0x7FFFFFFFull) return fail(c, DBLP_EINVAL, "loss_account: too many (worker, bucket) pairs");
     {
-        // Each block of emit_retx adds up the totals of the blocks before it (2048 of them: about a
-        // microsecond) unless they are so many that a pass in between is shorter.
-        const int scanned = blocks > PROBE_SCAN_BLOCKS ? 1 : 0;
         ProfScope ps(c, DBLP_K_PROBE);
-        hipLaunchKernelGGL(c->probe_block_pair ? loss_count<true> : loss_count<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g,
-                           c->d_bitmap, bound_ppm, ppw, pairs, d_missing, c->d_need, c->d_totals);
-        if (scanned) hipLaunchKernelGGL(scan_totals, dim3(1), dim3(1024), 0, c->stream, c->d_totals, (u32)blocks);
-        hipLaunchKernelGGL(c->probe_block_pair ? emit_retx<true> : emit_retx<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g, c->d_bitmap, ppw, pairs, (const u32*)c->d_need,
-                           (const u64*)c->d_totals, scanned, (u64*)d_retx_list, (u64)retx_capacity, c->d_mailbox);
+        if (blocks <= 8u * (u32)c->n_cus) {
+            const u64 tag = (u64)(++c->probe_no & 0xFFFFFFu) << PROBE_TAG_SHIFT;
+            hipLaunchKernelGGL(c->probe_block_pair ? probe_once<true> : probe_once<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g,
+                               c->d_bitmap, bound_ppm, ppw, pairs, d_missing, c->d_totals, tag, (u64*)d_retx_list, (u64)retx_capacity, c->d_mailbox);
+        } else {
+            hipLaunchKernelGGL(loss_count, dim3((u32)blocks), dim3(256), 0, c->stream, g, c->d_bitmap, bound_ppm, ppw, pairs, d_missing, c->d_need, c->d_totals);
+            hipLaunchKernelGGL(scan_totals, dim3(1), dim3(1024), 0, c->stream, c->d_totals, (u32)blocks, c->d_mailbox);
+            if (retx_capacity)
+                hipLaunchKernelGGL(emit_retx, dim3((u32)blocks), dim3(256), 0, c->stream, g, c->d_bitmap, ppw, pairs, (const u32*)c->d_need,
+                                   (const u64*)c->d_totals, (u64*)d_retx_list, (u64)retx_capacity);
+        }
     }
     LAUNCH_CHECK(c, "loss_account");
     HIP_TRY(c, hipStreamSynchronize(c->stream));

@@ -1,0 +1,71 @@
+"""GPU: a probe's counts, list and verdict at the edges of its launches, against plain torch on the flags of what arrived.
+
+The list is written in one launch by blocks that add up each other's lengths while there are at most eight blocks per
+CU (a wave takes up to 64 pairs, so up to 524288 pairs on 256 CUs), and in three launches beyond.  All values are
+integers and compared exactly."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+P, ROUND = 4, 9
+
+
+def _context(W, packets):
+    """Buckets of the given numbers of packets, the last packet of each a float short."""
+    import paper_2605_01989_amd as dblp
+    cnt = [n * P - 1 for n in packets]
+    off = [0]
+    for c in cnt:
+        off.append(off[-1] + c)
+    return dblp.Aggregator(W, off[-1], P, off[:-1], cnt)
+
+
+def _expect(alive, first, n_b, bound):
+    import torch
+    lost = torch.zeros(alive.shape[0], alive.shape[1] + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(~alive, 1, out=lost[:, 1:])
+    missing = lost[:, first[1:]] - lost[:, first[:-1]]
+    fails = missing > bound * n_b // 1_000_000
+    w, seq = torch.nonzero(~alive & fails.repeat_interleave(n_b, dim=1), as_tuple=True)
+    return missing.int().flatten(), (w << 32) | seq
+
+
+# one pair; a block's remainder; as many blocks as are resident, and one pair more; two pairs a wave; 64 a wave, and one
+# pair more than fit: three launches; long buckets of which a block takes one
+CASES = [(1, [1]), (3, [5, 70, 1, 64, 65, 129]), (32, [2] * 256), (33, [2] * 249), (64, [1, 300] * 64), (64, [3, 1] * 4096),
+         (64, [1] * 8193), (5, [40_000, 3, 33_000, 1])]
+
+
+@pytest.mark.parametrize("W,packets", CASES)
+def test_probe_lists_what_is_missing(W, packets):
+    import torch
+    agg = _context(W, packets)
+    n_b = torch.tensor(packets, device="cuda")
+    first = torch.cat([torch.zeros(1, dtype=torch.int64, device="cuda"), n_b.cumsum(0)])
+    gen = torch.Generator(device="cuda").manual_seed(W + len(packets))
+    grads = [torch.ones(agg.N, device="cuda") for _ in range(W)]
+    alive = torch.zeros(W, agg.n_pkts, dtype=torch.bool, device="cuda")
+    agg.begin_round(ROUND)
+    missing = torch.empty(W * agg.B, dtype=torch.int32, device="cuda")
+    out = torch.empty(W * agg.n_pkts + 1, dtype=torch.int64, device="cuda")
+    for more in (0.0, 0.5, 0.9, 1.0):            # what has arrived before each probe; every packet before the last
+        new = ~alive & (torch.rand(W, agg.n_pkts, generator=gen, device="cuda") < more)
+        w, seq = torch.nonzero(new, as_tuple=True)
+        n = w.numel()
+        if n:
+            packets_buf = torch.empty(n * agg.stride, dtype=torch.uint8, device="cuda")
+            src = torch.empty(n, dtype=torch.int16, device="cuda")
+            agg.packetize_list(ROUND, grads, (w << 32) | seq, n, packets_buf, src)
+            agg.apply_arrivals(packets_buf, src, n)
+        alive |= new
+        for bound in (0, 200_000, 1_000_000):
+            want_missing, want = _expect(alive, first, n_b, bound)
+            for cap in (out.numel(), want.numel() // 2, 0):
+                missing.fill_(-1)
+                out.fill_(-1)
+                count, met, truncated = agg.loss_account(bound, missing, out, cap)
+                assert (count, met, truncated) == (want.numel(), want.numel() == 0, want.numel() > cap)
+                assert torch.equal(missing, want_missing)
+                k = min(cap, count)
+                assert torch.equal(out[:k], want[:k]) and bool((out[k:] == -1).all())
+    assert bool(alive.all())
