@@ -1522,6 +1522,48 @@ __global__ __launch_bounds__(256) void emit_retx(Geo g, const u64* __restrict__ 
 // ------------------------------------------------------------------------------------------
 // finalize (zero-fill + mean over all W) with fused partial sums of squares; norm reduction
 // ------------------------------------------------------------------------------------------
+// Per-block partial sums that the last block of the same launch adds up.  words[0] numbers the launches that have used
+// the array; block i's sum is two words, tag << 32 | half of the double, stored and loaded as relaxed atomics at device scope.
+// The tag comes from device memory, not from the host, so that a launch recorded into a graph can be replayed.
+// The wait ends: a block waits for nothing before it tells its sum, and the block that waits is the last of its launch.
+// A second launch for the sum cost 2 to 4 us of the stream (3 workers x 5.3 M, copied out: 103.6 us a pass with it, 102.7 without).
+#define PARTIALS_WORDS(blocks) (1u + 2u * (blocks))
+__device__ __forceinline__ u32 partials_tag(const u64* words) { return (u32)words[0] + 1u; }
+__device__ __forceinline__ void tell_partial(u64* words, u32 i, u32 tag, double v) {
+    const u64 bits = (u64)__double_as_longlong(v), t = (u64)tag << 32;
+    __hip_atomic_store(&words[1 + 2 * i], t | (u32)bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&words[2 + 2 * i], t | (u32)(bits >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Sum of the n blocks' partials in a fixed order, in every thread.  All 256 threads of the launch's last block; n_max: of any launch.
+__device__ __forceinline__ double fold_partials(u64* words, u32 n, u32 tag, u32 n_max, double* wsum) {
+    double s = 0.0;
+    for (u32 i0 = threadIdx.x; i0 < n; i0 += 4 * 256) {
+        u64 lo[4], hi[4];
+        bool all;
+        do {
+            all = true;
+            #pragma unroll
+            for (u32 k = 0; k < 4; ++k) {
+                const u32 i = i0 + k * 256;
+                lo[k] = i < n ? __hip_atomic_load(&words[1 + 2 * i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (u64)tag << 32;
+                hi[k] = i < n ? __hip_atomic_load(&words[2 + 2 * i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (u64)tag << 32;
+            }
+            #pragma unroll
+            for (u32 k = 0; k < 4; ++k) all = all && (u32)(lo[k] >> 32) == tag && (u32)(hi[k] >> 32) == tag;
+        } while (!all);
+        #pragma unroll
+        for (u32 k = 0; k < 4; ++k) s += __longlong_as_double((long long)((hi[k] << 32) | (u32)lo[k]));
+    }
+    s = wave_sum_f64(s);
+    if (lane_id() == 0) wsum[threadIdx.x / WAVE] = s;
+    __syncthreads();
+    // every block has read words[0] by now.  Before the tags start again from 1, what longer launches left goes.
+    if (tag == 0xFFFFFFFFu)
+        for (u32 i = threadIdx.x; i < 2 * n_max; i += 256) words[1 + i] = 0;
+    if (threadIdx.x == 0) words[0] = tag == 0xFFFFFFFFu ? 0 : tag;
+    return (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+}
+
 // Compensation pass (Alg. "DBLP_RECV" last statements, Alg. "Server" mean).  Per packet span:
 //   some worker delivered it   out = src            (scale_mode 0: the gather already divided by W)
 //                              out = src / W        (scale_mode 1: W is not a power of two)
@@ -1539,16 +1581,16 @@ __global__ __launch_bounds__(256) void emit_retx(Geo g, const u64* __restrict__ 
 //   3 x 5.3 M, 1472 B (2 x 21 MB moved)     23 -> 13 us
 //   8 x 215 M, 1472 B (2 x 862 MB moved)   443 -> 387 us
 // move_home (in-place form, n_piece = 1): the homes of spans that were moved are reset to copy 0.
-// With scale_mode 1 the per-block sums of out^2 go to partials[blockIdx.x].  Otherwise the sum of
-// squares is already known: the gather kernels kept it per block in sumsq_rows, and the one extra
-// block of this launch (blockIdx.x == n_work_blocks) adds those rows up in a fixed order (fixed
-// for given launch sizes of the round's gather kernels) and writes the total to the host mailbox.
+// With scale_mode 1 the per-block sums of out^2 go to `partials`.  Otherwise the sum of squares is already known: the
+// gather kernels kept it per block in sumsq_rows.  The one extra block of this launch (blockIdx.x == n_work_blocks) adds
+// up the one or the other in a fixed order (fixed for given launch sizes of the round's gather kernels) and
+// writes the total to the host mailbox.
 #define FIN_PIECE 4096
 template <bool TABLE_IN_LDS>
 __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restrict__ bitmap, const float* acc0,
                                                      const float* acc1, uint8_t* __restrict__ home,
                                                      float* out, int scale_mode, float wf, int move_home,
-                                                     u32 grp_log2, u32 n_piece, double* __restrict__ partials, u32 n_work_blocks,
+                                                     u32 grp_log2, u32 n_piece, u64* partials, u32 n_max, u32 n_work_blocks,
                                                      const double* __restrict__ sumsq_rows, const u64* __restrict__ accept_rows,
                                                      u32 n_rows,
                                                      u64* __restrict__ counters, u64* __restrict__ mailbox) {
@@ -1560,7 +1602,7 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
     if (blockIdx.x >= n_work_blocks) {
         // the extra block: fixed-order sum of the gather's rows (sum of squares for Eq. 1, accepted
         // packets), and the round's counters mirrored into the host mailbox:
-        // mailbox[1] = sum of squares (when the gather kept it), mailbox[8..11] = accepted,
+        // mailbox[1] = sum of squares, mailbox[8..11] = accepted,
         // candidates, stale, invalid
         // Only the n_rows rows that a launch of this round can have written are read; the rest are zero.
         double s = 0.0;
@@ -1580,10 +1622,15 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
         const u32 a_lo = wave_reduce<OpAdd>((u32)(a & 0xFFFFFu)), a_hi = wave_reduce<OpAdd>((u32)(a >> 20));   // 64 x 2^20 fits 32 bits
         if (lane == 0) { wsum[wave_in_block] = s; asum[wave_in_block] = ((u64)a_hi << 20) + a_lo; }
         __syncthreads();
+        double total = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+        if (scale_mode) {
+            __syncthreads();
+            total = fold_partials(partials, n_work_blocks, partials_tag(partials), n_max, wsum);
+        }
         if (threadIdx.x == 0) {
             const u64 accepted = (asum[0] + asum[1]) + (asum[2] + asum[3]);
             counters[C_ACCEPTED] = accepted;
-            if (scale_mode == 0) ((double*)mailbox)[1] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+            ((double*)mailbox)[1] = total;
             mailbox[8] = accepted; mailbox[9] = counters[C_CANDIDATES];
             mailbox[10] = counters[C_STALE]; mailbox[11] = counters[C_INVALID];
         }
@@ -1688,40 +1735,77 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
         dsum = wave_sum_f64(dsum);
         if (lane == 0) wsum[wave_in_block] = dsum;
         __syncthreads();
-        if (threadIdx.x == 0) partials[blockIdx.x] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+        if (threadIdx.x == 0) tell_partial(partials, blockIdx.x, partials_tag(partials), (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]));
     }
 }
 
-// Sum of squares of a plain vector (16-byte aligned), same partials layout.
-__global__ __launch_bounds__(256) void sumsq_vec(const float* __restrict__ v, u64 n, double* __restrict__ partials) {
-    __shared__ double wsum[4];
+// Sum of squares of a plain vector (16-byte aligned).  Memory bounds it.  A block reads runs of SQ_RUN x 4 KB, all
+// loads of a run in flight, with the non-temporal hint, and two blocks per CU are enough: fewer DRAM rows are open at a time
+// than with eight blocks that read 4 KB here and there.  us (TB/s), before and now: 25.6 M floats 19.9, 18.4 (5.1, 5.6);
+// 124 M 79.6, 72.8 (6.3, 6.8); 1000 M 642, 554 (6.2, 7.2); runs of 8 and 16 with as many blocks 75.4 and 77.5 at 124 M, four
+// blocks per CU 74.6, eight 75.7.
+#define SQ_RUN 4
+#define SQ_BLOCKS_PER_CU 2
+__device__ __forceinline__ double vec_sumsq(const float* __restrict__ v, u64 n) {
     const u64 n4 = n / 4;
-    const float4* v4 = (const float4*)v;
-    const u64 stride = (u64)gridDim.x * blockDim.x;
+    const f4v* v4 = (const f4v*)v;
     double dsum = 0.0;
-    for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
-        float4 x = v4[i];
-        dsum += (double)((x.x * x.x + x.y * x.y) + (x.z * x.z + x.w * x.w));
+    auto add = [&](f4v x) { dsum += (double)((x.x * x.x + x.y * x.y) + (x.z * x.z + x.w * x.w)); };
+    for (u64 u0 = (u64)blockIdx.x * (SQ_RUN * 256); u0 < n4; u0 += (u64)gridDim.x * (SQ_RUN * 256)) {
+        const u64 u = u0 + threadIdx.x;
+        if (u0 + SQ_RUN * 256 <= n4) {
+            f4v x[SQ_RUN];
+            #pragma unroll
+            for (int k = 0; k < SQ_RUN; ++k) x[k] = __builtin_nontemporal_load(v4 + u + k * 256);
+            #pragma unroll
+            for (int k = 0; k < SQ_RUN; ++k) add(x[k]);
+        } else
+            for (int k = 0; k < SQ_RUN; ++k)
+                if (u + k * 256 < n4) add(v4[u + k * 256]);
     }
     if (blockIdx.x == 0 && threadIdx.x < (u32)(n - 4 * n4)) {
-        float x = v[4 * n4 + threadIdx.x];
+        const float x = v[4 * n4 + threadIdx.x];
         dsum += (double)(x * x);
     }
-    dsum = wave_sum_f64(dsum);
-    if (lane_id() == 0) wsum[threadIdx.x / WAVE] = dsum;
+    return wave_sum_f64(dsum);
+}
+
+// The sum of squares to the host mailbox: the launch's last block adds the blocks' sums up.
+__global__ __launch_bounds__(256) void sumsq_vec(const float* __restrict__ v, u64 n, u64* partials, u32 n_max, double* __restrict__ mailbox) {
+    __shared__ double wsum[4];
+    const u32 tag = partials_tag(partials);
+    const double w = vec_sumsq(v, n);
+    if (lane_id() == 0) wsum[threadIdx.x / WAVE] = w;
+    __syncthreads();
+    if (threadIdx.x == 0) tell_partial(partials, blockIdx.x, tag, (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]));
+    if (blockIdx.x != gridDim.x - 1) return;
+    __syncthreads();
+    const double total = fold_partials(partials, gridDim.x, tag, n_max, wsum);
+    if (threadIdx.x == 0) mailbox[0] = total;
+}
+
+// The same in two launches, for calls that may overlap: sums per block, and their sum in the order of fold_partials.
+__global__ __launch_bounds__(256) void sumsq_blocks(const float* __restrict__ v, u64 n, double* __restrict__ partials) {
+    __shared__ double wsum[4];
+    const double w = vec_sumsq(v, n);
+    if (lane_id() == 0) wsum[threadIdx.x / WAVE] = w;
     __syncthreads();
     if (threadIdx.x == 0) partials[blockIdx.x] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
 }
-
-// Fixed-order sum of the per-block partials; the result goes to the host mailbox.
-__global__ __launch_bounds__(256) void reduce_partials(const double* __restrict__ partials, u32 n, double* __restrict__ mailbox) {
+__global__ __launch_bounds__(256) void reduce_partials(const double* __restrict__ partials, u32 n, double* __restrict__ out) {
     __shared__ double wsum[4];
     double s = 0.0;
     for (u32 i = threadIdx.x; i < n; i += 256) s += partials[i];
     s = wave_sum_f64(s);
     if (lane_id() == 0) wsum[threadIdx.x / WAVE] = s;
     __syncthreads();
-    if (threadIdx.x == 0) mailbox[0] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+    if (threadIdx.x == 0) out[0] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+}
+
+// Blocks of a sum of squares over n floats: a rule of the size alone, so that all entry points add in the same order.
+static u32 sumsq_grid(u32 cus, u64 n) {
+    const u64 runs = (n / 4 + SQ_RUN * 256 - 1) / (SQ_RUN * 256), most = (u64)cus * SQ_BLOCKS_PER_CU;
+    return (u32)(runs == 0 ? 1 : runs < most ? runs : most);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1797,8 +1881,7 @@ struct dblp_ctx {
     double search_fraction; // share of the free memory the search may hold
     double search_seconds;  // its time limit
     int fold;               // W is a power of two: the gather stores sum / W
-    int norm_in_mailbox;    // the last finalize left the sum of squares in the host mailbox
-    int counters_in_mailbox; // ... and the round's counters (until the next batch or round)
+    int counters_in_mailbox; // the last finalize left the round's counters in the host mailbox (until the next batch or round)
     int mailbox_seen;       // the stream has been synchronised since that finalize
     int acc_policy;         // DBLP_ACC_*
     int last_pick;          // copy the last batch wrote new spans to
@@ -1809,7 +1892,8 @@ struct dblp_ctx {
     hipEvent_t cls_ev[2];
     int probe_block_pair;   // probe: a block per (worker, bucket) pair
     u32 probe_no;           // probes made: what their words in d_totals are told apart by
-    u32* d_need; u64* d_totals; double* d_partials;   // probe: list length per pair, and per block of pairs
+    u32* d_need; u64* d_totals;   // list length per pair, and per block of pairs
+    u64* d_partials; u32 max_partials;    // sums of squares per block, told to the launch's last block
     u32* d_block_tallies;   // [IDX_BLOCKS_PER_CU * n_cus][5], written by index_arrivals
     u64* d_accept_rows;     // [ACCEPT_ROWS] accepted packets per gather block
     u32 rows_used;          // largest gather grid launched in the open round
@@ -1819,7 +1903,6 @@ struct dblp_ctx {
     u64* d_mailbox;         // device address of h_mailbox
     // host copies of the geometry
     u32* h_first_seq; u64* h_b_off; u64* h_b_cnt;
-    u32 n_partials;         // blocks of the last finalize / sumsq launch
     // protocol state
     int round_open; int finalized; uint16_t round;
     double prev_norm; int have_prev;
@@ -1945,7 +2028,7 @@ static int set_accumulator_copies(dblp_ctx* c, int copies, int place) {
     if (hipStreamSynchronize(c->stream) != hipSuccess) return fail(c, DBLP_EHIP, "accumulator_copies: synchronize");
     for (int i = 0; i < 2; ++i) { if (c->acc_alloc[i]) (void)hipFree(c->acc_alloc[i]); c->acc_alloc[i] = nullptr; }
     c->n_acc = 1; c->acc_distinct = 0; c->place_ms[0] = c->place_ms[1] = 0.f; c->place_steps = 0; c->place_seconds = 0.0;
-    c->n_picked = 0; c->last_pick = 0; c->round_open = 0; c->finalized = 0; c->norm_in_mailbox = 0; c->counters_in_mailbox = 0;
+    c->n_picked = 0; c->last_pick = 0; c->round_open = 0; c->finalized = 0; c->counters_in_mailbox = 0;
     const size_t bytes = (c->N * sizeof(float) + 255) / 256 * 256;     // the scratch area starts aligned
     const size_t scratch = copies == 2 ? CLS_SCRATCH_BYTES : 0;
     if (hipMalloc(&c->acc_alloc[0], bytes + scratch) != hipSuccess) { (void)hipGetLastError(); return fail(c, DBLP_ENOMEM, "accumulator"); }
@@ -2198,7 +2281,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     if ((u64)c->n_cus * 16 > ACCEPT_ROWS) c->n_cus = ACCEPT_ROWS / 16;   // grids are sized n_cus x (<= 16) blocks
 
     const u64 pairs = (u64)g.W * B;
-    const u32 max_partials = (u32)c->n_cus * FIN_BLOCKS_PER_CU;
+    c->max_partials = (u32)c->n_cus * FIN_BLOCKS_PER_CU;
     u32 longest = 0;        // packets of the longest bucket
     for (u32 b = 0; b < B; ++b) longest = c->h_first_seq[b + 1] - c->h_first_seq[b] > longest ? c->h_first_seq[b + 1] - c->h_first_seq[b] : longest;
     c->probe_block_pair = pairs <= 8u * (u32)c->n_cus && longest > WAVE * WAVE * PROBE_UNROLL;
@@ -2212,7 +2295,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     ok = ok && hipMalloc(&c->d_counters, C_COUNT * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_need, pairs * sizeof(u32)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_totals, probe_blocks(c, pairs) * sizeof(u64)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_partials, max_partials * sizeof(double)) == hipSuccess;
+    ok = ok && hipMalloc(&c->d_partials, PARTIALS_WORDS(c->max_partials) * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_accept_rows, 2 * ACCEPT_ROWS * sizeof(u64)) == hipSuccess;   // + the sum-of-squares rows
     ok = ok && hipMalloc(&c->d_block_tallies, (size_t)c->n_cus * IDX_BLOCKS_PER_CU * 5 * sizeof(u32)) == hipSuccess;
     ok = ok && hipHostMalloc((void**)&c->h_mailbox, 16 * sizeof(u64), hipHostMallocMapped) == hipSuccess;
@@ -2252,6 +2335,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     hipLaunchKernelGGL(reset_counters, dim3(1), dim3(64), 0, c->stream, c->d_counters);
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (probe_blocks(c, pairs) + 255) / 256, 16)), dim3(256), 0, c->stream,
                        c->d_totals, probe_blocks(c, pairs), 0ull);
+    hipLaunchKernelGGL(fill_u64, dim3(8), dim3(256), 0, c->stream, c->d_partials, (u64)PARTIALS_WORDS(c->max_partials), 0ull);
     hipLaunchKernelGGL(fill_u64, dim3(32), dim3(256), 0, c->stream, c->d_accept_rows, (u64)(2 * ACCEPT_ROWS), 0ull);
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (n_pkts + 16 + 2047) / 2048, 16)), dim3(256), 0, c->stream,
                        (u64*)c->d_home, (u64)((n_pkts + 7) / 8 + 1), 0ull);
@@ -2323,7 +2407,7 @@ extern "C" int dblp_begin_round(dblp_ctx* c, uint16_t round) {
     hipLaunchKernelGGL(reset_round, dim3(grid_for(c, (n + 2 * ACCEPT_ROWS + 255) / 256, 16)), dim3(256), 0, c->stream,
                        c->d_bitmap, n, c->d_accept_rows, (u64)(2 * ACCEPT_ROWS), c->d_counters);
     LAUNCH_CHECK(c, "begin_round");
-    c->round = round; c->round_open = 1; c->finalized = 0; c->norm_in_mailbox = 0; c->counters_in_mailbox = 0;
+    c->round = round; c->round_open = 1; c->finalized = 0; c->counters_in_mailbox = 0;
     c->rows_used = 0;
     return DBLP_OK;
 }
@@ -2538,7 +2622,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         }
     }
     LAUNCH_CHECK(c, "apply_arrivals");
-    c->finalized = 0; c->norm_in_mailbox = 0; c->counters_in_mailbox = 0;
+    c->finalized = 0; c->counters_in_mailbox = 0;
     return DBLP_OK;
 }
 
@@ -2626,18 +2710,16 @@ extern "C" int dblp_finalize(dblp_ctx* c, int compensation, float* d_out) {
     {
         ProfScope ps(c, DBLP_K_FINALIZE);
         const size_t table = ((size_t)g.B + 1) * sizeof(u32);
-        void (*kern)(Geo, const u64*, const float*, const float*, uint8_t*, float*, int, float, int, u32, u32, double*, u32,
+        void (*kern)(Geo, const u64*, const float*, const float*, uint8_t*, float*, int, float, int, u32, u32, u64*, u32, u32,
                      const double*, const u64*, u32, u64*, u64*) = table <= IDX_TABLE_LDS_MAX ? finalize_pass<true> : finalize_pass<false>;
         hipLaunchKernelGGL(kern, dim3(grid), dim3(256), table <= IDX_TABLE_LDS_MAX ? table : 0, c->stream, g, c->d_bitmap,
                            (const float*)c->d_acc[0], (const float*)c->d_acc[1], c->d_home, out, c->fold ? 0 : 1, (float)g.W,
-                           in_place ? 1 : 0, grp_log2, n_piece, c->d_partials, work, (const double*)c->d_sumsq_rows, (const u64*)c->d_accept_rows,
+                           in_place ? 1 : 0, grp_log2, n_piece, c->d_partials, c->max_partials, work, (const double*)c->d_sumsq_rows, (const u64*)c->d_accept_rows,
                            c->rows_used, c->d_counters, c->d_mailbox);
     }
     LAUNCH_CHECK(c, "finalize");
     c->result_in_place = in_place ? 1 : 0;
-    c->n_partials = work;
     c->finalized = 1;
-    c->norm_in_mailbox = c->fold;
     c->counters_in_mailbox = 1;     // valid on the host once the stream has been synchronised (mailbox_seen)
     c->mailbox_seen = 0;
     return DBLP_OK;
@@ -2649,17 +2731,12 @@ extern "C" int dblp_phase_signal(dblp_ctx* c, const float* d_vec, double* h_norm
     HIP_TRY(c, hipSetDevice(c->device));
     if (d_vec) {
         if (((uintptr_t)d_vec & 15) != 0) return fail(c, DBLP_EINVAL, "phase_signal: d_vec must be 16-byte aligned");
-        const u32 n_partials = grid_for(c, (c->N / 4 + 255) / 256, FIN_BLOCKS_PER_CU);
-        hipLaunchKernelGGL(sumsq_vec, dim3(n_partials), dim3(256), 0, c->stream, d_vec, (u64)c->N, c->d_partials);
-        hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(256), 0, c->stream, c->d_partials, n_partials,
+        hipLaunchKernelGGL(sumsq_vec, dim3(sumsq_grid((u32)c->n_cus, c->N)), dim3(256), 0, c->stream, d_vec, (u64)c->N, c->d_partials, c->max_partials,
                            (double*)(c->d_mailbox + 1));
-        c->finalized = 0;   // neither the partials nor the mailbox belong to a finalize any more
-        c->norm_in_mailbox = 0;
+        c->finalized = 0;   // the mailbox does not belong to a finalize any more
+       
     } else {
         if (!c->finalized) return fail(c, DBLP_ESTATE, "phase_signal without a finalize in this round");
-        if (!c->norm_in_mailbox)     // W not a power of two: the finalize pass left per-block partial sums
-            hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(256), 0, c->stream, c->d_partials, c->n_partials,
-                               (double*)(c->d_mailbox + 1));
     }
     LAUNCH_CHECK(c, "phase_signal");
     HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -2712,12 +2789,10 @@ extern "C" int dblp_sumsq_static(int device, void* stream, const float* d_vec, u
         static_partials_ptr[device] = p;
     }
     double* partials = static_partials_ptr[device];
-    u64 blocks = (n_elems / 4 + 255) / 256;     // the grid rule of dblp_phase_signal, so the two agree to the bit
-    const u64 cap = (u64)static_cus[device] * FIN_BLOCKS_PER_CU < STATIC_PARTIALS ? (u64)static_cus[device] * FIN_BLOCKS_PER_CU : STATIC_PARTIALS;
-    if (blocks > cap) blocks = cap;
-    if (blocks == 0) blocks = 1;
-    hipLaunchKernelGGL(sumsq_vec, dim3((u32)blocks), dim3(256), 0, (hipStream_t)stream, d_vec, (u64)n_elems, partials);
-    hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(256), 0, (hipStream_t)stream, (const double*)partials, (u32)blocks, d_sumsq);
+    u32 blocks = sumsq_grid((u32)static_cus[device], n_elems);      // the grid rule of dblp_phase_signal, so the two agree to the bit
+    if (blocks > STATIC_PARTIALS) blocks = STATIC_PARTIALS;
+    hipLaunchKernelGGL(sumsq_blocks, dim3(blocks), dim3(256), 0, (hipStream_t)stream, d_vec, (u64)n_elems, partials);
+    hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(256), 0, (hipStream_t)stream, (const double*)partials, blocks, d_sumsq);
     e = hipGetLastError();
     if (e != hipSuccess) { snprintf(static_err, sizeof static_err, "sumsq_static: launch: %s", hipGetErrorString(e)); return DBLP_EHIP; }
     static_err[0] = 0;
