@@ -2155,10 +2155,14 @@ static u64 probe_blocks(const dblp_ctx* c, u64 pairs) {
     return (pairs + per - 1) / per;
 }
 
+// The instance for `np` KB of a packet per step.  4 KB of loads in flight per wave, 64 KB per CU, are enough; twice as
+// many only spread the DRAM accesses over more open rows.  us of a pass with 8 KB, 4 KB: 32 workers x 60 M in packets of 1000
+// floats 1530, 1461; 8 x 60 M of 4097 490, 465; 32 x 30 M of 16374 795, 746; 2 x 150 M of 366 464, 446; 8 x 124 M of 366
+// 989, 992; 16 x 355 M of 1024 4455, 4458.  For packets of one KB, which end with every step, more workers in a step are
+// worth more (8 x 60 M of 128: G 4 693, G 2 772).
 template <u32 LEAD>
 static burst_fn burst_kernel(u32 np) {
-    return np == 1 ? gather_burst<1, 4, LEAD> : np == 2 ? gather_burst<2, 4, LEAD> : np == 3 ? gather_burst<3, 2, LEAD>
-         : np == 4 || !LEAD ? gather_burst<4, 2, LEAD> : gather_burst<5, 2, 2>;
+    return np == 1 ? gather_burst<1, 4, LEAD> : np == 2 ? gather_burst<2, 2, LEAD> : np == 3 ? gather_burst<3, 1, LEAD> : gather_burst<4, 1, LEAD>;
 }
 
 // Units of 16 bytes from the packet's start (LEAD 2), or from the payload's (LEAD 0) where that takes one
@@ -2204,7 +2208,7 @@ static BurstPlan burst_plan(const Geo& g, u32 cus) {
     const u64 fill = (u64)(step == 8 ? 11u : 2u) * cus;
     b.min_seq = (u32)(least > fill ? (least < NONE32 ? least : NONE32) : fill);
     if (b.min_seq > g.n_pkts) return b;
-    b.n_piece = n_pass <= 5 ? 1 : (n_pass + 3) / 4;
+    b.n_piece = (n_pass + 3) / 4;                       // five passes are two pieces (16 x 100 M of 1200 floats: 1342 us as one, 1317 as two)
     const u32 np = (n_pass + b.n_piece - 1) / b.n_piece;
     b.n_piece = (n_pass + np - 1) / np;
     b.r_max = r; b.r_step = step;
