@@ -320,9 +320,6 @@ __global__ __launch_bounds__(256) void packetize_list_kernel(Geo g, GradPtrs gra
 // (LDS) and written to the block's row of block_tallies; fold_index_tallies adds the rows up.
 // No global atomics on shared counters: atomics of many waves (or even of a few thousand
 // blocks) on one address serialise in L2 at about 12 ns each.
-#ifndef IDX_UNROLL
-#define IDX_UNROLL 1     // arrivals in flight per thread of the index kernel
-#endif
 //
 // TABLE_IN_LDS: the block first copies the bucket boundaries (first_seq, B + 1 words of dynamic
 // shared memory) into LDS, so the ten dependent steps of the bucket search stay inside the CU.
@@ -338,63 +335,51 @@ __global__ __launch_bounds__(256) void index_arrivals(Geo g, const uint8_t* __re
                                                       u32* __restrict__ block_tallies) {
     __shared__ u32 sh[4][5];    // per wave: stale, invalid, candidates, lowest seq, highest seq + 1
     extern __shared__ u32 fs_lds[];
+    u32 n_stale = 0, n_inv = 0, n_cand = 0;
+    u32 seq_lo = 0xFFFFFFFFu, seq_hi = 0;
+    const u64 stride = (u64)gridDim.x * blockDim.x;
+    // Arrival k: its slot, worker and header.  live: neither lost nor outside the buffer.
+    u64 slot = 0;
+    uint2 hdr = make_uint2(0u, 0u);
+    u32 w = 0;
+    bool live = false;
+    auto fetch = [&](u64 k) {
+        live = k < n_arrivals;
+        if (!live) return;
+        if (FROM_QUEUE) {
+            const u64 e = queue[k];
+            slot = e & 0xFFFFFFFFull;
+            w = (u32)(e >> 32);             // bits 48..63 must be zero: w >= W below catches them
+        } else slot = order ? (u64)order[k] : k;
+        if (slot >= n_slots) { ++n_inv; live = false; return; }
+        // lost packets are never looked at
+        if (!FROM_QUEUE && mask && !((mask[slot >> 6] >> (slot & 63)) & 1ull)) { live = false; return; }
+        hdr = *(const uint2*)(packets + slot * g.stride);
+        if (!FROM_QUEUE) w = src_worker[slot];
+    };
+    // The first arrival is on its way while the table is: a short batch is one chain of loads (4 x 1 M elements in
+    // 1040-byte packets 4.0, 3.7 us).
+    u64 k = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+    fetch(k);
     const u32* fs = g.first_seq;
     if (TABLE_IN_LDS) {
         for (u32 i = threadIdx.x; i <= g.B; i += blockDim.x) fs_lds[i] = g.first_seq[i];
         __syncthreads();
         fs = fs_lds;
     }
-    u32 n_stale = 0, n_inv = 0, n_cand = 0;
-    u32 seq_lo = 0xFFFFFFFFu, seq_hi = 0;
-    const u64 stride = (u64)gridDim.x * blockDim.x;
-    // IDX_UNROLL arrivals per thread and trip: the loads of one stage (order, then mask word,
-    // header and worker) are issued for all of them before the first is used.
-    for (u64 k0 = (u64)blockIdx.x * blockDim.x + threadIdx.x; k0 < n_arrivals; k0 += IDX_UNROLL * stride) {
-        u64 slot[IDX_UNROLL];
-        bool live[IDX_UNROLL];
-        uint2 hdr[IDX_UNROLL];
-        u32 w[IDX_UNROLL];
-#pragma unroll
-        for (int j = 0; j < IDX_UNROLL; ++j) {
-            const u64 k = k0 + j * stride;
-            live[j] = k < n_arrivals;
-            if (FROM_QUEUE) {
-                const u64 e = live[j] ? queue[k] : 0;
-                slot[j] = e & 0xFFFFFFFFull;
-                w[j] = (u32)(e >> 32);      // bits 48..63 must be zero: w >= W below catches them
-            } else {
-                slot[j] = live[j] ? (order ? (u64)order[k] : k) : 0;
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < IDX_UNROLL; ++j) {
-            if (live[j] && slot[j] >= n_slots) { ++n_inv; live[j] = false; }
-            // lost packets are never looked at
-            if (!FROM_QUEUE && live[j] && mask && !((mask[slot[j] >> 6] >> (slot[j] & 63)) & 1ull)) live[j] = false;
-        }
-#pragma unroll
-        for (int j = 0; j < IDX_UNROLL; ++j) {
-            if (live[j]) {
-                hdr[j] = *(const uint2*)(packets + slot[j] * g.stride);
-                if (!FROM_QUEUE) w[j] = src_worker[slot[j]];
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < IDX_UNROLL; ++j) {
-            if (!live[j]) continue;
-            const u64 k = k0 + j * stride;
-            const u32 seq = hdr[j].x, round = hdr[j].y & 0xFFFFu, len = hdr[j].y >> 16;
-            if (round != cur_round) { ++n_stale; continue; }
-            if (w[j] >= g.W || seq >= g.n_pkts) { ++n_inv; continue; }
-            const u32 b = find_bucket(g, fs, seq);
-            u32 want = g.P;         // every packet of a bucket but its last one is full
-            if (seq + 1 == fs[b + 1]) { u64 elem; packet_span(g, seq, b, &elem, &want); }
-            if (len != want) { ++n_inv; continue; }
-            ++n_cand;
-            atomicMin(&pending[(u64)w[j] * g.n_pkts + seq], (k << 32) | slot[j]);
-            seq_lo = seq < seq_lo ? seq : seq_lo;
-            seq_hi = seq + 1 > seq_hi ? seq + 1 : seq_hi;
-        }
+    for (; k < n_arrivals; k += stride, fetch(k)) {
+        if (!live) continue;
+        const u32 seq = hdr.x, round = hdr.y & 0xFFFFu, len = hdr.y >> 16;
+        if (round != cur_round) { ++n_stale; continue; }
+        if (w >= g.W || seq >= g.n_pkts) { ++n_inv; continue; }
+        const u32 b = find_bucket(g, fs, seq);
+        u32 want = g.P;         // every packet of a bucket but its last one is full
+        if (seq + 1 == fs[b + 1]) { u64 elem; packet_span(g, seq, b, &elem, &want); }
+        if (len != want) { ++n_inv; continue; }
+        ++n_cand;
+        atomicMin(&pending[(u64)w * g.n_pkts + seq], (k << 32) | slot);
+        seq_lo = seq < seq_lo ? seq : seq_lo;
+        seq_hi = seq + 1 > seq_hi ? seq + 1 : seq_hi;
     }
     // loops above have lane-dependent trip counts; all 64 lanes are back here
     n_stale = wave_reduce<OpAdd>(n_stale); n_inv = wave_reduce<OpAdd>(n_inv);
@@ -899,6 +884,17 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
     }
 }
 
+// A batch of at least one arrival per two (worker, seq) pairs of the round is taken to touch all of it: its gather need not
+// read the index pass's tallies, a load and two barriers, before it starts (4 x 1 M elements in 1040-byte packets 10.8,
+// 8.1 us; 8 x 25.6 M in 1472-byte ones, in bursts, 156.7, 153.9).  What it looks through for nothing is 8 bytes of the
+// index for each packet that it gathers, at most.
+#define WHOLE_DIV 2
+__device__ __forceinline__ BatchInfo whole_round(const Geo& g) {
+    BatchInfo bi;
+    bi.lo = 0; bi.hi = g.n_pkts; bi.cand = (u64)g.n_pkts * g.W;
+    return bi;
+}
+
 // DENSE: the host knows that the batch is dense; otherwise the index pass's tallies decide.
 template <int NP, int G, int D, int NW, u32 LEAD, bool DENSE>
 __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void gather_stream(
@@ -906,7 +902,7 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
     const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters,
     u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
-    GatherShape dense, GatherShape sparse, u32 cus, u32 heavy, u32 table_at, u32 burst_seq, u32* __restrict__ told) {
+    GatherShape dense, GatherShape sparse, u32 cus, u32 heavy, u32 table_at, u32 burst_seq, u32 whole, u32* __restrict__ told) {
     extern __shared__ u32 sh_dyn[];                 // per wave: slots [W rounded up][sub + 1]; then the bucket table (table_at words in, 0: not there)
     __shared__ u32 sh_tally[NW * 5];
     const u32* fs = g.first_seq;
@@ -916,7 +912,13 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
         fs = tab;
     }
     // block 0 books the index pass's tallies; the barriers in there cover the table too
-    const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0 && !burst_seq, sh_tally);
+    BatchInfo bi;
+    if (DENSE && whole && blockIdx.x) bi = whole_round(g);
+    else {
+        bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0 && !burst_seq, sh_tally);
+        if (DENSE && whole) bi = whole_round(g);
+    }
+    if (DENSE && whole) __syncthreads();
     const bool is_sparse = !DENSE && batch_is_sparse(bi, g.W);
     if (!DENSE && told && blockIdx.x == 0 && threadIdx.x == 0) *told = is_sparse;    // for the trace group of the launch
     if (bi.hi == 0) return;                         // no candidate in this batch (uniform over the grid)
@@ -974,7 +976,7 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
     const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters,
     u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
-    u32 r_max, u32 r_step, u32 n_piece, u32 table_at, u32 image_at, u32 min_seq, u32 through_seq) {
+    u32 r_max, u32 r_step, u32 n_piece, u32 table_at, u32 image_at, u32 min_seq, u32 through_seq, u32 whole) {
     extern __shared__ __attribute__((aligned(16))) u32 sh_dyn[];
     __shared__ u32 sh_tally[BURST_WAVES * 5];
     __shared__ u32 sh_new[3][BURST_MAX / 32], sh_old[3][BURST_MAX / 32];     // by packet of the group: new copies; delivered before
@@ -993,7 +995,11 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
         fs = tab;
     }
     if (tid < 3 * (BURST_MAX / 32)) sh_new[0][tid] = sh_old[0][tid] = 0;
-    const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0, sh_tally);
+    BatchInfo bi = whole_round(g);
+    if (!whole || blockIdx.x == 0) {
+        const BatchInfo found = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0, sh_tally);
+        if (!whole) bi = found;
+    } else __syncthreads();
     // A batch that is none of this kernel's is left to the gather_stream launch that follows.
     if (bi.hi == 0 || (min_seq && (batch_is_sparse(bi, g.W) || bi.hi - bi.lo < min_seq))) return;
     // Groups of equal size but for one step: with all groups as long as the longest, the last turn of 4 x 61 M in 64
@@ -1636,16 +1642,30 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
         }
         return;
     }
+    const u32 wave = blockIdx.x * (blockDim.x / WAVE) + wave_in_block;
+    const u32 n_waves = n_work_blocks * (blockDim.x / WAVE);
+    const u32 grp = 1u << grp_log2;
+    const u64 n_items = (((u64)g.n_pkts + grp - 1) >> grp_log2) * n_piece;
+    // An item's workers' bitmap words (lane w loads worker w's: one load instruction for the wave, W <= 64) and
+    // the copies of its packets (meaningful where they arrived).  The first item's are on their way while the table is.
+    u32 gi = 0, piece = 0, seq0 = 0, n_t = 0, hm = 0;
+    u64 mine = 0;
+    auto fetch = [&](u64 item) {
+        if (item >= n_items) return;
+        gi = n_piece == 1 ? (u32)item : (u32)(item / n_piece);
+        piece = (u32)(item - (u64)gi * n_piece);
+        seq0 = gi << grp_log2;
+        n_t = g.n_pkts - seq0 < grp ? g.n_pkts - seq0 : grp;
+        mine = lane < g.W ? bitmap[(u64)lane * g.words_pw + (seq0 >> 6)] : 0ull;
+        hm = lane < n_t ? home[seq0 + lane] : 0;
+    };
+    fetch(wave);
     const u32* fs = g.first_seq;
     if (TABLE_IN_LDS) {
         for (u32 i = threadIdx.x; i <= g.B; i += blockDim.x) fs_lds[i] = g.first_seq[i];
         __syncthreads();
         fs = fs_lds;
     }
-    const u32 wave = blockIdx.x * (blockDim.x / WAVE) + wave_in_block;
-    const u32 n_waves = n_work_blocks * (blockDim.x / WAVE);
-    const u32 grp = 1u << grp_log2;
-    const u64 n_items = (((u64)g.n_pkts + grp - 1) >> grp_log2) * n_piece;
     const bool skip_same = scale_mode == 0;     // a span that already sits in `out` needs no copy
     double dsum = 0.0;
 
@@ -1684,13 +1704,7 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
         for (; c < c1; c += WAVE) o[c] = scaled(s[c]);
     };
 
-    for (u64 item = wave; item < n_items; item += n_waves) {
-        const u32 gi = n_piece == 1 ? (u32)item : (u32)(item / n_piece), piece = (u32)(item - (u64)gi * n_piece);
-        const u32 seq0 = gi << grp_log2, n_t = g.n_pkts - seq0 < grp ? g.n_pkts - seq0 : grp;
-        // OR of the workers' bitmap words: lane w loads worker w's word (one load instruction
-        // for the wave, W <= 64), the OR runs across the lanes
-        const u64 mine = lane < g.W ? bitmap[(u64)lane * g.words_pw + (seq0 >> 6)] : 0ull;
-        const u32 hm = lane < n_t ? home[seq0 + lane] : 0;       // copy of packet seq0 + lane (meaningful where it arrived)
+    for (u64 item = wave; item < n_items; item += n_waves, fetch(item)) {
         const u64 full = NONE64 >> (64 - n_t);
         const u64 any = uniform(((((u64)wave_reduce<OpOr>((u32)(mine >> 32)) << 32) | wave_reduce<OpOr>((u32)mine)) >> (seq0 & 63)) & full);
         const u64 second = (u64)__ballot(hm & 1u);
@@ -1855,7 +1869,7 @@ __global__ __launch_bounds__(256) void classify_rw(const uint8_t* __restrict__ s
 // ------------------------------------------------------------------------------------------
 // What the context's gather_burst launches are given (burst_plan); fn null: none are made.
 typedef void (*burst_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, u64*, double*, float,
-                         u32, u32, u32, u32, u32, u32, u32);
+                         u32, u32, u32, u32, u32, u32, u32, u32);
 struct BurstPlan { burst_fn fn; u32 r_max, r_step, n_piece, table_at, image_at, min_seq, through_seq; size_t lds; };
 
 struct dblp_ctx {
@@ -2497,7 +2511,7 @@ extern "C" int dblp_packetize_list(dblp_ctx* c, uint16_t round, const float* con
 }
 
 typedef void (*gather_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, u64*, double*, float,
-                          GatherShape, GatherShape, u32, u32, u32, u32, u32*);
+                          GatherShape, GatherShape, u32, u32, u32, u32, u32, u32*);
 
 // The instance for `np` KB of a packet per step; few: one to three workers.
 template <bool DENSE, u32 LEAD>
@@ -2556,6 +2570,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         // 0.4 us, and cost a round of 32 x 60 M elements in 129 steps 11.7 against 4.7 ms).
         const u64 pairs = (u64)g.W * g.n_pkts;
         const bool is_dense = n_arrivals * SPARSE_DIV >= pairs, small = n_arrivals * SPARSE_DIV * 8 < pairs;
+        const u32 whole = n_arrivals * WHOLE_DIV >= pairs;
         const u32 nw = small && g.stride < 8192 ? GS_WAVES      // 16 waves for a handful of 4 KB packets: 29 against 22 us
                                                 : block_waves(c);
         // Dense.  Packets of up to 5 KB are one piece, longer ones are cut evenly into pieces of 3 or 4 KB; in
@@ -2616,13 +2631,13 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
             hipLaunchKernelGGL(burst.fn, dim3(c->n_cus), dim3(BURST_WAVES * WAVE), burst.lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap,
                                c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
                                c->d_accept_rows, c->d_sumsq_rows, inv_w, burst.r_max, burst.r_step, burst.n_piece, burst.table_at, burst.image_at,
-                               is_dense ? 0u : burst.min_seq, burst.through_seq);
+                               is_dense ? 0u : burst.min_seq, burst.through_seq, whole);
         }
         if (!in_bursts || !is_dense) {
             if (grid > c->rows_used) c->rows_used = grid;
             hipLaunchKernelGGL(kern, dim3(grid), dim3(nw * WAVE), lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap,
                                c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
-                               c->d_accept_rows, c->d_sumsq_rows, inv_w, dense, sparse, (u32)c->n_cus, heavy, table_at, in_bursts ? burst.min_seq : 0u, ps.d_told());
+                               c->d_accept_rows, c->d_sumsq_rows, inv_w, dense, sparse, (u32)c->n_cus, heavy, table_at, in_bursts ? burst.min_seq : 0u, whole, ps.d_told());
         }
     }
     LAUNCH_CHECK(c, "apply_arrivals");
