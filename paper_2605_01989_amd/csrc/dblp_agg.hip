@@ -19,9 +19,8 @@
 // address space (classify_rw measures which copy a packet buffer should be paired with); a
 // per-packet byte map records where each span lives.
 //
-// The probe (Sec. "Dynamically Changing Loss Tolerance"): loss_count (popcount of bitmap words +
-// DPP wave reduction, list length per block of (worker, bucket) pairs) and emit_retx (ordered compaction
-// from the sum of the lengths before it on).  The mean of Alg. "Server" is formed as the payloads are summed when
+// The probe (Sec. "Dynamically Changing Loss Tolerance"): probe_once (popcount of bitmap words + DPP wave reduction,
+// list lengths that the blocks tell each other, ordered compaction).  The mean of Alg. "Server" is formed as the payloads are summed when
 // W is a power of two (the division is exact), and the gather kernels keep the sum of squares of
 // what they store, so finalize_pass only writes zeros where nothing arrived (and moves or copies
 // spans where the result is wanted elsewhere); for other W it divides and squares itself.
@@ -1266,13 +1265,11 @@ __device__ __forceinline__ u64 range_mask(u32 wd, u32 s0, u32 s1) {
     return m;
 }
 
-// BLOCK_PAIR (few pairs, buckets of more words than a wave keeps in flight): a block takes a pair, each of
-// its waves a quarter of the words (148 x 8, the longest of 105 k packets: 13 + 5 + 5 us with three launches, 6.5 + 6.4 now).  Otherwise
-// a wave takes `ppw` consecutive (worker, bucket) pairs, one per lane (ppw = 1 while there are fewer pairs
-// than waves, up to 64).  A pair of at most PROBE_SMALL bitmap words is its lane's own work, a larger one
-// the whole wave's, PROBE_UNROLL words per lane in flight.  Latency bounds both passes: with one wave per
-// pair, and one block that added the list lengths up between them, a probe over 120 k buckets x 16 workers
-// took 250 us and now takes 11, one of 161 x 8 took 14 and now takes 9.
+// BLOCK_PAIR (few pairs, buckets of more words than a wave keeps in flight): a block takes a pair, each of its waves a
+// quarter of the words (148 x 8, the longest of 105 k packets: a pass of 13 us with a wave per pair, 6.5 so).  Otherwise
+// a wave takes `ppw` consecutive (worker, bucket) pairs, one per lane (ppw = 1 while there are fewer pairs than waves, up
+// to 64).  A pair of at most PROBE_SMALL bitmap words is its lane's own work, a larger one the whole wave's, PROBE_UNROLL
+// words per lane in flight: with one wave per pair a probe over 120 k buckets x 16 workers took 250 us, and 11 so.
 #define PROBE_SMALL 4
 #define PROBE_UNROLL 8
 struct ProbePair {
