@@ -34,8 +34,8 @@ BENCH_DRAWN_ROUNDS = 3   # retransmission rounds with a drawn loss pattern; late
 # on and by workload; anything else reports null.
 # value = measured bytes / algorithmic bytes of a first-transmission launch.
 PMC_TRAFFIC_RATIO: dict[tuple[str, str], float] = {
-    ("594bae09504d7b2602fabbdb4a71c216bcb3912f096ff9ccd980af22d39aad34", "cfg5"): 1.062,   # profiles/receiver_path_cfg5.md
-    ("594bae09504d7b2602fabbdb4a71c216bcb3912f096ff9ccd980af22d39aad34", "cfg4"): 1.033,   # profiles/receiver_path_cfg4.md
+    ("ad43e3fd9f1f78752f18a4fc423b04e5e17f0abd2ce63b63c24256cc9b73af76", "cfg5"): 1.055,   # profiles/receiver_path_cfg5.md
+    ("ad43e3fd9f1f78752f18a4fc423b04e5e17f0abd2ce63b63c24256cc9b73af76", "cfg4"): 1.031,   # profiles/receiver_path_cfg4.md
 }
 
 
@@ -539,7 +539,7 @@ def main():
     for st in warm["per_step"]:
         log(f"[bench] warmup {st['it']}: bound={st['bound_ppm']} rounds={st['rounds']}")
     from paper_2605_01989_amd import binding
-    # the timed region brackets only the launches of the dominant kernel, gather_stream, with events
+    # the timed region brackets only the launches of the dominant kernel, the dense gather, with events
     # (two event records per dense batch; its launches on retransmission batches, which are sparse,
     # are a group of their own); the per-group breakdown comes from a replay of its first steps with
     # every group bracketed
@@ -550,7 +550,7 @@ def main():
 
     fill = L.N / (L.n_pkts * L.P)
     value = accepted_total * 4 * L.P * fill / wall / 1e9
-    # dominant kernel: gather_stream, which takes the first transmissions (a retransmission
+    # dominant kernel: the dense gather (gather_burst, gather_stream on small rounds), which takes the first transmissions (a retransmission
     # batch is sparse and of another trace group unless it is dense; one that is dense adds its
     # time here and not its bytes).  Algorithmic bytes = every packet accepted from a first transmission
     # read once (header + payload + padding = stride) + the accumulator written once per iteration.
@@ -560,7 +560,7 @@ def main():
     achieved = g_bytes / (g_ms * 1e-3) / 1e9 if g_ms > 0 else 0.0
     ratio_pmc = PMC_TRAFFIC_RATIO.get((_kernel_source_hash(), w.name))
     roofline = dict(bound="hbm", achieved=round(achieved, 1), peak=HBM_PEAK_GBPS, unit="GB/s",
-                    frac=round(achieved / HBM_PEAK_GBPS, 4), kernel="gather_stream",
+                    frac=round(achieved / HBM_PEAK_GBPS, 4), kernel="gather (dense batches)",
                     launches=g_n, avg_launch_ms=round(g_ms / max(g_n, 1), 4),
                     algorithmic_bytes_per_launch=round(g_bytes / max(g_n, 1)),
                     traffic=None if ratio_pmc is None else round(ratio_pmc * g_bytes / max(g_n, 1)))
