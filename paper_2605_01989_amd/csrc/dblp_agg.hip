@@ -1392,21 +1392,24 @@ __device__ __forceinline__ u64 wave_sum_u46(u64 v) {
     return ((u64)wave_reduce<OpAdd>(hi) << 40) + ((u64)wave_reduce<OpAdd>(mid) << 20) + wave_reduce<OpAdd>(lo);
 }
 
-// The probe in one launch, for up to eight blocks per CU: each block counts its pairs and tells the others the
+// The probe in one launch, for up to seven blocks per four CUs: each block counts its pairs and tells the others the
 // length of its part of the list; a block whose part is not empty, and the last one, which tells the host the whole
 // length, then add up what the blocks before it told.  totals[j] = tag | length, in one 64-bit word that is stored
 // and loaded as a relaxed atomic at device scope, so no fence is needed (one would write back the L2 that the gather has
 // just dirtied); the tag differs from probe to probe, so nothing is cleared in between.
 //
-// The wait ends: a block tells its length before it waits for anything, and waits only for blocks of lower index.  Of
-// the blocks that have not told theirs the one of lowest index is never kept from starting by this launch, as
-// workgroups of a launch start in index order on each XCD and all before it end without it.
-//
+// The wait ends: a block tells its length before it waits for anything, and waits only for blocks of lower index, so it
+// is enough that every block of the launch gets to start.  Waiting blocks alone cannot keep one from that: a launch takes
+// a quarter of what the chip holds at a time (seven blocks per CU), and kernels run from at most four hardware queues, so
+// even four such launches, of contexts on streams of their own, are resident as a whole.  Blocks of any other kernel end by
+// themselves.  More blocks than that take two launches, below.
 // Latency bounds the probe: a second launch for the list, which it was, costs its own start and a second walk to the same
 // words.  us of the two launches, and of this one, first probe of a round: 64 x 4 pairs of 64 packets 6.7, 4.2; 161 x 8
-// of 435 packets on average 8.9, 5.6; 148 x 8 of 2300 11.7, 9.8; 292 x 16 of 1190 15.7, 13.9.
+// of 435 packets on average 8.9, 5.6.  (Where blocks are many the two launches cost little more: 148 x 8 pairs of 2300
+// packets 11.7, 9.8; 292 x 16 of 1190 15.7, 13.9.)
 #define PROBE_TAG_SHIFT 40
-#define PROBE_POLL 8
+#define PROBE_POLL 2
+#define PROBE_RESIDENT 7         // blocks (a wave on each SIMD, 72 registers) that a CU holds
 template <bool BLOCK_PAIR>
 __global__ __launch_bounds__(256) void probe_once(Geo g, const u64* __restrict__ bitmap, u32 bound_ppm, u32 ppw, u64 pairs, u32* __restrict__ missing_out,
                                                   u64* totals, u64 tag, u64* __restrict__ list, u64 capacity, u64* __restrict__ mailbox) {
@@ -1460,18 +1463,19 @@ __global__ __launch_bounds__(256) void probe_once(Geo g, const u64* __restrict__
     probe_emit<BLOCK_PAIR>(g, bitmap, p, want, base + incl - want, ppw, list, capacity, sh);
 }
 
-// More blocks than that, in three launches.  Missing packets per pair, list length it asks for (need), and the block's
-// total of those.
+// More blocks than that, in two launches or three.  Missing packets per pair, list length it asks for (need), and the
+// block's total of those.
+template <bool BLOCK_PAIR>
 __global__ __launch_bounds__(256) void loss_count(Geo g, const u64* __restrict__ bitmap, u32 bound_ppm, u32 ppw, u64 pairs,
                                                   u32* __restrict__ missing_out, u32* __restrict__ need, u64* __restrict__ totals) {
     __shared__ u64 sh[4];
     const u32 lane = lane_id(), wave = uniform(threadIdx.x / WAVE);
-    const u64 pr = ((u64)blockIdx.x * 4 + wave) * ppw + lane;
+    const u64 pr = BLOCK_PAIR ? blockIdx.x : ((u64)blockIdx.x * 4 + wave) * ppw + lane;
     const bool valid = lane < ppw && pr < pairs;
     const ProbePair p(g, pr, valid);
-    const u32 got = probe_got<false>(g, bitmap, p, valid, ppw, sh);
+    const u32 got = probe_got<BLOCK_PAIR>(g, bitmap, p, valid, ppw, sh);
     u32 want = 0;
-    if (valid) {
+    if (valid && (!BLOCK_PAIR || wave == 0)) {
         u32 miss;
         want = probe_want(p, got, bound_ppm, &miss);
         if (missing_out) missing_out[pr] = miss;
@@ -1483,8 +1487,9 @@ __global__ __launch_bounds__(256) void loss_count(Geo g, const u64* __restrict__
     if (threadIdx.x == 0) totals[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
-// Exclusive prefix of totals[0..n) in place, by one block of 1024 threads; the host is told the sum.
-__global__ __launch_bounds__(1024) void scan_totals(u64* __restrict__ totals, u32 n, u64* __restrict__ mailbox) {
+// Where blocks are many: exclusive prefix of totals[0..n) in place, by one block of 1024 threads.
+#define PROBE_SCAN_BLOCKS 4096u
+__global__ __launch_bounds__(1024) void scan_totals(u64* __restrict__ totals, u32 n) {
     __shared__ u64 part[1024];
     const u32 t = threadIdx.x;
     u64 base = 0;
@@ -1502,24 +1507,36 @@ __global__ __launch_bounds__(1024) void scan_totals(u64* __restrict__ totals, u3
         base += part[1023];
         __syncthreads();
     }
-    if (t == 0) mailbox[0] = base;
 }
 
-// The list: block j writes the entries of the pairs that block j of loss_count counted, from totals[j] on.
+// The list: block j writes the entries of the pairs that block j of loss_count counted, from the sum of the
+// totals before its own on (scanned: totals holds those sums).  The last block tells the host the length.
+template <bool BLOCK_PAIR>
 __global__ __launch_bounds__(256) void emit_retx(Geo g, const u64* __restrict__ bitmap, u32 ppw, u64 pairs, const u32* __restrict__ need,
-                                                 const u64* __restrict__ totals, u64* __restrict__ list, u64 capacity) {
-    __shared__ u64 sh_sum[4];
+                                                 const u64* __restrict__ totals, int scanned, u64* __restrict__ list, u64 capacity,
+                                                 u64* __restrict__ mailbox) {
+    __shared__ u64 sh[4], sh_sum[4];
     const u32 lane = lane_id(), wave = uniform(threadIdx.x / WAVE);
-    const u64 pr = ((u64)blockIdx.x * 4 + wave) * ppw + lane;
+    const u64 pr = BLOCK_PAIR ? blockIdx.x : ((u64)blockIdx.x * 4 + wave) * ppw + lane;
     const bool valid = lane < ppw && pr < pairs;
     const u32 want = valid ? need[pr] : 0;
+    u64 before = 0;
+    if (scanned) before = threadIdx.x == 0 ? totals[blockIdx.x] : 0;
+    else
+        for (u32 i = threadIdx.x; i < blockIdx.x; i += 256) before += totals[i];
+    before = wave_sum_u46(before);
     const u32 inc_hi = wave_scan_incl<OpAdd>(want >> 16), inc_lo = wave_scan_incl<OpAdd>(want & 0xFFFFu);
     const u64 incl = ((u64)inc_hi << 16) + inc_lo;
-    if (lane == WAVE - 1) sh_sum[wave] = incl;
+    const u64 sum = ((u64)(u32)__builtin_amdgcn_readlane((int)inc_hi, 63) << 16) + (u32)__builtin_amdgcn_readlane((int)inc_lo, 63);
+    if (lane == 0) { sh[wave] = before; sh_sum[wave] = sum; }
     __syncthreads();
-    u64 base = totals[blockIdx.x];
-    for (u32 i = 0; i < wave; ++i) base += sh_sum[i];
-    probe_emit<false>(g, bitmap, ProbePair(g, pr, valid), want, base + incl - want, ppw, list, capacity, sh_sum);
+    u64 base = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) mailbox[0] = base + (BLOCK_PAIR ? sh_sum[0] : (sh_sum[0] + sh_sum[1]) + (sh_sum[2] + sh_sum[3]));
+    if (!BLOCK_PAIR)
+        for (u32 i = 0; i < wave; ++i) base += sh_sum[i];
+    if (capacity == 0) return;
+    __syncthreads();                // sh has been read
+    probe_emit<BLOCK_PAIR>(g, bitmap, ProbePair(g, pr, valid), want, base + incl - want, ppw, list, capacity, sh);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2680,16 +2697,19 @@ extern "C" int dblp_loss_account(dblp_ctx* c, uint32_t bound_ppm, uint32_t* d_mi
     if (blocks > 0x7FFFFFFFull) return fail(c, DBLP_EINVAL, "loss_account: too many (worker, bucket) pairs");
     {
         ProfScope ps(c, DBLP_K_PROBE);
-        if (blocks <= 8u * (u32)c->n_cus) {
+        if (blocks * 4 <= (u64)PROBE_RESIDENT * c->n_cus) {
             const u64 tag = (u64)(++c->probe_no & 0xFFFFFFu) << PROBE_TAG_SHIFT;
             hipLaunchKernelGGL(c->probe_block_pair ? probe_once<true> : probe_once<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g,
                                c->d_bitmap, bound_ppm, ppw, pairs, d_missing, c->d_totals, tag, (u64*)d_retx_list, (u64)retx_capacity, c->d_mailbox);
         } else {
-            hipLaunchKernelGGL(loss_count, dim3((u32)blocks), dim3(256), 0, c->stream, g, c->d_bitmap, bound_ppm, ppw, pairs, d_missing, c->d_need, c->d_totals);
-            hipLaunchKernelGGL(scan_totals, dim3(1), dim3(1024), 0, c->stream, c->d_totals, (u32)blocks, c->d_mailbox);
-            if (retx_capacity)
-                hipLaunchKernelGGL(emit_retx, dim3((u32)blocks), dim3(256), 0, c->stream, g, c->d_bitmap, ppw, pairs, (const u32*)c->d_need,
-                                   (const u64*)c->d_totals, (u64*)d_retx_list, (u64)retx_capacity);
+            // Each block of emit_retx adds up the totals of the blocks before it (2048 of them: about a
+            // microsecond) unless they are so many that a pass in between is shorter.
+            const int scanned = blocks > PROBE_SCAN_BLOCKS ? 1 : 0;
+            hipLaunchKernelGGL(c->probe_block_pair ? loss_count<true> : loss_count<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g,
+                               c->d_bitmap, bound_ppm, ppw, pairs, d_missing, c->d_need, c->d_totals);
+            if (scanned) hipLaunchKernelGGL(scan_totals, dim3(1), dim3(1024), 0, c->stream, c->d_totals, (u32)blocks);
+            hipLaunchKernelGGL(c->probe_block_pair ? emit_retx<true> : emit_retx<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g, c->d_bitmap, ppw, pairs,
+                               (const u32*)c->d_need, (const u64*)c->d_totals, scanned, (u64*)d_retx_list, (u64)retx_capacity, c->d_mailbox);
         }
     }
     LAUNCH_CHECK(c, "loss_account");

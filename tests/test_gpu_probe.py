@@ -1,8 +1,8 @@
 """GPU: a probe's counts, list and verdict at the edges of its launches, against plain torch on the flags of what arrived.
 
-The list is written in one launch by blocks that add up each other's lengths while there are at most eight blocks per
-CU (a wave takes up to 64 pairs, so up to 524288 pairs on 256 CUs), and in three launches beyond.  All values are
-integers and compared exactly."""
+The list is written in one launch by blocks that add up each other's lengths while there are at most seven blocks per
+four CUs (1792 pairs on 256 CUs, 448 where a block takes a pair), in two launches while there are at most 4096 blocks, and
+in three beyond.  All values are integers and compared exactly."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -30,10 +30,10 @@ def _expect(alive, first, n_b, bound):
     return missing.int().flatten(), (w << 32) | seq
 
 
-# one pair; a block's remainder; as many blocks as are resident, and one pair more; two pairs a wave; 64 a wave, and one
-# pair more than fit: three launches; long buckets of which a block takes one
-CASES = [(1, [1]), (3, [5, 70, 1, 64, 65, 129]), (32, [2] * 256), (33, [2] * 249), (64, [1, 300] * 64), (64, [3, 1] * 4096),
-         (64, [1] * 8193), (5, [40_000, 3, 33_000, 1])]
+# one pair; a block's remainder; as many pairs as one launch takes, and more; one pair a wave and two; 64 a wave, and more
+# blocks than are added up without a scan; long buckets of which a block takes one, in one launch and in two
+CASES = [(1, [1]), (3, [5, 70, 1, 64, 65, 129]), (7, [1, 300] * 128), (3, [2] * 598), (32, [2] * 256), (33, [2] * 249), (64, [3, 1] * 4096),
+         (64, [1] * 8193), (64, [1] * 16400), (5, [40_000, 3, 33_000, 1]), (64, [33_000, 3, 1, 70, 500, 9, 2, 64]), (56, [33_000] + [2] * 7), (50, [33_000] + [2] * 8)]
 
 
 @pytest.mark.parametrize("W,packets", CASES)
