@@ -34,8 +34,8 @@ BENCH_DRAWN_ROUNDS = 3   # retransmission rounds with a drawn loss pattern; late
 # on and by workload; anything else reports null.
 # value = measured bytes / algorithmic bytes of a first-transmission launch.
 PMC_TRAFFIC_RATIO: dict[tuple[str, str], float] = {
-    ("ad43e3fd9f1f78752f18a4fc423b04e5e17f0abd2ce63b63c24256cc9b73af76", "cfg5"): 1.055,   # profiles/receiver_path_cfg5.md
-    ("ad43e3fd9f1f78752f18a4fc423b04e5e17f0abd2ce63b63c24256cc9b73af76", "cfg4"): 1.031,   # profiles/receiver_path_cfg4.md
+    ("1594a66d8c11f15475761f79a93ac42f1e973cbfb30ce8d7e11f5e1e4c816a0c", "cfg5"): 1.055,   # profiles/receiver_path_cfg5.md
+    ("1594a66d8c11f15475761f79a93ac42f1e973cbfb30ce8d7e11f5e1e4c816a0c", "cfg4"): 1.031,   # profiles/receiver_path_cfg4.md
 }
 
 
