@@ -1007,11 +1007,11 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
     const u32 lo = uniform((u32)bi.lo / r_step * r_step), n_seq = uniform((u32)bi.hi) - lo;
     const BurstTurns split(n_seq, gridDim.x, r_max, r_step);
     const u32 r_long = uniform(split.r_long);
-    auto size_of = [&](u32 turn) { return uniform(split.size(turn)); };
     auto first_of = [&](u32 turn) {
         const u32 at = uniform(split.first(turn, blockIdx.x));
         return at < n_seq ? lo + at : NONE32;
     };
+    auto size_of = [&](u32 turn, u32 seq0) { return uniform(split.count(turn, g.n_pkts - seq0)); };       // of the group that starts there
     const bool through = n_seq <= through_seq;
     const u32 n_chunk = (r_long + WAVE - 1) / WAVE, n_pair = W * n_chunk;        // a pair: a worker's index entries of 64 sequence numbers
     const u32* const words = (const u32*)bitmap;
@@ -1023,7 +1023,7 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
         Entry e;
         e.p = NONE64; e.bits = 0;
         const u32 w = pair / n_chunk, t = (pair - w * n_chunk) * WAVE + lane, seq = s0 + t;
-        if (pair < n_pair && t < r && seq < g.n_pkts) {
+        if (pair < n_pair && t < r) {
             e.p = pending[(u64)w * g.n_pkts + seq];
             e.bits = words[2 * (u64)w * g.words_pw + (seq >> 5)];
         }
@@ -1034,7 +1034,7 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
     auto load_ahead = [&](u32 s0, u32 r) {
         #pragma unroll
         for (int j = 0; j < BURST_AHEAD; ++j) ahead[j] = load_entry(wave + j * BURST_WAVES, s0, r);
-        home_ahead = tid < r && s0 + tid < g.n_pkts ? home[s0 + tid] : 0;
+        home_ahead = tid < r ? home[s0 + tid] : 0;
     };
 
     // A group's arrival index -> slots, bitmap, spans, in its half of the tables (par) and its flags (f).
@@ -1043,11 +1043,11 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
         auto take_entry = [&](u32 pair, const Entry& e) {
             if (pair >= n_pair) return;
             const u32 w = pair / n_chunk, c = pair - w * n_chunk, t = c * WAVE + lane, seq = seq0 + t;
-            const bool in = t < r && seq < g.n_pkts;
+            const bool in = t < r;
             const bool had = in && (e.bits >> (seq & 31)) & 1u;             // delivered by an earlier batch
             const bool fresh = in && e.p != NONE64 && !had;
             const u64 nb = __ballot(fresh), hb = __ballot(had);
-            if (t < r) slots[w * pitch + t] = fresh ? (u32)e.p : NONE32;
+            if (in) slots[w * pitch + t] = fresh ? (u32)e.p : NONE32;
             if (in && e.p != NONE64) pending[(u64)w * g.n_pkts + seq] = NONE64;         // leave the index empty
             if (nb) {
                 if (r_step == 8) {      // a group owns its bytes of the bitmap
@@ -1066,7 +1066,7 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
         #pragma unroll
         for (int j = 0; j < BURST_AHEAD; ++j) take_entry(wave + j * BURST_WAVES, ahead[j]);
         for (u32 pair = wave + BURST_AHEAD * BURST_WAVES; pair < n_pair; pair += BURST_WAVES) take_entry(pair, load_entry(pair, seq0, r));
-        if (tid < r && seq0 + tid < g.n_pkts) {
+        if (tid < r) {
             const u32 seq = seq0 + tid, b = find_bucket(g, fs, seq);
             const u64 start = (u64)(seq - fs[b]) * g.P, left = g.b_cnt[b] - start, elem = g.b_off[b] + start;
             u32* const elem_of = sh_elem + par * 2 * r_max;
@@ -1077,18 +1077,18 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
 
     u32 par = 0, f = 0;
     u32 seq0 = first_of(0);
-    if (seq0 != NONE32) { load_ahead(seq0, size_of(0)); take_group(seq0, size_of(0), 0, 0); }
+    if (seq0 != NONE32) { load_ahead(seq0, size_of(0, seq0)); take_group(seq0, size_of(0, seq0), 0, 0); }
     __syncthreads();
     for (u32 turn = 0; seq0 != NONE32; ++turn, par ^= 1, f = f == 2 ? 0 : f + 1) {
-        const u32 n_t = g.n_pkts - seq0 < size_of(turn) ? g.n_pkts - seq0 : size_of(turn);
-        const u32 seq_next = first_of(turn + 1);
+        const u32 n_t = size_of(turn, seq0), seq_next = first_of(turn + 1);
+        const u32 n_next = seq_next != NONE32 ? size_of(turn + 1, seq_next) : 0;
         const u32* const slots = sh_dyn + par * W * pitch;
         const u32* const elem_of = sh_elem + par * 2 * r_max;
         const u32* const len_of = sh_len + par * r_max;
         const u32* const is_new = sh_new[f];
         const u32* const is_old = sh_old[f];
         auto flag = [](const u32* m, u32 t) { return (m[t >> 5] >> (t & 31)) & 1u; };
-        if (seq_next != NONE32) load_ahead(seq_next, size_of(turn + 1));
+        if (seq_next != NONE32) load_ahead(seq_next, n_next);
         const u64 e0 = uniform(((u64)elem_of[1] << 32) | elem_of[0]);
         const u32 pad = (u32)e0 & 31u;                  // the image starts where its first span lies in a 128-byte line
 
@@ -1204,7 +1204,7 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
                 if (left == 0 && todo == 0) break;
                 load();
             }
-        if (seq_next != NONE32) take_group(seq_next, size_of(turn + 1), par ^ 1, f == 2 ? 0 : f + 1);
+        if (seq_next != NONE32) take_group(seq_next, n_next, par ^ 1, f == 2 ? 0 : f + 1);
         __syncthreads();
         // ---- the image goes out, run by run of spans that belong to it
         float* const out = (pick ? acc1 : acc0) + (e0 - pad);

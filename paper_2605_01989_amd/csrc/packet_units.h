@@ -46,6 +46,10 @@ struct BurstTurns {
         n_long = steps - turns * (a - 1);
     }
     constexpr uint32_t size(uint32_t turn) const { return turn < n_long ? r_long : r_long - r_step; }
+    // Numbers of a group that exist where `left` of the round are left from its first on: the last group may reach
+    // past the round, where a number need not fit 32 bits.  (Past the range it stays whole: a group owns whole bytes of
+    // the bitmap.)
+    constexpr uint32_t count(uint32_t turn, uint32_t left) const { return left < size(turn) ? left : size(turn); }
     // First number of the block's group in that turn; none (n_seq): the block has no more.
     constexpr uint32_t first(uint32_t turn, uint32_t block) const {
         const uint64_t before = (uint64_t)turn * r_long - (turn > n_long ? (uint64_t)(turn - n_long) * r_step : 0u);

@@ -71,6 +71,25 @@ int main() {
         const BurstTurns s(n, 256, 256, 8);
         if (s.first(0, 0) != 0 || s.first(s.turns, 0) != n || s.first(s.turns - 1, 0) >= n) return 1;
     }
+    // Rounds up to the largest, batches that end before the round does: a group's numbers stay inside the round, so
+    // that the last of them fits 32 bits, and but for the round's end a group is whole steps.
+    for (uint32_t pkts : {0xFFFFFFFEu, 0xFFFFFF01u, 0xFFFFFF00u, 70000u, 70001u, 9u})
+        for (uint32_t step : {1u, 8u})
+            for (uint32_t lo : {0u, pkts / 16 * 8})
+                for (uint32_t short_of : {0u, 1u, 5u, 8u}) {
+                    const uint32_t n = pkts - lo - (short_of < pkts - lo ? short_of : 0u);
+                    const BurstTurns s(n, 256, 32 * step, step);
+                    for (uint32_t k = s.turns < 3 ? 0 : s.turns - 3; k < s.turns; ++k)
+                        for (uint32_t b = 0; b < 256; ++b) {
+                            const uint32_t at = s.first(k, b);
+                            if (at >= n) continue;
+                            const uint32_t seq0 = lo + at, c = s.count(k, pkts - seq0);
+                            if (c == 0 || c > s.size(k) || (uint64_t)seq0 + c > pkts || (c != s.size(k) && (uint64_t)seq0 + c != pkts)) {
+                                fprintf(stderr, "round of %u from %u on, %u numbers: group at %u holds %u\n", pkts, lo, n, seq0, c);
+                                return 1;
+                            }
+                        }
+                }
     return 0;
 }
 """
@@ -87,7 +106,7 @@ def test_every_unit_of_every_packet_length_is_read_where_it_lies(tmp_path):
 
 
 def test_groups_of_a_burst_cover_the_range_once(tmp_path):
-    """Ranges of 1 to 200 k sequence numbers over 1, 3 and 256 blocks, groups of 1 to 256."""
+    """Ranges of 1 to 200 k sequence numbers over 1, 3 and 256 blocks, groups of 1 to 256; the ends of the largest rounds."""
     src, exe = tmp_path / "turns.cpp", tmp_path / "turns"
     src.write_text(TURNS)
     subprocess.check_call(["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2605_01989_amd", "csrc"), "-o", str(exe), str(src)])
