@@ -250,6 +250,14 @@ int dblp_apply_arrivals_queue(dblp_ctx* ctx, const void* d_packets, uint64_t n_s
 int dblp_loss_account(dblp_ctx* ctx, uint32_t bound_ppm, uint32_t* d_missing, uint64_t* d_retx_list,
                       uint64_t retx_capacity, uint64_t* h_retx_count, int* h_all_met);
 
+/* How a probe of few (worker, bucket) pairs (1792 on 256 CUs, 448 with long buckets) waits inside its launch.  Its blocks
+ * tell each other the lengths of their parts of the list, and a block looks `polls` times at most (default 16384, 10 ms
+ * or more) for those of the blocks before it.  They can fail to start for that long where other launches hold the CUs:
+ * those of other streams or processes, or on a stream with few CUs of its own.  The block then ends, and
+ * dblp_loss_account makes the probe again in launches that wait for nothing: the result is the same, the call takes longer.
+ * 0: no block waits (every probe of more than one block is made a second time; for tests). */
+int dblp_probe_polls(dblp_ctx* ctx, uint32_t polls);
+
 /* Alg. "DBLP_RECV" last statements + Alg. "Server" mean: d_out[e] = acc[e] / W where
  * unreceived chunks count as zero (a span no worker delivered is exactly 0).  d_out: 16-byte
  * aligned, N floats.  Only DBLP_COMP_ZEROFILL_MEAN is defined by the paper; other values give
@@ -305,7 +313,7 @@ int dblp_get_prev_norm(const dblp_ctx* ctx, double* h_norm, int* h_have);
  * reads; further ones are dropped.  dblp_profile_enable may return ENOMEM. */
 #define DBLP_K_INDEX 0    /* header parse / validation / arrival index */
 #define DBLP_K_GATHER 1   /* payload gather + accumulate, dense batches */
-#define DBLP_K_PROBE 2    /* loss count + retransmit list (two or three launches, one bracket) */
+#define DBLP_K_PROBE 2    /* loss count + retransmit list (one, two or three launches, one bracket) */
 #define DBLP_K_FINALIZE 3 /* zero-fill mean + partial sums of squares */
 #define DBLP_K_GATHER_DIRECT 4 /* the same, sparse batches (retransmissions), and all of fewer than one arrival per
                                   64 (worker, sequence number) pairs of the round */

@@ -23,7 +23,7 @@ ACC_AUTO, ACC_FIRST, ACC_SECOND, ACC_ALTERNATE = 0, 1, 2, 3
 ACCMODE_SINGLE, ACCMODE_PAIR, ACCMODE_SEARCH = 0, 1, 2
 
 EXPORTS = ["dblp_create", "dblp_destroy", "dblp_layout", "dblp_accumulator_copies", "dblp_accumulator_policy", "dblp_accumulator_info", "dblp_accumulator_ptr", "dblp_begin_round", "dblp_packetize", "dblp_packetize_list",
-           "dblp_apply_arrivals", "dblp_apply_arrivals_queue", "dblp_loss_account", "dblp_finalize", "dblp_phase_signal",
+           "dblp_apply_arrivals", "dblp_apply_arrivals_queue", "dblp_loss_account", "dblp_probe_polls", "dblp_finalize", "dblp_phase_signal",
            "dblp_get_bitmap", "dblp_get_counters", "dblp_set_prev_norm", "dblp_get_prev_norm",
            "dblp_last_error", "dblp_profile_enable", "dblp_profile_read", "dblp_policy_two_level", "dblp_policy_three_level", "dblp_policy_linear", "dblp_clr_init", "dblp_clr_step",
            "dblp_sumsq_static", "dblp_sumsq_static_error"]
@@ -80,6 +80,7 @@ def lib():
         L.dblp_apply_arrivals.argtypes = [vp, vp, vp, u64, vp, vp, u64]
         L.dblp_apply_arrivals_queue.argtypes = [vp, vp, u64, vp, u64]
         L.dblp_loss_account.argtypes = [vp, u32, vp, vp, u64, ctypes.POINTER(u64), ctypes.POINTER(i32)]
+        L.dblp_probe_polls.argtypes = [vp, u32]
         L.dblp_finalize.argtypes = [vp, i32, vp]
         L.dblp_phase_signal.argtypes = [vp, vp, ctypes.POINTER(dbl), ctypes.POINTER(dbl), ctypes.POINTER(i32)]
         L.dblp_get_bitmap.argtypes = [vp, vp]
@@ -257,6 +258,10 @@ class Aggregator:
         rc = self._check(lib().dblp_loss_account(self._h, bound_ppm, _ptr(d_missing), _ptr(d_retx_list), cap,
                                                  ctypes.byref(count), ctypes.byref(met)), allow=(ECAPACITY,))
         return int(count.value), bool(met.value), rc == ECAPACITY
+
+    def probe_polls(self, polls: int):
+        """Looks that a block of a probe takes at the blocks before it; then the probe is made again, waiting for nothing."""
+        self._check(lib().dblp_probe_polls(self._h, polls))
 
     def finalize(self, d_out=None, compensation=COMP_ZEROFILL_MEAN):
         """d_out None: in place (the result is accumulator copy 0)."""

@@ -46,6 +46,7 @@ typedef uint32_t u32;
 
 // device counters (u64 each)
 enum { C_ACCEPTED = 0, C_STALE, C_INVALID, C_CANDIDATES, C_COUNT };
+#define M_PROBE_GAVE_UP 2        // word of the host mailbox: a block of probe_once has waited long enough
 
 struct Geo {
     const u32* first_seq;   // [B+1]
@@ -1398,21 +1399,23 @@ __device__ __forceinline__ u64 wave_sum_u46(u64 v) {
 // and loaded as a relaxed atomic at device scope, so no fence is needed (one would write back the L2 that the gather has
 // just dirtied); the tag differs from probe to probe, so nothing is cleared in between.
 //
-// The wait ends: a block tells its length before it waits for anything, and waits only for blocks of lower index, so it
-// is enough that every block of the launch gets to start.  Waiting blocks alone cannot keep one from that: a launch takes
-// a quarter of what the chip holds at a time (seven blocks per CU), and kernels run from at most four hardware queues, so
-// even four such launches, of contexts on streams of their own, are resident as a whole.  Blocks of any other kernel end by
-// themselves.  More blocks than that take two launches, below.
+// A block tells its length before it waits for anything, and waits only for blocks of lower index.  As a rule these
+// are running: a launch takes a quarter of what the chip holds at a time.  But nothing promises it: launches of other
+// contexts that wait too, on streams with few CUs, on many hardware queues or from other processes, can hold every place
+// that a block waited for could start in.  So a block looks `polls` times at most, then says so (mailbox[M_PROBE_GAVE_UP]) and
+// ends; the host, which waits for the launch anyway, then has the list made in the launches below, whose blocks wait
+// for nothing.
 // Latency bounds the probe: a second launch for the list, which it was, costs its own start and a second walk to the same
 // words.  us of the two launches, and of this one, first probe of a round: 64 x 4 pairs of 64 packets 6.7, 4.2; 161 x 8
 // of 435 packets on average 8.9, 5.6.  (Where blocks are many the two launches cost little more: 148 x 8 pairs of 2300
 // packets 11.7, 9.8; 292 x 16 of 1190 15.7, 13.9.)
 #define PROBE_TAG_SHIFT 40
 #define PROBE_POLL 2
-#define PROBE_RESIDENT 7         // blocks (a wave on each SIMD, 72 registers) that a CU holds
+#define PROBE_RESIDENT 7         // blocks (a wave on each SIMD) that a CU holds, or one fewer with more than 72 registers
+#define PROBE_LOOKS 16384u       // polls, unless the caller says otherwise: 10 ms or more
 template <bool BLOCK_PAIR>
 __global__ __launch_bounds__(256) void probe_once(Geo g, const u64* __restrict__ bitmap, u32 bound_ppm, u32 ppw, u64 pairs, u32* __restrict__ missing_out,
-                                                  u64* totals, u64 tag, u64* __restrict__ list, u64 capacity, u64* __restrict__ mailbox) {
+                                                  u64* totals, u64 tag, u32 polls, u64* __restrict__ list, u64 capacity, u64* __restrict__ mailbox) {
     __shared__ u64 sh[4], sh_sum[4];
     const u32 lane = lane_id(), wave = uniform(threadIdx.x / WAVE);
     const u64 pr = BLOCK_PAIR ? blockIdx.x : ((u64)blockIdx.x * 4 + wave) * ppw + lane;
@@ -1435,11 +1438,13 @@ __global__ __launch_bounds__(256) void probe_once(Geo g, const u64* __restrict__
     const bool last = blockIdx.x == gridDim.x - 1;
     if (!last && (mine == 0 || capacity == 0)) return;          // the same in all threads of the block
     u64 before = 0;
-    for (u32 i0 = threadIdx.x; i0 < blockIdx.x; i0 += PROBE_POLL * 256) {
-        u64 v[PROBE_POLL];
-        bool all;
+    u32 looks = 0;
+    bool all = true;
+    for (u32 i0 = threadIdx.x; all && i0 < blockIdx.x; i0 += PROBE_POLL * 256) {
+        u64 v[PROBE_POLL] = {};
         do {
-            all = true;
+            all = looks++ < polls;
+            if (!all) break;
             #pragma unroll
             for (u32 k = 0; k < PROBE_POLL; ++k) {
                 const u32 i = i0 + k * 256;
@@ -1449,11 +1454,16 @@ __global__ __launch_bounds__(256) void probe_once(Geo g, const u64* __restrict__
             for (u32 k = 0; k < PROBE_POLL; ++k) all = all && v[k] >> PROBE_TAG_SHIFT == tag >> PROBE_TAG_SHIFT;
         } while (!all);
         #pragma unroll
-        for (u32 k = 0; k < PROBE_POLL; ++k) before += v[k] ^ tag;
+        for (u32 k = 0; k < PROBE_POLL; ++k) before += all ? v[k] ^ tag : 0ull;
     }
     before = wave_sum_u46(before);
+    if (__ballot(!all)) before = NONE64;
     if (lane == 0) sh[wave] = before;
     __syncthreads();
+    if (sh[0] == NONE64 || sh[1] == NONE64 || sh[2] == NONE64 || sh[3] == NONE64) {
+        if (threadIdx.x == 0) mailbox[M_PROBE_GAVE_UP] = 1;
+        return;
+    }
     u64 base = (sh[0] + sh[1]) + (sh[2] + sh[3]);
     if (last && threadIdx.x == 0) mailbox[0] = base + mine;
     if (!BLOCK_PAIR)
@@ -1545,7 +1555,9 @@ __global__ __launch_bounds__(256) void emit_retx(Geo g, const u64* __restrict__ 
 // Per-block partial sums that the last block of the same launch adds up.  words[0] numbers the launches that have used
 // the array; block i's sum is two words, tag << 32 | half of the double, stored and loaded as relaxed atomics at device scope.
 // The tag comes from device memory, not from the host, so that a launch recorded into a graph can be replayed.
-// The wait ends: a block waits for nothing before it tells its sum, and the block that waits is the last of its launch.
+// The wait ends: no block waits before it tells its sum, and one block of a launch, the last, waits.  To keep a block from
+// starting, waiting ones of other launches would have to fill its XCD's CUs, eight to a CU, and those another XCD's in
+// turn: 16 such launches at once on streams of one CU per XCD, 512 on the whole chip, which runs fewer at a time.
 // A second launch for the sum cost 2 to 4 us of the stream (3 workers x 5.3 M, copied out: 103.6 us a pass with it, 102.7 without).
 #define PARTIALS_WORDS(blocks) (1u + 2u * (blocks))
 __device__ __forceinline__ u32 partials_tag(const u64* words) { return (u32)words[0] + 1u; }
@@ -1920,6 +1932,7 @@ struct dblp_ctx {
     hipEvent_t cls_ev[2];
     int probe_block_pair;   // probe: a block per (worker, bucket) pair
     u32 probe_no;           // probes made: what their words in d_totals are told apart by
+    u32 probe_polls;        // looks that a block of probe_once takes at the totals before its own
     u32* d_need; u64* d_totals;   // list length per pair, and per block of pairs
     u64* d_partials; u32 max_partials;    // sums of squares per block, told to the launch's last block
     u32* d_block_tallies;   // [IDX_BLOCKS_PER_CU * n_cus][5], written by index_arrivals
@@ -1965,13 +1978,15 @@ struct ProfScope {
         (void)hipEventRecord(a, c->stream);
     }
     u32* d_told() const { return a && kernel < 0 ? c->d_told + at : nullptr; }
-    ~ProfScope() {
+    ~ProfScope() { end(); }
+    void end() {                // before a wait that is no part of the launches
         if (!a) return;
         hipEvent_t b = prof_event(c);
-        if (!b) { c->ev_pool->push_back(a); return; }
+        if (!b) { c->ev_pool->push_back(a); a = nullptr; return; }
         (void)hipEventRecord(b, c->stream);
         if (c->timed->size() < c->timed->capacity()) c->timed->push_back({a, b, kernel, at});   // never reallocates
         else { c->ev_pool->push_back(a); c->ev_pool->push_back(b); }                            // buffer full: drop the sample
+        a = nullptr;
     }
 };
 
@@ -2280,6 +2295,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     c->N = cfg->n_elems; c->eta = cfg->eta; c->device = cfg->device; c->stream = (hipStream_t)cfg->stream;
     c->search_fraction = cfg->search_free_fraction > 0.0 ? cfg->search_free_fraction : 0.5;
     c->search_seconds = cfg->search_seconds > 0.0 ? cfg->search_seconds : 2.0;
+    c->probe_polls = PROBE_LOOKS;
     c->fold = (cfg->n_workers & (cfg->n_workers - 1)) == 0;
     c->result_in_place = c->fold ? 1 : 0;     // the in-place finalize exists for power-of-two worker counts
     c->timed = new (std::nothrow) std::vector<dblp_ctx::Timed>();
@@ -2697,11 +2713,20 @@ extern "C" int dblp_loss_account(dblp_ctx* c, uint32_t bound_ppm, uint32_t* d_mi
     if (blocks > 0x7FFFFFFFull) return fail(c, DBLP_EINVAL, "loss_account: too many (worker, bucket) pairs");
     {
         ProfScope ps(c, DBLP_K_PROBE);
-        if (blocks * 4 <= (u64)PROBE_RESIDENT * c->n_cus) {
-            const u64 tag = (u64)(++c->probe_no & 0xFFFFFFu) << PROBE_TAG_SHIFT;
+        bool done = blocks * 4 <= (u64)PROBE_RESIDENT * c->n_cus;
+        if (done) {
+            if ((++c->probe_no & 0xFFFFFFu) == 0) ++c->probe_no;        // 0 is no tag: the launches below leave totals without one
+            const u64 tag = (u64)(c->probe_no & 0xFFFFFFu) << PROBE_TAG_SHIFT;
+            volatile u64* const gave_up = c->h_mailbox + M_PROBE_GAVE_UP;
+            *gave_up = 0;
             hipLaunchKernelGGL(c->probe_block_pair ? probe_once<true> : probe_once<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g,
-                               c->d_bitmap, bound_ppm, ppw, pairs, d_missing, c->d_totals, tag, (u64*)d_retx_list, (u64)retx_capacity, c->d_mailbox);
-        } else {
+                               c->d_bitmap, bound_ppm, ppw, pairs, d_missing, c->d_totals, tag, c->probe_polls, (u64*)d_retx_list, (u64)retx_capacity, c->d_mailbox);
+            LAUNCH_CHECK(c, "loss_account");
+            ps.end();
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
+            done = *gave_up == 0;
+        }
+        if (!done) {
             // Each block of emit_retx adds up the totals of the blocks before it (2048 of them: about a
             // microsecond) unless they are so many that a pass in between is shorter.
             const int scanned = blocks > PROBE_SCAN_BLOCKS ? 1 : 0;
@@ -2710,15 +2735,22 @@ extern "C" int dblp_loss_account(dblp_ctx* c, uint32_t bound_ppm, uint32_t* d_mi
             if (scanned) hipLaunchKernelGGL(scan_totals, dim3(1), dim3(1024), 0, c->stream, c->d_totals, (u32)blocks);
             hipLaunchKernelGGL(c->probe_block_pair ? emit_retx<true> : emit_retx<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g, c->d_bitmap, ppw, pairs,
                                (const u32*)c->d_need, (const u64*)c->d_totals, scanned, (u64*)d_retx_list, (u64)retx_capacity, c->d_mailbox);
+            LAUNCH_CHECK(c, "loss_account");
+            ps.end();
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
         }
     }
-    LAUNCH_CHECK(c, "loss_account");
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
     c->mailbox_seen = 1;
     const u64 total = c->h_mailbox[0];
     *h_retx_count = total;
     *h_all_met = total == 0;
     if (total > retx_capacity) return fail(c, DBLP_ECAPACITY, "retransmit list truncated");
+    return DBLP_OK;
+}
+
+extern "C" int dblp_probe_polls(dblp_ctx* c, uint32_t polls) {
+    if (!c) return DBLP_EINVAL;
+    c->probe_polls = polls;
     return DBLP_OK;
 }
 

@@ -38,8 +38,21 @@ CASES = [(1, [1]), (3, [5, 70, 1, 64, 65, 129]), (7, [1, 300] * 128), (3, [2] * 
 
 @pytest.mark.parametrize("W,packets", CASES)
 def test_probe_lists_what_is_missing(W, packets):
-    import torch
+    _probes(W, packets, _context(W, packets))
+
+
+@pytest.mark.parametrize("polls", [0, 1])
+@pytest.mark.parametrize("W,packets", [c for c in CASES if c[0] * len(c[1]) <= 1792])
+def test_probe_whose_blocks_do_not_wait_is_made_again(W, packets, polls):
+    """With no look allowed every block that needs the ones before it gives up; with one, some may.  The answers are the
+    same, also of a probe that may wait and follows one that gave up (its words in the totals carry no tag)."""
     agg = _context(W, packets)
+    agg.probe_polls(polls)
+    _probes(W, packets, agg, lambda k: agg.probe_polls(16384 if k % 3 == 2 else polls))
+
+
+def _probes(W, packets, agg, before=None):
+    import torch
     n_b = torch.tensor(packets, device="cuda")
     first = torch.cat([torch.zeros(1, dtype=torch.int64, device="cuda"), n_b.cumsum(0)])
     gen = torch.Generator(device="cuda").manual_seed(W + len(packets))
@@ -60,7 +73,9 @@ def test_probe_lists_what_is_missing(W, packets):
         alive |= new
         for bound in (0, 200_000, 1_000_000):
             want_missing, want = _expect(alive, first, n_b, bound)
-            for cap in (out.numel(), want.numel() // 2, 0):
+            for k, cap in enumerate((out.numel(), want.numel() // 2, 0)):
+                if before is not None:
+                    before(k)
                 missing.fill_(-1)
                 out.fill_(-1)
                 count, met, truncated = agg.loss_account(bound, missing, out, cap)
@@ -69,3 +84,35 @@ def test_probe_lists_what_is_missing(W, packets):
                 k = min(cap, count)
                 assert torch.equal(out[:k], want[:k]) and bool((out[k:] == -1).all())
     assert bool(alive.all())
+
+
+def test_probes_of_several_contexts_at_once():
+    """Four contexts, each on a stream and in a thread of its own, of as many blocks as one launch takes."""
+    import threading
+
+    import torch
+    W, packets, found = 32, [65] * 56, [None] * 4
+    want = _expect(torch.zeros(W, 65 * 56, dtype=torch.bool, device="cuda"), torch.arange(57, device="cuda") * 65,
+                   torch.full((56,), 65, device="cuda"), 0)
+
+    def work(k):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            agg = _context(W, packets)
+            agg.begin_round(ROUND)
+            missing = torch.empty(W * agg.B, dtype=torch.int32, device="cuda")
+            out = torch.empty(W * agg.n_pkts, dtype=torch.int64, device="cuda")
+            ok = True
+            for _ in range(100):
+                out.fill_(-1)
+                ok = ok and agg.loss_account(0, missing, out) == (out.numel(), False, False)
+                ok = ok and torch.equal(missing, want[0]) and torch.equal(out, want[1])
+            found[k] = ok
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    torch.cuda.synchronize()
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert found == [True] * 4
