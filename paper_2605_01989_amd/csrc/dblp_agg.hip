@@ -2370,7 +2370,9 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     }
     c->d_sumsq_rows = (double*)(c->d_accept_rows + ACCEPT_ROWS);
     c->burst = burst_plan(g, (u32)c->n_cus);
-    if (c->burst.fn && hipFuncSetAttribute((const void*)c->burst.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->burst.lds) != hipSuccess) {
+    // The limit is the kernel's, not the context's: the same whatever the plan, so that contexts which share an instance
+    // do not lower it for each other.
+    if (c->burst.fn && hipFuncSetAttribute((const void*)c->burst.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)BURST_LDS) != hipSuccess) {
         (void)hipGetLastError();
         c->burst.fn = nullptr;
     }

@@ -142,3 +142,16 @@ def test_launches_that_decide_on_the_device(spread):
         alive[:, c.n_pkts // 3 + 5: c.n_pkts // 3 + 5 + int(c.n_pkts * 0.124)] = True
         alive &= c.rand(W, c.n_pkts) >= 0.03
     c.check([c.batch(alive, dup=0.0)], 3 if spread else 40)
+
+
+def test_a_later_context_with_smaller_groups_leaves_an_earlier_one_its_own():
+    """Two rounds whose bursts are the same kernel with images of different sizes; the smaller context is made second."""
+    W, P = 8, 366
+    c = _Case(W, P, 25_000_001, "ragged", seed=8)
+    first = c.batch(c.rand(W, c.n_pkts) >= 0.02)
+    ctx = c.make()
+    small = _Case(W, P, 5_400_007, "ragged", seed=9)
+    got, ref = c.receive([first], 1, ctx=ctx), c.receive([first], 40)
+    small.check([small.batch(small.rand(W, small.n_pkts) >= 0.02)], 12)
+    assert c.torch.equal(got[0].view(c.torch.int32), ref[0].view(c.torch.int32))
+    assert c.torch.equal(got[1], ref[1]) and got[2] == ref[2]
