@@ -164,12 +164,6 @@ __global__ __launch_bounds__(256) void fill_u64(u64* __restrict__ p, u64 n, u64 
     for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
 
-__global__ void reset_counters(u64* __restrict__ c) {
-    u32 t = threadIdx.x;
-    if (t >= C_COUNT) return;
-    c[t] = 0;
-}
-
 // Start of a round in one launch: bitmap and the gather kernels' per-block rows to zero, counters reset.
 __global__ __launch_bounds__(256) void reset_round(u64* __restrict__ bitmap, u64 n_bitmap, u64* __restrict__ rows, u64 n_rows,
                                                    u64* __restrict__ counters) {
@@ -332,7 +326,7 @@ __global__ __launch_bounds__(256) void index_arrivals(Geo g, const uint8_t* __re
                                                       const u64* __restrict__ mask, const u32* __restrict__ order,
                                                       const u64* __restrict__ queue,
                                                       u64 n_arrivals, u32 cur_round, u64* __restrict__ pending,
-                                                      u32* __restrict__ block_tallies) {
+                                                      u32* __restrict__ block_tallies, u64* __restrict__ any) {
     __shared__ u32 sh[4][5];    // per wave: stale, invalid, candidates, lowest seq, highest seq + 1
     extern __shared__ u32 fs_lds[];
     u32 n_stale = 0, n_inv = 0, n_cand = 0;
@@ -400,6 +394,7 @@ __global__ __launch_bounds__(256) void index_arrivals(Geo g, const uint8_t* __re
         }
         u32* row = block_tallies + (u64)blockIdx.x * 5;
         row[0] = t[0]; row[1] = t[1]; row[2] = t[2]; row[3] = lo; row[4] = hi;
+        if (any && t[2]) *any = 1;
     }
 }
 
@@ -886,13 +881,24 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
 
 // A batch of at least one arrival per two (worker, seq) pairs of the round is taken to touch all of it: its gather need not
 // read the index pass's tallies, a load and two barriers, before it starts (4 x 1 M elements in 1040-byte packets 10.8,
-// 8.1 us; 8 x 25.6 M in 1472-byte ones, in bursts, 156.7, 153.9).  What it looks through for nothing is 8 bytes of the
-// index for each packet that it gathers, at most.
+// 8.1 us; 8 x 25.6 M in 1472-byte ones, in bursts, 156.7, 153.9).  What it may look through for nothing is 16 bytes of the index
+// for each arrival at most, where the index pass has read each one's header; not even that where no arrival was valid,
+// which one word says (a stale round of 8 x 124 M 62.7 us; 99.7 without the word).  Slots that a mask says were lost count as arrivals but cost
+// the index pass nothing, so with a mask only rounds that the blocks walk in two turns are taken whole (8 x 124 M, a mask of 1 %
+// of the range 29 against 87 us; all lost 15 and 54).
 #define WHOLE_DIV 2
 __device__ __forceinline__ BatchInfo whole_round(const Geo& g) {
     BatchInfo bi;
     bi.lo = 0; bi.hi = g.n_pkts; bi.cand = (u64)g.n_pkts * g.W;
     return bi;
+}
+
+// any[at] says whether the index pass met a valid arrival.  (Never no when it did; where launches are recorded and told
+// again it may be yes when it did not.)  A gather clears the other word, for the next batch that uses one.
+__device__ __forceinline__ bool some_arrived(u64* __restrict__ any, u32 at) {
+    if (!any) return true;
+    if (blockIdx.x == 0 && threadIdx.x == 0) any[at ^ 1u] = 0;
+    return any[at] != 0;
 }
 
 // DENSE: the host knows that the batch is dense; otherwise the index pass's tallies decide.
@@ -902,10 +908,11 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
     const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters,
     u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
-    GatherShape dense, GatherShape sparse, u32 cus, u32 heavy, u32 table_at, u32 burst_seq, u32 whole, u32* __restrict__ told) {
+    GatherShape dense, GatherShape sparse, u32 cus, u32 heavy, u32 table_at, u32 burst_seq, u32 whole, u64* __restrict__ any, u32 any_at, u32* __restrict__ told) {
     extern __shared__ u32 sh_dyn[];                 // per wave: slots [W rounded up][sub + 1]; then the bucket table (table_at words in, 0: not there)
     __shared__ u32 sh_tally[NW * 5];
     const u32* fs = g.first_seq;
+    const bool some = some_arrived(any, any_at);
     if (table_at) {
         u32* tab = sh_dyn + table_at;
         for (u32 i = threadIdx.x; i <= g.B; i += blockDim.x) tab[i] = g.first_seq[i];
@@ -913,10 +920,12 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     }
     // block 0 books the index pass's tallies; the barriers in there cover the table too
     BatchInfo bi;
-    if (DENSE && whole && blockIdx.x) bi = whole_round(g);
-    else {
+    if (DENSE && whole && blockIdx.x) {
+        if (!some) return;
+        bi = whole_round(g);
+    } else {
         bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0 && !burst_seq, sh_tally);
-        if (DENSE && whole) bi = whole_round(g);
+        if (DENSE && whole && bi.hi) bi = whole_round(g);
     }
     if (DENSE && whole) __syncthreads();
     const bool is_sparse = !DENSE && batch_is_sparse(bi, g.W);
@@ -976,7 +985,7 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
     const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters,
     u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
-    u32 r_max, u32 r_step, u32 n_piece, u32 table_at, u32 image_at, u32 min_seq, u32 through_seq, u32 whole) {
+    u32 r_max, u32 r_step, u32 n_piece, u32 table_at, u32 image_at, u32 min_seq, u32 through_seq, u32 whole, u64* __restrict__ any, u32 any_at) {
     extern __shared__ __attribute__((aligned(16))) u32 sh_dyn[];
     __shared__ u32 sh_tally[BURST_WAVES * 5];
     __shared__ u32 sh_new[3][BURST_MAX / 32], sh_old[3][BURST_MAX / 32];     // by packet of the group: new copies; delivered before
@@ -989,6 +998,7 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
     u32* const sh_len = sh_elem + 4 * r_max;                    // [2][r_max]: floats | home << 16
     float* const image = (float*)(sh_dyn + image_at);
     const u32* fs = g.first_seq;
+    const bool some = some_arrived(any, any_at);
     if (table_at) {
         u32* tab = sh_dyn + table_at;
         for (u32 i = tid; i <= g.B; i += BURST_WAVES * WAVE) tab[i] = g.first_seq[i];
@@ -998,8 +1008,11 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
     BatchInfo bi = whole_round(g);
     if (!whole || blockIdx.x == 0) {
         const BatchInfo found = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0, sh_tally);
-        if (!whole) bi = found;
-    } else __syncthreads();
+        if (!whole || found.hi == 0) bi = found;
+    } else {
+        if (!some) return;
+        __syncthreads();
+    }
     // A batch that is none of this kernel's is left to the gather_stream launch that follows.
     if (bi.hi == 0 || (min_seq && (batch_is_sparse(bi, g.W) || bi.hi - bi.lo < min_seq))) return;
     // Groups of equal size but for one step: with all groups as long as the longest, the last turn of 4 x 61 M in 64
@@ -1895,7 +1908,7 @@ __global__ __launch_bounds__(256) void classify_rw(const uint8_t* __restrict__ s
 // ------------------------------------------------------------------------------------------
 // What the context's gather_burst launches are given (burst_plan); fn null: none are made.
 typedef void (*burst_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, u64*, double*, float,
-                         u32, u32, u32, u32, u32, u32, u32, u32);
+                         u32, u32, u32, u32, u32, u32, u32, u32, u64*, u32);
 struct BurstPlan { burst_fn fn; u32 r_max, r_step, n_piece, table_at, image_at, min_seq, through_seq; size_t lds; };
 
 struct dblp_ctx {
@@ -1908,7 +1921,8 @@ struct dblp_ctx {
     int n_cus;
     // device state
     u32* d_first_seq; u64* d_b_off; u64* d_b_cnt; u32* d_hint;
-    u64* d_bitmap; u64* d_pending; u64* d_counters;
+    u64* d_bitmap; u64* d_pending; u64* d_counters; u64* d_any;     // d_any: two words behind the counters, in turn
+    u32 any_no;             // batches that used one of them
     // accumulator: one or two copies (d_acc[1] == d_acc[0] when there is one); each copy's
     // allocation ends with CLS_SCRATCH_BYTES that classify_rw may overwrite
     void* acc_alloc[2]; float* d_acc[2]; float* d_scratch[2];
@@ -2340,7 +2354,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     ok = ok && hipMalloc(&c->d_bitmap, g.W * g.words_pw * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_pending, (u64)g.W * n_pkts * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_home, (n_pkts + 7) / 8 * 8 + 8) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_counters, C_COUNT * sizeof(u64)) == hipSuccess;
+    ok = ok && hipMalloc(&c->d_counters, (C_COUNT + 2) * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_need, pairs * sizeof(u32)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_totals, probe_blocks(c, pairs) * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_partials, PARTIALS_WORDS(c->max_partials) * sizeof(u64)) == hipSuccess;
@@ -2369,6 +2383,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
         g.hint = c->d_hint;
     }
     c->d_sumsq_rows = (double*)(c->d_accept_rows + ACCEPT_ROWS);
+    c->d_any = c->d_counters + C_COUNT;
     c->burst = burst_plan(g, (u32)c->n_cus);
     // The limit is the kernel's, not the context's: the same whatever the plan, so that contexts which share an instance
     // do not lower it for each other.
@@ -2382,7 +2397,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
                        c->d_pending, n_pending, NONE64);
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (g.W * g.words_pw + 255) / 256, 16)), dim3(256), 0, c->stream,
                        c->d_bitmap, g.W * g.words_pw, 0ull);
-    hipLaunchKernelGGL(reset_counters, dim3(1), dim3(64), 0, c->stream, c->d_counters);
+    hipLaunchKernelGGL(fill_u64, dim3(1), dim3(64), 0, c->stream, c->d_counters, (u64)(C_COUNT + 2), 0ull);
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (probe_blocks(c, pairs) + 255) / 256, 16)), dim3(256), 0, c->stream,
                        c->d_totals, probe_blocks(c, pairs), 0ull);
     hipLaunchKernelGGL(fill_u64, dim3(8), dim3(256), 0, c->stream, c->d_partials, (u64)PARTIALS_WORDS(c->max_partials), 0ull);
@@ -2543,7 +2558,7 @@ extern "C" int dblp_packetize_list(dblp_ctx* c, uint16_t round, const float* con
 }
 
 typedef void (*gather_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, u64*, double*, float,
-                          GatherShape, GatherShape, u32, u32, u32, u32, u32, u32*);
+                          GatherShape, GatherShape, u32, u32, u32, u32, u32, u64*, u32, u32*);
 
 // The instance for `np` KB of a packet per step; few: one to three workers.
 template <bool DENSE, u32 LEAD>
@@ -2578,73 +2593,79 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
     const int pick = pick_copy(c, d_packets, n_slots * g.stride, n_slots, n_arrivals);
     c->last_pick = pick;
     ++c->batch_no;
+    const bool lead = units_from_packet(g) || block_waves(c) == 16;
+    // Dense or sparse.  At least one arrival per SPARSE_DIV (worker, seq) pairs of the whole round is dense
+    // whatever range it touches, and the launch is told so.  Fewer are a retransmission or a step of a round
+    // that arrives in many steps; the number does not say which, so the blocks decide, from the sequence
+    // range that the index pass found (a launch that took fewer than one per 64 pairs for sparse saved it 0 to
+    // 0.4 us, and cost a round of 32 x 60 M elements in 129 steps 11.7 against 4.7 ms).
+    const u64 pairs = (u64)g.W * g.n_pkts;
+    const bool is_dense = n_arrivals * SPARSE_DIV >= pairs, small = n_arrivals * SPARSE_DIV * 8 < pairs;
+    const u32 nw = small && g.stride < 8192 ? GS_WAVES      // 16 waves for a handful of 4 KB packets: 29 against 22 us
+                                            : block_waves(c);
+    // Dense.  Packets of up to 5 KB are one piece, longer ones are cut evenly into pieces of 3 or 4 KB; in
+    // a short round finer, so that a group gives each of the block's waves a piece.
+    GatherShape dense, sparse;
+    const u32 n_pass = unit_passes(g, lead);
+    dense.n_piece = n_pass <= 5 ? 1 : (n_pass + 3) / 4;
+    const u32 heavy = (u64)g.W * g.stride >= HEAVY_BYTES ? 2 : (u64)g.W * g.stride >= HEAVY_BYTES / 2 ? 1 : 0;
+    dense.sub_log2 = group_log2(g.n_pkts, (u32)c->n_cus, dense.n_piece > 1, heavy);      // (the whole round's)
+    if (nw == 16) {
+        const u32 want = nw >> dense.sub_log2 < n_pass ? nw >> dense.sub_log2 : n_pass;
+        if (dense.n_piece < want) dense.n_piece = want;
+    }
+    const u32 np = (n_pass + dense.n_piece - 1) / dense.n_piece;
+    dense.n_piece = (n_pass + np - 1) / np;
+    // One to three workers: a step is one worker's piece, four of them in flight, and six blocks per
+    // CU (1 worker: 45 us, against 54 with three blocks, 68 with steps of four workers; 25.6 M elements of 366
+    // floats, 2 workers 61 against 73 with steps of four, 3 workers 78 and 82, 4 workers 98 and 97, 8 workers 176
+    // and 174).  More: 4 to 8 KB per step, two steps in flight, three blocks per CU for short packets, two for
+    // long ones (8992 B: 930 against 940 us; more blocks only spread the DRAM accesses over more open rows).
+    const bool few = g.W < 4;
+    const u32 per_cu = nw == 16 ? 1 : few ? (np <= 2 && is_dense ? 6 : 4) : np <= 2 ? 3 : 2;
+    const u64 groups = ((u64)g.n_pkts + (1u << dense.sub_log2) - 1) >> dense.sub_log2;
+    dense.blocks = grid_for(c, groups, per_cu);
+
+    // Sparse.  One worker's 2 KB per step.  Groups of 32 packets of up to 2 KB in long rounds, longer rows of the
+    // index and fewer empty groups to pass: 1 x 1.9 M packets of 136 bytes, 562 lost 26 us against 37 with 16; 8 x
+    // 340 k of 1472 B, 14 k lost 46 against 48 (with more of them, or in bursts, 16 would do better: 6.9 k lost
+    // there 50 against 43).  Otherwise as for dense batches.
+    sparse.n_piece = lead ? (g.units + 2 * WAVE - 1) / (2 * WAVE) : (g.P + 8 * WAVE - 1) / (8 * WAVE);
+    sparse.sub_log2 = sparse.n_piece == 1 && g.n_pkts >= (g.W <= 4 ? 32u : 64u) * (u32)c->n_cus ? 5 : group_log2(g.n_pkts, (u32)c->n_cus, sparse.n_piece > 1, heavy == 2 ? 2 : 0);
+    // Packets of 16 KB and more fill a block's waves four at a time: fewer to one block where lost packets
+    // follow each other (1 worker x 66 M in 64 KB packets, 12 lost 18 against 23 us, 247 lost 32 against 48; 4 x
+    // 61 M, 80 lost 29 against 42), until the groups get many.
+    if (sparse.n_piece >= 8 && sparse.sub_log2 > 2 && g.n_pkts <= 64u * (u32)c->n_cus) sparse.sub_log2 = 2;
+    sparse.blocks = grid_for(c, ((u64)g.n_pkts + (1u << sparse.sub_log2) - 1) >> sparse.sub_log2, nw == 16 ? 1 : 4);
+
+    // Bursts.  A batch of at least burst.min_seq packets per worker covers that many sequence numbers or more.  Known to be
+    // dense, it is one gather_burst launch; where the blocks have to find out, that launch leaves a sparse batch to a
+    // gather_stream launch after it, and the other way round.  The second launch costs about 3 us, so it is made
+    // for batches of 256 MB and more only, which take 60 us and more as a dense step and 130 as a retransmission.
+    const BurstPlan& burst = c->burst;
+    const bool in_bursts = burst.fn && n_arrivals >= (u64)burst.min_seq * g.W && (is_dense || n_arrivals * g.stride >= 256000000ull);
+
+    const u64 turns = in_bursts ? 8 : (groups + dense.blocks - 1) / dense.blocks;
+    const u32 whole = n_arrivals * WHOLE_DIV >= pairs && (!d_mask || turns <= 2);
+    u64* const any = whole && turns > 4 ? c->d_any : nullptr;           // (two turns for nothing take 1 us; the word costs 0.4 to 1.5)
+    const u32 any_at = any ? c->any_no++ & 1u : 0u;
+
     u32 n_tally_rows = 0;
     {
         ProfScope ps(c, DBLP_K_INDEX);
         const u32 grid = grid_for(c, (n_arrivals + 255) / 256, IDX_BLOCKS_PER_CU);
         const size_t table = ((size_t)g.B + 1) * sizeof(u32);
         const bool lds = table <= IDX_TABLE_LDS_MAX;
-        void (*idx)(Geo, const uint8_t*, const uint16_t*, u64, const u64*, const u32*, const u64*, u64, u32, u64*, u32*) =
+        void (*idx)(Geo, const uint8_t*, const uint16_t*, u64, const u64*, const u32*, const u64*, u64, u32, u64*, u32*, u64*) =
             lds ? (d_queue ? index_arrivals<true, true> : index_arrivals<true, false>)
                 : (d_queue ? index_arrivals<false, true> : index_arrivals<false, false>);
         hipLaunchKernelGGL(idx, dim3(grid), dim3(256), lds ? table : 0, c->stream, g,
                            (const uint8_t*)d_packets, d_src_worker, (u64)n_slots, (const u64*)d_mask, d_order,
-                           (const u64*)d_queue, (u64)n_arrivals, (u32)c->round, c->d_pending, c->d_block_tallies);
+                           (const u64*)d_queue, (u64)n_arrivals, (u32)c->round, c->d_pending, c->d_block_tallies, any ? any + any_at : nullptr);
         n_tally_rows = grid;
     }
     const float inv_w = c->fold ? 1.0f / (float)g.W : 1.0f;   // exact for the powers of two it is used with
     {
-        const bool lead = units_from_packet(g) || block_waves(c) == 16;
-        // Dense or sparse.  At least one arrival per SPARSE_DIV (worker, seq) pairs of the whole round is dense
-        // whatever range it touches, and the launch is told so.  Fewer are a retransmission or a step of a round
-        // that arrives in many steps; the number does not say which, so the blocks decide, from the sequence
-        // range that the index pass found (a launch that took fewer than one per 64 pairs for sparse saved it 0 to
-        // 0.4 us, and cost a round of 32 x 60 M elements in 129 steps 11.7 against 4.7 ms).
-        const u64 pairs = (u64)g.W * g.n_pkts;
-        const bool is_dense = n_arrivals * SPARSE_DIV >= pairs, small = n_arrivals * SPARSE_DIV * 8 < pairs;
-        const u32 whole = n_arrivals * WHOLE_DIV >= pairs;
-        const u32 nw = small && g.stride < 8192 ? GS_WAVES      // 16 waves for a handful of 4 KB packets: 29 against 22 us
-                                                : block_waves(c);
-        // Dense.  Packets of up to 5 KB are one piece, longer ones are cut evenly into pieces of 3 or 4 KB; in
-        // a short round finer, so that a group gives each of the block's waves a piece.
-        GatherShape dense, sparse;
-        const u32 n_pass = unit_passes(g, lead);
-        dense.n_piece = n_pass <= 5 ? 1 : (n_pass + 3) / 4;
-        const u32 heavy = (u64)g.W * g.stride >= HEAVY_BYTES ? 2 : (u64)g.W * g.stride >= HEAVY_BYTES / 2 ? 1 : 0;
-        dense.sub_log2 = group_log2(g.n_pkts, (u32)c->n_cus, dense.n_piece > 1, heavy);      // (the whole round's)
-        if (nw == 16) {
-            const u32 want = nw >> dense.sub_log2 < n_pass ? nw >> dense.sub_log2 : n_pass;
-            if (dense.n_piece < want) dense.n_piece = want;
-        }
-        const u32 np = (n_pass + dense.n_piece - 1) / dense.n_piece;
-        dense.n_piece = (n_pass + np - 1) / np;
-        // One to three workers: a step is one worker's piece, four of them in flight, and six blocks per
-        // CU (1 worker: 45 us, against 54 with three blocks, 68 with steps of four workers; 25.6 M elements of 366
-        // floats, 2 workers 61 against 73 with steps of four, 3 workers 78 and 82, 4 workers 98 and 97, 8 workers 176
-        // and 174).  More: 4 to 8 KB per step, two steps in flight, three blocks per CU for short packets, two for
-        // long ones (8992 B: 930 against 940 us; more blocks only spread the DRAM accesses over more open rows).
-        const bool few = g.W < 4;
-        const u32 per_cu = nw == 16 ? 1 : few ? (np <= 2 && is_dense ? 6 : 4) : np <= 2 ? 3 : 2;
-        dense.blocks = grid_for(c, ((u64)g.n_pkts + (1u << dense.sub_log2) - 1) >> dense.sub_log2, per_cu);
-        // Sparse.  One worker's 2 KB per step.  Groups of 32 packets of up to 2 KB in long rounds, longer rows of the
-        // index and fewer empty groups to pass: 1 x 1.9 M packets of 136 bytes, 562 lost 26 us against 37 with 16; 8 x
-        // 340 k of 1472 B, 14 k lost 46 against 48 (with more of them, or in bursts, 16 would do better: 6.9 k lost
-        // there 50 against 43).  Otherwise as for dense batches.
-        sparse.n_piece = lead ? (g.units + 2 * WAVE - 1) / (2 * WAVE) : (g.P + 8 * WAVE - 1) / (8 * WAVE);
-        sparse.sub_log2 = sparse.n_piece == 1 && g.n_pkts >= (g.W <= 4 ? 32u : 64u) * (u32)c->n_cus ? 5 : group_log2(g.n_pkts, (u32)c->n_cus, sparse.n_piece > 1, heavy == 2 ? 2 : 0);
-        // Packets of 16 KB and more fill a block's waves four at a time: fewer to one block where lost packets
-        // follow each other (1 worker x 66 M in 64 KB packets, 12 lost 18 against 23 us, 247 lost 32 against 48; 4 x
-        // 61 M, 80 lost 29 against 42), until the groups get many.
-        if (sparse.n_piece >= 8 && sparse.sub_log2 > 2 && g.n_pkts <= 64u * (u32)c->n_cus) sparse.sub_log2 = 2;
-        sparse.blocks = grid_for(c, ((u64)g.n_pkts + (1u << sparse.sub_log2) - 1) >> sparse.sub_log2, nw == 16 ? 1 : 4);
-
-        // Bursts.  A batch of at least burst.min_seq packets per worker covers that many sequence numbers or more.  Known to be
-        // dense, it is one gather_burst launch; where the blocks have to find out, that launch leaves a sparse batch to a
-        // gather_stream launch after it, and the other way round.  The second launch costs about 3 us, so it is made
-        // for batches of 256 MB and more only, which take 60 us and more as a dense step and 130 as a retransmission.
-        const BurstPlan& burst = c->burst;
-        const bool in_bursts = burst.fn && n_arrivals >= (u64)burst.min_seq * g.W && (is_dense || n_arrivals * g.stride >= 256000000ull);
-
         u32 slots = 0, grid = dense.blocks;
         for (u32 l = 0; l <= (dense.sub_log2 > 2 ? dense.sub_log2 : 2); ++l)        // whatever the launch may choose
             if (GS_TEAM_LDS(g.W, l) > slots) slots = GS_TEAM_LDS(g.W, l);
@@ -2663,13 +2684,13 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
             hipLaunchKernelGGL(burst.fn, dim3(c->n_cus), dim3(BURST_WAVES * WAVE), burst.lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap,
                                c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
                                c->d_accept_rows, c->d_sumsq_rows, inv_w, burst.r_max, burst.r_step, burst.n_piece, burst.table_at, burst.image_at,
-                               is_dense ? 0u : burst.min_seq, burst.through_seq, whole);
+                               is_dense ? 0u : burst.min_seq, burst.through_seq, whole, any, any_at);
         }
         if (!in_bursts || !is_dense) {
             if (grid > c->rows_used) c->rows_used = grid;
             hipLaunchKernelGGL(kern, dim3(grid), dim3(nw * WAVE), lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap,
                                c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
-                               c->d_accept_rows, c->d_sumsq_rows, inv_w, dense, sparse, (u32)c->n_cus, heavy, table_at, in_bursts ? burst.min_seq : 0u, whole, ps.d_told());
+                               c->d_accept_rows, c->d_sumsq_rows, inv_w, dense, sparse, (u32)c->n_cus, heavy, table_at, in_bursts ? burst.min_seq : 0u, whole, any, any_at, ps.d_told());
         }
     }
     LAUNCH_CHECK(c, "apply_arrivals");

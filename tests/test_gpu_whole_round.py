@@ -1,4 +1,5 @@
-"""GPU: batches of about half a round, where the gather stops asking the index pass which range was touched.
+"""GPU: batches of about half a round, where the gather stops asking the index pass which range was touched, and batches
+of as many arrivals, of which few are valid, or none.
 
 Against plain torch: the mean of at most four addends of a worker each, exact in float64 and rounded once per addition in
 float32 (three additions, a scaling by a power of two that is exact): within 3 * 2**-24 of the addends' magnitudes."""
@@ -63,3 +64,89 @@ def test_half_a_round(W, P, n, what):
         assert abs(norm - want) <= 4.5 * n * 2.0 ** -53 * want
         c = agg.get_counters()
         assert c == dict(accepted=int(flags.sum()), duplicate=0, stale=int(alive.sum()) if stale else 0, invalid=0)
+
+def _words(flags):
+    import torch
+    bits = torch.zeros(-(-flags.numel() // 64) * 64, dtype=torch.uint8, device="cuda")
+    bits[:flags.numel()] = flags
+    return (bits.view(-1, 8) * torch.tensor([1, 2, 4, 8, 16, 32, 64, 128], dtype=torch.uint8, device="cuda")).sum(1, dtype=torch.uint8).view(torch.int64)
+
+
+class _Buffer:
+    """Every worker's packets of one gradient (the same for all: the mean then says how many arrived) at shuffled slots."""
+
+    def __init__(self, W, P, n, rnd=ROUND):
+        import torch
+        import paper_2605_01989_amd as dblp
+        self.agg = agg = dblp.Aggregator(W, n, P, [0], [n])
+        gen = torch.Generator(device="cuda").manual_seed(W + n)
+        self.grad = torch.randn(n, generator=gen, device="cuda")
+        self.slots = W * agg.n_pkts
+        self.slot_of = torch.randperm(self.slots, generator=gen, device="cuda").view(W, -1)
+        self.u = torch.rand(W, agg.n_pkts, generator=gen, device="cuda")
+        self.src = torch.empty(self.slots, dtype=torch.int16, device="cuda")
+        self.fill(rnd)
+
+    def fill(self, rnd):
+        import torch
+        self.packets = torch.empty(self.slots * self.agg.stride, dtype=torch.uint8, device="cuda")
+        for w in range(self.agg.W):
+            self.agg.packetize(w, rnd, self.grad, 0, 0, self.agg.n_pkts, self.packets, self.src, d_slot_map=self.slot_of[w].int())
+
+    def mask(self, alive):
+        import torch
+        by_slot = torch.empty(self.slots, dtype=torch.bool, device="cuda")
+        by_slot[self.slot_of.reshape(-1)] = alive.reshape(-1)
+        return _words(by_slot)
+
+
+@pytest.mark.parametrize("W,P,n", [(4, 256, 300_000), (3, 366, 5_000_003), (8, 366, 30_000_001), (4, 16374, 40_000_000)])
+def test_few_of_many_slots(W, P, n):
+    """Batches over the whole buffer whose masks leave nothing, a hundredth of the range, a hundredth of the packets, and
+    nearly all; a round of another counter before the last."""
+    import torch
+    b = _Buffer(W, P, n)
+    agg, pkts = b.agg, b.agg.n_pkts
+    seq = torch.arange(pkts, device="cuda")
+    alive = torch.zeros(W, pkts, dtype=torch.bool, device="cuda")
+    copies = 0
+    out = torch.empty(n, device="cuda")
+    agg.begin_round(ROUND)
+    for k, flags in enumerate((b.u < -1, ((seq >= pkts // 3) & (seq < pkts // 3 + 1 + pkts // 100)).expand(W, pkts), b.u < 0.01, b.u < 0.98)):
+        if k == 3:
+            b.fill(ROUND + 1)
+            agg.apply_arrivals(b.packets, b.src, b.slots)
+            agg.apply_arrivals(b.packets, b.src, b.slots)
+            b.fill(ROUND)
+        copies += int((flags & alive).sum())
+        alive |= flags
+        agg.apply_arrivals(b.packets, b.src, b.slots, b.mask(flags))
+        agg.finalize(out)
+        got = alive.double().sum(0).repeat_interleave(P)[:n]
+        want = got * b.grad.double() / W
+        assert bool(((out.double() - want).abs() <= 4 * 2.0 ** -24 * W * want.abs()).all())
+        assert agg.get_counters() == dict(accepted=int(alive.sum()), duplicate=copies, stale=2 * b.slots if k == 3 else 0, invalid=0)
+
+
+def test_few_of_many_slots_take_few_slots_time():
+    """What the gather of a whole buffer costs where a hundredth of the range is alive, or nothing of this round."""
+    import torch
+    from paper_2605_01989_amd import binding
+    W, P, n = 8, 366, 124_000_000
+    b = _Buffer(W, P, n)
+    agg, pkts = b.agg, b.agg.n_pkts
+    seq = torch.arange(pkts, device="cuda")
+    some = b.mask(((seq >= pkts // 3) & (seq < pkts // 3 + pkts // 100)).expand(W, pkts))
+    agg.profile_enable((1 << binding.K_GATHER) | (1 << binding.K_GATHER_DIRECT))
+
+    def gather(rnd, mask):
+        times = []
+        for _ in range(9):
+            agg.begin_round(rnd)
+            agg.apply_arrivals(b.packets, b.src, b.slots, mask)
+            times.append(agg.profile_read(binding.K_GATHER)[0] + agg.profile_read(binding.K_GATHER_DIRECT)[0])
+        return sorted(times)[4]
+
+    full = gather(ROUND, None)
+    assert gather(ROUND, some) <= 0.06 * full
+    assert gather(ROUND + 1, None) <= 0.03 * full
