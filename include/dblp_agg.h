@@ -218,7 +218,10 @@ int dblp_packetize_list(dblp_ctx* ctx, uint16_t round, const float* const* h_gra
  * already in the bitmap -> duplicate; otherwise accepted: bitmap bit set and payload added
  * to the accumulator.  If two copies of one packet arrive in the same batch the earlier
  * arrival is used.  The sum over workers of one packet is formed in worker order, so the
- * result does not depend on the arrival permutation.  Requires begin_round. */
+ * result does not depend on the arrival permutation.  Requires begin_round.
+ * Large dense batches (from 50 to 600 MB of packets on, by worker count and packet length) are gathered in bursts: one block
+ * per CU holds most of the CU's LDS (up to 158 of 160 KB) and of its registers until the batch is done, so that kernels on
+ * other streams that use LDS start when it is: 0.1 to 4 ms. */
 int dblp_apply_arrivals(dblp_ctx* ctx, const void* d_packets, const uint16_t* d_src_worker,
                         uint64_t n_slots, const uint64_t* d_mask_words, const uint32_t* d_order,
                         uint64_t n_arrivals);
@@ -320,6 +323,8 @@ int dblp_get_prev_norm(const dblp_ctx* ctx, double* h_norm, int* h_have);
 #define DBLP_K_COUNT 5
 int dblp_profile_enable(dblp_ctx* ctx, int on);
 int dblp_profile_read(dblp_ctx* ctx, int kernel, double* h_total_ms, uint64_t* h_launches);
+/* Of the DBLP_K_GATHER launches that dblp_profile_read returned last, those that gathered in bursts (see dblp_apply_arrivals). */
+int dblp_profile_bursts(const dblp_ctx* ctx, uint64_t* h_bursts);
 
 /* Text of the last error on this context (valid until the next call on it). */
 const char* dblp_last_error(const dblp_ctx* ctx);

@@ -25,7 +25,7 @@ ACCMODE_SINGLE, ACCMODE_PAIR, ACCMODE_SEARCH = 0, 1, 2
 EXPORTS = ["dblp_create", "dblp_destroy", "dblp_layout", "dblp_accumulator_copies", "dblp_accumulator_policy", "dblp_accumulator_info", "dblp_accumulator_ptr", "dblp_begin_round", "dblp_packetize", "dblp_packetize_list",
            "dblp_apply_arrivals", "dblp_apply_arrivals_queue", "dblp_loss_account", "dblp_probe_polls", "dblp_finalize", "dblp_phase_signal",
            "dblp_get_bitmap", "dblp_get_counters", "dblp_set_prev_norm", "dblp_get_prev_norm",
-           "dblp_last_error", "dblp_profile_enable", "dblp_profile_read", "dblp_policy_two_level", "dblp_policy_three_level", "dblp_policy_linear", "dblp_clr_init", "dblp_clr_step",
+           "dblp_last_error", "dblp_profile_enable", "dblp_profile_read", "dblp_profile_bursts", "dblp_policy_two_level", "dblp_policy_three_level", "dblp_policy_linear", "dblp_clr_init", "dblp_clr_step",
            "dblp_sumsq_static", "dblp_sumsq_static_error"]
 
 
@@ -89,6 +89,7 @@ def lib():
         L.dblp_get_prev_norm.argtypes = [vp, ctypes.POINTER(dbl), ctypes.POINTER(i32)]
         L.dblp_profile_enable.argtypes = [vp, i32]
         L.dblp_profile_read.argtypes = [vp, i32, ctypes.POINTER(dbl), ctypes.POINTER(u64)]
+        L.dblp_profile_bursts.argtypes = [vp, ctypes.POINTER(u64)]
         L.dblp_last_error.argtypes = [vp]
         L.dblp_last_error.restype = ctypes.c_char_p
         for name in ("dblp_policy_two_level", "dblp_policy_three_level", "dblp_policy_linear"):
@@ -290,6 +291,12 @@ class Aggregator:
         ms, n = ctypes.c_double(), ctypes.c_uint64()
         self._check(lib().dblp_profile_read(self._h, kernel, ctypes.byref(ms), ctypes.byref(n)))
         return ms.value, int(n.value)
+
+    def profile_bursts(self) -> int:
+        """Of the K_GATHER launches that profile_read returned last, those in bursts."""
+        n = ctypes.c_uint64()
+        self._check(lib().dblp_profile_bursts(self._h, ctypes.byref(n)))
+        return int(n.value)
 
     def set_prev_norm(self, norm):
         self._check(lib().dblp_set_prev_norm(self._h, 0.0 if norm is None else norm, int(norm is not None)))

@@ -893,26 +893,36 @@ __device__ __forceinline__ BatchInfo whole_round(const Geo& g) {
     return bi;
 }
 
-// any[at] says whether the index pass met a valid arrival.  (Never no when it did; where launches are recorded and told
-// again it may be yes when it did not.)  A gather clears the other word, for the next batch that uses one.
-__device__ __forceinline__ bool some_arrived(u64* __restrict__ any, u32 at) {
-    if (!any) return true;
-    if (blockIdx.x == 0 && threadIdx.x == 0) any[at ^ 1u] = 0;
-    return any[at] != 0;
+// What a gather launch is told of its batch, and two kinds of words it may use:
+//   flags[F_ANY + i] says whether the index pass met a valid arrival.  (Never no when it did; where launches are recorded and
+//                    told again it may be yes when it did not.)  A gather clears the other one, for the next batch that uses one.
+//   flags[F_TOOK]    says whether the gather_burst launch before took the batch.
+enum { B_WHOLE = 1, B_ANY = 2, B_ANY_AT = 4, B_ASKED = 8 };
+enum { F_ANY = 0, F_TOOK = 2, F_COUNT };
+__device__ __forceinline__ bool some_arrived(u64* __restrict__ flags, u32 batch) {
+    if (!(batch & B_ANY)) return true;
+    const u32 at = batch & B_ANY_AT ? 1u : 0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) flags[F_ANY + (at ^ 1u)] = 0;
+    return flags[F_ANY + at] != 0;
 }
 
 // DENSE: the host knows that the batch is dense; otherwise the index pass's tallies decide.
+enum { TOLD_DENSE = 0, TOLD_SPARSE, TOLD_BURST };
 template <int NP, int G, int D, int NW, u32 LEAD, bool DENSE>
 __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void gather_stream(
     Geo g, const uint8_t* __restrict__ packets, u64* __restrict__ pending, u64* __restrict__ bitmap,
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
     const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters,
     u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
-    GatherShape dense, GatherShape sparse, u32 cus, u32 heavy, u32 table_at, u32 burst_seq, u32 whole, u64* __restrict__ any, u32 any_at, u32* __restrict__ told) {
+    GatherShape dense, GatherShape sparse, u32 cus, u32 heavy, u32 table_at, u32 batch, u64* __restrict__ flags, u32* __restrict__ told) {
     extern __shared__ u32 sh_dyn[];                 // per wave: slots [W rounded up][sub + 1]; then the bucket table (table_at words in, 0: not there)
     __shared__ u32 sh_tally[NW * 5];
     const u32* fs = g.first_seq;
-    const bool some = some_arrived(any, any_at);
+    if (!DENSE && batch & B_ASKED && flags[F_TOOK]) {
+        if (!DENSE && told && blockIdx.x == 0 && threadIdx.x == 0) *told = TOLD_BURST;
+        return;
+    }
+    const bool some = some_arrived(flags, batch);
     if (table_at) {
         u32* tab = sh_dyn + table_at;
         for (u32 i = threadIdx.x; i <= g.B; i += blockDim.x) tab[i] = g.first_seq[i];
@@ -920,18 +930,18 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     }
     // block 0 books the index pass's tallies; the barriers in there cover the table too
     BatchInfo bi;
-    if (DENSE && whole && blockIdx.x) {
+    const bool whole = DENSE && batch & B_WHOLE;
+    if (whole && blockIdx.x) {
         if (!some) return;
         bi = whole_round(g);
     } else {
-        bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0 && !burst_seq, sh_tally);
-        if (DENSE && whole && bi.hi) bi = whole_round(g);
+        bi = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0 && (DENSE || !(batch & B_ASKED)), sh_tally);     // (a gather_burst launch before has booked them)
+        if (whole && bi.hi) bi = whole_round(g);
     }
-    if (DENSE && whole) __syncthreads();
+    if (whole) __syncthreads();
     const bool is_sparse = !DENSE && batch_is_sparse(bi, g.W);
-    if (!DENSE && told && blockIdx.x == 0 && threadIdx.x == 0) *told = is_sparse;    // for the trace group of the launch
+    if (!DENSE && told && blockIdx.x == 0 && threadIdx.x == 0) *told = is_sparse ? TOLD_SPARSE : TOLD_DENSE;    // for the trace group of the launch
     if (bi.hi == 0) return;                         // no candidate in this batch (uniform over the grid)
-    if (!DENSE && burst_seq && !is_sparse && bi.hi - bi.lo >= burst_seq) return;       // the gather_burst launch before took it and booked the tallies
     if (is_sparse)
         gather_groups<2, 1, 2, NW, true, LEAD>(g, bi, sparse, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
     else {
@@ -985,7 +995,7 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
     const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters,
     u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
-    u32 r_max, u32 r_step, u32 n_piece, u32 table_at, u32 image_at, u32 min_seq, u32 through_seq, u32 whole, u64* __restrict__ any, u32 any_at) {
+    u32 r_max, u32 r_step, u32 n_piece, u32 table_at, u32 image_at, u32 min_seq, u32 through_seq, u32 batch, u64* __restrict__ flags) {
     extern __shared__ __attribute__((aligned(16))) u32 sh_dyn[];
     __shared__ u32 sh_tally[BURST_WAVES * 5];
     __shared__ u32 sh_new[3][BURST_MAX / 32], sh_old[3][BURST_MAX / 32];     // by packet of the group: new copies; delivered before
@@ -998,7 +1008,7 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
     u32* const sh_len = sh_elem + 4 * r_max;                    // [2][r_max]: floats | home << 16
     float* const image = (float*)(sh_dyn + image_at);
     const u32* fs = g.first_seq;
-    const bool some = some_arrived(any, any_at);
+    const bool some = some_arrived(flags, batch);
     if (table_at) {
         u32* tab = sh_dyn + table_at;
         for (u32 i = tid; i <= g.B; i += BURST_WAVES * WAVE) tab[i] = g.first_seq[i];
@@ -1006,6 +1016,7 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
     }
     if (tid < 3 * (BURST_MAX / 32)) sh_new[0][tid] = sh_old[0][tid] = 0;
     BatchInfo bi = whole_round(g);
+    const bool whole = batch & B_WHOLE;
     if (!whole || blockIdx.x == 0) {
         const BatchInfo found = fold_index_tallies(block_tallies, n_tally_rows, counters, blockIdx.x == 0, sh_tally);
         if (!whole || found.hi == 0) bi = found;
@@ -1014,7 +1025,10 @@ __global__ __launch_bounds__(BURST_WAVES * WAVE) void gather_burst(
         __syncthreads();
     }
     // A batch that is none of this kernel's is left to the gather_stream launch that follows.
-    if (bi.hi == 0 || (min_seq && (batch_is_sparse(bi, g.W) || bi.hi - bi.lo < min_seq))) return;
+    const bool mine = bi.hi != 0 && (min_seq == 0 || (!batch_is_sparse(bi, g.W) && bi.hi - bi.lo >= min_seq &&
+                                                      burst_pays(bi.cand, bi.hi - bi.lo, g.W, gridDim.x, r_max, NP * n_piece)));
+    if (min_seq && blockIdx.x == 0 && tid == 0) flags[F_TOOK] = mine;
+    if (!mine) return;
     // Groups of equal size but for one step: with all groups as long as the longest, the last turn of 4 x 61 M in 64
     // KB packets left two CUs in three idle (7.3 turns of two packets and an eighth of that; now seven of two and one of
     // one).
@@ -1908,8 +1922,8 @@ __global__ __launch_bounds__(256) void classify_rw(const uint8_t* __restrict__ s
 // ------------------------------------------------------------------------------------------
 // What the context's gather_burst launches are given (burst_plan); fn null: none are made.
 typedef void (*burst_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, u64*, double*, float,
-                         u32, u32, u32, u32, u32, u32, u32, u32, u64*, u32);
-struct BurstPlan { burst_fn fn; u32 r_max, r_step, n_piece, table_at, image_at, min_seq, through_seq; size_t lds; };
+                         u32, u32, u32, u32, u32, u32, u32, u32, u64*);
+struct BurstPlan { burst_fn fn; u32 kb, r_max, r_step, n_piece, table_at, image_at, min_seq, through_seq; size_t lds; };
 
 struct dblp_ctx {
     Geo g;
@@ -1921,8 +1935,8 @@ struct dblp_ctx {
     int n_cus;
     // device state
     u32* d_first_seq; u64* d_b_off; u64* d_b_cnt; u32* d_hint;
-    u64* d_bitmap; u64* d_pending; u64* d_counters; u64* d_any;     // d_any: two words behind the counters, in turn
-    u32 any_no;             // batches that used one of them
+    u64* d_bitmap; u64* d_pending; u64* d_counters; u64* d_flags;   // F_COUNT words behind the counters
+    u32 any_no;             // batches that used one of the first two
     // accumulator: one or two copies (d_acc[1] == d_acc[0] when there is one); each copy's
     // allocation ends with CLS_SCRATCH_BYTES that classify_rw may overwrite
     void* acc_alloc[2]; float* d_acc[2]; float* d_scratch[2];
@@ -1963,10 +1977,11 @@ struct dblp_ctx {
     double prev_norm; int have_prev;
     // optional per-kernel timing (HIP events on the context's stream)
     int profiling;          // bit k set: launches of kernel group k are bracketed by events
-    struct Timed { hipEvent_t a, b; int kernel; u32 told; };     // kernel < 0: minus the wanted groups; h_told[told] says which
+    struct Timed { hipEvent_t a, b; int kernel; u32 told; bool burst; };     // kernel < 0: minus the wanted groups; h_told[told] says which
     std::vector<Timed>* timed;        // recorded, not yet read
-    u32* h_told; u32* d_told;         // mapped host memory: a gather launch that decides on the device tells here what it was (0 dense, 1 sparse)
+    u32* h_told; u32* d_told;         // mapped host memory: a gather launch that decides on the device tells here what it was (TOLD_*)
     u32 n_told;                       // entries in use, by records not yet read
+    u64 n_burst;                      // of the dense gathers last read: those in bursts
     std::vector<hipEvent_t>* ev_pool; // free events
     char err[256];
 };
@@ -1983,8 +1998,8 @@ static hipEvent_t prof_event(dblp_ctx* c) {
 // Brackets one kernel launch with events when profiling is on.  `told`: the launch decides on the device whether it
 // is a dense or a sparse gather, so the bracket's group is known when it is read.
 struct ProfScope {
-    dblp_ctx* c; hipEvent_t a; int kernel; u32 at;
-    ProfScope(dblp_ctx* c_, int kernel_, bool told = false) : c(c_), a(nullptr), kernel(kernel_), at(0) {
+    dblp_ctx* c; hipEvent_t a; int kernel; u32 at; bool burst;
+    ProfScope(dblp_ctx* c_, int kernel_, bool told = false, bool burst_ = false) : c(c_), a(nullptr), kernel(kernel_), at(0), burst(burst_) {
         const int want = c->profiling & (told ? 1 << DBLP_K_GATHER | 1 << DBLP_K_GATHER_DIRECT : 1 << kernel);
         if (!want || (told && c->n_told >= PROF_MAX_RECORDS)) return;
         if (!(a = prof_event(c))) return;
@@ -1998,7 +2013,7 @@ struct ProfScope {
         hipEvent_t b = prof_event(c);
         if (!b) { c->ev_pool->push_back(a); a = nullptr; return; }
         (void)hipEventRecord(b, c->stream);
-        if (c->timed->size() < c->timed->capacity()) c->timed->push_back({a, b, kernel, at});   // never reallocates
+        if (c->timed->size() < c->timed->capacity()) c->timed->push_back({a, b, kernel, at, burst});   // never reallocates
         else { c->ev_pool->push_back(a); c->ev_pool->push_back(b); }                            // buffer full: drop the sample
         a = nullptr;
     }
@@ -2268,6 +2283,7 @@ static BurstPlan burst_plan(const Geo& g, u32 cus) {
     b.n_piece = (n_pass + 3) / 4;                       // five passes are two pieces (16 x 100 M of 1200 floats: 1342 us as one, 1317 as two)
     const u32 np = (n_pass + b.n_piece - 1) / b.n_piece;
     b.n_piece = (n_pass + np - 1) / np;
+    b.kb = np * b.n_piece;
     b.r_max = r; b.r_step = step;
     b.table_at = table_words ? BURST_INFO_LDS(g.W, r) : 0u;
     b.image_at = image_at(r);
@@ -2354,7 +2370,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     ok = ok && hipMalloc(&c->d_bitmap, g.W * g.words_pw * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_pending, (u64)g.W * n_pkts * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_home, (n_pkts + 7) / 8 * 8 + 8) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_counters, (C_COUNT + 2) * sizeof(u64)) == hipSuccess;
+    ok = ok && hipMalloc(&c->d_counters, (C_COUNT + F_COUNT) * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_need, pairs * sizeof(u32)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_totals, probe_blocks(c, pairs) * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_partials, PARTIALS_WORDS(c->max_partials) * sizeof(u64)) == hipSuccess;
@@ -2383,7 +2399,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
         g.hint = c->d_hint;
     }
     c->d_sumsq_rows = (double*)(c->d_accept_rows + ACCEPT_ROWS);
-    c->d_any = c->d_counters + C_COUNT;
+    c->d_flags = c->d_counters + C_COUNT;
     c->burst = burst_plan(g, (u32)c->n_cus);
     // The limit is the kernel's, not the context's: the same whatever the plan, so that contexts which share an instance
     // do not lower it for each other.
@@ -2397,7 +2413,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
                        c->d_pending, n_pending, NONE64);
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (g.W * g.words_pw + 255) / 256, 16)), dim3(256), 0, c->stream,
                        c->d_bitmap, g.W * g.words_pw, 0ull);
-    hipLaunchKernelGGL(fill_u64, dim3(1), dim3(64), 0, c->stream, c->d_counters, (u64)(C_COUNT + 2), 0ull);
+    hipLaunchKernelGGL(fill_u64, dim3(1), dim3(64), 0, c->stream, c->d_counters, (u64)(C_COUNT + F_COUNT), 0ull);
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (probe_blocks(c, pairs) + 255) / 256, 16)), dim3(256), 0, c->stream,
                        c->d_totals, probe_blocks(c, pairs), 0ull);
     hipLaunchKernelGGL(fill_u64, dim3(8), dim3(256), 0, c->stream, c->d_partials, (u64)PARTIALS_WORDS(c->max_partials), 0ull);
@@ -2558,7 +2574,7 @@ extern "C" int dblp_packetize_list(dblp_ctx* c, uint16_t round, const float* con
 }
 
 typedef void (*gather_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, u64*, double*, float,
-                          GatherShape, GatherShape, u32, u32, u32, u32, u32, u64*, u32, u32*);
+                          GatherShape, GatherShape, u32, u32, u32, u32, u64*, u32*);
 
 // The instance for `np` KB of a packet per step; few: one to three workers.
 template <bool DENSE, u32 LEAD>
@@ -2638,17 +2654,22 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
     if (sparse.n_piece >= 8 && sparse.sub_log2 > 2 && g.n_pkts <= 64u * (u32)c->n_cus) sparse.sub_log2 = 2;
     sparse.blocks = grid_for(c, ((u64)g.n_pkts + (1u << sparse.sub_log2) - 1) >> sparse.sub_log2, nw == 16 ? 1 : 4);
 
-    // Bursts.  A batch of at least burst.min_seq packets per worker covers that many sequence numbers or more.  Known to be
-    // dense, it is one gather_burst launch; where the blocks have to find out, that launch leaves a sparse batch to a
-    // gather_stream launch after it, and the other way round.  The second launch costs about 3 us, so it is made
-    // for batches of 256 MB and more only, which take 60 us and more as a dense step and 130 as a retransmission.
+    // Bursts.  A batch of at least burst.min_seq packets per worker covers that many sequence numbers or more.  Where the number
+    // of arrivals alone says that it is dense enough, it is one gather_burst launch.  Where the blocks have to find out (or
+    // with a mask, whose lost slots count as arrivals), that launch leaves a batch that is not to a gather_stream launch
+    // after it, which ends at once if it was.  The second launch costs 2 to 4 us, so it is made for batches of 256 MB and more only,
+    // which take 60 us and more as a dense step and 130 as a retransmission; and not for many arrivals of two or three
+    // workers, whose gather_stream of both kinds has fewer waves in flight (half of 2 x 150 M 297 us, 325 asked).
     const BurstPlan& burst = c->burst;
-    const bool in_bursts = burst.fn && n_arrivals >= (u64)burst.min_seq * g.W && (is_dense || n_arrivals * g.stride >= 256000000ull);
-
+    const bool enough = burst.fn && n_arrivals >= (u64)burst.min_seq * g.W;
+    const bool known = enough && is_dense && !d_mask && burst_pays(n_arrivals, g.n_pkts, g.W, (u32)c->n_cus, burst.r_max, burst.kb);
+    const bool asked = enough && !known && n_arrivals * g.stride >= 256000000ull && !(few && is_dense && !d_mask);
+    const bool in_bursts = known || asked, dense_only = is_dense && !asked;
     const u64 turns = in_bursts ? 8 : (groups + dense.blocks - 1) / dense.blocks;
-    const u32 whole = n_arrivals * WHOLE_DIV >= pairs && (!d_mask || turns <= 2);
-    u64* const any = whole && turns > 4 ? c->d_any : nullptr;           // (two turns for nothing take 1 us; the word costs 0.4 to 1.5)
+    const bool whole = n_arrivals * WHOLE_DIV >= pairs && !asked && (!d_mask || turns <= 2);
+    const bool any = whole && turns > 4;                // (two turns for nothing take 1 us; the word costs 0.4 to 1.5)
     const u32 any_at = any ? c->any_no++ & 1u : 0u;
+    const u32 batch = (whole ? B_WHOLE : 0) | (any ? B_ANY : 0) | (any_at ? B_ANY_AT : 0) | (asked ? B_ASKED : 0);
 
     u32 n_tally_rows = 0;
     {
@@ -2661,7 +2682,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
                 : (d_queue ? index_arrivals<false, true> : index_arrivals<false, false>);
         hipLaunchKernelGGL(idx, dim3(grid), dim3(256), lds ? table : 0, c->stream, g,
                            (const uint8_t*)d_packets, d_src_worker, (u64)n_slots, (const u64*)d_mask, d_order,
-                           (const u64*)d_queue, (u64)n_arrivals, (u32)c->round, c->d_pending, c->d_block_tallies, any ? any + any_at : nullptr);
+                           (const u64*)d_queue, (u64)n_arrivals, (u32)c->round, c->d_pending, c->d_block_tallies, any ? c->d_flags + F_ANY + any_at : nullptr);
         n_tally_rows = grid;
     }
     const float inv_w = c->fold ? 1.0f / (float)g.W : 1.0f;   // exact for the powers of two it is used with
@@ -2669,7 +2690,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         u32 slots = 0, grid = dense.blocks;
         for (u32 l = 0; l <= (dense.sub_log2 > 2 ? dense.sub_log2 : 2); ++l)        // whatever the launch may choose
             if (GS_TEAM_LDS(g.W, l) > slots) slots = GS_TEAM_LDS(g.W, l);
-        if (!is_dense) {
+        if (!dense_only) {
             if (GS_TEAM_LDS(g.W, sparse.sub_log2) > slots) slots = GS_TEAM_LDS(g.W, sparse.sub_log2);
             if (sparse.blocks > grid) grid = sparse.blocks;
         }
@@ -2677,20 +2698,20 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         const size_t table = ((size_t)g.B + 1) * sizeof(u32);
         const u32 table_at = table <= IDX_TABLE_LDS_MAX ? nw * slots : 0u;
         if (table_at) lds += table;
-        const gather_fn kern = is_dense ? gather_kernel<true>(nw, lead, few, np) : gather_kernel<false>(nw, lead, few, np);
-        ProfScope ps(c, small ? DBLP_K_GATHER_DIRECT : DBLP_K_GATHER, !is_dense && !small);
+        const gather_fn kern = dense_only ? gather_kernel<true>(nw, lead, few, np) : gather_kernel<false>(nw, lead, few, np);
+        ProfScope ps(c, small ? DBLP_K_GATHER_DIRECT : DBLP_K_GATHER, !dense_only && !small && !known, known);
         if (in_bursts) {
             if ((u32)c->n_cus > c->rows_used) c->rows_used = (u32)c->n_cus;
             hipLaunchKernelGGL(burst.fn, dim3(c->n_cus), dim3(BURST_WAVES * WAVE), burst.lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap,
                                c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
                                c->d_accept_rows, c->d_sumsq_rows, inv_w, burst.r_max, burst.r_step, burst.n_piece, burst.table_at, burst.image_at,
-                               is_dense ? 0u : burst.min_seq, burst.through_seq, whole, any, any_at);
+                               known ? 0u : burst.min_seq, burst.through_seq, batch, c->d_flags);
         }
-        if (!in_bursts || !is_dense) {
+        if (!known) {
             if (grid > c->rows_used) c->rows_used = grid;
             hipLaunchKernelGGL(kern, dim3(grid), dim3(nw * WAVE), lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap,
                                c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
-                               c->d_accept_rows, c->d_sumsq_rows, inv_w, dense, sparse, (u32)c->n_cus, heavy, table_at, in_bursts ? burst.min_seq : 0u, whole, any, any_at, ps.d_told());
+                               c->d_accept_rows, c->d_sumsq_rows, inv_w, dense, sparse, (u32)c->n_cus, heavy, table_at, batch, c->d_flags, ps.d_told());
         }
     }
     LAUNCH_CHECK(c, "apply_arrivals");
@@ -2947,23 +2968,32 @@ extern "C" int dblp_profile_read(dblp_ctx* c, int kernel, double* h_total_ms, ui
     if (!c || !h_total_ms || !h_launches || kernel < 0 || kernel >= DBLP_K_COUNT) return DBLP_EINVAL;
     HIP_TRY(c, hipSetDevice(c->device));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    double total = 0.0; u64 n = 0;
+    double total = 0.0; u64 n = 0, n_burst = 0;
     size_t kept = 0;                      // compact in place: no allocation on this path
     for (size_t i = 0; i < c->timed->size(); ++i) {
         dblp_ctx::Timed t = (*c->timed)[i];
         if (t.kernel < 0) {               // the launch has ended and told its group
             const int wanted = -t.kernel;
-            t.kernel = *(volatile u32*)(c->h_told + t.told) ? DBLP_K_GATHER_DIRECT : DBLP_K_GATHER;
+            const u32 told = *(volatile u32*)(c->h_told + t.told);
+            t.kernel = told == TOLD_SPARSE ? DBLP_K_GATHER_DIRECT : DBLP_K_GATHER;
+            t.burst = told == TOLD_BURST;
             if (!((wanted >> t.kernel) & 1)) { c->ev_pool->push_back(t.a); c->ev_pool->push_back(t.b); continue; }
         }
         if (t.kernel != kernel) { (*c->timed)[kept++] = t; continue; }
         float ms = 0.f;
-        if (hipEventElapsedTime(&ms, t.a, t.b) == hipSuccess) { total += ms; ++n; } else (void)hipGetLastError();
+        if (hipEventElapsedTime(&ms, t.a, t.b) == hipSuccess) { total += ms; ++n; n_burst += t.burst; } else (void)hipGetLastError();
         c->ev_pool->push_back(t.a); c->ev_pool->push_back(t.b);   // within the reserved capacity
     }
     c->timed->resize(kept);
     c->n_told = 0;                        // no record waits for an entry any more
     *h_total_ms = total; *h_launches = n;
+    if (kernel == DBLP_K_GATHER) c->n_burst = n_burst;
+    return DBLP_OK;
+}
+
+extern "C" int dblp_profile_bursts(const dblp_ctx* c, uint64_t* h_bursts) {
+    if (!c || !h_bursts) return DBLP_EINVAL;
+    *h_bursts = c->n_burst;
     return DBLP_OK;
 }
 

@@ -58,4 +58,20 @@ struct BurstTurns {
     }
 };
 
+// Whether a batch of `cand` packets in a range of n_seq sequence numbers has enough of them per number for bursts.  Each
+// turn of a burst has a part that does not overlap with its loads, and a step has room for several workers' pieces:
+// where few workers delivered a packet, neither is made up for by the stores.  So many packets per number: 3.2 where the
+// blocks take up to six turns; where they take more, 1 for packets in pieces, 1.9 for those of one KB (`kb`), 1.6 for
+// the others; and where there are few workers, four in five of them.  us of a pass, gather_stream and bursts, by the
+// share of the packets that arrived in one batch over the round: 2 workers x 150 M elements in 1472-byte packets (15 turns)
+// half 297, 387, 0.6 330, 365, 0.8 384, 351; 8 x 124 M (13) 0.13 311, 353, 0.2 361, 361, a quarter 399, 369; 8 x 60 M in 528-byte ones (7)
+// 0.13 308, 392, 0.2 342, 364, a quarter 365, 345; 8 x 25.6 M (3) 0.2 80, 93, a third 100, 103, half 131, 128; 16 x 34 M (4) 0.13 116,
+// 128, a quarter 166, 166, half 287, 267; 5 x 60 M in 2816-byte ones (6) half 171, 184, 0.8 244, 245, all 294, 283; 16 x 100 M in
+// 4112-byte ones (12) 0.13 282, 261; 8 x 124 M in 8992-byte ones (13) 0.13 201, 200, 0.16 245, 225.
+constexpr bool burst_pays(uint64_t cand, uint64_t n_seq, uint32_t n_workers, uint32_t n_blocks, uint32_t r_max, uint32_t kb) {
+    uint32_t tenths = n_seq <= 6ull * r_max * n_blocks ? 32 : kb > 4 ? 10 : kb == 1 ? 19 : 16;
+    if (tenths > 8 * n_workers) tenths = 8 * n_workers;
+    return cand * 10 >= n_seq * tenths;
+}
+
 #endif

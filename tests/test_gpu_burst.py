@@ -29,7 +29,8 @@ class _Case:
     def __init__(self, W, P, n, kind, seed, **acc):
         import torch
         import paper_2605_01989_amd as dblp
-        self.dblp, self.torch, self.W, self.P = dblp, torch, W, P
+        from paper_2605_01989_amd import binding
+        self.dblp, self.binding, self.torch, self.W, self.P = dblp, binding, torch, W, P
         cnt = _sizes(kind, n, P)
         off = [0]
         for c in cnt:
@@ -63,6 +64,7 @@ class _Case:
         agg = ctx or self.make()
         if policy is not None:
             agg.accumulator_policy(policy)
+        agg.profile_enable(1 << self.binding.K_GATHER)
         agg.begin_round(ROUND)
         for b in batches:
             edge = [self.n_pkts * i // pieces for i in range(pieces + 1)]
@@ -74,10 +76,13 @@ class _Case:
         agg.get_bitmap(bitmap)
         agg.finalize(out)
         norm = agg.phase_signal()[0]
-        return out, bitmap, agg.get_counters(), norm
+        agg.profile_read(self.binding.K_GATHER)
+        return out, bitmap, agg.get_counters(), norm, agg.profile_bursts()
 
-    def check(self, batches, pieces, policy=None):
+    def check(self, batches, pieces, policy=None, bursts=1):
+        """bursts: how many of the batches are to be gathered in bursts when they come whole."""
         got, ref = self.receive(batches, 1, policy=policy), self.receive(batches, pieces)
+        assert (got[4], ref[4]) == (bursts, 0)
         assert self.torch.equal(got[0].view(self.torch.int32), ref[0].view(self.torch.int32))
         assert self.torch.equal(got[1], ref[1])
         assert got[2] == ref[2]
@@ -113,7 +118,7 @@ def test_bursts_give_the_bits_of_the_general_path(W, P, n, kind):
 
 @pytest.mark.parametrize("copies", [1, 2])
 @pytest.mark.parametrize("W,P,n,kind", [(4, 128, 11_000_000, "ragged"), (16, 256, 8_800_001, "ragged"), (16, 1200, 13_000_001, "ragged"),
-                                        (16, 9000, 15_000_001, "ragged")])
+                                        (16, 9000, 15_000_001, "ragged"), (8, 128, 51_000_001, "ragged")])
 def test_bursts_add_to_spans_of_an_earlier_batch(W, P, n, kind, copies):
     """Half of the workers in one batch, the others in the next: spans are opened, updated, and, with two accumulator
     copies that take turns, updated in the copy they are in."""
@@ -126,7 +131,8 @@ def test_bursts_add_to_spans_of_an_earlier_batch(W, P, n, kind, copies):
     a[W // 2:] = False
     b[: W // 2] = False
     b[0] |= c.rand(c.n_pkts) < 0.5            # copies of what is there already
-    c.check([c.batch(a), c.batch(b)], 16, policy=binding.ACC_ALTERNATE if copies == 2 else None)
+    c.check([c.batch(a), c.batch(b)], 16, policy=binding.ACC_ALTERNATE if copies == 2 else None,
+            bursts=0 if W == 4 else 2)            # (of four workers two at a time are too few)
 
 
 @pytest.mark.parametrize("spread", [False, True])
@@ -141,7 +147,7 @@ def test_launches_that_decide_on_the_device(spread):
     else:
         alive[:, c.n_pkts // 3 + 5: c.n_pkts // 3 + 5 + int(c.n_pkts * 0.124)] = True
         alive &= c.rand(W, c.n_pkts) >= 0.03
-    c.check([c.batch(alive, dup=0.0)], 3 if spread else 40)
+    c.check([c.batch(alive, dup=0.0)], 3 if spread else 40, bursts=0 if spread else 1)
 
 
 def test_a_later_context_with_smaller_groups_leaves_an_earlier_one_its_own():
@@ -154,4 +160,45 @@ def test_a_later_context_with_smaller_groups_leaves_an_earlier_one_its_own():
     got, ref = c.receive([first], 1, ctx=ctx), c.receive([first], 40)
     small.check([small.batch(small.rand(W, small.n_pkts) >= 0.02)], 12)
     assert c.torch.equal(got[0].view(c.torch.int32), ref[0].view(c.torch.int32))
-    assert c.torch.equal(got[1], ref[1]) and got[2] == ref[2]
+    assert c.torch.equal(got[1], ref[1]) and got[2] == ref[2] and (got[4], ref[4]) == (1, 0)
+
+
+# (workers, floats, elements, share of the round) of thin batches over the round, of a share at which bursts pay, and at which
+# they do not; more and fewer than seven turns, packets of one KB and in pieces; 256 MB and more, where the blocks decide,
+# and less, where the number of arrivals does
+@pytest.mark.parametrize("W,P,n,share,bursts", [(2, 366, 100_000_000, 0.5, 0), (2, 366, 150_000_000, 0.9, 1), (8, 366, 50_000_000, 0.16, 0),
+                                                (8, 366, 80_000_000, 0.3, 1), (8, 128, 60_000_000, 0.15, 0), (8, 128, 60_000_000, 0.3, 1),
+                                                (8, 366, 25_600_000, 0.25, 0), (8, 366, 25_600_000, 0.5, 1), (8, 2243, 120_000_000, 0.16, 1),
+                                                (5, 700, 40_000_000, 0.6, 0)])
+def test_thin_batches(W, P, n, share, bursts):
+    c = _Case(W, P, n, "ragged", seed=W + n)
+    c.check([c.batch(c.rand(W, c.n_pkts) < share, dup=0.001)], 30, bursts=bursts)
+
+
+@pytest.mark.parametrize("share,bursts", [(0.03, 0), (0.98, 1)])
+@pytest.mark.parametrize("W,P,n", [(8, 366, 30_000_001), (16, 1024, 20_000_001)])
+def test_masked_batches(W, P, n, share, bursts):
+    """The whole buffer with a mask: the number of slots says nothing of what is alive.  Against the same packets as a queue, in pieces."""
+    c = _Case(W, P, n, "ragged", seed=n)
+    t = c.torch
+    b = c.batch(t.ones(W, c.n_pkts, dtype=t.bool, device="cuda"), dup=0.0)
+    slot, worker = b["queue"] & 0xFFFFFFFF, b["queue"] >> 32
+    alive = c.rand(b["n"]) < share                      # by slot
+    src = t.empty(b["n"], dtype=t.int16, device="cuda")
+    src[slot] = worker.to(t.int16)
+    bits = t.zeros(-(-b["n"] // 64) * 64, dtype=t.uint8, device="cuda")
+    bits[:b["n"]] = alive
+    words = (bits.view(-1, 8) * t.tensor([1, 2, 4, 8, 16, 32, 64, 128], dtype=t.uint8, device="cuda")).sum(1, dtype=t.uint8).view(t.int64)
+    agg = c.make()
+    agg.profile_enable(1 << c.binding.K_GATHER)
+    agg.begin_round(ROUND)
+    agg.apply_arrivals(b["packets"], src, b["n"], words, slot.int())
+    out = t.empty(c.n, device="cuda")
+    agg.finalize(out)
+    norm = agg.phase_signal()[0]
+    agg.profile_read(c.binding.K_GATHER)
+    keep = alive[slot]
+    ref = c.receive([dict(b, queue=b["queue"][keep].contiguous(), seq=b["seq"][keep])], 30)
+    assert (agg.profile_bursts(), ref[4]) == (bursts, 0)
+    assert t.equal(out.view(t.int32), ref[0].view(t.int32)) and agg.get_counters() == ref[2]
+    assert abs(norm - ref[3]) <= 1e-12 * ref[3]
