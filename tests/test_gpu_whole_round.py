@@ -128,6 +128,48 @@ def test_few_of_many_slots(W, P, n):
         assert agg.get_counters() == dict(accepted=int(alive.sum()), duplicate=copies, stale=2 * b.slots if k == 3 else 0, invalid=0)
 
 
+@pytest.mark.parametrize("masked", [False, True])
+def test_what_arrived_is_asked_on_every_replay(masked):
+    """A recorded round, told again on packets of this round, of another, and of this one again; masked: with the mask of
+    nearly all, of a hundredth, of nothing, and of nearly all."""
+    import torch
+    W, P, n = 8, 366, 30_000_001
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        b = _Buffer(W, P, n)
+        agg = b.agg
+        shares = (0.98, 0.01, -1.0, 0.98) if masked else (2.0, 2.0, -1.0, 2.0)
+        words = b.mask(b.u < 2)
+        out = torch.empty(n, device="cuda")
+
+        def receive():
+            agg.begin_round(ROUND)
+            agg.apply_arrivals(b.packets, b.src, b.slots, words if masked else None)
+            agg.finalize(out)
+
+        receive()
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        packets = b.packets
+        with torch.cuda.graph(graph, stream=side):
+            receive()
+        for share in shares:
+            alive = b.u < share
+            if masked:
+                words.copy_(b.mask(alive))
+            else:
+                b.fill(ROUND if share > 0 else ROUND + 1)
+                packets.copy_(b.packets)
+            out.fill_(7.0)
+            side.synchronize()
+            graph.replay()
+            norm = agg.phase_signal()[0]
+            want = alive.double().sum(0).repeat_interleave(P)[:n] * b.grad.double() / W
+            assert bool(((out.double() - want).abs() <= 4 * 2.0 ** -24 * W * want.abs()).all())
+            total = float(out.double().square().sum().sqrt())
+            assert abs(norm - total) <= 4.5 * n * 2.0 ** -53 * total
+
+
 def test_few_of_many_slots_take_few_slots_time():
     """What the gather of a whole buffer costs where a hundredth of the range is alive, or nothing of this round."""
     import torch
