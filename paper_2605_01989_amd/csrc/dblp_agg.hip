@@ -12,7 +12,7 @@
 //                    that an earlier batch delivered, sets the bitmap bits, then streams the
 //                    payloads of each packet from every delivering worker (16-byte loads,
 //                    worker order) into registers and writes the accumulator span once.
-//   gather_burst     the same for large dense batches, with the spans of many packets stored together.
+//   gather_burst     the same for large dense batches of two workers and more, with the spans of many packets stored together.
 // Every payload byte is read exactly once and the accumulator is written once per batch that
 // touches it; there are no floating-point atomics, so the sum is independent of the arrival
 // permutation.  The accumulator may exist in two copies placed in different thirds of the HBM
@@ -20,7 +20,7 @@
 // per-packet byte map records where each span lives.
 //
 // The probe (Sec. "Dynamically Changing Loss Tolerance"): probe_once (popcount of bitmap words + DPP wave reduction,
-// list lengths that the blocks tell each other, ordered compaction).  The mean of Alg. "Server" is formed as the payloads are summed when
+// list lengths that the blocks tell each other, ordered compaction), or loss_count and emit_retx where blocks are many.  The mean of Alg. "Server" is formed as the payloads are summed when
 // W is a power of two (the division is exact), and the gather kernels keep the sum of squares of
 // what they store, so finalize_pass only writes zeros where nothing arrived (and moves or copies
 // spans where the result is wanted elsewhere); for other W it divides and squares itself.
@@ -502,11 +502,11 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Unit u (16 bytes) of a packet of `len` floats in the grid that LEAD says: which of its floats are payload.
 __device__ __forceinline__ double squares(f4v v) {
     return (((double)v.x * (double)v.x + (double)v.y * (double)v.y) + (double)v.z * (double)v.z) + (double)v.w * (double)v.w;
 }
 
+// Unit u (16 bytes) of a packet of `len` floats in the grid that LEAD says: which of its floats are payload.
 template <u32 LEAD>
 struct SpanUnit {
     u32 u, n_tail;              // n_tail: floats of a last unit that is not full
@@ -964,8 +964,8 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
 // the block reads nothing.  In turn, a loop with this access pattern, 32 workers x 1472 B, 8.5 GB: stored at once per
 // packet 1711 us, in bursts of 23 KB 1629, of 70 KB and more 1450 to 1500; read only 1290.  Three things that looked
 // natural made it slower: loads of the next group in flight while the image goes out (8 workers, 9.8 GB: 1709 us
-// without, 1788 with), two blocks per CU (1927), and more than one step of loads in flight per wave (equal, or up to
-// 2 % slower).  What stays between two groups is kept short instead: a group's arrival index is loaded a whole group
+// without, 1788 with), two blocks per CU (1927), and a second step of loads in flight per wave (equal, or up to
+// 2 % slower; what larger steps cost stands at burst_kernel).  What stays between two groups is kept short instead: a group's arrival index is loaded a whole group
 // ahead and brought into LDS by each wave as it ends its share of the group before.
 //
 // Against gather_stream, us per launch (whole pass in brackets), buffers where the allocator put them:
@@ -1851,7 +1851,8 @@ __global__ __launch_bounds__(256) void sumsq_vec(const float* __restrict__ v, u6
     if (threadIdx.x == 0) mailbox[0] = total;
 }
 
-// The same in two launches, for calls that may overlap: sums per block, and their sum in the order of fold_partials.
+// The same in two launches, for calls without a context, whose words no call owns: sums per block, and their sum in the order of
+// fold_partials.  (Calls on one GPU share the array of sums, and the caller orders them.)
 __global__ __launch_bounds__(256) void sumsq_blocks(const float* __restrict__ v, u64 n, double* __restrict__ partials) {
     __shared__ double wsum[4];
     const double w = vec_sumsq(v, n);
@@ -2245,8 +2246,9 @@ static burst_fn burst_kernel(u32 np) {
 static bool units_from_packet(const Geo& g) { return !(g.P <= 1024 && (g.P + 255) / 256 < (g.P + 2 + 255) / 256); }
 static u32 unit_passes(const Geo& g, bool lead) { return lead ? (g.units + WAVE - 1) / WAVE : (g.P + 4 * WAVE - 1) / (4 * WAVE); }
 
-// The line between gather_burst and gather_stream, by the bytes
-// that a batch reads (us of a whole pass with gather_stream, with bursts; P = 366 unless said):
+// The line between gather_burst and gather_stream, by the bytes that a batch reads (measured on 256 CUs and not scaled
+// with their number: what a smaller part of the chip would ask for is not known; us of a whole pass with gather_stream,
+// with bursts; P = 366 unless said):
 //   8 workers and more   150 MB (8 x 5 M elements, 160 MB: 116, 113; 16 x 2 M, 128 MB: 106, 106; 32 x 1 M: 114, 116)
 //   5 to 7               300 MB (6 x 10 M: 156, 155; 5 x 10 M: 149, 149; 6 x 25 M: 281, 269; 5 x 25 M: 261, 252)
 //   by the bytes that it writes, where these weigh more and a group's turn is short:
@@ -2265,7 +2267,7 @@ static BurstPlan burst_plan(const Geo& g, u32 cus) {
     const bool lead = units_from_packet(g);
     const u32 n_pass = unit_passes(g, lead);
     const u64 span = 4ull * g.P, packets = (u64)g.W * g.stride;         // bytes written and read per sequence number
-    const u64 least = g.W > 1 && g.P <= 128 ? 48000000ull / packets : g.W >= 8 ? 150000000ull / packets : g.W >= 5 ? 300000000ull / packets
+    const u64 least = g.P <= 128 ? 48000000ull / packets : g.W >= 8 ? 150000000ull / packets : g.W >= 5 ? 300000000ull / packets
                     : g.W >= 3 ? 144000000ull / span : 256000000ull / span;
     const size_t table = ((size_t)g.B + 1) * sizeof(u32);
     const u32 table_words = table <= IDX_TABLE_LDS_MAX ? g.B + 1 : 0u;
@@ -2846,7 +2848,6 @@ extern "C" int dblp_phase_signal(dblp_ctx* c, const float* d_vec, double* h_norm
         hipLaunchKernelGGL(sumsq_vec, dim3(sumsq_grid((u32)c->n_cus, c->N)), dim3(256), 0, c->stream, d_vec, (u64)c->N, c->d_partials, c->max_partials,
                            (double*)(c->d_mailbox + 1));
         c->finalized = 0;   // the mailbox does not belong to a finalize any more
-       
     } else {
         if (!c->finalized) return fail(c, DBLP_ESTATE, "phase_signal without a finalize in this round");
     }
