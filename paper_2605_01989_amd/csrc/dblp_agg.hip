@@ -1571,8 +1571,8 @@ __global__ __launch_bounds__(256) void emit_retx(Geo g, const u64* __restrict__ 
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) mailbox[0] = base + (BLOCK_PAIR ? sh_sum[0] : (sh_sum[0] + sh_sum[1]) + (sh_sum[2] + sh_sum[3]));
     if (!BLOCK_PAIR)
         for (u32 i = 0; i < wave; ++i) base += sh_sum[i];
-    if (capacity == 0) return;
-    __syncthreads();                // sh has been read
+    if (capacity == 0 || sum == 0) return;      // (a block that takes a pair: the same in all its waves)
+    if (BLOCK_PAIR) __syncthreads();            // sh has been read
     probe_emit<BLOCK_PAIR>(g, bitmap, ProbePair(g, pr, valid), want, base + incl - want, ppw, list, capacity, sh);
 }
 
