@@ -156,6 +156,8 @@ __device__ __forceinline__ void packet_span(const Geo& g, u32 seq, u32 b, u64* e
     *len = left < g.P ? (u32)left : g.P;
 }
 
+#define ACCEPT_ROWS 8192   // >= blocks of any gather launch (n_cus * blocks per CU)
+
 // ------------------------------------------------------------------------------------------
 // small utility kernels
 // ------------------------------------------------------------------------------------------
@@ -164,7 +166,14 @@ __global__ __launch_bounds__(256) void fill_u64(u64* __restrict__ p, u64 n, u64 
     for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
 
-// Start of a round in one launch: bitmap and the gather kernels' per-block rows to zero, counters reset.
+// What a round counts in: the delivery bitmap, the gather kernels' per-block rows, the counters.  A context keeps two of
+// them.  The finalize of a round clears the one that is not in use while it is about it, and the next begin_round changes
+// over to that and launches nothing.  A launch cost the host 2.6 us before it could make the next, and small rounds are chains
+// of launches and waits (us of a pass: 4 x 1 M elements in 1040-byte packets 45.1, 43.3; 3 x 5.3 M 102.0, 98.6; 1 x 25.6 M
+// 111.2, 108.6).
+struct RoundState { u64* bitmap; u64* rows; u64* counters; u32 rows_used; };    // rows_used: of the rows, those that may not be zero
+
+// Start of a round where no finalize has cleared the other state, in one launch: all of it to zero.
 __global__ __launch_bounds__(256) void reset_round(u64* __restrict__ bitmap, u64 n_bitmap, u64* __restrict__ rows, u64 n_rows,
                                                    u64* __restrict__ counters) {
     const u64 stride = (u64)gridDim.x * blockDim.x;
@@ -1652,7 +1661,7 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
                                                      u32 grp_log2, u32 n_piece, u64* partials, u32 n_max, u32 n_work_blocks,
                                                      const double* __restrict__ sumsq_rows, const u64* __restrict__ accept_rows,
                                                      u32 n_rows,
-                                                     u64* __restrict__ counters, u64* __restrict__ mailbox) {
+                                                     u64* __restrict__ counters, u64* __restrict__ mailbox, RoundState other) {
     __shared__ double wsum[4];
     __shared__ u64 asum[4];
     extern __shared__ u32 fs_lds[];             // bucket boundaries (B + 1 words) when TABLE_IN_LDS
@@ -1694,6 +1703,15 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
             mailbox[10] = counters[C_STALE]; mailbox[11] = counters[C_INVALID];
         }
         return;
+    }
+    if (other.bitmap) {         // the state of the next round
+        const u64 n_words = (u64)g.W * g.words_pw, n = n_words + 2 * other.rows_used, first = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+        for (u64 i = first; i < n; i += (u64)n_work_blocks * blockDim.x) {
+            const u64 r = i - n_words;
+            if (i < n_words) other.bitmap[i] = 0;
+            else other.rows[r < other.rows_used ? r : r - other.rows_used + ACCEPT_ROWS] = 0;
+        }
+        if (first < C_COUNT) other.counters[first] = 0;
     }
     const u32 wave = blockIdx.x * (blockDim.x / WAVE) + wave_in_block;
     const u32 n_waves = n_work_blocks * (blockDim.x / WAVE);
@@ -1936,7 +1954,11 @@ struct dblp_ctx {
     int n_cus;
     // device state
     u32* d_first_seq; u64* d_b_off; u64* d_b_cnt; u32* d_hint;
-    u64* d_bitmap; u64* d_pending; u64* d_counters; u64* d_flags;   // F_COUNT words behind the counters
+    RoundState state[2];    // the open round's (cur) and the other one; both kinds of rows, [ACCEPT_ROWS] each, lie in one allocation
+    int cur;
+    int other_clean;        // the state that is not in use is all zero, once what has been launched has ended
+    int recorded;           // calls were recorded into a graph, which holds the addresses of one state: it stays in use
+    u64* d_pending; u64* d_flags;   // F_COUNT words
     u32 any_no;             // batches that used one of the first two
     // accumulator: one or two copies (d_acc[1] == d_acc[0] when there is one); each copy's
     // allocation ends with CLS_SCRATCH_BYTES that classify_rw may overwrite
@@ -1965,10 +1987,7 @@ struct dblp_ctx {
     u32* d_need; u64* d_totals;   // list length per pair, and per block of pairs
     u64* d_partials; u32 max_partials;    // sums of squares per block, told to the launch's last block
     u32* d_block_tallies;   // [IDX_BLOCKS_PER_CU * n_cus][5], written by index_arrivals
-    u64* d_accept_rows;     // [ACCEPT_ROWS] accepted packets per gather block
-    u32 rows_used;          // largest gather grid launched in the open round
     int result_in_place;    // the form of the last dblp_finalize (in place until one says otherwise): prices the second copy
-    double* d_sumsq_rows;   // [ACCEPT_ROWS] sum of squares of what each gather block stored (same allocation)
     u64* h_mailbox;         // pinned host memory, 16 x u64, also mapped into the device
     u64* d_mailbox;         // device address of h_mailbox
     // host copies of the geometry
@@ -2054,9 +2073,9 @@ extern "C" int dblp_destroy(dblp_ctx* c) {
     if (!c) return DBLP_OK;
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
-    void* dev[] = {c->d_first_seq, c->d_b_off, c->d_b_cnt, c->d_hint, c->d_bitmap, c->d_pending,
-                   c->acc_caller ? nullptr : c->acc_alloc[0], c->acc_caller ? nullptr : c->acc_alloc[1], c->d_home, c->d_counters, c->d_need, c->d_totals, c->d_partials, c->d_block_tallies,
-                   c->d_accept_rows};
+    void* dev[] = {c->d_first_seq, c->d_b_off, c->d_b_cnt, c->d_hint, c->state[0].bitmap, c->state[1].bitmap, c->d_pending,
+                   c->acc_caller ? nullptr : c->acc_alloc[0], c->acc_caller ? nullptr : c->acc_alloc[1], c->d_home, c->state[0].counters, c->state[1].counters, c->d_flags, c->d_need, c->d_totals, c->d_partials, c->d_block_tallies,
+                   c->state[0].rows, c->state[1].rows};
     for (void* p : dev) if (p) (void)hipFree(p);
     for (hipEvent_t e : c->cls_ev) if (e) (void)hipEventDestroy(e);
     if (c->h_mailbox) (void)hipHostFree(c->h_mailbox);
@@ -2209,7 +2228,6 @@ static int pick_copy(dblp_ctx* c, const void* d_packets, u64 bytes, u64 n_slots,
 #ifndef FIN_BLOCKS_PER_CU
 #define FIN_BLOCKS_PER_CU 8
 #endif
-#define ACCEPT_ROWS 8192   // >= blocks of any gather launch (n_cus * blocks per CU)
 #ifndef IDX_BLOCKS_PER_CU
 #define IDX_BLOCKS_PER_CU 4   // 2-4 blocks per CU index 3 % faster than 8: its bound is requests to memory, not latency
 #endif
@@ -2297,6 +2315,23 @@ static BurstPlan burst_plan(const Geo& g, u32 cus) {
     return b;
 }
 
+static void reset_state(dblp_ctx* c, int i) {
+    RoundState& st = c->state[i];
+    const u64 n = c->g.W * c->g.words_pw;
+    hipLaunchKernelGGL(reset_round, dim3(grid_for(c, (n + 2 * ACCEPT_ROWS + 255) / 256, 16)), dim3(256), 0, c->stream,
+                       st.bitmap, n, st.rows, (u64)(2 * ACCEPT_ROWS), st.counters);
+    st.rows_used = 0;
+}
+
+// A call that is recorded now will be told again with the state's addresses as they are, and a begin_round among the
+// recorded ones has to clear it each time: from the first such call on, one state stays in use and each begin_round launches.
+static void note_recording(dblp_ctx* c) {
+    if (c->recorded || !c->stream) return;      // (the null stream cannot be recorded)
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) { (void)hipGetLastError(); c->recorded = 1; }
+    else if (st != hipStreamCaptureStatusNone) c->recorded = 1;
+}
+
 extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     if (!out || !cfg || !cfg->buckets) return DBLP_EINVAL;
     if (cfg->n_workers == 0 || cfg->n_workers > DBLP_MAX_WORKERS) return DBLP_EINVAL;
@@ -2369,14 +2404,17 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     ok = ok && hipMalloc(&c->d_first_seq, (B + 1) * sizeof(u32)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_b_off, B * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_b_cnt, B * sizeof(u64)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_bitmap, g.W * g.words_pw * sizeof(u64)) == hipSuccess;
+    for (RoundState& st : c->state) {
+        ok = ok && hipMalloc(&st.bitmap, g.W * g.words_pw * sizeof(u64)) == hipSuccess;
+        ok = ok && hipMalloc(&st.rows, 2 * ACCEPT_ROWS * sizeof(u64)) == hipSuccess;    // accepted packets, sums of squares
+        ok = ok && hipMalloc(&st.counters, C_COUNT * sizeof(u64)) == hipSuccess;
+    }
     ok = ok && hipMalloc(&c->d_pending, (u64)g.W * n_pkts * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_home, (n_pkts + 7) / 8 * 8 + 8) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_counters, (C_COUNT + F_COUNT) * sizeof(u64)) == hipSuccess;
+    ok = ok && hipMalloc(&c->d_flags, F_COUNT * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_need, pairs * sizeof(u32)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_totals, probe_blocks(c, pairs) * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_partials, PARTIALS_WORDS(c->max_partials) * sizeof(u64)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_accept_rows, 2 * ACCEPT_ROWS * sizeof(u64)) == hipSuccess;   // + the sum-of-squares rows
     ok = ok && hipMalloc(&c->d_block_tallies, (size_t)c->n_cus * IDX_BLOCKS_PER_CU * 5 * sizeof(u32)) == hipSuccess;
     ok = ok && hipHostMalloc((void**)&c->h_mailbox, 16 * sizeof(u64), hipHostMallocMapped) == hipSuccess;
     if (!ok) { (void)hipGetLastError(); dblp_destroy(c); return DBLP_ENOMEM; }
@@ -2400,8 +2438,6 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
         if (ce != hipSuccess) { (void)hipGetLastError(); dblp_destroy(c); return DBLP_EHIP; }
         g.hint = c->d_hint;
     }
-    c->d_sumsq_rows = (double*)(c->d_accept_rows + ACCEPT_ROWS);
-    c->d_flags = c->d_counters + C_COUNT;
     c->burst = burst_plan(g, (u32)c->n_cus);
     // The limit is the kernel's, not the context's: the same whatever the plan, so that contexts which share an instance
     // do not lower it for each other.
@@ -2413,13 +2449,12 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     const u64 n_pending = (u64)g.W * n_pkts;
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (n_pending + 255) / 256, 16)), dim3(256), 0, c->stream,
                        c->d_pending, n_pending, NONE64);
-    hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (g.W * g.words_pw + 255) / 256, 16)), dim3(256), 0, c->stream,
-                       c->d_bitmap, g.W * g.words_pw, 0ull);
-    hipLaunchKernelGGL(fill_u64, dim3(1), dim3(64), 0, c->stream, c->d_counters, (u64)(C_COUNT + F_COUNT), 0ull);
+    for (int i = 0; i < 2; ++i) reset_state(c, i);
+    c->other_clean = 1;
+    hipLaunchKernelGGL(fill_u64, dim3(1), dim3(64), 0, c->stream, c->d_flags, (u64)F_COUNT, 0ull);
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (probe_blocks(c, pairs) + 255) / 256, 16)), dim3(256), 0, c->stream,
                        c->d_totals, probe_blocks(c, pairs), 0ull);
     hipLaunchKernelGGL(fill_u64, dim3(8), dim3(256), 0, c->stream, c->d_partials, (u64)PARTIALS_WORDS(c->max_partials), 0ull);
-    hipLaunchKernelGGL(fill_u64, dim3(32), dim3(256), 0, c->stream, c->d_accept_rows, (u64)(2 * ACCEPT_ROWS), 0ull);
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (n_pkts + 16 + 2047) / 2048, 16)), dim3(256), 0, c->stream,
                        (u64*)c->d_home, (u64)((n_pkts + 7) / 8 + 1), 0ull);
     e = hipStreamSynchronize(c->stream);
@@ -2486,12 +2521,15 @@ extern "C" int dblp_begin_round(dblp_ctx* c, uint16_t round) {
     if (!c) return DBLP_EINVAL;
     if (!c->acc_alloc[0]) return fail(c, DBLP_ESTATE, "begin_round: no accumulator (dblp_accumulator_copies ran out of memory)");
     HIP_TRY(c, hipSetDevice(c->device));
-    const u64 n = c->g.W * c->g.words_pw;
-    hipLaunchKernelGGL(reset_round, dim3(grid_for(c, (n + 2 * ACCEPT_ROWS + 255) / 256, 16)), dim3(256), 0, c->stream,
-                       c->d_bitmap, n, c->d_accept_rows, (u64)(2 * ACCEPT_ROWS), c->d_counters);
-    LAUNCH_CHECK(c, "begin_round");
+    note_recording(c);
+    if (c->other_clean && !c->recorded) {
+        c->cur ^= 1;
+        c->other_clean = 0;
+    } else {
+        reset_state(c, c->cur);
+        LAUNCH_CHECK(c, "begin_round");
+    }
     c->round = round; c->round_open = 1; c->finalized = 0; c->counters_in_mailbox = 0;
-    c->rows_used = 0;
     return DBLP_OK;
 }
 
@@ -2607,6 +2645,7 @@ static u32 block_waves(const dblp_ctx* c) {
 static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src_worker, uint64_t n_slots,
                        const uint64_t* d_mask, const uint32_t* d_order, const uint64_t* d_queue, uint64_t n_arrivals) {
     HIP_TRY(c, hipSetDevice(c->device));
+    note_recording(c);
     const Geo& g = c->g;
     const int pick = pick_copy(c, d_packets, n_slots * g.stride, n_slots, n_arrivals);
     c->last_pick = pick;
@@ -2671,6 +2710,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
     const bool whole = n_arrivals * WHOLE_DIV >= pairs && !asked && (!d_mask || turns <= 2);
     const bool any = whole && turns > 4;                // (two turns for nothing take 1 us; the word costs 0.4 to 1.5)
     const u32 any_at = any ? c->any_no++ & 1u : 0u;
+    RoundState& now = c->state[c->cur];
     const u32 batch = (whole ? B_WHOLE : 0) | (any ? B_ANY : 0) | (any_at ? B_ANY_AT : 0) | (asked ? B_ASKED : 0);
 
     u32 n_tally_rows = 0;
@@ -2703,17 +2743,17 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         const gather_fn kern = dense_only ? gather_kernel<true>(nw, lead, few, np) : gather_kernel<false>(nw, lead, few, np);
         ProfScope ps(c, small ? DBLP_K_GATHER_DIRECT : DBLP_K_GATHER, !dense_only && !small && !known, known);
         if (in_bursts) {
-            if ((u32)c->n_cus > c->rows_used) c->rows_used = (u32)c->n_cus;
-            hipLaunchKernelGGL(burst.fn, dim3(c->n_cus), dim3(BURST_WAVES * WAVE), burst.lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap,
-                               c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
-                               c->d_accept_rows, c->d_sumsq_rows, inv_w, burst.r_max, burst.r_step, burst.n_piece, burst.table_at, burst.image_at,
+            if ((u32)c->n_cus > now.rows_used) now.rows_used = (u32)c->n_cus;
+            hipLaunchKernelGGL(burst.fn, dim3(c->n_cus), dim3(BURST_WAVES * WAVE), burst.lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, now.bitmap,
+                               c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, now.counters,
+                               now.rows, (double*)(now.rows + ACCEPT_ROWS), inv_w, burst.r_max, burst.r_step, burst.n_piece, burst.table_at, burst.image_at,
                                known ? 0u : burst.min_seq, burst.through_seq, batch, c->d_flags);
         }
         if (!known) {
-            if (grid > c->rows_used) c->rows_used = grid;
-            hipLaunchKernelGGL(kern, dim3(grid), dim3(nw * WAVE), lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, c->d_bitmap,
-                               c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, c->d_counters,
-                               c->d_accept_rows, c->d_sumsq_rows, inv_w, dense, sparse, (u32)c->n_cus, heavy, table_at, batch, c->d_flags, ps.d_told());
+            if (grid > now.rows_used) now.rows_used = grid;
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(nw * WAVE), lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, now.bitmap,
+                               c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, now.counters,
+                               now.rows, (double*)(now.rows + ACCEPT_ROWS), inv_w, dense, sparse, (u32)c->n_cus, heavy, table_at, batch, c->d_flags, ps.d_told());
         }
     }
     LAUNCH_CHECK(c, "apply_arrivals");
@@ -2754,6 +2794,7 @@ extern "C" int dblp_loss_account(dblp_ctx* c, uint32_t bound_ppm, uint32_t* d_mi
     if (bound_ppm > 1000000u) return fail(c, DBLP_EINVAL, "loss_account: bound above 100%");
     HIP_TRY(c, hipSetDevice(c->device));
     const Geo& g = c->g;
+    const u64* const bitmap = c->state[c->cur].bitmap;
     const u64 pairs = (u64)g.W * g.B, blocks = probe_blocks(c, pairs);
     const u32 ppw = probe_ppw(c, pairs);
     if (blocks > 0x7FFFFFFFull) return fail(c, DBLP_EINVAL, "loss_account: too many (worker, bucket) pairs");
@@ -2766,7 +2807,7 @@ extern "C" int dblp_loss_account(dblp_ctx* c, uint32_t bound_ppm, uint32_t* d_mi
             volatile u64* const gave_up = c->h_mailbox + M_PROBE_GAVE_UP;
             *gave_up = 0;
             hipLaunchKernelGGL(c->probe_block_pair ? probe_once<true> : probe_once<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g,
-                               c->d_bitmap, bound_ppm, ppw, pairs, d_missing, c->d_totals, tag, c->probe_polls, (u64*)d_retx_list, (u64)retx_capacity, c->d_mailbox);
+                               bitmap, bound_ppm, ppw, pairs, d_missing, c->d_totals, tag, c->probe_polls, (u64*)d_retx_list, (u64)retx_capacity, c->d_mailbox);
             LAUNCH_CHECK(c, "loss_account");
             ps.end();
             HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -2777,9 +2818,9 @@ extern "C" int dblp_loss_account(dblp_ctx* c, uint32_t bound_ppm, uint32_t* d_mi
             // microsecond) unless they are so many that a pass in between is shorter.
             const int scanned = blocks > PROBE_SCAN_BLOCKS ? 1 : 0;
             hipLaunchKernelGGL(c->probe_block_pair ? loss_count<true> : loss_count<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g,
-                               c->d_bitmap, bound_ppm, ppw, pairs, d_missing, c->d_need, c->d_totals);
+                               bitmap, bound_ppm, ppw, pairs, d_missing, c->d_need, c->d_totals);
             if (scanned) hipLaunchKernelGGL(scan_totals, dim3(1), dim3(1024), 0, c->stream, c->d_totals, (u32)blocks);
-            hipLaunchKernelGGL(c->probe_block_pair ? emit_retx<true> : emit_retx<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g, c->d_bitmap, ppw, pairs,
+            hipLaunchKernelGGL(c->probe_block_pair ? emit_retx<true> : emit_retx<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g, bitmap, ppw, pairs,
                                (const u32*)c->d_need, (const u64*)c->d_totals, scanned, (u64*)d_retx_list, (u64)retx_capacity, c->d_mailbox);
             LAUNCH_CHECK(c, "loss_account");
             ps.end();
@@ -2819,19 +2860,27 @@ extern "C" int dblp_finalize(dblp_ctx* c, int compensation, float* d_out) {
     const u32 n_piece = in_place ? 1 : (u32)((((u64)g.P << grp_log2) + FIN_PIECE - 1) / FIN_PIECE);
     const u64 items = (((u64)g.n_pkts + (1u << grp_log2) - 1) >> grp_log2) * n_piece;
     const u32 work = grid_for(c, (items + 3) / 4, FIN_BLOCKS_PER_CU);
+    note_recording(c);
+    const RoundState& now = c->state[c->cur];
+    RoundState other = c->state[c->cur ^ 1];
+    if (c->other_clean || c->recorded) other.bitmap = nullptr;
     const u32 grid = work + 1;      // one more block sums the gather's rows: accepted packets, and the sum of squares for Eq. 1
     float* out = in_place ? c->d_acc[0] : d_out;
     {
         ProfScope ps(c, DBLP_K_FINALIZE);
         const size_t table = ((size_t)g.B + 1) * sizeof(u32);
         void (*kern)(Geo, const u64*, const float*, const float*, uint8_t*, float*, int, float, int, u32, u32, u64*, u32, u32,
-                     const double*, const u64*, u32, u64*, u64*) = table <= IDX_TABLE_LDS_MAX ? finalize_pass<true> : finalize_pass<false>;
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(256), table <= IDX_TABLE_LDS_MAX ? table : 0, c->stream, g, c->d_bitmap,
+                     const double*, const u64*, u32, u64*, u64*, RoundState) = table <= IDX_TABLE_LDS_MAX ? finalize_pass<true> : finalize_pass<false>;
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(256), table <= IDX_TABLE_LDS_MAX ? table : 0, c->stream, g, (const u64*)now.bitmap,
                            (const float*)c->d_acc[0], (const float*)c->d_acc[1], c->d_home, out, c->fold ? 0 : 1, (float)g.W,
-                           in_place ? 1 : 0, grp_log2, n_piece, c->d_partials, c->max_partials, work, (const double*)c->d_sumsq_rows, (const u64*)c->d_accept_rows,
-                           c->rows_used, c->d_counters, c->d_mailbox);
+                           in_place ? 1 : 0, grp_log2, n_piece, c->d_partials, c->max_partials, work, (const double*)(now.rows + ACCEPT_ROWS), (const u64*)now.rows,
+                           now.rows_used, now.counters, c->d_mailbox, other);
     }
     LAUNCH_CHECK(c, "finalize");
+    if (other.bitmap) {
+        c->other_clean = 1;
+        c->state[c->cur ^ 1].rows_used = 0;
+    }
     c->result_in_place = in_place ? 1 : 0;
     c->finalized = 1;
     c->counters_in_mailbox = 1;     // valid on the host once the stream has been synchronised (mailbox_seen)
@@ -2915,7 +2964,8 @@ extern "C" int dblp_sumsq_static(int device, void* stream, const float* d_vec, u
 extern "C" int dblp_get_bitmap(dblp_ctx* c, uint64_t* d_out) {
     if (!c || !d_out) return DBLP_EINVAL;
     HIP_TRY(c, hipSetDevice(c->device));
-    HIP_TRY(c, hipMemcpyAsync(d_out, c->d_bitmap, c->g.W * c->g.words_pw * sizeof(u64), hipMemcpyDeviceToDevice, c->stream));
+    note_recording(c);
+    HIP_TRY(c, hipMemcpyAsync(d_out, c->state[c->cur].bitmap, c->g.W * c->g.words_pw * sizeof(u64), hipMemcpyDeviceToDevice, c->stream));
     return DBLP_OK;
 }
 
@@ -2932,10 +2982,10 @@ extern "C" int dblp_get_counters(dblp_ctx* c, uint64_t h[4]) {
     }
     HIP_TRY(c, hipSetDevice(c->device));
     u64 tmp[C_COUNT];
-    hipLaunchKernelGGL(fold_accept_rows, dim3(1), dim3(256), 0, c->stream, c->d_accept_rows, (u32)ACCEPT_ROWS,
-                       c->d_counters);
+    hipLaunchKernelGGL(fold_accept_rows, dim3(1), dim3(256), 0, c->stream, c->state[c->cur].rows, (u32)ACCEPT_ROWS,
+                       c->state[c->cur].counters);
     LAUNCH_CHECK(c, "get_counters");
-    HIP_TRY(c, hipMemcpyAsync(tmp, c->d_counters, sizeof tmp, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(tmp, c->state[c->cur].counters, sizeof tmp, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     h[0] = tmp[C_ACCEPTED];
     h[1] = tmp[C_CANDIDATES] - tmp[C_ACCEPTED];   // valid arrivals that were not the first copy of their packet
