@@ -324,6 +324,13 @@ __global__ __launch_bounds__(256) void packetize_list_kernel(Geo g, GradPtrs gra
 // No global atomics on shared counters: atomics of many waves (or even of a few thousand
 // blocks) on one address serialise in L2 at about 12 ns each.
 //
+// `few`: the batch is a small one that gather_few will take (below).
+struct ArrivalList {
+    u64* entries;           // per arrival: bucket << 32 | sequence number, NONE64 of one that is not valid; null: none is made
+    u32* first;             // per sequence number: the batch's first arrival with it; all-ones between batches
+    u32 n;
+};
+//
 // TABLE_IN_LDS: the block first copies the bucket boundaries (first_seq, B + 1 words of dynamic
 // shared memory) into LDS, so the ten dependent steps of the bucket search stay inside the CU.
 // FROM_QUEUE: arrival k is the descriptor queue[k] = slot | worker << 32 (one coalesced 8-byte
@@ -335,7 +342,7 @@ __global__ __launch_bounds__(256) void index_arrivals(Geo g, const uint8_t* __re
                                                       const u64* __restrict__ mask, const u32* __restrict__ order,
                                                       const u64* __restrict__ queue,
                                                       u64 n_arrivals, u32 cur_round, u64* __restrict__ pending,
-                                                      u32* __restrict__ block_tallies, u64* __restrict__ any) {
+                                                      u32* __restrict__ block_tallies, u64* __restrict__ any, ArrivalList few) {
     __shared__ u32 sh[4][5];    // per wave: stale, invalid, candidates, lowest seq, highest seq + 1
     extern __shared__ u32 fs_lds[];
     u32 n_stale = 0, n_inv = 0, n_cand = 0;
@@ -371,6 +378,7 @@ __global__ __launch_bounds__(256) void index_arrivals(Geo g, const uint8_t* __re
         fs = fs_lds;
     }
     for (; k < n_arrivals; k += stride, fetch(k)) {
+        if (few.entries) few.entries[k] = NONE64;
         if (!live) continue;
         const u32 seq = hdr.x, round = hdr.y & 0xFFFFu, len = hdr.y >> 16;
         if (round != cur_round) { ++n_stale; continue; }
@@ -381,6 +389,10 @@ __global__ __launch_bounds__(256) void index_arrivals(Geo g, const uint8_t* __re
         if (len != want) { ++n_inv; continue; }
         ++n_cand;
         atomicMin(&pending[(u64)w * g.n_pkts + seq], (k << 32) | slot);
+        if (few.entries) {
+            few.entries[k] = (u64)b << 32 | seq;
+            atomicMin(&few.first[seq], (u32)k);
+        }
         seq_lo = seq < seq_lo ? seq : seq_lo;
         seq_hi = seq + 1 > seq_hi ? seq + 1 : seq_hi;
     }
@@ -454,6 +466,7 @@ __device__ __forceinline__ BatchInfo fold_index_tallies(const u32* __restrict__ 
 // sequence range it touches (retransmission batches), or one packet.  Sparse batches go through gather_stream in a
 // way of their own (below); where the host cannot tell, the launch holds both and its blocks decide.
 #define SPARSE_DIV 8
+enum { TOLD_DENSE = 0, TOLD_SPARSE, TOLD_BURST };       // what a launch that decides on the device tells its trace group
 __device__ __forceinline__ bool batch_is_sparse(const BatchInfo& bi, u32 W) {
     return bi.cand == 1 || bi.cand * SPARSE_DIV < (bi.hi - bi.lo) * W;
 }
@@ -888,6 +901,202 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
     }
 }
 
+// A retransmission of few packets is a chain of memory trips, whatever bandwidth there is, and by groups it is long: the
+// tallies, the index of whole groups looked through for the entries, the entries again, the payload, and in
+// a group with several packets the packets one after the other by one wave.  Where a batch holds at most FEW_MAX arrivals, and fewer than
+// one per FEW_DIV sequence numbers of the round, the index pass also lists what it found, and a wave takes entries of the list, one output packet
+// each: the entry; what its number leads to (all workers' index entries and bitmap words, the span); the payloads
+// and the span's old contents; the store.  Several arrivals of one number are one output packet, taken by the one that the
+// index pass noted as the first.  Packets of three and more pieces are taken by the block's waves together.  The sums and
+// their order are those of the groups.
+//
+// A batch that turns out to be dense goes by groups after all: neighbours in the bitmap are set by atomics here, one
+// after the other.  It pays the list, 0 to 0.6 us of 14 to 20.  us of index pass and gather, by groups and by the list:
+//                                spread evenly              in runs of 20 of one worker
+//   8 x 70 k of 1472 B, 273       18.5 -> 11.5               30 -> 11
+//     4.4 k                       27 -> 17                   46 -> 16
+//     17 k                        41 -> 34                   59 -> 31
+//   4 x 312 k of 272 B, 39 k      63 -> 38                  111 -> 36
+//     78 k                        91 -> 68                  133 -> 63
+//   8 x 27 k of 8992 B, 1.7 k     34 -> 22                   59 -> 21
+//   4 x 3.7 k of 64 KB, 465       53 -> 29                   71 -> 28
+//   16 x 29 k of 4112 B, 7.3 k    37 -> 29                   47 -> 28
+// and by the list where it holds as many arrivals as every second number: 1 x 35 k 40 -> 53, 8 x 35 k 50 -> 60.
+#define FEW_DIV 4u
+#define FEW_MAX 131072u
+#define FEW_DEPTH(np) ((np) == 1 ? 8 : (np) == 2 ? 4 : 2)    // workers' pieces that a step loads
+#define FEW_TEAM(g, np) ((g).units > 2u * (np) * WAVE)       // packets of three and more pieces
+
+// What a sequence number of the list leads to; lane w: worker w's.
+struct FewFound { u64 p, bits; u32 seq, home, fs; u64 off, cnt; };
+__device__ __forceinline__ FewFound few_look_up(const Geo& g, u64 e, const u64* pending, const u64* bitmap, const uint8_t* home) {
+    FewFound f;
+    const u32 lane = lane_id(), b = (u32)(e >> 32);
+    f.seq = (u32)e;
+    f.p = NONE64; f.bits = 0;
+    if (lane < g.W) {
+        f.p = pending[(u64)lane * g.n_pkts + f.seq];
+        f.bits = bitmap[(u64)lane * g.words_pw + (f.seq >> 6)];
+    }
+    f.home = home[f.seq];
+    f.fs = g.first_seq[b]; f.off = g.b_off[b]; f.cnt = g.b_cnt[b];
+    return f;
+}
+
+// Entry of the list that a lane of a team takes, from k0 on (below); NONE64 behind the last one.
+template <bool TEAM, int NW>
+__device__ __forceinline__ u64 few_entry(const ArrivalList& few, u64 k0, u32 n_blocks) {
+    const u64 k = k0 + (u64)lane_id() * (TEAM ? n_blocks : n_blocks * NW);
+    return k < few.n ? few.entries[k] : NONE64;
+}
+template <bool TEAM, int NW>
+__device__ __forceinline__ u32 few_team() { return TEAM ? blockIdx.x : blockIdx.x * NW + uniform(threadIdx.x / WAVE); }
+
+template <int NP, int NW, u32 LEAD, bool TEAM>
+__device__ __forceinline__ void gather_few(const Geo& g, const uint8_t* __restrict__ packets, u64* __restrict__ pending, u64* __restrict__ bitmap,
+                                           float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick, const ArrivalList& few, u64 e, u32 n_blocks,
+                                           u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w) {
+    __shared__ u32 sh_accepted[NW];
+    __shared__ double sh_sq[NW];
+    const u32 lane = lane_id(), wave = uniform(threadIdx.x / WAVE);
+    constexpr int D = FEW_DEPTH(NP);
+    constexpr u32 team = TEAM ? NW : 1;
+    const u32 n_teams = TEAM ? n_blocks : n_blocks * NW;
+    const bool leader = !TEAM || wave == 0;
+    u32 accepted = 0;
+    double sq = 0.0;
+    auto take = [&](const FewFound& f) {
+        const u32 seq = f.seq;
+        const bool had = (f.bits >> (seq & 63)) & 1ull;             // delivered by an earlier batch
+        const bool fresh = f.p != NONE64 && !had;                   // a copy of a delivered packet is dropped
+        const u64 new_w = uniform((u64)__ballot(fresh)), old_w = uniform((u64)__ballot(had));
+        const u32 slot32 = (u32)f.p;
+        if (TEAM) __syncthreads();      // every wave of the block has read the entries before they are reset
+        if (leader) {
+            if (f.p != NONE64) pending[(u64)lane * g.n_pkts + seq] = NONE64;    // leave the index empty
+            if (fresh) atomicOr(&bitmap[(u64)lane * g.words_pw + (seq >> 6)], 1ull << (seq & 63));
+            if (lane == 0) {
+                few.first[seq] = NONE32;
+                if (new_w && !old_w) home[seq] = (uint8_t)pick;
+            }
+            accepted += (u32)__popcll(new_w);
+        }
+        if (!new_w) return;
+        const u64 start = (u64)(seq - f.fs) * g.P, left_in = uniform(f.cnt) - start;
+        const u32 len = uniform(left_in < g.P ? (u32)left_in : g.P);
+        const u32 h = uniform(old_w ? f.home & 1u : pick);
+        float* const span = (h ? acc1 : acc0) + uniform(f.off + start);
+        float* const dst = span - LEAD;             // float position i of the unit grid -> dst[i]
+        for (u32 piece = TEAM ? wave : 0; piece * (NP * 256u) < len + LEAD; piece += team) {
+            const u32 skip = piece * (NP * 1024u), have = unit_have<LEAD>(len, skip);
+            int off[NP];
+            f4v a[NP], old[NP];
+            #pragma unroll
+            for (int q = 0; q < NP; ++q) { off[q] = unit_offset<LEAD>(len, skip, q * WAVE + lane); a[q] = f4v{0.f, 0.f, 0.f, 0.f}; }
+            {   // the 16-byte units that lie in the span whole (and the first four floats for unit 0)
+                __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)uniform((u64)span), 0, (int)uniform(old_w ? 4 * len : 0u), BUF_RAW);
+                #pragma unroll
+                for (int q = 0; q < NP; ++q) {
+                    const u32 u = (piece * NP + q) * WAVE + lane;
+                    const bool whole = !LEAD ? u < len >> 2 : u == 0 ? len >= 4 : 4 * u + 2 <= len;
+                    old[q] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r, !whole ? 0x40000000 : u == 0 ? 0 : (int)(16 * u - 4 * LEAD), 0, 0));
+                }
+            }
+            for (u64 left = new_w; left;) {
+                f4v v[D][NP];
+                #pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    if (d && left == 0) {
+                        #pragma unroll
+                        for (int q = 0; q < NP; ++q) v[d][q] = f4v{0.f, 0.f, 0.f, 0.f};
+                        continue;
+                    }
+                    const u32 w = (u32)__builtin_ctzll(left);
+                    left &= left - 1;
+                    const u32 slot = (u32)__builtin_amdgcn_readlane((int)slot32, (int)w);
+                    __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+                        (void*)(packets + uniform((u64)slot * g.stride + unit_base<LEAD>(skip))), 0, (int)uniform(have), BUF_RAW);
+                    #pragma unroll
+                    for (int q = 0; q < NP; ++q)
+                        v[d][q] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r, off[q], 0, BUF_NT));
+                }
+                #pragma unroll
+                for (int d = 0; d < D; ++d)
+                    #pragma unroll
+                    for (int q = 0; q < NP; ++q) a[q] += v[d][q];
+            }
+            #pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                const SpanUnit<LEAD> su((piece * NP + q) * WAVE + lane, len);
+                float* o = dst + 4 * su.u;
+                f4v r = su.take(a[q] * inv_w, len);
+                if (old_w) {                                        // result = old value + this batch's sum
+                    f4v ov = old[q];
+                    if (su.head) ov = f4v{0.f, 0.f, ov.x, ov.y};
+                    if (su.part || (su.head && len < 4)) ov = su.floats(o);
+                    sq -= squares(ov);
+                    r = ov + r;
+                }
+                sq += squares(r);
+                su.store(o, r);
+            }
+        }
+    };
+
+    // A team's entries lie n_teams apart, so that the first ones of a number, which a list sorted by worker has
+    // at its beginning, fall to all teams; 64 of them at a time, one per lane.
+    for (u64 k0 = few_team<TEAM, NW>();;) {
+        auto look_up = [&](u32 i) {
+            return few_look_up(g, (u64)(u32)__builtin_amdgcn_readlane((int)(u32)(e >> 32), (int)i) << 32 | (u32)__builtin_amdgcn_readlane((int)(u32)e, (int)i), pending, bitmap, home);
+        };
+        // most teams have one entry, and it is the first with its number: both are asked at once
+        const u32 first = e != NONE64 ? few.first[(u32)e] : NONE32;
+        FewFound f;
+        const bool ahead = uniform(e) != NONE64;
+        if (ahead) f = look_up(0);
+        u64 mine = uniform((u64)__ballot(e != NONE64 && first == (u32)(k0 + (u64)lane * n_teams)));
+        if (mine && !(ahead && (mine & 1ull))) f = look_up((u32)__builtin_ctzll(mine));
+        while (mine) {
+            mine &= mine - 1;
+            const FewFound at = f;
+            if (mine) f = look_up((u32)__builtin_ctzll(mine));
+            take(at);
+        }
+        k0 += (u64)WAVE * n_teams;
+        if (k0 >= few.n) break;
+        e = few_entry<TEAM, NW>(few, k0, n_blocks);
+    }
+    // accepted packets and sum-of-squares change of this block: plain adds to the block's own rows
+    sq = wave_sum_f64(sq);
+    if (lane == 0) { sh_accepted[wave] = accepted; sh_sq[wave] = sq; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        u32 total = 0;
+        double t = 0.0;
+        #pragma unroll
+        for (int i = 0; i < NW; ++i) { total += sh_accepted[i]; t += sh_sq[i]; }
+        if (total) { accept_rows[blockIdx.x] += total; sumsq_rows[blockIdx.x] += t; }
+    }
+}
+
+// gather_few for batches so small that it is the better way whatever they are (few_always): nobody waits for the tallies, and
+// one block more than take entries books them.
+template <int NP, u32 LEAD, bool TEAM>
+__global__ __launch_bounds__(GS_WAVES * WAVE) void gather_list(Geo g, const uint8_t* __restrict__ packets, u64* __restrict__ pending, u64* __restrict__ bitmap,
+                                                               float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick, ArrivalList few,
+                                                               const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters,
+                                                               u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w, u32* __restrict__ told) {
+    __shared__ u32 sh_tally[GS_WAVES * 5];
+    const u32 n_blocks = gridDim.x - 1;
+    if (blockIdx.x == n_blocks) {
+        const BatchInfo bi = fold_index_tallies(block_tallies, n_tally_rows, counters, true, sh_tally);
+        if (told && threadIdx.x == 0) *told = batch_is_sparse(bi, g.W) ? TOLD_SPARSE : TOLD_DENSE;
+        return;
+    }
+    gather_few<NP, GS_WAVES, LEAD, TEAM>(g, packets, pending, bitmap, acc0, acc1, home, pick, few, few_entry<TEAM, GS_WAVES>(few, few_team<TEAM, GS_WAVES>(), n_blocks),
+                                         n_blocks, accept_rows, sumsq_rows, inv_w);
+}
+
 // A batch of at least one arrival per two (worker, seq) pairs of the round is taken to touch all of it: its gather need not
 // read the index pass's tallies, a load and two barriers, before it starts (4 x 1 M elements in 1040-byte packets 10.8,
 // 8.1 us; 8 x 25.6 M in 1472-byte ones, in bursts, 156.7, 153.9).  What it may look through for nothing is 16 bytes of the index
@@ -916,14 +1125,13 @@ __device__ __forceinline__ bool some_arrived(u64* __restrict__ flags, u32 batch)
 }
 
 // DENSE: the host knows that the batch is dense; otherwise the index pass's tallies decide.
-enum { TOLD_DENSE = 0, TOLD_SPARSE, TOLD_BURST };
 template <int NP, int G, int D, int NW, u32 LEAD, bool DENSE>
 __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void gather_stream(
     Geo g, const uint8_t* __restrict__ packets, u64* __restrict__ pending, u64* __restrict__ bitmap,
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
     const u32* __restrict__ block_tallies, u32 n_tally_rows, u64* __restrict__ counters,
     u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w,
-    GatherShape dense, GatherShape sparse, u32 cus, u32 heavy, u32 table_at, u32 batch, u64* __restrict__ flags, u32* __restrict__ told) {
+    GatherShape dense, GatherShape sparse, u32 cus, u32 heavy, u32 table_at, u32 batch, u64* __restrict__ flags, u32* __restrict__ told, ArrivalList few) {
     extern __shared__ u32 sh_dyn[];                 // per wave: slots [W rounded up][sub + 1]; then the bucket table (table_at words in, 0: not there)
     __shared__ u32 sh_tally[NW * 5];
     const u32* fs = g.first_seq;
@@ -931,6 +1139,11 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
         if (!DENSE && told && blockIdx.x == 0 && threadIdx.x == 0) *told = TOLD_BURST;
         return;
     }
+    constexpr int FP = NP > 4 ? 3 : NP;             // KB of a piece, and whether the block takes them together, where the batch is few packets
+    const bool teams = !DENSE && few.entries && FEW_TEAM(g, FP);
+    u64 entry = NONE64;
+    if (!DENSE && few.entries)                      // on its way while the tallies are
+        entry = teams ? few_entry<true, NW>(few, few_team<true, NW>(), gridDim.x) : few_entry<false, NW>(few, few_team<false, NW>(), gridDim.x);
     const bool some = some_arrived(flags, batch);
     if (table_at) {
         u32* tab = sh_dyn + table_at;
@@ -951,6 +1164,14 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     const bool is_sparse = !DENSE && batch_is_sparse(bi, g.W);
     if (!DENSE && told && blockIdx.x == 0 && threadIdx.x == 0) *told = is_sparse ? TOLD_SPARSE : TOLD_DENSE;    // for the trace group of the launch
     if (bi.hi == 0) return;                         // no candidate in this batch (uniform over the grid)
+    if (!DENSE && few.entries) {
+        if (is_sparse) {
+            if (teams) gather_few<FP, NW, LEAD, true>(g, packets, pending, bitmap, acc0, acc1, home, pick, few, entry, gridDim.x, accept_rows, sumsq_rows, inv_w);
+            else gather_few<FP, NW, LEAD, false>(g, packets, pending, bitmap, acc0, acc1, home, pick, few, entry, gridDim.x, accept_rows, sumsq_rows, inv_w);
+            return;
+        }
+        for (u64 i = bi.lo + (u64)blockIdx.x * blockDim.x + threadIdx.x; i < bi.hi; i += (u64)gridDim.x * blockDim.x) few.first[i] = NONE32;
+    }
     if (is_sparse)
         gather_groups<2, 1, 2, NW, true, LEAD>(g, bi, sparse, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
     else {
@@ -1959,6 +2180,7 @@ struct dblp_ctx {
     int other_clean;        // the state that is not in use is all zero, once what has been launched has ended
     int recorded;           // calls were recorded into a graph, which holds the addresses of one state: it stays in use
     u64* d_pending; u64* d_flags;   // F_COUNT words
+    ArrivalList few; u64 max_few;   // arrivals of a batch that gather_few takes, at most
     u32 any_no;             // batches that used one of the first two
     // accumulator: one or two copies (d_acc[1] == d_acc[0] when there is one); each copy's
     // allocation ends with CLS_SCRATCH_BYTES that classify_rw may overwrite
@@ -2074,7 +2296,7 @@ extern "C" int dblp_destroy(dblp_ctx* c) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     void* dev[] = {c->d_first_seq, c->d_b_off, c->d_b_cnt, c->d_hint, c->state[0].bitmap, c->state[1].bitmap, c->d_pending,
-                   c->acc_caller ? nullptr : c->acc_alloc[0], c->acc_caller ? nullptr : c->acc_alloc[1], c->d_home, c->state[0].counters, c->state[1].counters, c->d_flags, c->d_need, c->d_totals, c->d_partials, c->d_block_tallies,
+                   c->acc_caller ? nullptr : c->acc_alloc[0], c->acc_caller ? nullptr : c->acc_alloc[1], c->d_home, c->state[0].counters, c->state[1].counters, c->d_flags, c->few.entries, c->few.first, c->d_need, c->d_totals, c->d_partials, c->d_block_tallies,
                    c->state[0].rows, c->state[1].rows};
     for (void* p : dev) if (p) (void)hipFree(p);
     for (hipEvent_t e : c->cls_ev) if (e) (void)hipEventDestroy(e);
@@ -2412,6 +2634,9 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     ok = ok && hipMalloc(&c->d_pending, (u64)g.W * n_pkts * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_home, (n_pkts + 7) / 8 * 8 + 8) == hipSuccess;
     ok = ok && hipMalloc(&c->d_flags, F_COUNT * sizeof(u64)) == hipSuccess;
+    c->max_few = g.n_pkts / FEW_DIV < FEW_MAX ? g.n_pkts / FEW_DIV : FEW_MAX;
+    ok = ok && hipMalloc(&c->few.entries, (c->max_few + 1) * sizeof(u64)) == hipSuccess;
+    ok = ok && hipMalloc(&c->few.first, (n_pkts + 1) / 2 * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_need, pairs * sizeof(u32)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_totals, probe_blocks(c, pairs) * sizeof(u64)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_partials, PARTIALS_WORDS(c->max_partials) * sizeof(u64)) == hipSuccess;
@@ -2451,6 +2676,8 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
                        c->d_pending, n_pending, NONE64);
     for (int i = 0; i < 2; ++i) reset_state(c, i);
     c->other_clean = 1;
+    hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (n_pkts / 2 + 256) / 256, 16)), dim3(256), 0, c->stream,
+                       (u64*)c->few.first, (u64)((n_pkts + 1) / 2), NONE64);
     hipLaunchKernelGGL(fill_u64, dim3(1), dim3(64), 0, c->stream, c->d_flags, (u64)F_COUNT, 0ull);
     hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (probe_blocks(c, pairs) + 255) / 256, 16)), dim3(256), 0, c->stream,
                        c->d_totals, probe_blocks(c, pairs), 0ull);
@@ -2614,7 +2841,7 @@ extern "C" int dblp_packetize_list(dblp_ctx* c, uint16_t round, const float* con
 }
 
 typedef void (*gather_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, u64*, double*, float,
-                          GatherShape, GatherShape, u32, u32, u32, u32, u64*, u32*);
+                          GatherShape, GatherShape, u32, u32, u32, u32, u64*, u32*, ArrivalList);
 
 // The instance for `np` KB of a packet per step; few: one to three workers.
 template <bool DENSE, u32 LEAD>
@@ -2630,6 +2857,23 @@ template <bool DENSE>
 static gather_fn gather_kernel(u32 nw, bool lead, bool few, u32 np) {
     if (nw == 16) return np == 1 ? gather_stream<1, 4, 2, 16, 2, DENSE> : np == 2 ? gather_stream<2, 2, 2, 16, 2, DENSE> : gather_stream<4, 2, 2, 16, 2, DENSE>;
     return lead ? short_kernel<DENSE, 2>(few, np) : short_kernel<DENSE, 0>(few, np);
+}
+
+typedef void (*list_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, ArrivalList, const u32*, u32, u64*, u64*, double*, float, u32*);
+// The instance for pieces of `np` KB; units are counted from the payload in packets of up to four passes only.
+static list_fn list_kernel(bool lead, u32 np, bool team) {
+    if (team) return np == 3 ? gather_list<3, 2, true> : gather_list<4, 2, true>;
+    if (lead) return np == 1 ? gather_list<1, 2, false> : np == 2 ? gather_list<2, 2, false> : np == 3 ? gather_list<3, 2, false> : gather_list<4, 2, false>;
+    return np == 1 ? gather_list<1, 0, false> : np == 2 ? gather_list<2, 0, false> : np == 3 ? gather_list<3, 0, false> : gather_list<4, 0, false>;
+}
+// Batches that a gather_list launch takes whatever they are: as few as that it is the shorter way for dense ones too (us of
+// a batch that is dense, and of one that is not, by a launch that decides and by the list: 1 x 512 packets of 1472 B 14.6, 13.0 and 13.1, 11.5, of
+// 1024 14.7, 16.0 and 13.4, 11.6; 3 x 512 15.5, 14.8 and 13.6, 11.8; 8 x 192 15.8, 13.2 and 14.0, 12.4, 8 x 512 16.0, 19.6 and 15.6, 14.1), and
+// no packet is summed in many steps one after the other (eight: 32 workers of 1472 B 17.0 to 22.2, 17.6; 16: 64 workers 20.6 to 22.8, 22.0 to 25.0;
+// 24: 48 x 2816 B 22.4, 25.2; 32: 32 x 4816 B 25.7, 33.8).
+static bool few_always(const Geo& g, u64 n, u32 kb, bool team) {
+    const u32 pieces = (g.units + kb * WAVE - 1) / (kb * WAVE), steps = (g.W + FEW_DEPTH(kb) - 1) / FEW_DEPTH(kb) * (team ? (pieces + GS_WAVES - 1) / GS_WAVES : pieces);
+    return n <= 1536 && n <= 384ull * g.W && steps <= 8;
 }
 
 #define HEAVY_BYTES 131072u  // from all workers for one sequence number
@@ -2706,6 +2950,8 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
     const bool known = enough && is_dense && !d_mask && burst_pays(n_arrivals, g.n_pkts, g.W, (u32)c->n_cus, burst.r_max, burst.kb);
     const bool asked = enough && !known && n_arrivals * g.stride >= 256000000ull && !(few && is_dense && !d_mask);
     const bool in_bursts = known || asked, dense_only = is_dense && !asked;
+    ArrivalList list = {nullptr, nullptr, 0};
+    if (!in_bursts && !is_dense && n_arrivals <= c->max_few) { list = c->few; list.n = (u32)n_arrivals; }
     const u64 turns = in_bursts ? 8 : (groups + dense.blocks - 1) / dense.blocks;
     const bool whole = n_arrivals * WHOLE_DIV >= pairs && !asked && (!d_mask || turns <= 2);
     const bool any = whole && turns > 4;                // (two turns for nothing take 1 us; the word costs 0.4 to 1.5)
@@ -2719,22 +2965,40 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         const u32 grid = grid_for(c, (n_arrivals + 255) / 256, IDX_BLOCKS_PER_CU);
         const size_t table = ((size_t)g.B + 1) * sizeof(u32);
         const bool lds = table <= IDX_TABLE_LDS_MAX;
-        void (*idx)(Geo, const uint8_t*, const uint16_t*, u64, const u64*, const u32*, const u64*, u64, u32, u64*, u32*, u64*) =
+        void (*idx)(Geo, const uint8_t*, const uint16_t*, u64, const u64*, const u32*, const u64*, u64, u32, u64*, u32*, u64*, ArrivalList) =
             lds ? (d_queue ? index_arrivals<true, true> : index_arrivals<true, false>)
                 : (d_queue ? index_arrivals<false, true> : index_arrivals<false, false>);
         hipLaunchKernelGGL(idx, dim3(grid), dim3(256), lds ? table : 0, c->stream, g,
                            (const uint8_t*)d_packets, d_src_worker, (u64)n_slots, (const u64*)d_mask, d_order,
-                           (const u64*)d_queue, (u64)n_arrivals, (u32)c->round, c->d_pending, c->d_block_tallies, any ? c->d_flags + F_ANY + any_at : nullptr);
+                           (const u64*)d_queue, (u64)n_arrivals, (u32)c->round, c->d_pending, c->d_block_tallies, any ? c->d_flags + F_ANY + any_at : nullptr,
+                           list);
         n_tally_rows = grid;
     }
     const float inv_w = c->fold ? 1.0f / (float)g.W : 1.0f;   // exact for the powers of two it is used with
-    {
+    const u32 passes = unit_passes(g, units_from_packet(g)), list_kb = (passes + (passes + 3) / 4 - 1) / ((passes + 3) / 4);
+    const bool team = FEW_TEAM(g, list_kb);
+    if (list.entries && few_always(g, n_arrivals, list_kb, team)) {
+        const u32 blocks = grid_for(c, team ? n_arrivals : (n_arrivals + GS_WAVES - 1) / GS_WAVES, 4);
+        ProfScope ps(c, DBLP_K_GATHER_DIRECT, !small);
+        if (blocks > now.rows_used) now.rows_used = blocks;
+        hipLaunchKernelGGL(list_kernel(units_from_packet(g), list_kb, team), dim3(blocks + 1), dim3(GS_WAVES * WAVE), 0, c->stream, g, (const uint8_t*)d_packets,
+                           c->d_pending, now.bitmap, c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, list, (const u32*)c->d_block_tallies, n_tally_rows,
+                           now.counters, now.rows, (double*)(now.rows + ACCEPT_ROWS), inv_w, ps.d_told());
+    } else {
         u32 slots = 0, grid = dense.blocks;
         for (u32 l = 0; l <= (dense.sub_log2 > 2 ? dense.sub_log2 : 2); ++l)        // whatever the launch may choose
             if (GS_TEAM_LDS(g.W, l) > slots) slots = GS_TEAM_LDS(g.W, l);
         if (!dense_only) {
             if (GS_TEAM_LDS(g.W, sparse.sub_log2) > slots) slots = GS_TEAM_LDS(g.W, sparse.sub_log2);
             if (sparse.blocks > grid) grid = sparse.blocks;
+            // Few arrivals: a team for each, and, should they be dense, a group for each sequence number that they can touch.
+            const u64 teams = FEW_TEAM(g, np > 4 ? 3 : np) ? n_arrivals : (n_arrivals + nw - 1) / nw, groups_touched = ((n_arrivals * SPARSE_DIV + g.W - 1) / g.W >> (heavy ? 0 : 3)) + 2;
+            if (list.entries) {
+                const u64 most = teams > groups_touched ? teams : groups_touched;
+                if (grid > most) grid = (u32)most;
+                if (dense.blocks > grid) dense.blocks = grid;
+                if (sparse.blocks > grid) sparse.blocks = grid;
+            }
         }
         size_t lds = (size_t)nw * slots * sizeof(u32);
         const size_t table = ((size_t)g.B + 1) * sizeof(u32);
@@ -2753,7 +3017,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
             if (grid > now.rows_used) now.rows_used = grid;
             hipLaunchKernelGGL(kern, dim3(grid), dim3(nw * WAVE), lds, c->stream, g, (const uint8_t*)d_packets, c->d_pending, now.bitmap,
                                c->d_acc[0], c->d_acc[1], c->d_home, (u32)pick, (const u32*)c->d_block_tallies, n_tally_rows, now.counters,
-                               now.rows, (double*)(now.rows + ACCEPT_ROWS), inv_w, dense, sparse, (u32)c->n_cus, heavy, table_at, batch, c->d_flags, ps.d_told());
+                               now.rows, (double*)(now.rows + ACCEPT_ROWS), inv_w, dense, sparse, (u32)c->n_cus, heavy, table_at, batch, c->d_flags, ps.d_told(), list);
         }
     }
     LAUNCH_CHECK(c, "apply_arrivals");
