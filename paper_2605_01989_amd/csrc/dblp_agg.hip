@@ -24,7 +24,6 @@
 // W is a power of two (the division is exact), and the gather kernels keep the sum of squares of
 // what they store, so finalize_pass only writes zeros where nothing arrived (and moves or copies
 // spans where the result is wanted elsewhere); for other W it divides and squares itself.
-#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -2216,7 +2215,6 @@ struct dblp_ctx {
     // host copies of the geometry
     u32* h_first_seq; u64* h_b_off; u64* h_b_cnt;
     // protocol state
-    hipEvent_t done;        // end of the last launch that a call waits for
     int round_open; int finalized; uint16_t round;
     double prev_norm; int have_prev;
     // optional per-kernel timing (HIP events on the context's stream)
@@ -2285,25 +2283,6 @@ static int fail_hip(dblp_ctx* c, hipError_t e, const char* what) {
         if (e__ != hipSuccess) return fail_hip((c), e__, name);     \
     } while (0)
 
-// The last launch of a call that returns what it finds: it carries the event that the call then waits for, where
-// hipStreamSynchronize has the stream work off a marker behind the launch first (a launch of 30 us and the wait for it 42.3, 40.6
-// us; a pass of 3 workers x 5.3 M elements, two such waits, 95.2, 90.8, of 4 x 1 M, one or two, 59.6, 58.0).  The event is the launch's own end,
-// after everything before it on the stream, with the release to the host that the marker has.
-// On a stream that is being recorded nothing is waited for: the launch goes without it, and hipStreamSynchronize refuses.
-static bool recording(const dblp_ctx* c) {
-    if (!c->stream) return false;               // (the null stream cannot be recorded)
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return true;
-}
-#define LAUNCH_LAST(c, end, fn, grid, block, lds, ...)                                                              \
-    do {                                                                                                            \
-        if (end) hipExtLaunchKernelGGL(fn, grid, block, lds, (c)->stream, nullptr, end, 0, __VA_ARGS__);            \
-        else hipLaunchKernelGGL(fn, grid, block, lds, (c)->stream, __VA_ARGS__);                                    \
-    } while (0)
-static hipError_t wait_last(const dblp_ctx* c, hipEvent_t end) { return end ? hipEventSynchronize(end) : hipStreamSynchronize(c->stream); }
-
 static u32 grid_for(const dblp_ctx* c, u64 blocks_wanted, u32 blocks_per_cu) {
     u64 cap = (u64)c->n_cus * blocks_per_cu;
     u64 g = blocks_wanted < cap ? blocks_wanted : cap;
@@ -2321,7 +2300,6 @@ extern "C" int dblp_destroy(dblp_ctx* c) {
                    c->state[0].rows, c->state[1].rows};
     for (void* p : dev) if (p) (void)hipFree(p);
     for (hipEvent_t e : c->cls_ev) if (e) (void)hipEventDestroy(e);
-    if (c->done) (void)hipEventDestroy(c->done);
     if (c->h_mailbox) (void)hipHostFree(c->h_mailbox);
     if (c->h_told) (void)hipHostFree(c->h_told);
     if (c->timed) { for (auto& t : *c->timed) { (void)hipEventDestroy(t.a); (void)hipEventDestroy(t.b); } delete c->timed; }
@@ -2570,7 +2548,10 @@ static void reset_state(dblp_ctx* c, int i) {
 // A call that is recorded now will be told again with the state's addresses as they are, and a begin_round among the
 // recorded ones has to clear it each time: from the first such call on, one state stays in use and each begin_round launches.
 static void note_recording(dblp_ctx* c) {
-    if (!c->recorded && recording(c)) c->recorded = 1;
+    if (c->recorded || !c->stream) return;      // (the null stream cannot be recorded)
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) { (void)hipGetLastError(); c->recorded = 1; }
+    else if (st != hipStreamCaptureStatusNone) c->recorded = 1;
 }
 
 extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
@@ -2663,7 +2644,6 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     ok = ok && hipHostMalloc((void**)&c->h_mailbox, 16 * sizeof(u64), hipHostMallocMapped) == hipSuccess;
     if (!ok) { (void)hipGetLastError(); dblp_destroy(c); return DBLP_ENOMEM; }
     ok = ok && hipHostGetDevicePointer((void**)&c->d_mailbox, c->h_mailbox, 0) == hipSuccess;
-    ok = ok && hipEventCreateWithFlags(&c->done, hipEventDisableTiming | hipEventReleaseToSystem) == hipSuccess;
     ok = ok && hipMemcpyAsync(c->d_first_seq, c->h_first_seq, (B + 1) * sizeof(u32), hipMemcpyHostToDevice, c->stream) == hipSuccess;
     ok = ok && hipMemcpyAsync(c->d_b_off, c->h_b_off, B * sizeof(u64), hipMemcpyHostToDevice, c->stream) == hipSuccess;
     ok = ok && hipMemcpyAsync(c->d_b_cnt, c->h_b_cnt, B * sizeof(u64), hipMemcpyHostToDevice, c->stream) == hipSuccess;
@@ -2812,20 +2792,18 @@ extern "C" int dblp_packetize(dblp_ctx* c, uint32_t w, uint16_t round, const flo
     if (lo < elem_base || hi > elem_base + n_grad) return fail(c, DBLP_EINVAL, "packetize: packets outside the gradient window");
     HIP_TRY(c, hipSetDevice(c->device));
     *(volatile u64*)(c->h_mailbox + 4) = 0;
-    const hipEvent_t end = recording(c) ? nullptr : c->done;
     const size_t table = ((size_t)c->g.B + 1) * sizeof(u32);
-    const bool lds = table <= IDX_TABLE_LDS_MAX;
-    void (*const kern)(Geo, u32, u32, const float*, u64, u32, u32, const u32*, u64, u64, uint8_t*, uint16_t*, u64*) = lds ? packetize_kernel<true> : packetize_kernel<false>;
-    const dim3 grid(grid_for(c, (n_pkts + 3) / 4, 8));
-    if (d_slot_map)
-        LAUNCH_LAST(c, end, kern, grid, dim3(256), lds ? table : 0, c->g, w, (u32)round, d_grad, (u64)elem_base, (u32)first_seq, (u32)n_pkts, d_slot_map,
-                    (u64)slot_base, (u64)n_slots, (uint8_t*)d_packets, d_src_worker, c->d_mailbox + 4);
+    if (table <= IDX_TABLE_LDS_MAX)
+        hipLaunchKernelGGL(packetize_kernel<true>, dim3(grid_for(c, (n_pkts + 3) / 4, 8)), dim3(256), table, c->stream, c->g, w,
+                           (u32)round, d_grad, (u64)elem_base, (u32)first_seq, (u32)n_pkts, d_slot_map, (u64)slot_base,
+                           (u64)n_slots, (uint8_t*)d_packets, d_src_worker, c->d_mailbox + 4);
     else
-        hipLaunchKernelGGL(kern, grid, dim3(256), lds ? table : 0, c->stream, c->g, w, (u32)round, d_grad, (u64)elem_base, (u32)first_seq, (u32)n_pkts, d_slot_map,
-                           (u64)slot_base, (u64)n_slots, (uint8_t*)d_packets, d_src_worker, c->d_mailbox + 4);
+        hipLaunchKernelGGL(packetize_kernel<false>, dim3(grid_for(c, (n_pkts + 3) / 4, 8)), dim3(256), 0, c->stream, c->g, w,
+                           (u32)round, d_grad, (u64)elem_base, (u32)first_seq, (u32)n_pkts, d_slot_map, (u64)slot_base,
+                           (u64)n_slots, (uint8_t*)d_packets, d_src_worker, c->d_mailbox + 4);
     LAUNCH_CHECK(c, "packetize");
     if (d_slot_map) {   // slots come from device memory: the kernel checks them, report here
-        HIP_TRY(c, wait_last(c, end));
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
         if (*(volatile u64*)(c->h_mailbox + 4)) return fail(c, DBLP_EINVAL, "packetize: slot map entry outside the packet buffer");
     }
     return DBLP_OK;
@@ -2847,14 +2825,17 @@ extern "C" int dblp_packetize_list(dblp_ctx* c, uint16_t round, const float* con
     }
     HIP_TRY(c, hipSetDevice(c->device));
     *(volatile u64*)(c->h_mailbox + 4) = 0;
-    const hipEvent_t end = recording(c) ? nullptr : c->done;
     const size_t table = ((size_t)c->g.B + 1) * sizeof(u32);
-    const bool lds = table <= IDX_TABLE_LDS_MAX;
-    void (*const kern)(Geo, GradPtrs, u32, const u64*, u64, u64, uint8_t*, uint16_t*, u64*) = lds ? packetize_list_kernel<true> : packetize_list_kernel<false>;
-    LAUNCH_LAST(c, end, kern, dim3(grid_for(c, (n + 3) / 4, 8)), dim3(256), lds ? table : 0, c->g, gp, (u32)round, (const u64*)d_list, (u64)n, (u64)slot_base,
-                (uint8_t*)d_packets, d_src_worker, c->d_mailbox + 4);
+    if (table <= IDX_TABLE_LDS_MAX)
+        hipLaunchKernelGGL(packetize_list_kernel<true>, dim3(grid_for(c, (n + 3) / 4, 8)), dim3(256), table, c->stream, c->g, gp,
+                           (u32)round, (const u64*)d_list, (u64)n, (u64)slot_base, (uint8_t*)d_packets, d_src_worker,
+                           c->d_mailbox + 4);
+    else
+        hipLaunchKernelGGL(packetize_list_kernel<false>, dim3(grid_for(c, (n + 3) / 4, 8)), dim3(256), 0, c->stream, c->g, gp,
+                           (u32)round, (const u64*)d_list, (u64)n, (u64)slot_base, (uint8_t*)d_packets, d_src_worker,
+                           c->d_mailbox + 4);
     LAUNCH_CHECK(c, "packetize_list");
-    HIP_TRY(c, wait_last(c, end));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
     if (*(volatile u64*)(c->h_mailbox + 4)) return fail(c, DBLP_EINVAL, "packetize_list: list entry with worker or seq out of range");
     return DBLP_OK;
 }
@@ -3081,7 +3062,6 @@ extern "C" int dblp_loss_account(dblp_ctx* c, uint32_t bound_ppm, uint32_t* d_mi
     const u64 pairs = (u64)g.W * g.B, blocks = probe_blocks(c, pairs);
     const u32 ppw = probe_ppw(c, pairs);
     if (blocks > 0x7FFFFFFFull) return fail(c, DBLP_EINVAL, "loss_account: too many (worker, bucket) pairs");
-    const hipEvent_t end = recording(c) ? nullptr : c->done;
     {
         ProfScope ps(c, DBLP_K_PROBE);
         bool done = blocks * 4 <= (u64)PROBE_RESIDENT * c->n_cus;
@@ -3090,12 +3070,11 @@ extern "C" int dblp_loss_account(dblp_ctx* c, uint32_t bound_ppm, uint32_t* d_mi
             const u64 tag = (u64)(c->probe_no & 0xFFFFFFu) << PROBE_TAG_SHIFT;
             volatile u64* const gave_up = c->h_mailbox + M_PROBE_GAVE_UP;
             *gave_up = 0;
-            void (*const kern)(Geo, const u64*, u32, u32, u64, u32*, u64*, u64, u32, u64*, u64, u64*) = c->probe_block_pair ? probe_once<true> : probe_once<false>;
-            LAUNCH_LAST(c, end, kern, dim3((u32)blocks), dim3(256), 0, g, bitmap, bound_ppm, ppw, pairs, d_missing, c->d_totals, tag, c->probe_polls, (u64*)d_retx_list,
-                        (u64)retx_capacity, c->d_mailbox);
+            hipLaunchKernelGGL(c->probe_block_pair ? probe_once<true> : probe_once<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g,
+                               bitmap, bound_ppm, ppw, pairs, d_missing, c->d_totals, tag, c->probe_polls, (u64*)d_retx_list, (u64)retx_capacity, c->d_mailbox);
             LAUNCH_CHECK(c, "loss_account");
             ps.end();
-            HIP_TRY(c, wait_last(c, end));
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
             done = *gave_up == 0;
         }
         if (!done) {
@@ -3105,12 +3084,11 @@ extern "C" int dblp_loss_account(dblp_ctx* c, uint32_t bound_ppm, uint32_t* d_mi
             hipLaunchKernelGGL(c->probe_block_pair ? loss_count<true> : loss_count<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g,
                                bitmap, bound_ppm, ppw, pairs, d_missing, c->d_need, c->d_totals);
             if (scanned) hipLaunchKernelGGL(scan_totals, dim3(1), dim3(1024), 0, c->stream, c->d_totals, (u32)blocks);
-            void (*const kern)(Geo, const u64*, u32, u64, const u32*, const u64*, int, u64*, u64, u64*) = c->probe_block_pair ? emit_retx<true> : emit_retx<false>;
-            LAUNCH_LAST(c, end, kern, dim3((u32)blocks), dim3(256), 0, g, bitmap, ppw, pairs, (const u32*)c->d_need, (const u64*)c->d_totals, scanned, (u64*)d_retx_list,
-                        (u64)retx_capacity, c->d_mailbox);
+            hipLaunchKernelGGL(c->probe_block_pair ? emit_retx<true> : emit_retx<false>, dim3((u32)blocks), dim3(256), 0, c->stream, g, bitmap, ppw, pairs,
+                               (const u32*)c->d_need, (const u64*)c->d_totals, scanned, (u64*)d_retx_list, (u64)retx_capacity, c->d_mailbox);
             LAUNCH_CHECK(c, "loss_account");
             ps.end();
-            HIP_TRY(c, wait_last(c, end));
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
         }
     }
     c->mailbox_seen = 1;
@@ -3178,16 +3156,16 @@ extern "C" int dblp_phase_signal(dblp_ctx* c, const float* d_vec, double* h_norm
     if (!c) return DBLP_EINVAL;
     if (!h_norm || !h_rel_delta || !h_critical) return fail(c, DBLP_EINVAL, "phase_signal: null host pointer");
     HIP_TRY(c, hipSetDevice(c->device));
-    const hipEvent_t end = d_vec && !recording(c) ? c->done : nullptr;
     if (d_vec) {
         if (((uintptr_t)d_vec & 15) != 0) return fail(c, DBLP_EINVAL, "phase_signal: d_vec must be 16-byte aligned");
-        LAUNCH_LAST(c, end, sumsq_vec, dim3(sumsq_grid((u32)c->n_cus, c->N)), dim3(256), 0, d_vec, (u64)c->N, c->d_partials, c->max_partials, (double*)(c->d_mailbox + 1));
+        hipLaunchKernelGGL(sumsq_vec, dim3(sumsq_grid((u32)c->n_cus, c->N)), dim3(256), 0, c->stream, d_vec, (u64)c->N, c->d_partials, c->max_partials,
+                           (double*)(c->d_mailbox + 1));
         c->finalized = 0;   // the mailbox does not belong to a finalize any more
     } else {
         if (!c->finalized) return fail(c, DBLP_ESTATE, "phase_signal without a finalize in this round");
     }
     LAUNCH_CHECK(c, "phase_signal");
-    HIP_TRY(c, wait_last(c, end));          // without a vector: for whatever has been launched since the finalize
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
     c->mailbox_seen = 1;
     double ss;
     memcpy(&ss, c->h_mailbox + 1, sizeof ss);

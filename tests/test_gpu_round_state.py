@@ -112,43 +112,3 @@ def test_part_of_a_round_recorded(what):
                     side.synchronize()
                     graph.replay()
             rx.check(flags, scalars=what == "begin and arrivals")     # (what the host keeps of a call, it keeps when that is recorded)
-
-
-_RECORD = """
-import ctypes, sys, torch
-import paper_2605_01989_amd as dblp
-hip = ctypes.CDLL("libamdhip64.so")
-side = torch.cuda.Stream()
-with torch.cuda.stream(side):
-    agg = dblp.Aggregator(4, 30011, 64, [0], [30011])
-    vec, src = torch.ones(30011, device="cuda"), torch.empty(5, dtype=torch.int16, device="cuda")
-    retx, missing = torch.arange(3000, device="cuda"), torch.empty(4, dtype=torch.int32, device="cuda")
-    packets = torch.empty(5 * agg.stride, dtype=torch.uint8, device="cuda")
-    slots = torch.arange(5, device="cuda").int()
-    call = [lambda: agg.loss_account(0, missing, retx), lambda: agg.phase_signal(vec),
-            lambda: agg.packetize_list(5, [vec] * 4, retx, 5, packets, src),
-            lambda: agg.packetize(0, 5, vec, 0, 0, 5, packets, src, d_slot_map=slots)][int(sys.argv[1])]
-    agg.begin_round(5)
-    call()
-    side.synchronize()
-    stream, graph = ctypes.c_void_p(side.cuda_stream), ctypes.c_void_p()
-    assert hip.hipStreamBeginCapture(stream, 1) == 0            # this thread's calls only
-    try:
-        call()
-        print("answered", flush=True)
-    except dblp.binding.DblpError as e:
-        print("refused" if e.code == dblp.binding.EHIP else e, flush=True)
-    hip.hipStreamEndCapture(stream, ctypes.byref(graph))
-"""
-
-
-@pytest.mark.parametrize("call", range(4))
-def test_scalars_are_refused_on_a_stream_that_is_recorded(call):
-    """Calls that return host scalars would return what an earlier call found.  In a process of its own: what the
-    runtime keeps of a recording that failed is no concern of the other tests."""
-    import os
-    import subprocess
-    import sys
-    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-    done = subprocess.run([sys.executable, "-c", _RECORD, str(call)], cwd=root, capture_output=True, text=True, timeout=100)
-    assert "refused" in done.stdout.split(), done.stdout + done.stderr
