@@ -1861,9 +1861,9 @@ __device__ __forceinline__ double fold_partials(u64* words, u32 n, u32 tag, u32 
 //                              no scaling (in-place form: only moved and missing spans are touched)
 //   nobody delivered it        out = 0 exactly
 // A wave takes a group of 2^grp_log2 consecutive packets (at most 64: one bitmap word), or one of the
-// n_piece pieces of at most FIN_PIECE elements of its range.  Consecutive packets are consecutive elements,
+// n_piece pieces of per_piece elements of its range.  Consecutive packets are consecutive elements,
 // across bucket boundaries too, so a group that arrived whole and lives in one copy is a plain copy of its
-// range in aligned 16-byte units, four in flight per lane; other groups go run by run.  Memory bounds
+// range in aligned 16-byte units, four in flight per lane (PAST: eight, and past the caches); other groups go run by run.  Memory bounds
 // it; a wave's share is bounded in elements because with 8 packets per wave, whatever their length, a round
 // of long packets had a few hundred waves, and groups that cross a bucket went element by element:
 //   3 workers x 15.5 M in 64 KB packets    568 -> 27 us
@@ -1874,12 +1874,11 @@ __device__ __forceinline__ double fold_partials(u64* words, u32 n, u32 tag, u32 
 // gather kernels kept it per block in sumsq_rows.  The one extra block of this launch (blockIdx.x == n_work_blocks) adds
 // up the one or the other in a fixed order (fixed for given launch sizes of the round's gather kernels) and
 // writes the total to the host mailbox.
-#define FIN_PIECE 4096
-template <bool TABLE_IN_LDS>
+template <bool TABLE_IN_LDS, bool PAST>
 __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restrict__ bitmap, const float* acc0,
                                                      const float* acc1, uint8_t* __restrict__ home,
                                                      float* out, int scale_mode, float wf, int move_home,
-                                                     u32 grp_log2, u32 n_piece, u64* partials, u32 n_max, u32 n_work_blocks,
+                                                     u32 grp_log2, u32 n_piece, u32 per_piece, u64* partials, u32 n_max, u32 n_work_blocks,
                                                      const double* __restrict__ sumsq_rows, const u64* __restrict__ accept_rows,
                                                      u32 n_rows,
                                                      u64* __restrict__ counters, u64* __restrict__ mailbox, RoundState other) {
@@ -1986,14 +1985,22 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
             return;
         }
         const f4v* s = (const f4v*)src;
-        for (; c + 3 * WAVE < c1; c += 4 * WAVE) {
-            f4v v[4];
+        constexpr int R = PAST ? 8 : 4;             // units in flight per lane
+        for (; c < c1; c += R * WAVE) {
+            f4v v[R];
             #pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = s[c + k * WAVE];
+            for (int k = 0; k < R; ++k) {
+                v[k] = zero;
+                if (c + k * WAVE < c1) v[k] = PAST ? __builtin_nontemporal_load(s + c + k * WAVE) : s[c + k * WAVE];
+            }
             #pragma unroll
-            for (int k = 0; k < 4; ++k) o[c + k * WAVE] = scaled(v[k]);
+            for (int k = 0; k < R; ++k) {
+                if (c + k * WAVE >= c1) break;
+                const f4v r = scaled(v[k]);
+                if (PAST) __builtin_nontemporal_store(r, o + c + k * WAVE);
+                else o[c + k * WAVE] = r;
+            }
         }
-        for (; c < c1; c += WAVE) o[c] = scaled(s[c]);
     };
 
     for (u64 item = wave; item < n_items; item += n_waves, fetch(item)) {
@@ -2016,7 +2023,7 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
             return ((u64)(u32)__builtin_amdgcn_readlane((int)(u32)(elem_l >> 32), (int)t) << 32) | (u32)__builtin_amdgcn_readlane((int)(u32)elem_l, (int)t);
         };
         const u64 g0 = elem_of(0), g1 = elem_of(n_t - 1) + (u32)__builtin_amdgcn_readlane((int)len_l, (int)(n_t - 1));
-        const u64 p0 = g0 + (u64)piece * FIN_PIECE, p1 = n_piece == 1 || p0 + FIN_PIECE > g1 ? g1 : p0 + FIN_PIECE;
+        const u64 p0 = g0 + (u64)piece * per_piece, p1 = n_piece == 1 || p0 + per_piece > g1 ? g1 : p0 + per_piece;
         if (p0 >= p1) continue;
         if (todo == full && any == full && ((second & full) == 0 || (second & full) == full)) {
             write_range((second & 1ull) ? acc1 : acc0, p0, p1);
@@ -2447,9 +2454,13 @@ static int pick_copy(dblp_ctx* c, const void* d_packets, u64 bytes, u64 n_slots,
     return pick;
 }
 
-#ifndef FIN_BLOCKS_PER_CU
 #define FIN_BLOCKS_PER_CU 8
-#endif
+// Elements from which a copy goes past the caches, eight units in flight per lane: what a large gradient's lines would displace is
+// worth more than they are, and the mean is read again only once it has all been written.  us of a pass that copies out, and in
+// brackets with a kernel that reads the mean behind it, before and now: 3 x 22 M elements 187, 177 (222, 214); 13 x 22 M 336, 332 (372, 365); 1 x 60 M
+// 242, 215 (316, 303); 1 x 137 M 583, 526 (778, 714); 3 x 200 M 1000, 983 (1266, 1253).  Below, the caches hold it: 4 x 16 M 122.5,
+// 122.5 (143, 146), 1 x 12 M 73, 75 (88, 91), 3 x 8 M 106, 108 (122, 126).
+#define FIN_PAST 20000000ull
 #ifndef IDX_BLOCKS_PER_CU
 #define IDX_BLOCKS_PER_CU 4   // 2-4 blocks per CU index 3 % faster than 8: its bound is requests to memory, not latency
 #endif
@@ -3117,11 +3128,15 @@ extern "C" int dblp_finalize(dblp_ctx* c, int compensation, float* d_out) {
     const Geo& g = c->g;
     // Packets per wave: where the result is left in place most waves have nothing to write, so they look
     // at a whole bitmap word (fewer packets when they are long: what is written is written by one wave);
-    // into another buffer as many as make about 4096 elements, longer ones in pieces.
+    // into another buffer as many as make up to 8192 elements, in pieces of up to 4096 and of equal size (past the caches
+    // whole groups of 4096; of a short gradient 2048, so that all CUs have some: 6 workers x 0.9 M elements, a pass 75.1 -> 72.7
+    // us, 3 x 2.8 M 79.1 -> 77.9, but 13 x 5.7 M 161 -> 164).
     u32 grp_log2 = 6;
-    const u64 most = in_place ? 32768 : 2 * FIN_PIECE;
+    const bool past = !in_place && c->N >= FIN_PAST, brief = c->N < 4000000ull;
+    const u64 most = in_place ? 32768 : brief ? 2048 : past ? 4096 : 8192;
     while (grp_log2 > 0 && ((u64)g.P << grp_log2) > most) --grp_log2;
-    const u32 n_piece = in_place ? 1 : (u32)((((u64)g.P << grp_log2) + FIN_PIECE - 1) / FIN_PIECE);
+    const u64 elems = (u64)g.P << grp_log2, cap = brief ? 2048 : 4096;
+    const u32 n_piece = in_place ? 1 : (u32)((elems + cap - 1) / cap), per_piece = (u32)(((elems + n_piece - 1) / n_piece + 255) / 256 * 256);
     const u64 items = (((u64)g.n_pkts + (1u << grp_log2) - 1) >> grp_log2) * n_piece;
     const u32 work = grid_for(c, (items + 3) / 4, FIN_BLOCKS_PER_CU);
     note_recording(c);
@@ -3133,11 +3148,12 @@ extern "C" int dblp_finalize(dblp_ctx* c, int compensation, float* d_out) {
     {
         ProfScope ps(c, DBLP_K_FINALIZE);
         const size_t table = ((size_t)g.B + 1) * sizeof(u32);
-        void (*kern)(Geo, const u64*, const float*, const float*, uint8_t*, float*, int, float, int, u32, u32, u64*, u32, u32,
-                     const double*, const u64*, u32, u64*, u64*, RoundState) = table <= IDX_TABLE_LDS_MAX ? finalize_pass<true> : finalize_pass<false>;
+        void (*kern)(Geo, const u64*, const float*, const float*, uint8_t*, float*, int, float, int, u32, u32, u32, u64*, u32, u32,
+                     const double*, const u64*, u32, u64*, u64*, RoundState) =
+            table <= IDX_TABLE_LDS_MAX ? (past ? finalize_pass<true, true> : finalize_pass<true, false>) : (past ? finalize_pass<false, true> : finalize_pass<false, false>);
         hipLaunchKernelGGL(kern, dim3(grid), dim3(256), table <= IDX_TABLE_LDS_MAX ? table : 0, c->stream, g, (const u64*)now.bitmap,
                            (const float*)c->d_acc[0], (const float*)c->d_acc[1], c->d_home, out, c->fold ? 0 : 1, (float)g.W,
-                           in_place ? 1 : 0, grp_log2, n_piece, c->d_partials, c->max_partials, work, (const double*)(now.rows + ACCEPT_ROWS), (const u64*)now.rows,
+                           in_place ? 1 : 0, grp_log2, n_piece, per_piece, c->d_partials, c->max_partials, work, (const double*)(now.rows + ACCEPT_ROWS), (const u64*)now.rows,
                            now.rows_used, now.counters, c->d_mailbox, other);
     }
     LAUNCH_CHECK(c, "finalize");
