@@ -2181,7 +2181,8 @@ struct dblp_ctx {
     hipStream_t stream;
     int n_cus;
     // device state
-    u32* d_first_seq; u64* d_b_off; u64* d_b_cnt; u32* d_hint;
+    u64* slab;              // what follows, but for the hints and the accumulator
+    u32* d_hint;
     RoundState state[2];    // the open round's (cur) and the other one; both kinds of rows, [ACCEPT_ROWS] each, lie in one allocation
     int cur;
     int other_clean;        // the state that is not in use is all zero, once what has been launched has ended
@@ -2221,6 +2222,7 @@ struct dblp_ctx {
     u64* d_mailbox;         // device address of h_mailbox
     // host copies of the geometry
     u32* h_first_seq; u64* h_b_off; u64* h_b_cnt;
+    u64* h_tables;          // the three as they lie on the device
     // protocol state
     int round_open; int finalized; uint16_t round;
     double prev_norm; int have_prev;
@@ -2302,16 +2304,14 @@ extern "C" int dblp_destroy(dblp_ctx* c) {
     if (!c) return DBLP_OK;
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
-    void* dev[] = {c->d_first_seq, c->d_b_off, c->d_b_cnt, c->d_hint, c->state[0].bitmap, c->state[1].bitmap, c->d_pending,
-                   c->acc_caller ? nullptr : c->acc_alloc[0], c->acc_caller ? nullptr : c->acc_alloc[1], c->d_home, c->state[0].counters, c->state[1].counters, c->d_flags, c->few.entries, c->few.first, c->d_need, c->d_totals, c->d_partials, c->d_block_tallies,
-                   c->state[0].rows, c->state[1].rows};
+    void* dev[] = {c->slab, c->d_hint, c->acc_caller ? nullptr : c->acc_alloc[0], c->acc_caller ? nullptr : c->acc_alloc[1]};
     for (void* p : dev) if (p) (void)hipFree(p);
     for (hipEvent_t e : c->cls_ev) if (e) (void)hipEventDestroy(e);
     if (c->h_mailbox) (void)hipHostFree(c->h_mailbox);
     if (c->h_told) (void)hipHostFree(c->h_told);
     if (c->timed) { for (auto& t : *c->timed) { (void)hipEventDestroy(t.a); (void)hipEventDestroy(t.b); } delete c->timed; }
     if (c->ev_pool) { for (auto e : *c->ev_pool) (void)hipEventDestroy(e); delete c->ev_pool; }
-    free(c->h_first_seq); free(c->h_b_off); free(c->h_b_cnt);
+    free(c->h_first_seq); free(c->h_b_off); free(c->h_b_cnt); free(c->h_tables);
     free(c);
     return DBLP_OK;
 }
@@ -2633,33 +2633,40 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     u32 longest = 0;        // packets of the longest bucket
     for (u32 b = 0; b < B; ++b) longest = c->h_first_seq[b + 1] - c->h_first_seq[b] > longest ? c->h_first_seq[b + 1] - c->h_first_seq[b] : longest;
     c->probe_block_pair = pairs <= 8u * (u32)c->n_cus && longest > WAVE * WAVE * PROBE_UNROLL;
-    bool ok = true;
-    ok = ok && hipMalloc(&c->d_first_seq, (B + 1) * sizeof(u32)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_b_off, B * sizeof(u64)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_b_cnt, B * sizeof(u64)) == hipSuccess;
-    for (RoundState& st : c->state) {
-        ok = ok && hipMalloc(&st.bitmap, g.W * g.words_pw * sizeof(u64)) == hipSuccess;
-        ok = ok && hipMalloc(&st.rows, 2 * ACCEPT_ROWS * sizeof(u64)) == hipSuccess;    // accepted packets, sums of squares
-        ok = ok && hipMalloc(&st.counters, C_COUNT * sizeof(u64)) == hipSuccess;
-    }
-    ok = ok && hipMalloc(&c->d_pending, (u64)g.W * n_pkts * sizeof(u64)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_home, (n_pkts + 7) / 8 * 8 + 8) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_flags, F_COUNT * sizeof(u64)) == hipSuccess;
     c->max_few = g.n_pkts / FEW_DIV < FEW_MAX ? g.n_pkts / FEW_DIV : FEW_MAX;
-    ok = ok && hipMalloc(&c->few.entries, (c->max_few + 1) * sizeof(u64)) == hipSuccess;
-    ok = ok && hipMalloc(&c->few.first, (n_pkts + 1) / 2 * sizeof(u64)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_need, pairs * sizeof(u32)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_totals, probe_blocks(c, pairs) * sizeof(u64)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_partials, PARTIALS_WORDS(c->max_partials) * sizeof(u64)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_block_tallies, (size_t)c->n_cus * IDX_BLOCKS_PER_CU * 5 * sizeof(u32)) == hipSuccess;
+    // One allocation for all of it, and two launches to fill it: a context of 1 M elements and 4 workers is made in 130 us (with an
+    // allocation each 184).
+    const u64 n_totals = probe_blocks(c, pairs), n_pending = (u64)g.W * n_pkts, n_first = (n_pkts + 1) / 2, n_home = (n_pkts + 7) / 8 + 1;
+    u64 size = 0;
+    auto part = [&](u64 words) { const u64 at = size; size += (words + 31) / 32 * 32; return at; };      // of 8 bytes, 256-byte aligned
+    const u64 at_first = part(B / 2 + 1), at_off = part(B), at_cnt = part(B), tables = size;               // as on the host
+    const u64 at_tallies = part((u64)c->n_cus * IDX_BLOCKS_PER_CU * 5 / 2 + 1), at_need = part((pairs + 1) / 2), at_list = part(c->max_few + 1);
+    const u64 zeros = size;
+    const u64 at_flags = part(F_COUNT), at_partials = part(PARTIALS_WORDS(c->max_partials)), at_totals = part(n_totals);
+    u64 at_state[2][3];
+    for (auto& at : at_state) { at[0] = part(C_COUNT); at[1] = part(2 * ACCEPT_ROWS); at[2] = part(g.W * g.words_pw); }     // rows: accepted packets, sums of squares
+    const u64 at_home = part(n_home), n_zeros = size - zeros;
+    const u64 ones = size, at_list_first = part(n_first), at_pending = part(n_pending), n_ones = size - ones;
+    bool ok = hipMalloc(&c->slab, size * sizeof(u64)) == hipSuccess;
+    c->h_tables = (u64*)calloc(tables, sizeof(u64));
+    if (!c->h_tables) ok = false;
+    if (ok) {
+        u64* const base = c->slab;
+        c->d_block_tallies = (u32*)(base + at_tallies); c->d_need = (u32*)(base + at_need);
+        c->d_flags = base + at_flags; c->d_partials = base + at_partials; c->d_totals = base + at_totals;
+        for (int k = 0; k < 2; ++k) c->state[k] = {base + at_state[k][2], base + at_state[k][1], base + at_state[k][0], 0};
+        c->d_home = (uint8_t*)(base + at_home);
+        c->few.entries = base + at_list; c->few.first = (u32*)(base + at_list_first); c->d_pending = base + at_pending;
+        g.first_seq = (const u32*)(base + at_first); g.b_off = base + at_off; g.b_cnt = base + at_cnt;
+        memcpy(c->h_tables + at_first, c->h_first_seq, (B + 1) * sizeof(u32));
+        memcpy(c->h_tables + at_off, c->h_b_off, B * sizeof(u64));
+        memcpy(c->h_tables + at_cnt, c->h_b_cnt, B * sizeof(u64));
+    }
     ok = ok && hipHostMalloc((void**)&c->h_mailbox, 16 * sizeof(u64), hipHostMallocMapped) == hipSuccess;
     if (!ok) { (void)hipGetLastError(); dblp_destroy(c); return DBLP_ENOMEM; }
     ok = ok && hipHostGetDevicePointer((void**)&c->d_mailbox, c->h_mailbox, 0) == hipSuccess;
-    ok = ok && hipMemcpyAsync(c->d_first_seq, c->h_first_seq, (B + 1) * sizeof(u32), hipMemcpyHostToDevice, c->stream) == hipSuccess;
-    ok = ok && hipMemcpyAsync(c->d_b_off, c->h_b_off, B * sizeof(u64), hipMemcpyHostToDevice, c->stream) == hipSuccess;
-    ok = ok && hipMemcpyAsync(c->d_b_cnt, c->h_b_cnt, B * sizeof(u64), hipMemcpyHostToDevice, c->stream) == hipSuccess;
+    ok = ok && hipMemcpyAsync(c->slab + at_first, c->h_tables, tables * sizeof(u64), hipMemcpyHostToDevice, c->stream) == hipSuccess;
     if (!ok) { (void)hipGetLastError(); dblp_destroy(c); return DBLP_EHIP; }
-    g.first_seq = c->d_first_seq; g.b_off = c->d_b_off; g.b_cnt = c->d_b_cnt;
     if (((size_t)B + 1) * sizeof(u32) > IDX_TABLE_LDS_MAX) {
         const size_t n = (size_t)g.words_pw + 1;
         u32* h = (u32*)malloc(n * sizeof(u32));
@@ -2682,19 +2689,9 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
         c->burst.fn = nullptr;
     }
 
-    const u64 n_pending = (u64)g.W * n_pkts;
-    hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (n_pending + 255) / 256, 16)), dim3(256), 0, c->stream,
-                       c->d_pending, n_pending, NONE64);
-    for (int i = 0; i < 2; ++i) reset_state(c, i);
+    hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (n_ones + 255) / 256, 16)), dim3(256), 0, c->stream, c->slab + ones, n_ones, NONE64);
+    hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (n_zeros + 255) / 256, 16)), dim3(256), 0, c->stream, c->slab + zeros, n_zeros, 0ull);
     c->other_clean = 1;
-    hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (n_pkts / 2 + 256) / 256, 16)), dim3(256), 0, c->stream,
-                       (u64*)c->few.first, (u64)((n_pkts + 1) / 2), NONE64);
-    hipLaunchKernelGGL(fill_u64, dim3(1), dim3(64), 0, c->stream, c->d_flags, (u64)F_COUNT, 0ull);
-    hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (probe_blocks(c, pairs) + 255) / 256, 16)), dim3(256), 0, c->stream,
-                       c->d_totals, probe_blocks(c, pairs), 0ull);
-    hipLaunchKernelGGL(fill_u64, dim3(8), dim3(256), 0, c->stream, c->d_partials, (u64)PARTIALS_WORDS(c->max_partials), 0ull);
-    hipLaunchKernelGGL(fill_u64, dim3(grid_for(c, (n_pkts + 16 + 2047) / 2048, 16)), dim3(256), 0, c->stream,
-                       (u64*)c->d_home, (u64)((n_pkts + 7) / 8 + 1), 0ull);
     e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess || hipGetLastError() != hipSuccess) { dblp_destroy(c); return DBLP_EHIP; }
     // accumulator last
