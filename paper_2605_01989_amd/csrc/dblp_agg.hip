@@ -472,8 +472,8 @@ __device__ __forceinline__ bool batch_is_sparse(const BatchInfo& bi, u32 W) {
 }
 
 // A block takes a group of `sub` = 16 (8 to 1 in short ranges, 32 in sparse batches, where a single wave may take one)
-// consecutive sequence numbers: every wave reads the group's arrival index (64 / sub workers x sub packets per load), ballots which packets are
-// new, and keeps their slots in its own LDS rows; after a barrier the first wave resets the index
+// consecutive sequence numbers: every wave reads the group's arrival index (64 / sub workers x sub packets per load; of many workers
+// its share), ballots which packets are new, and keeps their slots in LDS; after a barrier the first wave resets the index
 // entries and sets the bitmap, whose bytes the group owns (8, 16 or 32 bits: a plain store, where one
 // memory-side atomic per worker and group took up to a microsecond of a small group's time).  The
 // waves then share the group's packets, cut into pieces of NP KB when they are longer than 5 KB.
@@ -594,7 +594,12 @@ __host__ __device__ static inline u32 group_log2(u64 n, u32 cus, bool pieces, u3
 struct GatherShape { u32 sub_log2, n_piece, blocks; };
 
 // The gather of one batch by blocks 0 .. s.blocks - 1 of the launch.  fs: the bucket boundaries.
-template <int NP, int G, int D, int NW, bool SPARSE, u32 LEAD>
+// MANY (more than 16 workers, whose index is several trips to memory, one after the other): the block's waves share a group's
+// rows of the index out instead of each reading all of them.  us of index pass and gather, rows read by all and shared
+// out: 32 workers x 82 k numbers of 1472 B, 78 k packets late 90, 82, 210 k late 140, 131; 64 x 33 k, 63 k late 72, 62, 168 k late
+// 118, 107; whole rounds of 24 to 64 workers 0.5 to 1 % either way.  With fewer workers the waves' waiting for each other is all
+// that it gives: 4 x 4096 packets of 1040 B 14.4, 15.8; 16 x 5465, 2.6 k late 17.7, 18.2.
+template <int NP, int G, int D, int NW, bool SPARSE, u32 LEAD, bool MANY>
 __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi, const GatherShape& s, const u32* fs, u32* sh_slots,
                                               const uint8_t* __restrict__ packets, u64* __restrict__ pending, u64* __restrict__ bitmap,
                                               float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
@@ -602,12 +607,17 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
     __shared__ u32 sh_accepted[NW];
     __shared__ double sh_sq[NW];
     __shared__ u32 sh_tile[4];      // sparse: groups of the tile that hold an arrival; groups left to the whole block
+    __shared__ u32 sh_any[3][2];    // MANY: of three groups in turn, packets with a new copy; packets with contents
     if (blockIdx.x >= s.blocks) return;
+    u32 turn = 0, f = 0;            // MANY: groups that the block has taken together, modulo 2 and 3
+    if (MANY) {
+        if (threadIdx.x < 6) sh_any[0][threadIdx.x] = 0;
+        __syncthreads();
+    }
     const u32 lane = lane_id();
     const u32 wave = uniform(threadIdx.x / WAVE);
     const u32 sub_log2 = s.sub_log2, n_piece = s.n_piece, n_blocks = s.blocks;
     const u32 W = g.W, sub = 1u << sub_log2, wpl = WAVE >> sub_log2, pitch = sub + 1;
-    u32* const slots = sh_slots + wave * GS_TEAM_LDS(W, sub_log2);
     const u64 lo = bi.lo, hi = bi.hi;
     const u32 s_lane = lane & (sub - 1), w_sub = lane >> sub_log2;
     const u64 submask = NONE64 >> (WAVE - sub);
@@ -685,18 +695,21 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
         const u32 word = seq0 >> 6, shift = seq0 & 63;
         u64 elem_l = 0, new_any = 0, old_any = 0;
         u32 len_l = 0, home_l = pick;
-        for (u32 w0 = 0; w0 < W; w0 += J * wpl) {
+        const bool split = MANY && !solo;       // a row is read by one wave only
+        u32* const slots = sh_slots + (split ? turn : wave) * GS_TEAM_LDS(W, sub_log2);
+        const u32 w_step = split ? NW * wpl : wpl, w_first = split ? wave * wpl : 0;
+        for (u32 w0 = w_first; w0 < W || (MANY && w0 == w_first); w0 += J * w_step) {
             u64 p[J], bits[J], nb[J];
             #pragma unroll
             for (int j = 0; j < J; ++j) {
-                const u32 w = w0 + j * wpl + w_sub;
+                const u32 w = w0 + j * w_step + w_sub;
                 p[j] = NONE64; bits[j] = 0;
                 if (w < W && seq_l < g.n_pkts) {
                     p[j] = pending[(u64)w * g.n_pkts + seq_l];
                     bits[j] = bitmap[(u64)w * g.words_pw + word];
                 }
             }
-            if (w0 == 0 && lane < sub && seq_l < g.n_pkts) {
+            if (w0 == w_first && lane < sub && seq_l < g.n_pkts) {
                 const u32 b = find_bucket(g, fs, seq_l);
                 const u64 start = (u64)(seq_l - fs[b]) * g.P;
                 const u64 left = g.b_cnt[b] - start;
@@ -707,8 +720,8 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
             #pragma unroll
             for (int j = 0; j < J; ++j) {
                 nb[j] = 0;
-                if (w0 + j * wpl >= W) continue;
-                const u32 w = w0 + j * wpl + w_sub;
+                if (w0 + j * w_step >= W) continue;
+                const u32 w = w0 + j * w_step + w_sub;
                 const bool had = (bits[j] >> (shift + s_lane)) & 1ull;      // delivered by an earlier batch
                 const bool fresh = p[j] != NONE64 && !had;                  // a copy of a delivered packet is dropped
                 nb[j] = __ballot(fresh);
@@ -728,11 +741,11 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
                         break;
                     }
                 }
-            } else __syncthreads();  // every wave of the block has read the index before the first one resets it
-            if (leader) {
+            } else if (!split) __syncthreads();     // every wave of the block has read the index before the first one resets it
+            if (leader || split) {
                 #pragma unroll
                 for (int j = 0; j < J; ++j) {
-                    const u32 w = w0 + j * wpl + w_sub;
+                    const u32 w = w0 + j * w_step + w_sub;
                     if (p[j] != NONE64) pending[(u64)w * g.n_pkts + seq_l] = NONE64;   // leave the index empty
                     const u64 mine = (nb[j] >> (w_sub << sub_log2)) & submask;
                     // a group owns its 1, 2, 4 or 8 bytes of the bitmap: no atomics
@@ -749,6 +762,15 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
             }
         }
         new_any = uniform(new_any & submask); old_any = uniform(old_any & submask);
+        if (split) {
+            if (lane == 0 && new_any) atomicOr(&sh_any[f][0], (u32)new_any);
+            if (lane == 0 && old_any) atomicOr(&sh_any[f][1], (u32)old_any);
+            __syncthreads();                    // and all waves are done with the group before
+            new_any = uniform(sh_any[f][0]); old_any = uniform(sh_any[f][1]);
+            const u32 z = f == 0 ? 2 : f - 1;
+            if (threadIdx.x < 2) sh_any[z][threadIdx.x] = 0;        // the words of the group before are those of the group after the next
+            turn ^= 1; f = f == 2 ? 0 : f + 1;
+        }
         if (heavy || new_any == 0) continue;
         if (lane < sub && !((old_any >> lane) & 1u)) {
             home_l = pick;
@@ -1125,7 +1147,7 @@ __device__ __forceinline__ bool some_arrived(u64* __restrict__ flags, u32 batch)
 }
 
 // DENSE: the host knows that the batch is dense; otherwise the index pass's tallies decide.
-template <int NP, int G, int D, int NW, u32 LEAD, bool DENSE>
+template <int NP, int G, int D, int NW, u32 LEAD, bool DENSE, bool MANY>
 __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void gather_stream(
     Geo g, const uint8_t* __restrict__ packets, u64* __restrict__ pending, u64* __restrict__ bitmap,
     float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick,
@@ -1173,14 +1195,14 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
         for (u64 i = bi.lo + (u64)blockIdx.x * blockDim.x + threadIdx.x; i < bi.hi; i += (u64)gridDim.x * blockDim.x) few.first[i] = NONE32;
     }
     if (is_sparse)
-        gather_groups<2, 1, 2, NW, true, LEAD>(g, bi, sparse, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
+        gather_groups<2, 1, 2, NW, true, LEAD, MANY>(g, bi, sparse, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
     else {
         // a dense batch's groups are sized for the range that it covers: a step of a round that arrives in many
         // steps is a short round.  Blocks of four waves: at least a piece for each.
         u32 l = group_log2(bi.hi - bi.lo, cus, dense.n_piece > 1, heavy);
         if (NW == GS_WAVES) while (dense.n_piece << l < GS_WAVES) ++l;
         dense.sub_log2 = uniform(l);
-        gather_groups<NP, G, D, NW, false, LEAD>(g, bi, dense, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
+        gather_groups<NP, G, D, NW, false, LEAD, MANY>(g, bi, dense, fs, sh_dyn, packets, pending, bitmap, acc0, acc1, home, pick, accept_rows, sumsq_rows, inv_w);
     }
 }
 
@@ -2851,20 +2873,28 @@ extern "C" int dblp_packetize_list(dblp_ctx* c, uint16_t round, const float* con
 typedef void (*gather_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, const u32*, u32, u64*, u64*, double*, float,
                           GatherShape, GatherShape, u32, u32, u32, u32, u64*, u32*, ArrivalList);
 
-// The instance for `np` KB of a packet per step; few: one to three workers.
+// The instance for `np` KB of a packet per step and w workers.
+template <bool DENSE, u32 LEAD, bool MANY>
+static gather_fn short_kernel(u32 np) {
+    return np == 1 ? gather_stream<1, 4, 2, 4, LEAD, DENSE, MANY> : np == 2 ? gather_stream<2, 4, 2, 4, LEAD, DENSE, MANY>
+         : np == 3 ? gather_stream<3, 2, 2, 4, LEAD, DENSE, MANY> : np == 4 || !LEAD ? gather_stream<4, 2, 2, 4, LEAD, DENSE, MANY>
+                                                                                    : gather_stream<5, 1, 3, 4, 2, DENSE, MANY>;
+}
 template <bool DENSE, u32 LEAD>
-static gather_fn short_kernel(bool few, u32 np) {
-    if (few) return np == 1 ? gather_stream<1, 1, 4, 4, LEAD, DENSE> : np == 2 ? gather_stream<2, 1, 4, 4, LEAD, DENSE>
-                  : np == 3 ? gather_stream<3, 1, 3, 4, LEAD, DENSE> : np == 4 || !LEAD ? gather_stream<4, 1, 3, 4, LEAD, DENSE>
-                                                                                       : gather_stream<5, 1, 3, 4, 2, DENSE>;
-    return np == 1 ? gather_stream<1, 4, 2, 4, LEAD, DENSE> : np == 2 ? gather_stream<2, 4, 2, 4, LEAD, DENSE>
-         : np == 3 ? gather_stream<3, 2, 2, 4, LEAD, DENSE> : np == 4 || !LEAD ? gather_stream<4, 2, 2, 4, LEAD, DENSE>
-                                                                              : gather_stream<5, 1, 3, 4, 2, DENSE>;
+static gather_fn short_kernel(u32 w, u32 np) {
+    if (w < 4) return np == 1 ? gather_stream<1, 1, 4, 4, LEAD, DENSE, false> : np == 2 ? gather_stream<2, 1, 4, 4, LEAD, DENSE, false>
+                    : np == 3 ? gather_stream<3, 1, 3, 4, LEAD, DENSE, false> : np == 4 || !LEAD ? gather_stream<4, 1, 3, 4, LEAD, DENSE, false>
+                                                                                                : gather_stream<5, 1, 3, 4, 2, DENSE, false>;
+    return w > 16 ? short_kernel<DENSE, LEAD, true>(np) : short_kernel<DENSE, LEAD, false>(np);
+}
+template <bool DENSE, bool MANY>
+static gather_fn long_kernel(u32 np) {
+    return np == 1 ? gather_stream<1, 4, 2, 16, 2, DENSE, MANY> : np == 2 ? gather_stream<2, 2, 2, 16, 2, DENSE, MANY> : gather_stream<4, 2, 2, 16, 2, DENSE, MANY>;
 }
 template <bool DENSE>
-static gather_fn gather_kernel(u32 nw, bool lead, bool few, u32 np) {
-    if (nw == 16) return np == 1 ? gather_stream<1, 4, 2, 16, 2, DENSE> : np == 2 ? gather_stream<2, 2, 2, 16, 2, DENSE> : gather_stream<4, 2, 2, 16, 2, DENSE>;
-    return lead ? short_kernel<DENSE, 2>(few, np) : short_kernel<DENSE, 0>(few, np);
+static gather_fn gather_kernel(u32 nw, bool lead, u32 w, u32 np) {
+    if (nw == 16) return w > 16 ? long_kernel<DENSE, true>(np) : long_kernel<DENSE, false>(np);
+    return lead ? short_kernel<DENSE, 2>(w, np) : short_kernel<DENSE, 0>(w, np);
 }
 
 typedef void (*list_fn)(Geo, const uint8_t*, u64*, u64*, float*, float*, uint8_t*, u32, ArrivalList, const u32*, u32, u64*, u64*, double*, float, u32*);
@@ -3012,7 +3042,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
         const size_t table = ((size_t)g.B + 1) * sizeof(u32);
         const u32 table_at = table <= IDX_TABLE_LDS_MAX ? nw * slots : 0u;
         if (table_at) lds += table;
-        const gather_fn kern = dense_only ? gather_kernel<true>(nw, lead, few, np) : gather_kernel<false>(nw, lead, few, np);
+        const gather_fn kern = dense_only ? gather_kernel<true>(nw, lead, g.W, np) : gather_kernel<false>(nw, lead, g.W, np);
         ProfScope ps(c, small ? DBLP_K_GATHER_DIRECT : DBLP_K_GATHER, !dense_only && !small && !known, known);
         if (in_bursts) {
             if ((u32)c->n_cus > now.rows_used) now.rows_used = (u32)c->n_cus;

@@ -91,7 +91,7 @@ class _Rx:
 # one packet length for each instance: pieces of 1 to 4 KB counted from the payload and from the packet, packets of two
 # pieces, packets that a block takes together; 16 waves where packets are heavy and few
 SHAPES = [(1, 256, 9000), (3, 255, 40_000), (8, 200, 9000), (2, 512, 6000), (8, 366, 30_000), (5, 768, 3000), (4, 700, 3000), (16, 1024, 5000), (4, 1000, 2500),
-          (4, 1200, 2000), (3, 1800, 1500), (2, 2243, 2400), (4, 16374, 240), (64, 366, 4000), (40, 1200, 200), (64, 300, 9000)]
+          (4, 1200, 2000), (17, 366, 3000), (24, 200, 6000), (3, 1800, 1500), (2, 2243, 2400), (4, 16374, 240), (64, 366, 4000), (40, 1200, 200), (64, 300, 9000)]
 
 
 @pytest.mark.parametrize("W,P,pkts", SHAPES)
@@ -111,7 +111,7 @@ def test_few_packets(W, P, pkts, queue):
     rx.deliver(w[order], seq[order], queue)
     rx.check()
     most = max(4, n // 4)
-    for m in (1, 3, min(64, most), min(most, 384 * W, 1536), min(most, 1537 if W > 4 else 384 * W + 1), most):
+    for m in (1, 3, min(64, most), min(most, 384 * W, 1536), min(most, 1537 if W > 4 else 384 * W + 1), most, n // 2):      # (the last by groups)
         w, seq = pick(m)
         if m > 8:                                   # copies in the batch, one number from all workers, both ends
             w[1], seq[1] = w[0], seq[0]
