@@ -1752,7 +1752,98 @@ __global__ __launch_bounds__(256) void probe_once(Geo g, const u64* __restrict__
     probe_emit<BLOCK_PAIR>(g, bitmap, p, want, base + incl - want, ppw, list, capacity, sh);
 }
 
-// More blocks than that, in two launches or three.  Missing packets per pair, list length it asks for (need), and the
+// The probe of a short round: every block reads the whole bitmap into LDS and counts all pairs for itself, so nobody waits for
+// anybody; the blocks share out the bitmap's words when it comes to the list.  A pair's count is the difference of two entries of a prefix
+// sum over the words' bits, whatever the buckets' sizes, and a missing packet's place in the list its pair's plus
+// its number less those that arrived.  Latency bounds it: one trip to memory, LDS and three scans, where probe_once tells lengths from block
+// to block and takes a pair's list bit by bit.  us until the host has the answer, probe_once and this, by the words of the bitmap:
+//                                          2 % lost, all in the list    half lost        nothing arrived
+//   256, 4 workers x 64 buckets             17.5, 17.0                   21.6, 16.5       24.8, 16.5
+//   678, 3 x 1                              18.0, 16.1                   30.0, 16.0       39.0, 16.1
+//   1093, 1 x 161                           17.3, 17.7                   20.4, 17.0       22.6, 17.0
+//   2015, 13 x 16                           17.7, 17.0                   23.2, 17.0       27.0, 17.1
+//   3992, 8 x 161 (not taken)               18.3, 19.3                   21.8, 19.1       24.9, 19.2
+// Above PROBE_ALL_WORDS the usual probe with few losses takes longer, as every block reads all of it.
+#define PROBE_ALL_THREADS 1024u
+#define PROBE_ALL_WORDS 2048u
+#define PROBE_ALL_PAIRS 8192u
+#define PROBE_ALL_SHARE 16u          // words of the bitmap per block: one a wave
+#define PROBE_ALL_LDS(words, B, pairs) (8u * (words) + 4u * ((words) + 1u + (B) + 1u + (pairs)))
+__global__ __launch_bounds__(PROBE_ALL_THREADS) void probe_all(Geo g, const u64* __restrict__ bitmap, u32 bound_ppm, u32 n_words, u32 pairs,
+                                                               u32* __restrict__ missing_out, u64* __restrict__ list, u64 capacity, u64* __restrict__ mailbox) {
+    extern __shared__ __attribute__((aligned(16))) u64 sh_words[];
+    u32* const before = (u32*)(sh_words + n_words);         // [n_words + 1]: packets that arrived in the words before
+    u32* const fs = before + n_words + 1;                   // [B + 1]
+    u32* const place = fs + g.B + 1;                        // [pairs]: where the pair's entries begin; all-ones: it has none
+    __shared__ u32 part[PROBE_ALL_THREADS / WAVE];
+    const u32 t = threadIdx.x, lane = lane_id(), wave = uniform(t / WAVE), wpw = (u32)g.words_pw;
+    #pragma unroll 4
+    for (u32 i = t; i < n_words; i += PROBE_ALL_THREADS) sh_words[i] = bitmap[i];
+    for (u32 i = t; i <= g.B; i += PROBE_ALL_THREADS) fs[i] = g.first_seq[i];
+    __syncthreads();
+    // Sum over the threads before this one, and over all.
+    auto scan = [&](u32 v, u32* all) {
+        const u32 incl = wave_scan_incl<OpAdd>(v);
+        if (lane == WAVE - 1) part[wave] = incl;
+        __syncthreads();
+        u32 own = incl - v, sum = 0;
+        for (u32 k = 0; k < PROBE_ALL_THREADS / WAVE; ++k) {
+            if (k < wave) own += part[k];
+            sum += part[k];
+        }
+        __syncthreads();
+        *all = sum;
+        return own;
+    };
+    u32 total;
+    {
+        const u32 per = (n_words + PROBE_ALL_THREADS - 1) / PROBE_ALL_THREADS, i0 = t * per;
+        u32 n = 0;
+        for (u32 i = i0; i < i0 + per && i < n_words; ++i) n += (u32)__popcll(sh_words[i]);
+        u32 at = scan(n, &total);
+        for (u32 i = i0; i < i0 + per && i < n_words; ++i) { before[i] = at; at += (u32)__popcll(sh_words[i]); }
+        if (t == 0) before[n_words] = total;
+    }
+    __syncthreads();
+    // Packets of the workers before w, and of w below number s, that arrived (s may be n_pkts).
+    auto arrived = [&](u32 w, u32 s) {
+        const u32 i = w * wpw + (s >> 6);
+        return before[i] + (s & 63 ? (u32)__popcll(sh_words[i] & ((1ull << (s & 63)) - 1)) : 0u);
+    };
+    {
+        const u32 per = (pairs + PROBE_ALL_THREADS - 1) / PROBE_ALL_THREADS, p0 = t * per;
+        u32 n = 0;
+        for (u32 pr = p0; pr < p0 + per && pr < pairs; ++pr) {
+            const u32 w = pr / g.B, b = pr - w * g.B, n_b = fs[b + 1] - fs[b], miss = n_b - (arrived(w, fs[b + 1]) - arrived(w, fs[b]));
+            const u32 want = (u64)miss > ((u64)bound_ppm * n_b) / 1000000ull ? miss : 0u;
+            if (missing_out && blockIdx.x == 0) missing_out[pr] = miss;
+            place[pr] = want;
+            n += want;
+        }
+        u32 at = scan(n, &total);
+        for (u32 pr = p0; pr < p0 + per && pr < pairs; ++pr) {
+            const u32 want = place[pr];
+            place[pr] = want ? at : NONE32;
+            at += want;
+        }
+    }
+    if (blockIdx.x == 0 && t == 0) mailbox[0] = total;
+    if (capacity == 0 || total == 0) return;
+    __syncthreads();
+    // A wave takes a word, a lane a packet: what is missing goes out in order, whatever the number of buckets and losses.
+    for (u32 i = blockIdx.x * (PROBE_ALL_THREADS / WAVE) + wave; i < n_words; i += gridDim.x * (PROBE_ALL_THREADS / WAVE)) {
+        const u32 w = i / wpw, s = (i - w * wpw) * 64 + lane;
+        if (s >= g.n_pkts || (sh_words[i] >> lane) & 1ull) continue;
+        u32 b = 0, hi = g.B;
+        while (hi - b > 1) { const u32 mid = (b + hi) >> 1; if (fs[mid] <= s) b = mid; else hi = mid; }
+        const u32 from = place[w * g.B + b];
+        if (from == NONE32) continue;
+        const u64 pos = (u64)from + (s - fs[b]) - (arrived(w, s) - arrived(w, fs[b]));
+        if (pos < capacity) list[pos] = ((u64)w << 32) | s;
+    }
+}
+
+// More blocks than probe_once takes, in two launches or three.  Missing packets per pair, list length it asks for (need), and the
 // block's total of those.
 template <bool BLOCK_PAIR>
 __global__ __launch_bounds__(256) void loss_count(Geo g, const u64* __restrict__ bitmap, u32 bound_ppm, u32 ppw, u64 pairs,
@@ -2233,7 +2324,8 @@ struct dblp_ctx {
     struct Picked { const void* p; u64 bytes; int pick; } picked[32];   // measured buffers
     u32 n_picked;
     hipEvent_t cls_ev[2];
-    int probe_block_pair;   // probe: a block per (worker, bucket) pair
+    int probe_all;          // probe: by probe_all
+    int probe_block_pair;   // else: a block per (worker, bucket) pair
     u32 probe_no;           // probes made: what their words in d_totals are told apart by
     u32 probe_polls;        // looks that a block of probe_once takes at the totals before its own
     u32* d_need; u64* d_totals;   // list length per pair, and per block of pairs
@@ -2703,6 +2795,10 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
         if (ce != hipSuccess) { (void)hipGetLastError(); dblp_destroy(c); return DBLP_EHIP; }
         g.hint = c->d_hint;
     }
+    const u64 all_words = (u64)g.W * g.words_pw;
+    c->probe_all = all_words <= PROBE_ALL_WORDS && pairs <= PROBE_ALL_PAIRS &&
+                   hipFuncSetAttribute((const void*)probe_all, hipFuncAttributeMaxDynamicSharedMemorySize, (int)PROBE_ALL_LDS(PROBE_ALL_WORDS, PROBE_ALL_PAIRS, PROBE_ALL_PAIRS)) == hipSuccess;
+    (void)hipGetLastError();
     c->burst = burst_plan(g, (u32)c->n_cus);
     // The limit is the kernel's, not the context's: the same whatever the plan, so that contexts which share an instance
     // do not lower it for each other.
@@ -3100,7 +3196,15 @@ extern "C" int dblp_loss_account(dblp_ctx* c, uint32_t bound_ppm, uint32_t* d_mi
     const u64 pairs = (u64)g.W * g.B, blocks = probe_blocks(c, pairs);
     const u32 ppw = probe_ppw(c, pairs);
     if (blocks > 0x7FFFFFFFull) return fail(c, DBLP_EINVAL, "loss_account: too many (worker, bucket) pairs");
-    {
+    if (c->probe_all) {
+        const u64 words = (u64)g.W * g.words_pw;
+        ProfScope ps(c, DBLP_K_PROBE);
+        hipLaunchKernelGGL(probe_all, dim3((u32)(words + PROBE_ALL_SHARE - 1) / PROBE_ALL_SHARE), dim3(PROBE_ALL_THREADS), PROBE_ALL_LDS((u32)words, g.B, (u32)pairs), c->stream, g,
+                           bitmap, bound_ppm, (u32)words, (u32)pairs, d_missing, (u64*)d_retx_list, (u64)retx_capacity, c->d_mailbox);
+        LAUNCH_CHECK(c, "loss_account");
+        ps.end();
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+    } else {
         ProfScope ps(c, DBLP_K_PROBE);
         bool done = blocks * 4 <= (u64)PROBE_RESIDENT * c->n_cus;
         if (done) {

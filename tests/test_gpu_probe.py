@@ -86,6 +86,14 @@ def _probes(W, packets, agg, before=None):
     assert bool(alive.all())
 
 
+# short rounds, which every block counts for itself: as many words and pairs as that takes, and more; whole words; buckets that
+# end with a word, inside it, and many in one
+@pytest.mark.parametrize("W,packets", [(1, [64]), (1, [63, 1]), (2, [64, 128, 64]), (3, [1] * 130), (32, [4096]), (32, [4000, 1, 95]), (33, [4000]),
+                                       (32, [8] * 256), (64, [1] * 129), (5, [200, 1, 1, 1, 3000, 62, 64, 7]), (64, [2040, 8])])
+def test_probe_of_a_short_round(W, packets):
+    _probes(W, packets, _context(W, packets))
+
+
 def test_probes_of_several_contexts_at_once():
     """Four contexts, each on a stream and in a thread of its own, of as many blocks as one launch takes."""
     import threading
