@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256) void fold_accept_rows(const u64* __restrict__ 
 // ------------------------------------------------------------------------------------------
 // sender: gradient -> wire packets
 // ------------------------------------------------------------------------------------------
-// One wave writes one packet: lane l builds 16-byte units l, l + 64, ... (header in the first 8
+// One wave writes one packet (write_packet; short ones several at once, write_packets below): lane l builds 16-byte units l, l + 64, ... (header in the first 8
 // bytes of unit 0, zero padding after the payload) and stores them aligned.  A unit inside the payload is
 // one 16-byte load at the gradient's own (4-byte) alignment (two 8-byte loads where it was even and four
 // single ones elsewhere: 25.6 M elements, 205 MB moved, ten sets of buffers in turn 48.3 -> 45.8 us, one set 37.8 ->
@@ -248,13 +248,58 @@ __device__ __forceinline__ void write_packet(const float* __restrict__ src, u32 
     }
 }
 
+// Several short packets by one wave, whose units lie one after the other over its lanes: lane j < n_k holds packet j (dst null: it is
+// skipped), and a unit's lane asks that one for what it needs.  A wave for each packet leaves lanes of its last pass empty, has few
+// bytes in flight where packets are short, and searches the bucket once per packet where here up to 64 lanes search at the same time.
+// 60 M elements, 161 buckets, slots in order and by a map (us, a wave for each packet -> several):
+//   payload of 14 floats 1148 -> 103, 1304 -> 239; 64: 314 -> 100, 380 -> 186; 126: 174 -> 91, 212 -> 116; 254: 96.9 -> 91.2, 125 -> 113;
+//   300: 117 -> 95.4, 142 -> 120; 366: 94.2 -> 87.8, 119 -> 114; 430: 89.1 -> 88.6, 115 -> 113; 500: 91.7 -> 89.3, 118 -> 118;
+//   lists of 3 % of eight workers' packets 126: 60.8 -> 41.8, 366: 42.1 -> 40.1, 500: 40.1 -> 39.2.
+// 4 passes of 64 units: with 5 most of this was 30 % slower (payload 64 132 us, 254 116), with 2 and 3 packets of 300 to 500 floats
+// fill the passes worse (300: 124 and 97.9, 500: 92.1 and 93.3).  Packets of which two don't fit go one by one.
+#define SENDER_PASSES 4
+struct SentPacket { const float* src; u32 len, seq; uint8_t* dst; };
+struct SenderSplit { u32 k, inv; };              // packets per wave (0: one, by write_packet); unit f of a wave belongs to its packet f * inv >> 16 (exact for f < 256)
+__device__ __forceinline__ u64 lane_value(u64 v, u32 from) { return ((u64)(u32)__shfl((int)(u32)(v >> 32), (int)from) << 32) | (u32)__shfl((int)(u32)v, (int)from); }
+__device__ __forceinline__ void write_packets(const SentPacket& mine, u32 n_k, u32 inv, u32 round, u32 units, u32 lane) {
+    uint4 q[SENDER_PASSES];
+    uint4* out[SENDER_PASSES];
+    const u32 all = n_k * units;
+    #pragma unroll
+    for (int p = 0; p < SENDER_PASSES; ++p) {
+        out[p] = nullptr;
+        q[p] = make_uint4(0u, 0u, 0u, 0u);
+        if (p * WAVE >= all) continue;                      // the same in all lanes
+        const u32 f = p * WAVE + lane, j = f < all ? f * inv >> 16 : 0u, u = f - j * units;
+        const float* const src = (const float*)lane_value((u64)mine.src, j);
+        uint8_t* const dst = (uint8_t*)lane_value((u64)mine.dst, j);
+        const u32 len = (u32)__shfl((int)mine.len, (int)j), seq = (u32)__shfl((int)mine.seq, (int)j);
+        if (f >= all || !dst) continue;
+        out[p] = (uint4*)dst + u;
+        const u32 p0 = 4 * u;
+        if (p0 >= 2 && p0 + 1 < len) {
+            const u4v_a4 t = *(const u4v_a4*)(src + (p0 - 2));
+            q[p] = make_uint4(t.x, t.y, t.z, t.w);
+        } else {
+            if (p0 >= 2 && p0 - 2 < len) q[p].x = __float_as_uint(src[p0 - 2]);
+            if (p0 >= 2 && p0 - 1 < len) q[p].y = __float_as_uint(src[p0 - 1]);
+            if (p0 < len) q[p].z = __float_as_uint(src[p0]);
+            if (p0 + 1 < len) q[p].w = __float_as_uint(src[p0 + 1]);
+        }
+        if (u == 0) { q[p].x = seq; q[p].y = (round & 0xFFFFu) | (len << 16); }
+    }
+    #pragma unroll
+    for (int p = 0; p < SENDER_PASSES; ++p)
+        if (out[p]) st_stream4(out[p], q[p]);
+}
+
 // *bad (host memory, mapped) becomes 1 when an entry has to be skipped: the host reads it after the wait it
 // needs anyway, where a counter in device memory cost a copy back (10 us of a 77 us retransmission).
 //
 // Sender, a range of sequence numbers of one worker: packet first_seq + i -> slot slot_map[i] (or
 // slot_base + i).  The bucket boundaries are searched in LDS when the table fits (TABLE_IN_LDS).
-template <bool TABLE_IN_LDS>
-__global__ __launch_bounds__(256) void packetize_kernel(Geo g, u32 w, u32 round, const float* __restrict__ grad,
+template <bool TABLE_IN_LDS, bool SHORT>
+__global__ __launch_bounds__(256) void packetize_kernel(Geo g, SenderSplit split, u32 w, u32 round, const float* __restrict__ grad,
                                                         u64 elem_base, u32 first_seq, u32 n, const u32* __restrict__ slot_map,
                                                         u64 slot_base, u64 n_slots, uint8_t* __restrict__ packets,
                                                         uint16_t* __restrict__ src_worker, u64* __restrict__ bad) {
@@ -268,6 +313,29 @@ __global__ __launch_bounds__(256) void packetize_kernel(Geo g, u32 w, u32 round,
     u32 lane = lane_id();
     u32 wave = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
     u32 n_waves = gridDim.x * blockDim.x / WAVE;
+    if (SHORT) {
+        const u32 k = split.k;
+        for (u64 i0 = (u64)wave * k; i0 < n; i0 += (u64)n_waves * k) {
+            const u32 n_k = n - i0 < k ? (u32)(n - i0) : k;
+            SentPacket mine = {nullptr, 0, 0, nullptr};
+            if (lane < n_k) {
+                const u32 seq = first_seq + (u32)i0 + lane;
+                const u64 slot = slot_map ? (u64)slot_map[i0 + lane] : slot_base + i0 + lane;
+                if (slot >= n_slots) *bad = 1;
+                else {
+                    const u32 b = find_bucket(g, fs, seq);
+                    const u64 start = (u64)(seq - fs[b]) * g.P, left = g.b_cnt[b] - start;
+                    mine.src = grad + (g.b_off[b] + start - elem_base);
+                    mine.len = left < g.P ? (u32)left : g.P;
+                    mine.seq = seq;
+                    mine.dst = packets + slot * g.stride;
+                    src_worker[slot] = (uint16_t)w;
+                }
+            }
+            write_packets(mine, n_k, split.inv, round, g.units, lane);
+        }
+        return;
+    }
     for (u32 i = wave; i < n; i += n_waves) {
         u32 seq = first_seq + i;
         u64 slot = slot_map ? (u64)slot_map[i] : slot_base + i;
@@ -288,8 +356,8 @@ __global__ __launch_bounds__(256) void packetize_kernel(Geo g, u32 w, u32 round,
 struct GradPtrs { const float* p[DBLP_MAX_WORKERS]; };
 
 // One wave per list entry (w << 32 | seq): worker w's packet seq -> slot slot_base + i.
-template <bool TABLE_IN_LDS>
-__global__ __launch_bounds__(256) void packetize_list_kernel(Geo g, GradPtrs grads, u32 round, const u64* __restrict__ list,
+template <bool TABLE_IN_LDS, bool SHORT>
+__global__ __launch_bounds__(256) void packetize_list_kernel(Geo g, SenderSplit split, GradPtrs grads, u32 round, const u64* __restrict__ list,
                                                              u64 n, u64 slot_base, uint8_t* __restrict__ packets,
                                                              uint16_t* __restrict__ src_worker, u64* __restrict__ bad) {
     extern __shared__ u32 fs_lds[];
@@ -302,6 +370,29 @@ __global__ __launch_bounds__(256) void packetize_list_kernel(Geo g, GradPtrs gra
     const u32 lane = lane_id();
     const u64 wave = ((u64)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
     const u64 n_waves = (u64)gridDim.x * blockDim.x / WAVE;
+    if (SHORT) {
+        const u32 k = split.k;
+        for (u64 i0 = wave * k; i0 < n; i0 += n_waves * k) {
+            const u32 n_k = n - i0 < k ? (u32)(n - i0) : k;
+            SentPacket mine = {nullptr, 0, 0, nullptr};
+            if (lane < n_k) {
+                const u64 e = list[i0 + lane], slot = slot_base + i0 + lane;
+                const u32 w = (u32)(e >> 32), seq = (u32)e;
+                if (w >= g.W || seq >= g.n_pkts) *bad = 1;
+                else {
+                    const u32 b = find_bucket(g, fs, seq);
+                    const u64 start = (u64)(seq - fs[b]) * g.P, left = g.b_cnt[b] - start;
+                    mine.src = grads.p[w] + (g.b_off[b] + start);
+                    mine.len = left < g.P ? (u32)left : g.P;
+                    mine.seq = seq;
+                    mine.dst = packets + slot * g.stride;
+                    src_worker[slot] = (uint16_t)w;
+                }
+            }
+            write_packets(mine, n_k, split.inv, round, g.units, lane);
+        }
+        return;
+    }
     for (u64 i = wave; i < n; i += n_waves) {
         const u64 e = list[i];
         const u32 w = (u32)(e >> 32), seq = (u32)e;
@@ -322,17 +413,18 @@ __global__ __launch_bounds__(256) void packetize_list_kernel(Geo g, GradPtrs gra
 // ------------------------------------------------------------------------------------------
 // receiver step 1: index the arrivals
 // ------------------------------------------------------------------------------------------
+struct ArrivalList {
+    u64* entries;           // per arrival: bucket << 32 | sequence number, NONE64 of one that is not valid; null: none is made
+    u32* first;             // per sequence number: the batch's first arrival with it; all-ones between batches
+    u32 n;
+};
+
 // Grid-stride over arrivals.  Per-thread tallies are reduced per wave (DPP) and per block
 // (LDS) and written to the block's row of block_tallies; fold_index_tallies adds the rows up.
 // No global atomics on shared counters: atomics of many waves (or even of a few thousand
 // blocks) on one address serialise in L2 at about 12 ns each.
 //
 // `few`: the batch is a small one that gather_few will take (below).
-struct ArrivalList {
-    u64* entries;           // per arrival: bucket << 32 | sequence number, NONE64 of one that is not valid; null: none is made
-    u32* first;             // per sequence number: the batch's first arrival with it; all-ones between batches
-    u32 n;
-};
 //
 // TABLE_IN_LDS: the block first copies the bucket boundaries (first_seq, B + 1 words of dynamic
 // shared memory) into LDS, so the ten dependent steps of the bucket search stay inside the CU.
@@ -2906,6 +2998,23 @@ static void seq_window(const dblp_ctx* c, u64 first_seq, u64 n, u64* lo, u64* hi
     *lo = e0; *hi = e1 + l1;
 }
 
+// Packets that a wave of the sender takes at once: as many as fill the lanes of its passes best, of a short list fewer, so that
+// every CU has 16 waves' worth (300 k elements in packets of 64, 4.7 k of them: 6 us either way).  0: one, by write_packet.
+static SenderSplit sender_split(const dblp_ctx* c, u64 n) {
+    const u32 units = c->g.units;
+    SenderSplit best = {0, (65536 + units - 1) / units};
+    u32 fill = 0;
+    for (u32 k = 2; k <= WAVE && k * units <= SENDER_PASSES * WAVE && (u64)k * c->n_cus * 16 <= n; ++k) {
+        const u32 passes = (k * units + WAVE - 1) / WAVE, here = k * units * 1000 / (passes * WAVE);
+        if (here >= fill) { fill = here; best.k = k; }
+    }
+    return best;
+}
+static u32 sender_grid(const dblp_ctx* c, const SenderSplit& split, u64 n) {
+    const u64 waves = split.k ? (n + split.k - 1) / split.k : n;
+    return grid_for(c, (waves + 3) / 4, 8);
+}
+
 extern "C" int dblp_packetize(dblp_ctx* c, uint32_t w, uint16_t round, const float* d_grad, uint64_t elem_base,
                               uint64_t n_grad, uint64_t first_seq, uint64_t n_pkts, const uint32_t* d_slot_map,
                               uint64_t slot_base, uint64_t n_slots, void* d_packets, uint16_t* d_src_worker) {
@@ -2922,14 +3031,12 @@ extern "C" int dblp_packetize(dblp_ctx* c, uint32_t w, uint16_t round, const flo
     HIP_TRY(c, hipSetDevice(c->device));
     *(volatile u64*)(c->h_mailbox + 4) = 0;
     const size_t table = ((size_t)c->g.B + 1) * sizeof(u32);
-    if (table <= IDX_TABLE_LDS_MAX)
-        hipLaunchKernelGGL(packetize_kernel<true>, dim3(grid_for(c, (n_pkts + 3) / 4, 8)), dim3(256), table, c->stream, c->g, w,
-                           (u32)round, d_grad, (u64)elem_base, (u32)first_seq, (u32)n_pkts, d_slot_map, (u64)slot_base,
-                           (u64)n_slots, (uint8_t*)d_packets, d_src_worker, c->d_mailbox + 4);
-    else
-        hipLaunchKernelGGL(packetize_kernel<false>, dim3(grid_for(c, (n_pkts + 3) / 4, 8)), dim3(256), 0, c->stream, c->g, w,
-                           (u32)round, d_grad, (u64)elem_base, (u32)first_seq, (u32)n_pkts, d_slot_map, (u64)slot_base,
-                           (u64)n_slots, (uint8_t*)d_packets, d_src_worker, c->d_mailbox + 4);
+    const SenderSplit split = sender_split(c, n_pkts);
+    const bool lds = table <= IDX_TABLE_LDS_MAX;
+    void (*const kern)(Geo, SenderSplit, u32, u32, const float*, u64, u32, u32, const u32*, u64, u64, uint8_t*, uint16_t*, u64*) =
+        split.k ? (lds ? packetize_kernel<true, true> : packetize_kernel<false, true>) : (lds ? packetize_kernel<true, false> : packetize_kernel<false, false>);
+    hipLaunchKernelGGL(kern, dim3(sender_grid(c, split, n_pkts)), dim3(256), lds ? table : 0, c->stream, c->g, split, w, (u32)round, d_grad, (u64)elem_base,
+                       (u32)first_seq, (u32)n_pkts, d_slot_map, (u64)slot_base, (u64)n_slots, (uint8_t*)d_packets, d_src_worker, c->d_mailbox + 4);
     LAUNCH_CHECK(c, "packetize");
     if (d_slot_map) {   // slots come from device memory: the kernel checks them, report here
         HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -2955,14 +3062,12 @@ extern "C" int dblp_packetize_list(dblp_ctx* c, uint16_t round, const float* con
     HIP_TRY(c, hipSetDevice(c->device));
     *(volatile u64*)(c->h_mailbox + 4) = 0;
     const size_t table = ((size_t)c->g.B + 1) * sizeof(u32);
-    if (table <= IDX_TABLE_LDS_MAX)
-        hipLaunchKernelGGL(packetize_list_kernel<true>, dim3(grid_for(c, (n + 3) / 4, 8)), dim3(256), table, c->stream, c->g, gp,
-                           (u32)round, (const u64*)d_list, (u64)n, (u64)slot_base, (uint8_t*)d_packets, d_src_worker,
-                           c->d_mailbox + 4);
-    else
-        hipLaunchKernelGGL(packetize_list_kernel<false>, dim3(grid_for(c, (n + 3) / 4, 8)), dim3(256), 0, c->stream, c->g, gp,
-                           (u32)round, (const u64*)d_list, (u64)n, (u64)slot_base, (uint8_t*)d_packets, d_src_worker,
-                           c->d_mailbox + 4);
+    const SenderSplit split = sender_split(c, n);
+    const bool lds = table <= IDX_TABLE_LDS_MAX;
+    void (*const kern)(Geo, SenderSplit, GradPtrs, u32, const u64*, u64, u64, uint8_t*, uint16_t*, u64*) =
+        split.k ? (lds ? packetize_list_kernel<true, true> : packetize_list_kernel<false, true>) : (lds ? packetize_list_kernel<true, false> : packetize_list_kernel<false, false>);
+    hipLaunchKernelGGL(kern, dim3(sender_grid(c, split, n)), dim3(256), lds ? table : 0, c->stream, c->g, split, gp, (u32)round, (const u64*)d_list, (u64)n,
+                       (u64)slot_base, (uint8_t*)d_packets, d_src_worker, c->d_mailbox + 4);
     LAUNCH_CHECK(c, "packetize_list");
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     if (*(volatile u64*)(c->h_mailbox + 4)) return fail(c, DBLP_EINVAL, "packetize_list: list entry with worker or seq out of range");
