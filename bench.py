@@ -34,8 +34,8 @@ BENCH_DRAWN_ROUNDS = 3   # retransmission rounds with a drawn loss pattern; late
 # on and by workload; anything else reports null.
 # value = measured bytes / algorithmic bytes of a first-transmission launch.
 PMC_TRAFFIC_RATIO: dict[tuple[str, str], float] = {
-    ("3348d76963b46b495ecfc38d7a445afe6567a2609c0d4f2a88faf9cc322576b9", "cfg5"): 1.055,   # profiles/receiver_path_cfg5.md
-    ("3348d76963b46b495ecfc38d7a445afe6567a2609c0d4f2a88faf9cc322576b9", "cfg4"): 1.031,   # profiles/receiver_path_cfg4.md
+    ("4b20297c12eb2db69177a813a9f74fbe08280cd008f960bb2d586088049ab532", "cfg5"): 1.055,   # profiles/receiver_path_cfg5.md
+    ("4b20297c12eb2db69177a813a9f74fbe08280cd008f960bb2d586088049ab532", "cfg4"): 1.031,   # profiles/receiver_path_cfg4.md
 }
 
 
