@@ -40,6 +40,7 @@
 
 #include "../../include/dblp_agg.h"
 #include "packet_units.h"
+#include "long_sum.h"
 
 typedef unsigned long long u64;
 typedef uint32_t u32;
@@ -160,6 +161,10 @@ __device__ __forceinline__ void packet_span(const Geo& g, u32 seq, u32 b, u64* e
 }
 
 #define ACCEPT_ROWS 8192   // >= blocks of any gather launch (n_cus * blocks per CU)
+// Long accumulators that a list's gather shares out over its blocks, up to 1024: atomics on one word take turns, about 12 ns each.
+#define LONG_COPIES 32u
+#define LONG_PITCH 32u
+#define LONG_ALL (LONG_COPIES * LONG_PITCH)
 
 // ------------------------------------------------------------------------------------------
 // small utility kernels
@@ -169,19 +174,20 @@ __global__ __launch_bounds__(256) void fill_u64(u64* __restrict__ p, u64 n, u64 
     for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
 
-// What a round counts in: the delivery bitmap, the gather kernels' per-block rows, the counters.  A context keeps two of
+// What a round counts in: the long accumulators (LONG_ALL words) and right behind them the delivery bitmap, the gather kernels'
+// per-block rows (accepted packets, sums of squares: [ACCEPT_ROWS] each, in one piece), the counters.  A context keeps two of
 // them.  The finalize of a round clears the one that is not in use while it is about it, and the next begin_round changes
 // over to that and launches nothing.  A launch cost the host 2.6 us before it could make the next, and small rounds are chains
 // of launches and waits (us of a pass: 4 x 1 M elements in 1040-byte packets 45.1, 43.3; 3 x 5.3 M 102.0, 98.6; 1 x 25.6 M
 // 111.2, 108.6).
-struct RoundState { u64* bitmap; u64* rows; u64* counters; u32 rows_used; };    // rows_used: of the rows, those that may not be zero
+struct RoundState { u64* bitmap; u64* rows; u64* counters; u32 rows_used, listed; };    // rows_used: of the rows, those that may not be zero; listed: whether a list was gathered
 
-// Start of a round where no finalize has cleared the other state, in one launch: all of it to zero.
-__global__ __launch_bounds__(256) void reset_round(u64* __restrict__ bitmap, u64 n_bitmap, u64* __restrict__ rows, u64 n_rows,
+// Start of a round where no finalize has cleared the other state, in one launch: all of it to zero.  words: accumulators and bitmap.
+__global__ __launch_bounds__(256) void reset_round(u64* __restrict__ words, u64 n_words, u64* __restrict__ rows, u64 n_rows,
                                                    u64* __restrict__ counters) {
     const u64 stride = (u64)gridDim.x * blockDim.x;
-    for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n_bitmap + n_rows; i += stride) {
-        if (i < n_bitmap) bitmap[i] = 0; else rows[i - n_bitmap] = 0;
+    for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n_words + n_rows; i += stride) {
+        if (i < n_words) words[i] = 0; else rows[i - n_words] = 0;
     }
     if (blockIdx.x == 0 && threadIdx.x < C_COUNT) counters[threadIdx.x] = 0;
 }
@@ -1025,7 +1031,8 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
 // each: the entry; what its number leads to (all workers' index entries and bitmap words, the span); the payloads
 // and the span's old contents; the store.  Several arrivals of one number are one output packet, taken by the one that the
 // index pass noted as the first.  Packets of three and more pieces are taken by the block's waves together.  The sums and
-// their order are those of the groups.
+// their order are those of the groups; the squares of a packet are added up by one wave, and the packets' in a long
+// accumulator, so that the norm does not depend on the order of arrival either.
 //
 // A batch that turns out to be dense goes by groups after all: neighbours in the bitmap are set by atomics here, one
 // after the other.  It pays the list, 0 to 0.6 us of 14 to 20.  us of index pass and gather, by groups and by the list:
@@ -1074,14 +1081,16 @@ __device__ __forceinline__ void gather_few(const Geo& g, const uint8_t* __restri
                                            float* acc0, float* acc1, uint8_t* __restrict__ home, u32 pick, const ArrivalList& few, u64 e, u32 n_blocks,
                                            u64* __restrict__ accept_rows, double* __restrict__ sumsq_rows, float inv_w) {
     __shared__ u32 sh_accepted[NW];
-    __shared__ double sh_sq[NW];
+    __shared__ u64 sh_long[NW][LONG_WORDS];     // per wave: a long accumulator of its changes of the sum of squares
+    __shared__ double sh_odd[NW];               // and the infinities and NaN, which that does not take
     const u32 lane = lane_id(), wave = uniform(threadIdx.x / WAVE);
     constexpr int D = FEW_DEPTH(NP);
     constexpr u32 team = TEAM ? NW : 1;
     const u32 n_teams = TEAM ? n_blocks : n_blocks * NW;
     const bool leader = !TEAM || wave == 0;
     u32 accepted = 0;
-    double sq = 0.0;
+    if (lane < LONG_WORDS) sh_long[wave][lane] = 0;
+    if (lane == 0) sh_odd[wave] = 0.0;
     auto take = [&](const FewFound& f) {
         const u32 seq = f.seq;
         const bool had = (f.bits >> (seq & 63)) & 1ull;             // delivered by an earlier batch
@@ -1104,6 +1113,7 @@ __device__ __forceinline__ void gather_few(const Geo& g, const uint8_t* __restri
         const u32 h = uniform(old_w ? f.home & 1u : pick);
         float* const span = (h ? acc1 : acc0) + uniform(f.off + start);
         float* const dst = span - LEAD;             // float position i of the unit grid -> dst[i]
+        double sq = 0.0;        // change of the sum of squares of the stored values
         for (u32 piece = TEAM ? wave : 0; piece * (NP * 256u) < len + LEAD; piece += team) {
             const u32 skip = piece * (NP * 1024u), have = unit_have<LEAD>(len, skip);
             int off[NP];
@@ -1158,6 +1168,10 @@ __device__ __forceinline__ void gather_few(const Geo& g, const uint8_t* __restri
                 su.store(o, r);
             }
         }
+        sq = wave_sum_f64(sq);
+        const u64 bits = (u64)__double_as_longlong(sq);
+        if (long_fits(bits)) { if (lane < LONG_WORDS) sh_long[wave][lane] += long_word(bits, lane); }
+        else if (lane == 0) sh_odd[wave] += sq;
     };
 
     // A team's entries lie n_teams apart, so that the first ones of a number, which a list sorted by worker has
@@ -1183,16 +1197,23 @@ __device__ __forceinline__ void gather_few(const Geo& g, const uint8_t* __restri
         if (k0 >= few.n) break;
         e = few_entry<TEAM, NW>(few, k0, n_blocks);
     }
-    // accepted packets and sum-of-squares change of this block: plain adds to the block's own rows
-    sq = wave_sum_f64(sq);
-    if (lane == 0) { sh_accepted[wave] = accepted; sh_sq[wave] = sq; }
+    // Accepted packets of this block, to its own row (an atomic nobody waits for, where += waits for what was there).  Its change of
+    // the sum of squares: integers, added to one of the long accumulators, since which block a packet falls to depends on when it arrived.
+    if (lane == 0) sh_accepted[wave] = accepted;
     __syncthreads();
+    if (threadIdx.x < LONG_WORDS) {
+        u64 t = 0;
+        #pragma unroll
+        for (int i = 0; i < NW; ++i) t += sh_long[i][threadIdx.x];
+        if (t) atomicAdd(bitmap - LONG_ALL + blockIdx.x % LONG_COPIES * LONG_PITCH + threadIdx.x, t);
+    }
     if (threadIdx.x == 0) {
         u32 total = 0;
-        double t = 0.0;
+        double odd = 0.0;
         #pragma unroll
-        for (int i = 0; i < NW; ++i) { total += sh_accepted[i]; t += sh_sq[i]; }
-        if (total) { accept_rows[blockIdx.x] += total; sumsq_rows[blockIdx.x] += t; }
+        for (int i = 0; i < NW; ++i) { total += sh_accepted[i]; odd += sh_odd[i]; }
+        if (total) atomicAdd(&accept_rows[blockIdx.x], (u64)total);
+        if (!(odd == 0.0)) sumsq_rows[blockIdx.x] += odd;       // the same sum in any order
     }
 }
 
@@ -2079,8 +2100,9 @@ __device__ __forceinline__ double fold_partials(u64* words, u32 n, u32 tag, u32 
 //   8 x 215 M, 1472 B (2 x 862 MB moved)   443 -> 387 us
 // move_home (in-place form, n_piece = 1): the homes of spans that were moved are reset to copy 0.
 // With scale_mode 1 the per-block sums of out^2 go to `partials`.  Otherwise the sum of squares is already known: the
-// gather kernels kept it per block in sumsq_rows.  The one extra block of this launch (blockIdx.x == n_work_blocks) adds
-// up the one or the other in a fixed order (fixed for given launch sizes of the round's gather kernels) and
+// gather kernels kept it per block in sumsq_rows, and that of batches gathered by a list (`listed`) in the long accumulators before the
+// bitmap.  The one extra block of this launch (blockIdx.x == n_work_blocks) adds
+// up the one or the other in an order that the sizes of the round's batches fix, not that of the arrivals, and
 // writes the total to the host mailbox.
 template <bool TABLE_IN_LDS, bool PAST>
 __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restrict__ bitmap, const float* acc0,
@@ -2088,10 +2110,11 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
                                                      float* out, int scale_mode, float wf, int move_home,
                                                      u32 grp_log2, u32 n_piece, u32 per_piece, u64* partials, u32 n_max, u32 n_work_blocks,
                                                      const double* __restrict__ sumsq_rows, const u64* __restrict__ accept_rows,
-                                                     u32 n_rows,
+                                                     u32 n_rows, u32 listed,
                                                      u64* __restrict__ counters, u64* __restrict__ mailbox, RoundState other) {
     __shared__ double wsum[4];
     __shared__ u64 asum[4];
+    __shared__ u64 lsum[4][LONG_PITCH];
     extern __shared__ u32 fs_lds[];             // bucket boundaries (B + 1 words) when TABLE_IN_LDS
     const u32 lane = lane_id();
     const u32 wave_in_block = threadIdx.x / WAVE;
@@ -2102,7 +2125,9 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
         // candidates, stale, invalid
         // Only the n_rows rows that a launch of this round can have written are read; the rest are zero.
         double s = 0.0;
-        u64 a = 0;
+        u64 a = 0, l = 0;                                   // l: word lane % LONG_PITCH of the thread's accumulators
+        #pragma unroll
+        for (u32 i = 0; i < LONG_ALL; i += 256) l += listed ? bitmap[(int)(i + threadIdx.x) - (int)LONG_ALL] : 0ull;
         for (u32 i0 = 0; i0 < n_rows; i0 += 4 * 256) {      // four independent loads of each kind in flight
             double sv[4]; u64 av[4];
             #pragma unroll
@@ -2117,8 +2142,15 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
         s = wave_sum_f64(s);
         const u32 a_lo = wave_reduce<OpAdd>((u32)(a & 0xFFFFFu)), a_hi = wave_reduce<OpAdd>((u32)(a >> 20));   // 64 x 2^20 fits 32 bits
         if (lane == 0) { wsum[wave_in_block] = s; asum[wave_in_block] = ((u64)a_hi << 20) + a_lo; }
+        l += lane_value(l, lane ^ LONG_PITCH);
+        if (lane < LONG_PITCH) lsum[wave_in_block][lane] = l;
         __syncthreads();
         double total = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+        if (listed && wave_in_block == 0) {
+            // The words as doubles, as exact as their size allows (below 2^53 they are), added up.
+            const long long word = lane < LONG_WORDS ? (long long)((lsum[0][lane] + lsum[1][lane]) + (lsum[2][lane] + lsum[3][lane])) : 0;
+            total += wave_sum_f64(ldexp((double)word, (int)(32 * lane) - LONG_SHIFT));
+        }
         if (scale_mode) {
             __syncthreads();
             total = fold_partials(partials, n_work_blocks, partials_tag(partials), n_max, wsum);
@@ -2133,10 +2165,11 @@ __global__ __launch_bounds__(256) void finalize_pass(Geo g, const u64* __restric
         return;
     }
     if (other.bitmap) {         // the state of the next round
-        const u64 n_words = (u64)g.W * g.words_pw, n = n_words + 2 * other.rows_used, first = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+        const u64 n_words = LONG_ALL + (u64)g.W * g.words_pw, n = n_words + 2 * other.rows_used, first = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+        u64* const words = other.bitmap - LONG_ALL;
         for (u64 i = first; i < n; i += (u64)n_work_blocks * blockDim.x) {
             const u64 r = i - n_words;
-            if (i < n_words) other.bitmap[i] = 0;
+            if (i < n_words) words[i] = 0;
             else other.rows[r < other.rows_used ? r : r - other.rows_used + ACCEPT_ROWS] = 0;
         }
         if (first < C_COUNT) other.counters[first] = 0;
@@ -2391,7 +2424,7 @@ struct dblp_ctx {
     // device state
     u64* slab;              // what follows, but for the hints and the accumulator
     u32* d_hint;
-    RoundState state[2];    // the open round's (cur) and the other one; both kinds of rows, [ACCEPT_ROWS] each, lie in one allocation
+    RoundState state[2];    // the open round's (cur) and the other one
     int cur;
     int other_clean;        // the state that is not in use is all zero, once what has been launched has ended
     int recorded;           // calls were recorded into a graph, which holds the addresses of one state: it stays in use
@@ -2759,10 +2792,10 @@ static BurstPlan burst_plan(const Geo& g, u32 cus) {
 
 static void reset_state(dblp_ctx* c, int i) {
     RoundState& st = c->state[i];
-    const u64 n = c->g.W * c->g.words_pw;
+    const u64 n = LONG_ALL + c->g.W * c->g.words_pw;
     hipLaunchKernelGGL(reset_round, dim3(grid_for(c, (n + 2 * ACCEPT_ROWS + 255) / 256, 16)), dim3(256), 0, c->stream,
-                       st.bitmap, n, st.rows, (u64)(2 * ACCEPT_ROWS), st.counters);
-    st.rows_used = 0;
+                       st.bitmap - LONG_ALL, n, st.rows, (u64)(2 * ACCEPT_ROWS), st.counters);
+    st.rows_used = 0; st.listed = 0;
 }
 
 // A call that is recorded now will be told again with the state's addresses as they are, and a begin_round among the
@@ -2853,7 +2886,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     const u64 zeros = size;
     const u64 at_flags = part(F_COUNT), at_partials = part(PARTIALS_WORDS(c->max_partials)), at_totals = part(n_totals);
     u64 at_state[2][3];
-    for (auto& at : at_state) { at[0] = part(C_COUNT); at[1] = part(2 * ACCEPT_ROWS); at[2] = part(g.W * g.words_pw); }     // rows: accepted packets, sums of squares
+    for (auto& at : at_state) { at[0] = part(C_COUNT); at[1] = part(2 * ACCEPT_ROWS); at[2] = part(LONG_ALL + g.W * g.words_pw) + LONG_ALL; }
     const u64 at_home = part(n_home), n_zeros = size - zeros;
     const u64 ones = size, at_list_first = part(n_first), at_pending = part(n_pending), n_ones = size - ones;
     bool ok = hipMalloc(&c->slab, size * sizeof(u64)) == hipSuccess;
@@ -2863,7 +2896,7 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
         u64* const base = c->slab;
         c->d_block_tallies = (u32*)(base + at_tallies); c->d_need = (u32*)(base + at_need);
         c->d_flags = base + at_flags; c->d_partials = base + at_partials; c->d_totals = base + at_totals;
-        for (int k = 0; k < 2; ++k) c->state[k] = {base + at_state[k][2], base + at_state[k][1], base + at_state[k][0], 0};
+        for (int k = 0; k < 2; ++k) c->state[k] = {base + at_state[k][2], base + at_state[k][1], base + at_state[k][0], 0, 0};
         c->d_home = (uint8_t*)(base + at_home);
         c->few.entries = base + at_list; c->few.first = (u32*)(base + at_list_first); c->d_pending = base + at_pending;
         g.first_seq = (const u32*)(base + at_first); g.b_off = base + at_off; g.b_cnt = base + at_cnt;
@@ -3199,6 +3232,7 @@ static int apply_batch(dblp_ctx* c, const void* d_packets, const uint16_t* d_src
     const bool any = whole && turns > 4;                // (two turns for nothing take 1 us; the word costs 0.4 to 1.5)
     const u32 any_at = any ? c->any_no++ & 1u : 0u;
     RoundState& now = c->state[c->cur];
+    if (list.entries) now.listed = 1;
     const u32 batch = (whole ? B_WHOLE : 0) | (any ? B_ANY : 0) | (any_at ? B_ANY_AT : 0) | (asked ? B_ASKED : 0);
 
     u32 n_tally_rows = 0;
@@ -3388,17 +3422,17 @@ extern "C" int dblp_finalize(dblp_ctx* c, int compensation, float* d_out) {
         ProfScope ps(c, DBLP_K_FINALIZE);
         const size_t table = ((size_t)g.B + 1) * sizeof(u32);
         void (*kern)(Geo, const u64*, const float*, const float*, uint8_t*, float*, int, float, int, u32, u32, u32, u64*, u32, u32,
-                     const double*, const u64*, u32, u64*, u64*, RoundState) =
+                     const double*, const u64*, u32, u32, u64*, u64*, RoundState) =
             table <= IDX_TABLE_LDS_MAX ? (past ? finalize_pass<true, true> : finalize_pass<true, false>) : (past ? finalize_pass<false, true> : finalize_pass<false, false>);
         hipLaunchKernelGGL(kern, dim3(grid), dim3(256), table <= IDX_TABLE_LDS_MAX ? table : 0, c->stream, g, (const u64*)now.bitmap,
                            (const float*)c->d_acc[0], (const float*)c->d_acc[1], c->d_home, out, c->fold ? 0 : 1, (float)g.W,
                            in_place ? 1 : 0, grp_log2, n_piece, per_piece, c->d_partials, c->max_partials, work, (const double*)(now.rows + ACCEPT_ROWS), (const u64*)now.rows,
-                           now.rows_used, now.counters, c->d_mailbox, other);
+                           now.rows_used, c->fold ? now.listed : 0u, now.counters, c->d_mailbox, other);
     }
     LAUNCH_CHECK(c, "finalize");
     if (other.bitmap) {
         c->other_clean = 1;
-        c->state[c->cur ^ 1].rows_used = 0;
+        c->state[c->cur ^ 1].rows_used = 0; c->state[c->cur ^ 1].listed = 0;
     }
     c->result_in_place = in_place ? 1 : 0;
     c->finalized = 1;

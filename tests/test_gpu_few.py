@@ -167,3 +167,87 @@ def test_few_packets_in_a_recorded_round():
             graph.replay()
             assert agg.phase_signal()[0] == norm and agg.get_counters() == counts
             assert torch.equal(out.view(torch.int32), want.view(torch.int32))
+
+
+def _apply_in_turn(rx, packets, batches):
+    """A round of the given batches of (worker, number) pairs: the mean's bits and the norm."""
+    import torch
+    agg = rx.agg
+    agg.begin_round(ROUND)
+    for w, seq in batches:
+        agg.apply_arrivals_queue(packets, rx.W * rx.pkts, ((w * rx.pkts + seq) | (w << 32)).contiguous())
+    out = torch.empty(rx.n, device="cuda")
+    agg.finalize(out)
+    return out, agg.phase_signal()[0]
+
+
+def _all_packets(rx):
+    import torch
+    agg = rx.agg
+    packets = torch.empty(rx.W * rx.pkts * agg.stride, dtype=torch.uint8, device="cuda")
+    src = torch.empty(rx.W * rx.pkts, dtype=torch.int16, device="cuda")
+    for w in range(rx.W):
+        agg.packetize(w, ROUND, rx.grads[w], 0, 0, rx.pkts, packets, src, slot_base=w * rx.pkts)
+    return packets
+
+
+# batches that a launch of their own takes, and larger ones; packets of a wave and of a block, blocks of 16 waves; many workers
+@pytest.mark.parametrize("W,P,pkts,m", [(1, 256, 9000, 1400), (4, 366, 30_000, 1500), (4, 366, 30_000, 6000), (16, 64, 40_000, 10_000), (2, 2243, 6000, 700),
+                                        (2, 2243, 9000, 2000), (4, 16374, 1200, 250), (32, 366, 12_000, 3000), (64, 1200, 240, 60)])
+def test_order_of_arrival_changes_no_bit(W, P, pkts, m):
+    """The mean and the norm, of a small batch onto a large one and of small batches alone, in several orders."""
+    import torch
+    rx = _Rx(W, P, [(pkts // 2) * P + 1, (pkts // 2 - 1) * P], W + m)
+    gen, n = rx.gen, rx.pkts
+    for wide in (False, True):
+        if wide:            # packets of very different size, whose squares' last bits get lost one way or another
+            size = torch.exp2(torch.randint(-20, 20, (n,), generator=gen, device="cuda").float())[rx.packet]
+            rx.grads = [g * size for g in rx.grads]
+        packets = _all_packets(rx)
+        late = torch.zeros(W * n, dtype=torch.bool, device="cuda")
+        late[torch.randperm(W * n, generator=gen, device="cuda")[:m]] = True
+        late = late.view(W, n)
+        first, (w, seq) = torch.nonzero(~late, as_tuple=True), torch.nonzero(late, as_tuple=True)
+        for before in ([first], [], [(w[:m // 2], seq[:m // 2])]):
+            rest = (w, seq) if not before or before[0] is first else (w[m // 2:], seq[m // 2:])
+            k = rest[0].numel()
+            want = None
+            for order in (torch.arange(k, device="cuda"), torch.arange(k - 1, -1, -1, device="cuda"), *(torch.randperm(k, generator=gen, device="cuda") for _ in range(3))):
+                out, norm = _apply_in_turn(rx, packets, before + [(rest[0][order], rest[1][order])])
+                if want is None:
+                    want = out, norm
+                    exact = float(out.double().square().sum().sqrt())
+                    # sums in double while the spans are stored, or (W no power of two, not here) in the copy
+                    assert abs(norm - exact) <= 4.5 * rx.n * 2.0 ** -53 * exact
+                assert torch.equal(out.view(torch.int32), want[0].view(torch.int32))
+                assert norm == want[1]
+
+
+@pytest.mark.parametrize("m", [300, 3000])
+def test_norm_of_the_smallest_and_largest_floats(m):
+    """A batch of few packets alone, of the smallest floats that there are to the largest; then with infinities and NaN."""
+    import torch
+    P, n = 200, 20_000
+    rx = _Rx(1, P, [P * n], m)
+    seq = torch.randperm(n, generator=rx.gen, device="cuda")[:m]
+    w = torch.zeros_like(seq)
+    plain = rx.grads[0]
+    for scale in (2.0 ** -149, 2.0 ** -140, 2.0 ** -75, 1.0, 2.0 ** 100):
+        rx.grads = [(plain * scale if scale > 2.0 ** -149 else plain.sign() * 2.0 ** -149)]
+        out, norm = _apply_in_turn(rx, _all_packets(rx), [(w, seq)])
+        exact = float(out.double().square().sum().sqrt())
+        assert exact > 0 and abs(norm - exact) <= 4.5 * rx.n * 2.0 ** -53 * exact
+    at = int(seq[m // 2]) * P + 3
+    rx.grads = [torch.full_like(plain, -3.4028234663852886e38)]
+    out, norm = _apply_in_turn(rx, _all_packets(rx), [(w, seq)])
+    exact = 3.4028234663852886e38 * (m * P) ** 0.5
+    assert abs(norm - exact) <= 4.5 * rx.n * 2.0 ** -53 * exact
+    for odd in (float("inf"), float("-inf"), float("nan")):
+        rx.grads = [plain.clone()]
+        rx.grads[0][at] = odd
+        norm = _apply_in_turn(rx, _all_packets(rx), [(w, seq)])[1]
+        assert norm != norm if odd != odd else norm == float("inf")
+    rx.grads = [plain]                  # and of the next round nothing is left
+    out, norm = _apply_in_turn(rx, _all_packets(rx), [(w, seq)])
+    exact = float(out.double().square().sum().sqrt())
+    assert abs(norm - exact) <= 4.5 * rx.n * 2.0 ** -53 * exact
