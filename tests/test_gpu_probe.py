@@ -1,6 +1,7 @@
 """GPU: a probe's counts, list and verdict at the edges of its launches, against plain torch on the flags of what arrived.
 
-The list is written in one launch by blocks that add up each other's lengths while there are at most seven blocks per
+Short rounds (at most 2048 bitmap words and 8192 pairs) are probed in one launch whose blocks count all pairs for themselves.  In
+longer ones the list is written in one launch by blocks that add up each other's lengths while there are at most seven blocks per
 four CUs (1792 pairs on 256 CUs, 448 where a block takes a pair), in two launches while there are at most 4096 blocks, and
 in three beyond.  All values are integers and compared exactly."""
 import pytest
@@ -30,22 +31,32 @@ def _expect(alive, first, n_b, bound):
     return missing.int().flatten(), (w << 32) | seq
 
 
-# one pair; a block's remainder; as many pairs as one launch takes, and more; one pair a wave and two; 64 a wave, and more
-# blocks than are added up without a scan; long buckets of which a block takes one, in one launch and in two
-CASES = [(1, [1]), (3, [5, 70, 1, 64, 65, 129]), (7, [1, 300] * 128), (3, [2] * 598), (32, [2] * 256), (33, [2] * 249), (64, [3, 1] * 4096),
-         (64, [1] * 8193), (64, [1] * 16400), (5, [40_000, 3, 33_000, 1]), (64, [33_000, 3, 1, 70, 500, 9, 2, 64]), (56, [33_000] + [2] * 7), (50, [33_000] + [2] * 8)]
+# short rounds: one pair; a few; many
+SHORT = [(1, [1]), (3, [5, 70, 1, 64, 65, 129]), (3, [2] * 598), (32, [2] * 256)]
+# longer ones: one pair, a block's, and 64, a wave's each; a block's remainder; as many pairs as one launch takes, and more; one pair a
+# wave and two; 64 a wave, and more blocks than are added up without a scan; long buckets of which a block takes one, in one launch and in two
+LONG = [(1, [131_073]), (64, [2100]), (33, [5, 70, 1, 64, 65, 4000]), (7, [1, 300] * 128), (3, [74] * 598), (32, [17] * 256), (33, [2] * 249), (64, [3, 1] * 4096),
+        (64, [1] * 8193), (64, [1] * 16400), (5, [40_000, 3, 33_000, 1]), (64, [33_000, 3, 1, 70, 500, 9, 2, 64]), (56, [33_000] + [2] * 7), (50, [33_000] + [2] * 8)]
+CASES = SHORT + LONG
+
+
+def _is_short(agg):
+    return agg.W * agg.words_pw <= 2048 and agg.W * agg.B <= 8192
 
 
 @pytest.mark.parametrize("W,packets", CASES)
 def test_probe_lists_what_is_missing(W, packets):
-    _probes(W, packets, _context(W, packets))
+    agg = _context(W, packets)
+    assert _is_short(agg) == ((W, packets) in SHORT)
+    _probes(W, packets, agg)
 
 
 @pytest.mark.parametrize("polls", [0, 1])
 @pytest.mark.parametrize("W,packets", [c for c in CASES if c[0] * len(c[1]) <= 1792])
 def test_probe_whose_blocks_do_not_wait_is_made_again(W, packets, polls):
     """With no look allowed every block that needs the ones before it gives up; with one, some may.  The answers are the
-    same, also of a probe that may wait and follows one that gave up (its words in the totals carry no tag)."""
+    same, also of a probe that may wait and follows one that gave up (its words in the totals carry no tag).  In a short round
+    nobody waits, whatever is allowed."""
     agg = _context(W, packets)
     agg.probe_polls(polls)
     _probes(W, packets, agg, lambda k: agg.probe_polls(16384 if k % 3 == 2 else polls))
@@ -99,9 +110,9 @@ def test_probes_of_several_contexts_at_once():
     import threading
 
     import torch
-    W, packets, found = 32, [65] * 56, [None] * 4
-    want = _expect(torch.zeros(W, 65 * 56, dtype=torch.bool, device="cuda"), torch.arange(57, device="cuda") * 65,
-                   torch.full((56,), 65, device="cuda"), 0)
+    W, packets, found = 32, [80] * 56, [None] * 4
+    want = _expect(torch.zeros(W, 80 * 56, dtype=torch.bool, device="cuda"), torch.arange(57, device="cuda") * 80,
+                   torch.full((56,), 80, device="cuda"), 0)
 
     def work(k):
         stream = torch.cuda.Stream()
@@ -110,7 +121,7 @@ def test_probes_of_several_contexts_at_once():
             agg.begin_round(ROUND)
             missing = torch.empty(W * agg.B, dtype=torch.int32, device="cuda")
             out = torch.empty(W * agg.n_pkts, dtype=torch.int64, device="cuda")
-            ok = True
+            ok = not _is_short(agg)         # its blocks wait for each other
             for _ in range(100):
                 out.fill_(-1)
                 ok = ok and agg.loss_account(0, missing, out) == (out.numel(), False, False)
