@@ -129,7 +129,7 @@ def test_dense_gather_at_the_edges_of_passes_pieces_and_groups(W, P, n):
         assert stats["rel_to_addends"] <= FLOAT_TOL
 
 
-@pytest.mark.parametrize("loss", [0.05, 0.012])       # both instances launched; the sparse one alone
+@pytest.mark.parametrize("loss", [0.1, 0.05, 0.012])       # (from three workers on) by groups; by the list or by groups; by the list
 @pytest.mark.parametrize("W,P,n", [(2, 1, 3000), (3, 2, 900), (4, 3, 900), (5, 5, 700), (8, 6, 700), (1, 510, 400), (4, 511, 130),
                                    (9, 512, 65), (3, 514, 97), (17, 1023, 33), (64, 366, 40), (2, 4097, 129),
                                    (4, 256, 700), (3, 255, 301), (8, 512, 130), (2, 1024, 302), (5, 767, 64),
@@ -179,10 +179,12 @@ def test_last_packets_of_every_remainder_and_beside_piece_edges(P, W, filler):
 
 
 @pytest.mark.parametrize("per_seq", [0.004, 0.1])        # groups looked through first, and not
-@pytest.mark.parametrize("W,P,n", [(1, 3, 140_000), (5, 2, 140_003), (40, 2, 70_001), (3, 520, 40_000), (64, 600, 2000)])
-def test_sparse_gather_shares_groups_between_waves_and_blocks(W, P, n, per_seq):
+@pytest.mark.parametrize("W,P,n,by_list", [(1, 3, 140_000, True), (5, 2, 140_003, True), (40, 2, 70_001, True), (3, 520, 40_000, True), (64, 600, 2000, True),
+                                           (1, 3, 1_060_000, False), (5, 2, 140_003, False), (40, 2, 70_001, False), (3, 520, 40_000, False), (64, 600, 2000, False)])
+def test_sparse_gather_shares_groups_between_waves_and_blocks(W, P, n, by_list, per_seq):
     """Scattered packets, which single waves take, beside runs of 300 sequence numbers lost by all workers, which are left to
-    the whole block: tiles of several groups per block and of one, with packets of one and of two pieces."""
+    the whole block: tiles of several groups per block and of one, with packets of one and of two pieces.  (by_list: as few
+    arrivals as there are; most of these batches are then gathered by the list of what arrived.)"""
     sc = build_scenario(mk(W, [P * (n // 3) + 1, P * (n - n // 3) - (P // 2)], P))
     L = sc.L
     held = np.random.default_rng(n).random((L.W, L.n_pkts)) < per_seq / W
@@ -192,8 +194,9 @@ def test_sparse_gather_shares_groups_between_waves_and_blocks(W, P, n, per_seq):
     o, g = both(sc, queue=True)
     for rx in (o, g):
         rx.begin_round(sc.rnd_id)
-        for part in (~held, held):
-            rx.apply(0, held.size, None, np.sort(sc.slot_of[part]))
+        rx.apply(0, held.size, None, np.sort(sc.slot_of[~held]))
+        late = np.sort(sc.slot_of[held])
+        rx.apply(0, held.size, None, late if by_list else _past_the_list(late, L))
     assert g.bitmap().all() and g.counters() == o.counters() and o.counters()["accepted"] == held.size
     from harness import abs_scale
     ref, got = o.finalize(), g.finalize().astype(np.float64)
@@ -224,6 +227,15 @@ def test_rounds_that_arrive_in_many_contiguous_steps(W, P, n, steps):
     ref, got = o.finalize(), g.finalize().astype(np.float64)
     assert (np.abs(got - ref) <= FLOAT_TOL * abs_scale(sc, np.ones((L.W, L.n_pkts)))).all()
     assert g.phase_signal()[0] == pytest.approx(o.phase_signal()[0], rel=1e-6)
+
+
+def _past_the_list(slots, L):
+    """The arrivals `slots`, and as many with a slot outside the buffer as it takes for the batch not to be gathered by the list of what
+    arrived (more than a quarter as many arrivals as sequence numbers, or 131072); sparse by number all the same."""
+    n = min(L.n_pkts // 4, 131072) + 1
+    assert n * 8 < L.W * L.n_pkts
+    slots = np.asarray(slots)
+    return np.concatenate([slots, np.full(max(0, n - slots.size), L.W * L.n_pkts + 3)])
 
 
 # ------------------------------------------------------------------------------ two accumulator copies
@@ -510,10 +522,12 @@ def test_a_round_recorded_under_stream_capture_replays_to_the_eager_result():
             g.agg.set_prev_norm(None)
 
 
+@pytest.mark.parametrize("by_list", [True, False])
 @pytest.mark.parametrize("W,n_elems", [(2, 1_200_000), (20, 120_000)])
-def test_small_batches_scattered_over_a_long_round(W, n_elems):
+def test_small_batches_scattered_over_a_long_round(W, n_elems, by_list):
     """A dense first batch, then batches of a handful of packets scattered over a round of up to 1.2 M
-    sequence numbers (the direct gather looks through the arrival index of many groups at once and
+    sequence numbers (by the list of what arrived, or handed over in a crowd of arrivals that are not valid: then the gather looks
+    through the arrival index of many groups at once and
     walks the few that hold an entry: more than 64 groups per block at the larger size), a batch that
     fills a contiguous run, and one that is mostly copies of delivered packets."""
     sc = build_scenario(mk(W, [n_elems, 37], 1, place="worker_major", order="identity"))
@@ -530,7 +544,7 @@ def test_small_batches_scattered_over_a_long_round(W, n_elems):
     for rx in (o, g):
         rx.begin_round(sc.rnd_id)
         for b in batches:
-            rx.apply(0, n, None, b.astype(np.uint32))
+            rx.apply(0, n, None, (b if by_list or b is batches[0] else _past_the_list(b, L)).astype(np.uint32))
     delivered = np.ones(n, dtype=bool)
     delivered[np.setdiff1d(held, np.concatenate([run, scattered[:33]]))] = False
     assert np.array_equal(o.bitmap().reshape(-1).astype(bool), delivered)
@@ -1032,12 +1046,13 @@ def test_probe_counts_and_lists_of_few_and_many_buckets(W, B, big, ppm):
 # ------------------------------------------------------------------------------ trace groups of the gather
 @pytest.mark.parametrize("mask", ["both", "dense", "sparse"])
 @pytest.mark.parametrize("own_buffer", [False, True])
-def test_gather_launches_count_in_the_group_that_they_belong_to(own_buffer, mask):
+@pytest.mark.parametrize("W", [4, 8])                    # by the list of what arrived, and by groups
+def test_gather_launches_count_in_the_group_that_they_belong_to(W, own_buffer, mask):
     """A contiguous step and a scattered retransmission, each of one arrival per 20 pairs of the round, handed over in
     the whole round's buffer or in one of their own: the step counts as dense, the retransmission as sparse,
     whichever buffer they come in and whichever of the two groups is traced."""
     from paper_2605_01989_amd import binding
-    sc = build_scenario(mk(4, [366 * 2000], 366, place="worker_major"))
+    sc = build_scenario(mk(W, [366 * 2000], 366, place="worker_major"))
     L = sc.L
     g = GpuRx(sc, queue=True); g.packetize_all()
     step = np.zeros((L.W, L.n_pkts), dtype=bool)
