@@ -33,7 +33,9 @@
  *     (tested: replays give the bits of the eager run).  The context's host-side
  *     bookkeeping is done when the calls are made, i.e. at capture: replay the
  *     recorded round as a whole, and call the functions that return host scalars
- *     outside the capture, after a replay.
+ *     outside the capture, after a replay.  From the first call that was recorded on, every
+ *     dblp_begin_round of the context launches a kernel, recorded or not (otherwise only those
+ *     do that follow a round without a dblp_finalize).
  *   - A context is not thread-safe; use one per host thread.
  *
  * Geometry.  The gradient has N fp32 elements, tiled in order by B buckets
@@ -108,10 +110,12 @@ typedef struct {
 #define DBLP_ACCMODE_PAIR 1   /* two copies, the second a plain allocation (or d_accumulator[1]) */
 #define DBLP_ACCMODE_SEARCH 2 /* two copies, the second searched for in another third of HBM; one copy if none is found */
 
-/* Allocates the context and its device state (bitmap W x ceil(n_pkts/64) words, arrival
+/* Allocates the context and its device state: two bitmaps of W x ceil(n_pkts/64) words (the next
+ * round's is cleared while a round ends) with 140 KB of counters each, arrival
  * index W x n_pkts x 8 bytes, accumulator N floats in one or two copies unless the caller
- * supplies them, one byte per packet sequence number, per-bucket counters, and with more than
- * 4095 buckets 4 bytes per 64 packets).  Under
+ * supplies them, five bytes per packet sequence number and two more for each of the first 524288
+ * (the list of what arrived in a batch of few packets), per-bucket counters, and with more than
+ * 4095 buckets 4 bytes per 64 packets.  Under
  * DBLP_ACCMODE_SEARCH it also searches for the second accumulator copy (see below) within the
  * limits given in the configuration.  *out is set only on success.  Errors: EINVAL (bad table,
  * W too large, n_pkts >= 2^32, unknown mode, misaligned or inconsistent caller buffers), ENOMEM,

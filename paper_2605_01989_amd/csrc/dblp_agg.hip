@@ -2464,7 +2464,7 @@ struct dblp_ctx {
     u64* d_mailbox;         // device address of h_mailbox
     // host copies of the geometry
     u32* h_first_seq; u64* h_b_off; u64* h_b_cnt;
-    u64* h_tables;          // the three as they lie on the device
+    u64* h_tables;          // the three as they lie on the device, while dblp_create copies them there
     // protocol state
     int round_open; int finalized; uint16_t round;
     double prev_norm; int have_prev;
@@ -2940,6 +2940,8 @@ extern "C" int dblp_create(dblp_ctx** out, const dblp_config* cfg) {
     c->other_clean = 1;
     e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess || hipGetLastError() != hipSuccess) { dblp_destroy(c); return DBLP_EHIP; }
+    free(c->h_tables);
+    c->h_tables = nullptr;
     // accumulator last
     if (cfg->d_accumulator[0]) {
         c->acc_caller = 1;
