@@ -361,7 +361,7 @@ __global__ __launch_bounds__(256) void packetize_kernel(Geo g, SenderSplit split
 
 struct GradPtrs { const float* p[DBLP_MAX_WORKERS]; };
 
-// One wave per list entry (w << 32 | seq): worker w's packet seq -> slot slot_base + i.
+// List entry i (w << 32 | seq): worker w's packet seq -> slot slot_base + i.  A wave takes one entry, or several at once (SHORT).
 template <bool TABLE_IN_LDS, bool SHORT>
 __global__ __launch_bounds__(256) void packetize_list_kernel(Geo g, SenderSplit split, GradPtrs grads, u32 round, const u64* __restrict__ list,
                                                              u64 n, u64 slot_base, uint8_t* __restrict__ packets,
@@ -698,7 +698,9 @@ struct GatherShape { u32 sub_log2, n_piece, blocks; };
 // MANY (more than 16 workers, whose index is several trips to memory, one after the other): the block's waves share a group's
 // rows of the index out instead of each reading all of them.  us of index pass and gather, rows read by all and shared
 // out: 32 workers x 82 k numbers of 1472 B, 78 k packets late 90, 82, 210 k late 140, 131; 64 x 33 k, 63 k late 72, 62, 168 k late
-// 118, 107; whole rounds of 24 to 64 workers 0.5 to 1 % either way.  With fewer workers the waves' waiting for each other is all
+// 118, 107.  Whole rounds: in blocks of 16 waves 64 x 200 of 2416 B 24.8, 24.0, 33 x 200 of 4096 B 22.4, 21.5, 24 x 150 of 14.8 KB 25.6,
+// 24.9; 64 x 300 of 272 B 27.6, 26.2, 64 x 1500 of 4112 B 85.9, 83.3, 64 x 6000 of 1472 B 114.9, 115.0; but 17 x 400 of 4112 B 19.9, 20.8, 32 x 300
+// of 8992 B 30.6, 31.4: 0.4 % over 55 shapes, more the more workers.  With fewer workers the waves' waiting for each other is all
 // that it gives: 4 x 4096 packets of 1040 B 14.4, 15.8; 16 x 5465, 2.6 k late 17.7, 18.2.
 template <int NP, int G, int D, int NW, bool SPARSE, u32 LEAD, bool MANY>
 __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi, const GatherShape& s, const u32* fs, u32* sh_slots,
@@ -1026,12 +1028,12 @@ __device__ __forceinline__ void gather_groups(const Geo& g, const BatchInfo& bi,
 
 // A retransmission of few packets is a chain of memory trips, whatever bandwidth there is, and by groups it is long: the
 // tallies, the index of whole groups looked through for the entries, the entries again, the payload, and in
-// a group with several packets the packets one after the other by one wave.  Where a batch holds at most FEW_MAX arrivals, and fewer than
+// a group with several packets the packets one after the other by one wave.  Where a batch holds at most FEW_MAX arrivals, and at most
 // one per FEW_DIV sequence numbers of the round, the index pass also lists what it found, and a wave takes entries of the list, one output packet
 // each: the entry; what its number leads to (all workers' index entries and bitmap words, the span); the payloads
 // and the span's old contents; the store.  Several arrivals of one number are one output packet, taken by the one that the
 // index pass noted as the first.  Packets of three and more pieces are taken by the block's waves together.  The sums and
-// their order are those of the groups; the squares of a packet are added up by one wave, and the packets' in a long
+// their order are those of the groups; a wave adds up the squares of its part of a packet, and these sums go into a long
 // accumulator, so that the norm does not depend on the order of arrival either.
 //
 // A batch that turns out to be dense goes by groups after all: neighbours in the bitmap are set by atomics here, one
