@@ -41,7 +41,7 @@ PMC_TRAFFIC_RATIO: dict[tuple[str, str], float] = {
 
 def _kernel_source_hash() -> str:
     src = os.path.join(ROOT, "paper_2605_01989_amd", "csrc")
-    return hashlib.sha256(b"".join(open(os.path.join(src, f), "rb").read() for f in ("dblp_agg.hip", "packet_units.h"))).hexdigest()
+    return hashlib.sha256(b"".join(open(os.path.join(src, f), "rb").read() for f in ("dblp_agg.hip", "packet_units.h", "long_sum.h"))).hexdigest()
 
 
 def log(*a):

@@ -1881,7 +1881,10 @@ __global__ __launch_bounds__(256) void probe_once(Geo g, const u64* __restrict__
 //   1093, 1 x 161                           17.3, 17.7                   20.4, 17.0       22.6, 17.0
 //   2015, 13 x 16                           17.7, 17.0                   23.2, 17.0       27.0, 17.1
 //   3992, 8 x 161 (not taken)               18.3, 19.3                   21.8, 19.1       24.9, 19.2
-// Above PROBE_ALL_WORDS the usual probe with few losses takes longer, as every block reads all of it.
+// Above PROBE_ALL_WORDS the usual probe with few losses takes longer, as every block reads all of it.  Below, with 161 buckets and
+// few losses, it takes 0.1 to 0.4 us longer too (1093 words 17.7, 18.0; 4 x 161, 1060 words 17.9, 18.2; 8 x 161, 1872 words 18.3, 18.6;
+// 499 words 17.6, 17.8; 1952 words 18.1, 17.9; with 16 x 300, 32 x 64 or 13 x 16 buckets 0.2 to 0.7 less): a search of eight steps for the
+// bucket of what is missing.  It is taken there all the same, for the 3 to 8 us that it saves where much is lost.
 #define PROBE_ALL_THREADS 1024u
 #define PROBE_ALL_WORDS 2048u
 #define PROBE_ALL_PAIRS 8192u
@@ -2703,7 +2706,8 @@ static int pick_copy(dblp_ctx* c, const void* d_packets, u64 bytes, u64 n_slots,
 // worth more than they are, and the mean is read again only once it has all been written.  us of a pass that copies out, and in
 // brackets with a kernel that reads the mean behind it, before and now: 3 x 22 M elements 187, 177 (222, 214); 13 x 22 M 336, 332 (372, 365); 1 x 60 M
 // 242, 215 (316, 303); 1 x 137 M 583, 526 (778, 714); 3 x 200 M 1000, 983 (1266, 1253).  Below, the caches hold it: 4 x 16 M 122.5,
-// 122.5 (143, 146), 1 x 12 M 73, 75 (88, 91), 3 x 8 M 106, 108 (122, 126).
+// 122.5 (143, 146), 1 x 12 M 73, 75 (88, 91), 3 x 8 M 106, 108 (122, 126).  The launch alone: 3 x 22 M 56, 41; 4 x 60 M 117, 91; 1 x 137 M
+// 249, 221; 3 x 200 M 343, 310.
 #define FIN_PAST 20000000ull
 #ifndef IDX_BLOCKS_PER_CU
 #define IDX_BLOCKS_PER_CU 4   // 2-4 blocks per CU index 3 % faster than 8: its bound is requests to memory, not latency
@@ -3406,8 +3410,9 @@ extern "C" int dblp_finalize(dblp_ctx* c, int compensation, float* d_out) {
     // Packets per wave: where the result is left in place most waves have nothing to write, so they look
     // at a whole bitmap word (fewer packets when they are long: what is written is written by one wave);
     // into another buffer as many as make up to 8192 elements, in pieces of up to 4096 and of equal size (past the caches
-    // whole groups of 4096; of a short gradient 2048, so that all CUs have some: 6 workers x 0.9 M elements, a pass 75.1 -> 72.7
-    // us, 3 x 2.8 M 79.1 -> 77.9, but 13 x 5.7 M 161 -> 164).
+    // whole groups of 4096; of a short gradient 2048, so that all CUs have some).  us of the launch, each alone: pieces of equal size
+    // against 4096 and what is left, 3 x 5.3 M in 366-float packets 20.1, 19.5, 13 x 5.7 M 21.0, 20.3; pieces of 4096 and of 2048, 6 x 0.9 M 12.4, 10.9, 1 x 1.9 M
+    // in 16374-float ones 12.4, 10.7, 3 x 2.8 M 14.9, 14.7 (and above 4 M elements a pass of 13 x 5.7 M 161, 164).
     u32 grp_log2 = 6;
     const bool past = !in_place && c->N >= FIN_PAST, brief = c->N < 4000000ull;
     const u64 most = in_place ? 32768 : brief ? 2048 : past ? 4096 : 8192;
