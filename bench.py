@@ -34,8 +34,8 @@ BENCH_DRAWN_ROUNDS = 3   # retransmission rounds with a drawn loss pattern; late
 # on and by workload; anything else reports null.
 # value = measured bytes / algorithmic bytes of a first-transmission launch.
 PMC_TRAFFIC_RATIO: dict[tuple[str, str], float] = {
-    ("4b20297c12eb2db69177a813a9f74fbe08280cd008f960bb2d586088049ab532", "cfg5"): 1.055,   # profiles/receiver_path_cfg5.md
-    ("4b20297c12eb2db69177a813a9f74fbe08280cd008f960bb2d586088049ab532", "cfg4"): 1.031,   # profiles/receiver_path_cfg4.md
+    ("5b341c40235bff14d8b2460757654e8641168260bb20f76d66cb1862c41cb3b9", "cfg5"): 1.055,   # profiles/receiver_path_cfg5.md
+    ("5b341c40235bff14d8b2460757654e8641168260bb20f76d66cb1862c41cb3b9", "cfg4"): 1.031,   # profiles/receiver_path_cfg4.md
 }
 
 
